@@ -371,12 +371,20 @@ int fpq_packed_check(const void* packed, int64_t N, int64_t Cin, int kh, int kw,
     return FPQ_OK;
 }
 
-// workspace of the search: [1024 partial maxima][absmax, 256 bytes][per-block error sums]
+// workspace of the search: [1024 partial maxima][256 bytes][per-block error sums, or the binned form's tables]
+static size_t search_direct_workspace(size_t n, int n_enc, int n_bias)
+{
+    const int nb = search_blocks(n);
+    return 4096 + 256 + align_up((size_t)(nb > 0 ? nb : 1) * (size_t)(n_enc * n_bias) * sizeof(float), 256);
+}
+
 size_t fpq_search_workspace_size(size_t n, int n_enc, int n_bias)
 {
     if (n_enc < 1 || n_enc > kSearchMaxEncodings || n_bias < 1 || n_bias > 128) return 0;
-    const int nb = search_blocks(n);
-    return 4096 + 256 + align_up((size_t)(nb > 0 ? nb : 1) * (size_t)(n_enc * n_bias) * sizeof(float), 256);
+    const size_t direct = search_direct_workspace(n, n_enc, n_bias), binned = search_binned_bytes(n, n_enc * n_bias);
+    // both forms put the mean errors (one double per candidate) behind their sums when more than one workgroup adds those
+    const size_t mse = align_up((size_t)(n_enc * n_bias) * sizeof(double), 256);
+    return n < 65536 ? direct : binned ? 4096 + 256 + binned + mse : direct + mse;
 }
 
 int fpq_search_format(const float* x, size_t n, const int32_t* ebits, const int32_t* mbits, int n_enc, int n_bias,
@@ -396,17 +404,16 @@ int fpq_search_format(const float* x, size_t n, const int32_t* ebits, const int3
         a.enc[i].b0 = 1 << (e - 1);
         a.enc[i].c0 = fpq_format_max(e, m, a.enc[i].b0);
     }
-    if (workspace_bytes < fpq_search_workspace_size(n, n_enc, n_bias)) return FPQ_ERR_WORKSPACE;
+    if (workspace_bytes < search_direct_workspace(n, n_enc, n_bias)) return FPQ_ERR_WORKSPACE;
     if ((reinterpret_cast<uintptr_t>(workspace) & 255) || (reinterpret_cast<uintptr_t>(x) & 3) ||
         (reinterpret_cast<uintptr_t>(result) & 3))
         return FPQ_ERR_ALIGN;
     hipStream_t s = static_cast<hipStream_t>(stream);
     float* maxparts = static_cast<float*>(workspace);
-    float* absmax = maxparts + 1024;
-    float* partial = absmax + 64;
-    int st = launch_absmax(x, n, 1.0f, absmax, nullptr, maxparts, s);
+    float* partial = maxparts + 1024 + 64;
+    int st = launch_absmax_partials(x, n, maxparts, s);
     if (st) return st;
-    return launch_search(x, n, a, absmax, partial, mse_out, result, s);
+    return launch_search(x, n, a, maxparts, partial, workspace_bytes - 4096 - 256, mse_out, result, s);
 }
 
 size_t fpq_gemm_workspace_size(int64_t M, int64_t N, int64_t K, int x_is_fp32)

@@ -204,7 +204,10 @@ static inline int search_blocks(size_t n)
     size_t g = (n + 2047) / 2048;
     return (int)(g > 1024 ? 1024 : g);
 }
-int launch_search(const float* x, size_t n, const SearchArgs& a, const float* absmax_dev, float* partial,
+// maxparts: what launch_absmax_partials left; partial: workspace of partial_bytes (the binned form of large tensors wants
+// search_binned_bytes plus one double per candidate; with less the direct form runs).
+size_t search_binned_bytes(size_t n, int nc);
+int launch_search(const float* x, size_t n, const SearchArgs& a, const float* maxparts, float* partial, size_t partial_bytes,
                   float* mse_out, fpq_search_result* result, hipStream_t st);
 
 // Rounding learning (Section V-B): launchers of rounding.hip.

@@ -93,3 +93,37 @@ def test_search_result_feeds_the_quantizer():
     torch.cuda.synchronize()
     err = np.mean((x.astype(np.float64) - deq.cpu().numpy().astype(np.float64)) ** 2)
     assert abs(err - r.mse) <= 1e-4 * r.mse
+
+
+def _outliers_and_tiny(n):
+    """One huge value, so that most of the tensor lies tens of binades below the maximum, and values down to subnormals."""
+    x = synth.activations((n,), 12)
+    x[::7] *= np.float32(1e-3)
+    x[5::1000] *= np.float32(1e-12)
+    x[9::5000] = np.float32(1e-40)
+    x[3] = np.float32(1e9)
+    return x
+
+
+BINNED = 400000   # from here on (at 444 candidates) the errors come from interval moments
+
+
+@pytest.mark.parametrize("n", [BINNED - 1, BINNED, (1 << 19) + 3])
+@pytest.mark.parametrize("encodings", [FP8, FP8 + FP4])
+def test_search_large_tensors_match_oracle(n, encodings):
+    check(synth.activations((n,), 77), encodings, 111)
+
+
+def test_search_large_tensors_of_unusual_values():
+    check(_outliers_and_tiny(BINNED + 1), FP8, 111)
+    wide = np.exp(np.random.default_rng(1).uniform(-70, 5, BINNED)).astype(np.float32)
+    check(wide, FP8 + [(6, 1)], 111)                                # spread over a hundred binades
+    wide[:] = np.float32(1e-30)
+    wide[0] = np.float32(1.0)                                       # all but one value far below every interval
+    check(wide, FP8, 111)
+    s = np.float32(0.37)
+    x = (np.array([0, .5, 1, 1.5, 2, 3, 4, 6] * (BINNED // 4), np.float32) * s).astype(np.float32)
+    r = check(x, FP4 + [(3, 0)], 128)
+    assert (r.encoding, r.bias_index, r.mse) == (1, 127, 0.0)       # exactly zero, as with the direct evaluation
+    r = check(np.zeros(BINNED, np.float32), FP8, 111)
+    assert (r.encoding, r.bias_index, r.mse) == (0, 0, 0.0)

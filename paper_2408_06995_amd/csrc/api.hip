@@ -1,6 +1,7 @@
 // C ABI of libfpq (see include/fpq.h): argument validation on the host, then kernel launches on
 // the caller's stream.  No entry point allocates, synchronizes or keeps a pointer.
 #include <math.h>
+#include <stdlib.h>
 #include <string.h>
 
 #include "fpq_dev.h"
@@ -93,9 +94,13 @@ int resolve_kinds(fpq_format_t fx, float cx, fpq_format_t fw, float cw, int acc_
         if (xk == OPK_GENERIC8 || wk == OPK_GENERIC8 || wk == OPK_GENERIC4) return FPQ_ERR_UNSUPPORTED;
     } else if (acc_mode == FPQ_ACC_FP32) {
         if (!(xk == OPK_FP8 && (wk == OPK_FP8 || wk == OPK_FP4))) {
-            xk = OPK_GENERIC8;
-            wk = is_four_bit(fw) ? OPK_GENERIC4 : OPK_GENERIC8;
-            ax = aw = 1.0f;
+            // exponents of at most 4 bits fit a half's 5 without meeting its infinities; biases so far out that the factor
+            // 2^(15 - b) of the two operands could leave fp32 take the arithmetic decode, as wider exponents do
+            const bool half = fx.ebits <= 4 && fw.ebits <= 4 && abs(fx.bias) <= 48 && abs(fw.bias) <= 48;
+            xk = half ? OPK_HALF8 : OPK_GENERIC8;
+            wk = is_four_bit(fw) ? (half ? OPK_HALF4 : OPK_GENERIC4) : (half ? OPK_HALF8 : OPK_GENERIC8);
+            ax = half ? (float)ldexp(1.0, 15 - fx.bias) : 1.0f;
+            aw = half ? (float)ldexp(1.0, 15 - fw.bias) : 1.0f;
         }
     } else {
         return FPQ_ERR_UNSUPPORTED;

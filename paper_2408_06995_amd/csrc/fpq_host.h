@@ -63,7 +63,9 @@ enum OperandKind : int {
     OPK_BF8 = 1,      // (5, 2, b): hardware E5M2 bit pattern, value * 2^(15 - b)
     OPK_FP4 = 2,      // (2, 1, b): hardware E2M1 bit pattern, value * 2^(1 - b), two codes per byte
     OPK_GENERIC8 = 3, // any other format, one code per byte, decoded arithmetically
-    OPK_GENERIC4 = 4  // any other format of <= 4 bits, two codes per byte, decoded arithmetically
+    OPK_GENERIC4 = 4, // any other format of <= 4 bits, two codes per byte, decoded arithmetically
+    OPK_HALF8 = 5,    // a format with e <= 4, one code per byte, moved into the bits of a half: value * 2^(b - 15)
+    OPK_HALF4 = 6     // the same with two codes per byte
 };
 
 struct GemmArgs {

@@ -11,8 +11,9 @@
 // Codes stay codes (1 byte, or 4 bits for FP4 weights) all the way into registers.  Two arithmetic
 // back ends consume them:
 //   ACC_FP32      codes are expanded to bf16 in registers (hardware scaled converts for E4M3 /
-//                 E2M1 bit patterns, shifts and one multiply for any other ExMy) and multiplied by
-//                 the bf16 MFMA, whose fp32 accumulation keeps every product bit;
+//                 E2M1 bit patterns, shifts and two multiplies for formats with e >= 5) or, for the other
+//                 formats, shifted into halves, and multiplied by the bf16 / f16 MFMA, whose fp32
+//                 accumulation keeps every product bit;
 //   ACC_FP8_MFMA  codes are fed to the 8-bit / 4-bit MFMA (32x32x64) directly.
 // K ordering inside a 128-code step is private to this file: any order is valid as long as both
 // operands use the same one, and each back end picks the order its register layout wants.
@@ -216,7 +217,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, int block, uint8_t*
                     for (int i = 0; i < MI; ++i)
 #pragma unroll
                         for (int jj = 0; jj < NI; ++jj)
-                            acc[i][jj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pfr[i], qfr[jj], acc[i][jj], 0, 0, 0);
+                            acc[i][jj] = mfma_exact<PKIND>(pfr[i], qfr[jj], acc[i][jj]);
                 }
             }
         } else {
@@ -722,6 +723,9 @@ int launch_gemm_grouped(const GroupedArgs& g, hipStream_t st)
     }
     if (a.xkind == OPK_FP8 && a.wkind == OPK_FP8) return launch_grouped_one<OPK_FP8, OPK_FP8, FPQ_ACC_FP32>(g, st);
     if (a.xkind == OPK_FP8 && a.wkind == OPK_FP4) return launch_grouped_one<OPK_FP8, OPK_FP4, FPQ_ACC_FP32>(g, st);
+    if (a.xkind == OPK_HALF8)
+        return kind_is_4bit(a.wkind) ? launch_grouped_one<OPK_HALF8, OPK_HALF4, FPQ_ACC_FP32>(g, st)
+                                     : launch_grouped_one<OPK_HALF8, OPK_HALF8, FPQ_ACC_FP32>(g, st);
     if (kind_is_4bit(a.wkind)) return launch_grouped_one<OPK_GENERIC8, OPK_GENERIC4, FPQ_ACC_FP32>(g, st);
     return launch_grouped_one<OPK_GENERIC8, OPK_GENERIC8, FPQ_ACC_FP32>(g, st);
 }
@@ -750,6 +754,9 @@ int launch_gemm(const GemmArgs& a, hipStream_t st)
     }
     if (a.xkind == OPK_FP8 && a.wkind == OPK_FP8) return launch_conv_or_linear<OPK_FP8, OPK_FP8, FPQ_ACC_FP32>(a, st);
     if (a.xkind == OPK_FP8 && a.wkind == OPK_FP4) return launch_conv_or_linear<OPK_FP8, OPK_FP4, FPQ_ACC_FP32>(a, st);
+    if (a.xkind == OPK_HALF8)
+        return kind_is_4bit(a.wkind) ? launch_conv_or_linear<OPK_HALF8, OPK_HALF4, FPQ_ACC_FP32>(a, st)
+                                     : launch_conv_or_linear<OPK_HALF8, OPK_HALF8, FPQ_ACC_FP32>(a, st);
     // every other pairing: arithmetic decode of both operands
     if (kind_is_4bit(a.wkind)) return launch_conv_or_linear<OPK_GENERIC8, OPK_GENERIC4, FPQ_ACC_FP32>(a, st);
     return launch_conv_or_linear<OPK_GENERIC8, OPK_GENERIC8, FPQ_ACC_FP32>(a, st);

@@ -81,6 +81,18 @@ __device__ __forceinline__ uint32_t generic_pair(uint32_t c0, uint32_t c1, const
     return b0 | (b1 << 16);
 }
 
+// Codes of a format with e <= 4 as halves: the exponent and mantissa fields, shifted into place, are a half whose value is
+// Eq. (5) times 2^(b - 15), the subnormal row included (a half's own subnormals); the factor goes into the epilogue.
+// Given words with a code in the top bits of each half, one arithmetic shift moves the fields down and one mask takes the
+// copies of the sign away: with the byte permute three vector instructions per pair, where the arithmetic decode of
+// generic_pair takes about fourteen.  Halves of at most 8 significant bits multiply exactly into fp32.
+typedef short v2s __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t half_pair(uint32_t top, short shift, uint32_t mask)
+{
+    const v2s s = {shift, shift};
+    return __builtin_bit_cast(uint32_t, (v2s)(__builtin_bit_cast(v2s, top) >> s)) & mask;
+}
+
 template <int KIND>
 __device__ __forceinline__ v8bf decode8(uint32_t lo, uint32_t hi, const GenFmt& f)
 {
@@ -109,6 +121,24 @@ __device__ __forceinline__ v8bf decode8(uint32_t lo, uint32_t hi, const GenFmt& 
         o.u[1] = generic_pair((lo >> 16) & 0xffu, lo >> 24, f);
         o.u[2] = generic_pair(hi & 0xffu, (hi >> 8) & 0xffu, f);
         o.u[3] = generic_pair((hi >> 16) & 0xffu, hi >> 24, f);
+    } else if constexpr (KIND == OPK_HALF8 || KIND == OPK_HALF4) {
+        const int em = f.e + f.m;
+        const short shift = (short)(5 - f.e);
+        const uint32_t one = 0x8000u | (((1u << em) - 1u) << (10 - f.m));
+        const uint32_t mask = one | (one << 16);
+        if constexpr (KIND == OPK_HALF8) {
+            const uint32_t a = lo << (7 - em), b = hi << (7 - em);            // sign in bit 7 of every byte
+            o.u[0] = half_pair(__builtin_amdgcn_perm(a, a, 0x010c000cu), shift, mask);   // bytes 0, 1 into the halves' upper bytes
+            o.u[1] = half_pair(__builtin_amdgcn_perm(a, a, 0x030c020cu), shift, mask);
+            o.u[2] = half_pair(__builtin_amdgcn_perm(b, b, 0x010c000cu), shift, mask);
+            o.u[3] = half_pair(__builtin_amdgcn_perm(b, b, 0x030c020cu), shift, mask);
+        } else {                                                              // eight 4-bit codes in lo
+            const uint32_t odd = lo << (3 - em), even = odd << 4;             // sign in bit 7 of every byte, codes 2j + 1 / 2j
+            o.u[0] = half_pair(__builtin_amdgcn_perm(odd, even, 0x040c000cu), shift, mask);
+            o.u[1] = half_pair(__builtin_amdgcn_perm(odd, even, 0x050c010cu), shift, mask);
+            o.u[2] = half_pair(__builtin_amdgcn_perm(odd, even, 0x060c020cu), shift, mask);
+            o.u[3] = half_pair(__builtin_amdgcn_perm(odd, even, 0x070c030cu), shift, mask);
+        }
     } else {   // OPK_GENERIC4: eight 4-bit codes in lo
         o.u[0] = generic_pair(lo & 0xfu, (lo >> 4) & 0xfu, f);
         o.u[1] = generic_pair((lo >> 8) & 0xfu, (lo >> 12) & 0xfu, f);
@@ -118,7 +148,18 @@ __device__ __forceinline__ v8bf decode8(uint32_t lo, uint32_t hi, const GenFmt& 
     return o.v;
 }
 
-constexpr bool kind_is_4bit(int k) { return k == OPK_FP4 || k == OPK_GENERIC4; }
+constexpr bool kind_is_4bit(int k) { return k == OPK_FP4 || k == OPK_GENERIC4 || k == OPK_HALF4; }
+
+// One 32 x 32 x 16 step of the fp32-accumulate mode on fragments of decode8 (both operands are halves or both bf16).
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+template <int KIND>
+__device__ __forceinline__ v16f mfma_exact(v8bf a, v8bf b, v16f c)
+{
+    if constexpr (KIND == OPK_HALF8 || KIND == OPK_HALF4)
+        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b), c, 0, 0, 0);
+    else
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
 // Format selector of the f8f6f4 MFMA: 0 = E4M3, 1 = E5M2, 4 = E2M1.
 constexpr int mfma_fmt(int k) { return k == OPK_FP8 ? 0 : (k == OPK_BF8 ? 1 : 4); }
 

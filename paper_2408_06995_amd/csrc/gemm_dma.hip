@@ -131,6 +131,7 @@ bool gemm_dma_applicable(const GemmArgs& a)
     if (a.yq) return a.xkind == OPK_FP8 && (a.wkind == OPK_FP8 || a.wkind == OPK_FP4);   // codes out: see gemm_dma_q.hip
     if (a.acc_mode == FPQ_ACC_FP8_MFMA) return a.xkind == OPK_FP8 && (a.wkind == OPK_FP8 || a.wkind == OPK_FP4);
     return (a.xkind == OPK_FP8 && (a.wkind == OPK_FP8 || a.wkind == OPK_FP4)) ||
+           (a.xkind == OPK_HALF8 && (a.wkind == OPK_HALF8 || a.wkind == OPK_HALF4)) ||
            (a.xkind == OPK_GENERIC8 && (a.wkind == OPK_GENERIC8 || a.wkind == OPK_GENERIC4));
 }
 
@@ -144,6 +145,8 @@ int launch_gemm_dma(const GemmArgs& a, hipStream_t st)
     }
     if (a.xkind == OPK_FP8 && a.wkind == OPK_FP8) return launch_dma_shape<OPK_FP8, OPK_FP8, FPQ_ACC_FP32>(a, st);
     if (a.xkind == OPK_FP8 && a.wkind == OPK_FP4) return launch_dma_shape<OPK_FP8, OPK_FP4, FPQ_ACC_FP32>(a, st);
+    if (a.xkind == OPK_HALF8 && a.wkind == OPK_HALF4) return launch_dma_shape<OPK_HALF8, OPK_HALF4, FPQ_ACC_FP32>(a, st);
+    if (a.xkind == OPK_HALF8 && a.wkind == OPK_HALF8) return launch_dma_shape<OPK_HALF8, OPK_HALF8, FPQ_ACC_FP32>(a, st);
     if (a.xkind == OPK_GENERIC8 && a.wkind == OPK_GENERIC4) return launch_dma_shape<OPK_GENERIC8, OPK_GENERIC4, FPQ_ACC_FP32>(a, st);
     if (a.xkind == OPK_GENERIC8 && a.wkind == OPK_GENERIC8) return launch_dma_shape<OPK_GENERIC8, OPK_GENERIC8, FPQ_ACC_FP32>(a, st);
     return FPQ_ERR_UNSUPPORTED;

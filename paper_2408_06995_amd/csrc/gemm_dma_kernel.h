@@ -406,8 +406,7 @@ __global__ __launch_bounds__(256, ((BX <= 128 && NSTAGE <= 2) ? 2 : 1)) void gem
 #pragma unroll
             for (int k = 0; k < NM; ++k) {
                 const int i = k / NI, jj = k - i * NI;
-                acc[i][jj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[st & 1][i], frag[st & 1][MI + jj], acc[i][jj],
-                                                                    0, 0, 0);
+                acc[i][jj] = mfma_exact<PKIND>(frag[st & 1][i], frag[st & 1][MI + jj], acc[i][jj]);
                 if (st == 6 && k == 0) tail_sync(mode);
 #pragma unroll
                 for (int f = k; f < NF; f += NM) {

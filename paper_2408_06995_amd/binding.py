@@ -1,9 +1,12 @@
-"""Thin ctypes binding of libfpq.so: same names as the C ABI (include/fpq.h), argument marshalling only.
+"""Thin binding of libfpq.so: same names as the C ABI (include/fpq.h), argument marshalling only.
 
 Tensors are torch tensors on the GPU (PyTorch supplies device memory and streams, nothing else);
-every function below forwards their data pointers to the C entry point of the same name on the
+every function forwards their data pointers to the C entry point of the same name on the
 current torch stream and raises FpqError on a non-zero status.  There is no CPU fallback: if the
 shared library is missing or does not load, importing the functions' library handle fails.
+
+The calls that a program makes per layer and step are in the native extension _fpqcall (csrc/pycall.cpp, parameters and
+defaults at the end of this file); what is called once (sizes, plans, packing) goes through ctypes here.
 """
 import ctypes as C
 import os
@@ -256,16 +259,6 @@ def fpq_search_workspace_size(n, n_enc, n_bias):
     return lib().fpq_search_workspace_size(n, int(n_enc), int(n_bias))
 
 
-def fpq_search_format(x, encodings, n_bias, mse_out, result, workspace):
-    """encodings: [(e, m), ...]; mse_out: float32 tensor [n_enc * n_bias] or None; result: uint8 tensor of 40 bytes
-    (read it back with search_result())."""
-    ee = (C.c_int32 * len(encodings))(*[int(e) for e, _ in encodings])
-    mm = (C.c_int32 * len(encodings))(*[int(m) for _, m in encodings])
-    _check(lib().fpq_search_format(_ptr(x), x.numel(), C.cast(ee, C.c_void_p), C.cast(mm, C.c_void_p), len(encodings),
-                                   int(n_bias), _ptr(mse_out), _ptr(result), _ptr(workspace),
-                                   workspace.numel() * workspace.element_size(), _stream()), "fpq_search_format")
-
-
 def search_result(result):
     """Device result buffer of fpq_search_format -> fpq_search_result (synchronises)."""
     return fpq_search_result.from_buffer_copy(bytes(result.cpu().numpy().tobytes()[:C.sizeof(fpq_search_result)]))
@@ -282,22 +275,6 @@ def fpq_count_zeros(x, x_kind, n, f, count_out, workspace):
                                  _stream()), "fpq_count_zeros")
 
 
-def fpq_absmax(x, maxval, absmax_out, scale_out, workspace):
-    _check(lib().fpq_absmax(_ptr(x), x.numel(), float(maxval), _ptr(absmax_out), _ptr(scale_out), _ptr(workspace),
-                            workspace.numel() * workspace.element_size(), _stream()), "fpq_absmax")
-
-
-def fpq_quantize(x, f, scale, scale_dev, codes):
-    _check(lib().fpq_quantize(_ptr(x), x.numel(), fmt(f), float(scale), _ptr(scale_dev), _ptr(codes), _stream()),
-           "fpq_quantize")
-
-
-def fpq_quantize_nhwc(x, f, scale, scale_dev, codes):
-    B, Cc, H, W = x.shape
-    _check(lib().fpq_quantize_nhwc(_ptr(x), B, Cc, H, W, fmt(f), float(scale), _ptr(scale_dev), _ptr(codes), _stream()),
-           "fpq_quantize_nhwc")
-
-
 def fpq_dequantize(codes, f, scale, out):
     _check(lib().fpq_dequantize(_ptr(codes), codes.numel(), fmt(f), float(scale), _ptr(out), _stream()), "fpq_dequantize")
 
@@ -308,12 +285,6 @@ def fpq_pack_weights(w, f, scale, mask, packed, scale_out, codes_out=None):
     _check(lib().fpq_pack_weights(_ptr(w), N, Cin, kh, kw, fmt(f), _ptr(scale), _ptr(mask), _ptr(packed),
                                   packed.numel() * packed.element_size(), _ptr(scale_out), _ptr(codes_out), _stream()),
            "fpq_pack_weights")
-
-
-def fpq_gemm(x, x_is_fp32, fx, sx, sx_dev, packed_w, fw, sw, bias, y, M, N, K, acc_mode=FPQ_ACC_FP32, workspace=None):
-    wb = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().fpq_gemm(_ptr(x), int(x_is_fp32), fmt(fx), float(sx), _ptr(sx_dev), _ptr(packed_w), fmt(fw), _ptr(sw),
-                          _ptr(bias), _ptr(y), M, N, K, int(acc_mode), _ptr(workspace), wb, _stream()), "fpq_gemm")
 
 
 def gemm_problems(items):
@@ -330,12 +301,6 @@ def fpq_gemm_grouped_workspace_size(problems, x_is_fp32):
     return lib().fpq_gemm_grouped_workspace_size(problems, len(problems), int(x_is_fp32))
 
 
-def fpq_gemm_grouped(problems, x_is_fp32, fx, fw, acc_mode=FPQ_ACC_FP32, workspace=None):
-    wb = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().fpq_gemm_grouped(problems, len(problems), int(x_is_fp32), fmt(fx), fmt(fw), int(acc_mode), _ptr(workspace),
-                                  wb, _stream()), "fpq_gemm_grouped")
-
-
 def fpq_packed_sparse_size(N, Cin, kh, kw, f):
     return lib().fpq_packed_sparse_size(N, Cin, kh, kw, fmt(f))
 
@@ -349,37 +314,12 @@ def fpq_pack_weights_sparse(w, f, scale, mask, packed, scale_out, codes_out, dro
                                          _ptr(dropped_out), _stream()), "fpq_pack_weights_sparse")
 
 
-def fpq_gemm_sparse(x, x_is_fp32, fx, sx, sx_dev, packed_sparse, fw, sw, bias, y, M, N, K, workspace=None):
-    wb = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().fpq_gemm_sparse(_ptr(x), int(x_is_fp32), fmt(fx), float(sx), _ptr(sx_dev), _ptr(packed_sparse), fmt(fw),
-                                 _ptr(sw), _ptr(bias), _ptr(y), M, N, K, _ptr(workspace), wb, _stream()), "fpq_gemm_sparse")
-
-
-def fpq_conv2d_sparse(x, x_is_fp32, fx, sx, sx_dev, packed_sparse, fw, sw, bias, y, B, Cin, H, W, Cout, kh, kw, stride, pad,
-                      workspace=None):
-    wb = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().fpq_conv2d_sparse(_ptr(x), int(x_is_fp32), fmt(fx), float(sx), _ptr(sx_dev), _ptr(packed_sparse), fmt(fw),
-                                   _ptr(sw), _ptr(bias), _ptr(y), B, Cin, H, W, Cout, kh, kw, stride, pad, _ptr(workspace), wb,
-                                   _stream()), "fpq_conv2d_sparse")
-
-
 class fpq_int_params(C.Structure):
     _fields_ = [("scale", C.c_float), ("zero_point", C.c_int32), ("min", C.c_float), ("max", C.c_float)]
 
 
-def fpq_int_calibrate(x, bits, params_out, workspace):
-    """params_out: uint8 tensor of 16 bytes (read it back with int_params())."""
-    _check(lib().fpq_int_calibrate(_ptr(x), x.numel(), int(bits), _ptr(params_out), _ptr(workspace),
-                                   workspace.numel() * workspace.element_size(), _stream()), "fpq_int_calibrate")
-
-
 def int_params(params):
     return fpq_int_params.from_buffer_copy(bytes(params.cpu().numpy().tobytes()[:C.sizeof(fpq_int_params)]))
-
-
-def fpq_int_quantize(x, bits, scale, zero_point, params_dev, codes):
-    _check(lib().fpq_int_quantize(_ptr(x), x.numel(), int(bits), float(scale), int(zero_point), _ptr(params_dev), _ptr(codes),
-                                  _stream()), "fpq_int_quantize")
 
 
 def fpq_int_packed_size(N, K, bits):
@@ -396,12 +336,6 @@ def fpq_int_gemm_workspace_size(M):
     return lib().fpq_int_gemm_workspace_size(M)
 
 
-def fpq_int_gemm(xcodes, sx, zx, px_dev, packed_w, wbits, sw, zw, bias, y, M, N, K, workspace):
-    _check(lib().fpq_int_gemm(_ptr(xcodes), float(sx), int(zx), _ptr(px_dev), _ptr(packed_w), int(wbits), _ptr(sw), _ptr(zw),
-                              _ptr(bias), _ptr(y), M, N, K, _ptr(workspace), workspace.numel() * workspace.element_size(),
-                              _stream()), "fpq_int_gemm")
-
-
 FPQ_PROBE_MFMA_BF16, FPQ_PROBE_MFMA_FP8, FPQ_PROBE_COPY, FPQ_PROBE_MFMA_DECODE_64, FPQ_PROBE_MFMA_DECODE_32, FPQ_PROBE_FILL = 0, 1, 2, 3, 4, 5
 
 
@@ -413,36 +347,6 @@ def fpq_probe_peak(kind, iterations, src, dst):
     return work.value
 
 
-def fpq_gemm_noalloc(x, x_is_fp32, fx, sx, sx_dev, packed_w, fw, sw, bias, y, M, N, K, acc_mode=FPQ_ACC_FP32):
-    _check(lib().fpq_gemm_noalloc(_ptr(x), int(x_is_fp32), fmt(fx), float(sx), _ptr(sx_dev), _ptr(packed_w), fmt(fw),
-                                  _ptr(sw), _ptr(bias), _ptr(y), M, N, K, int(acc_mode), _stream()), "fpq_gemm_noalloc")
-
-
-def fpq_conv2d(x, x_is_fp32, fx, sx, sx_dev, packed_w, fw, sw, bias, y, B, Cin, H, W, Cout, kh, kw, stride, pad,
-               acc_mode=FPQ_ACC_FP32, workspace=None):
-    wb = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().fpq_conv2d(_ptr(x), int(x_is_fp32), fmt(fx), float(sx), _ptr(sx_dev), _ptr(packed_w), fmt(fw), _ptr(sw),
-                            _ptr(bias), _ptr(y), B, Cin, H, W, Cout, kh, kw, stride, pad, int(acc_mode),
-                            _ptr(workspace), wb, _stream()), "fpq_conv2d")
-
-
-def fpq_gemm_codes_out(x, x_is_fp32, fx, sx, sx_dev, packed_w, fw, sw, bias, fy, sy, sy_dev, yq, M, N, K,
-                       acc_mode=FPQ_ACC_FP32, workspace=None):
-    wb = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().fpq_gemm_codes_out(_ptr(x), int(x_is_fp32), fmt(fx), float(sx), _ptr(sx_dev), _ptr(packed_w), fmt(fw),
-                                    _ptr(sw), _ptr(bias), fmt(fy), float(sy), _ptr(sy_dev), _ptr(yq), M, N, K,
-                                    int(acc_mode), _ptr(workspace), wb, _stream()), "fpq_gemm_codes_out")
-
-
-def fpq_conv2d_codes_out(x, x_is_fp32, fx, sx, sx_dev, packed_w, fw, sw, bias, fy, sy, sy_dev, yq, B, Cin, H, W, Cout,
-                         kh, kw, stride, pad, acc_mode=FPQ_ACC_FP32, workspace=None):
-    wb = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().fpq_conv2d_codes_out(_ptr(x), int(x_is_fp32), fmt(fx), float(sx), _ptr(sx_dev), _ptr(packed_w), fmt(fw),
-                                      _ptr(sw), _ptr(bias), fmt(fy), float(sy), _ptr(sy_dev), _ptr(yq), B, Cin, H, W,
-                                      Cout, kh, kw, stride, pad, int(acc_mode), _ptr(workspace), wb, _stream()),
-           "fpq_conv2d_codes_out")
-
-
 def fpq_rl_workspace_size(M, N, K):
     return lib().fpq_rl_workspace_size(M, N, K)
 
@@ -450,13 +354,6 @@ def fpq_rl_workspace_size(M, N, K):
 def fpq_rl_init_alpha(w, sw, f, alpha):
     N, K = w.shape
     _check(lib().fpq_rl_init_alpha(_ptr(w), _ptr(sw), N, K, fmt(f), _ptr(alpha), _stream()), "fpq_rl_init_alpha")
-
-
-def fpq_rl_step(w, sw, f, alpha, a, lr, reg_weight, loss_out, grad_out, workspace):
-    N, K = w.shape
-    _check(lib().fpq_rl_step(_ptr(w), _ptr(sw), N, K, fmt(f), _ptr(alpha), _ptr(a), a.shape[0], float(lr), float(reg_weight),
-                             _ptr(loss_out), _ptr(grad_out), _ptr(workspace), workspace.numel() * workspace.element_size(),
-                             _stream()), "fpq_rl_step")
 
 
 def fpq_rl_mask(alpha, mask):
@@ -471,3 +368,51 @@ def fpq_packed_check(packed, N, Cin, kh, kw, f):
 def fpq_rl_im2col(x, kh, kw, stride, pad, a):
     B_, C_, H, W = x.shape
     _check(lib().fpq_rl_im2col(_ptr(x), B_, C_, H, W, kh, kw, stride, pad, _ptr(a), _stream()), "fpq_rl_im2col")
+
+
+# ---- calls made per layer and step: native marshalling (csrc/pycall.cpp)
+#
+#   fpq_gemm(x, x_is_fp32, fx, sx, sx_dev, packed_w, fw, sw, bias, y, M, N, K, acc_mode=FPQ_ACC_FP32, workspace=None)
+#   fpq_gemm_noalloc(..., M, N, K, acc_mode=FPQ_ACC_FP32)
+#   fpq_conv2d(x, x_is_fp32, fx, sx, sx_dev, packed_w, fw, sw, bias, y, B, Cin, H, W, Cout, kh, kw, stride, pad,
+#              acc_mode=FPQ_ACC_FP32, workspace=None)
+#   fpq_gemm_codes_out(x, x_is_fp32, fx, sx, sx_dev, packed_w, fw, sw, bias, fy, sy, sy_dev, yq, M, N, K,
+#                      acc_mode=FPQ_ACC_FP32, workspace=None)
+#   fpq_conv2d_codes_out(..., fy, sy, sy_dev, yq, B, Cin, H, W, Cout, kh, kw, stride, pad, acc_mode=FPQ_ACC_FP32, workspace=None)
+#   fpq_gemm_sparse(x, x_is_fp32, fx, sx, sx_dev, packed_sparse, fw, sw, bias, y, M, N, K, workspace=None)
+#   fpq_conv2d_sparse(..., y, B, Cin, H, W, Cout, kh, kw, stride, pad, workspace=None)
+#   fpq_gemm_grouped(problems, x_is_fp32, fx, fw, acc_mode=FPQ_ACC_FP32, workspace=None)     problems: gemm_problems()
+#   fpq_absmax(x, maxval, absmax_out, scale_out, workspace)
+#   fpq_quantize(x, f, scale, scale_dev, codes)
+#   fpq_quantize_nhwc(x, f, scale, scale_dev, codes)
+#   fpq_int_calibrate(x, bits, params_out, workspace)            params_out: uint8 tensor of 16 bytes (see int_params())
+#   fpq_int_quantize(x, bits, scale, zero_point, params_dev, codes)
+#   fpq_int_gemm(xcodes, sx, zx, px_dev, packed_w, wbits, sw, zw, bias, y, M, N, K, workspace)
+#   fpq_rl_step(w, sw, f, alpha, a, lr, reg_weight, loss_out, grad_out, workspace)
+#   fpq_search_format(x, encodings, n_bias, mse_out, result, workspace)
+#       encodings: [(e, m), ...]; mse_out: float32 tensor [n_enc * n_bias] or None; result: uint8 tensor of 40 bytes
+#       (read it back with search_result())
+
+NATIVE = ["fpq_gemm", "fpq_gemm_noalloc", "fpq_conv2d", "fpq_gemm_codes_out", "fpq_conv2d_codes_out",
+          "fpq_gemm_sparse", "fpq_conv2d_sparse", "fpq_gemm_grouped", "fpq_absmax", "fpq_quantize",
+          "fpq_quantize_nhwc", "fpq_int_calibrate", "fpq_int_quantize", "fpq_int_gemm", "fpq_rl_step",
+          "fpq_search_format"]
+
+
+def _resolve(name):
+    return C.cast(getattr(lib(), name), C.c_void_p).value
+
+
+def _not_built(name):
+    def missing(*args, **kwargs):
+        raise ImportError("_fpqcall not built: run `python -m paper_2408_06995_amd.build` (needed by %s)" % name)
+    return missing
+
+
+try:
+    from . import _fpqcall
+except ImportError:
+    globals().update((_n, _not_built(_n)) for _n in NATIVE)
+else:
+    _fpqcall.setup(_resolve, _check)
+    globals().update((_n, getattr(_fpqcall, _n)) for _n in NATIVE)

@@ -1,15 +1,17 @@
-"""Build libfpq.so (HIP, gfx950 only) in-tree with hipcc.
+"""Build libfpq.so (HIP, gfx950 only) and the binding's native calls (_fpqcall.so) in-tree.
 
 Usage: python -m paper_2408_06995_amd.build
 """
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libfpq.so")
+CALLS = os.path.join(HERE, "_fpqcall.so")
 OBJ = os.path.join(HERE, "_build")
 SOURCES = ["api.hip", "quant.hip", "search.hip", "sparsity.hip", "rounding.hip", "gemm.hip", "gemm_dma.hip", "gemm_dma_q.hip", "peaks.hip", "gemm_sparse.hip", "igemm.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
@@ -28,8 +30,14 @@ def _compile(src):
     return obj
 
 
+def build_calls():
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-missing-field-initializers",
+                           "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "pycall.cpp"), "-o", CALLS])
+
+
 def build():
     os.makedirs(OBJ, exist_ok=True)
+    build_calls()
     with ThreadPoolExecutor(max_workers=7) as ex:
         objs = list(ex.map(_compile, SOURCES))
     subprocess.check_call(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", OUT])

@@ -186,3 +186,10 @@ def test_argument_checks():
     assert L.fpq_rl_step(P, P, 4, 4, B.fmt((2, 1, 1, 5.0)), P, P, 4, 0.1, 0.1, P, None, P, 1 << 20, None) == -2
     assert L.fpq_rl_init_alpha(P, None, 4, 4, f, P, None) == -1
     assert B.fpq_rl_workspace_size(0, 4, 4) == 0
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (5, 3, 2), (16, 64, 16), (17, 65, 15), (33, 128, 48), (130, 67, 129), (257, 129, 66),
+                                   (300, 64, 4), (96, 132, 100), (2050, 130, 36)])
+def test_step_at_tile_edges(M, N, K):
+    """Shapes either side of the tiles (64, 128 rows), of the steps of 16 k and of the loads' four elements, in both products."""
+    check_step(N, K, M, E2M1, 9700 + M)

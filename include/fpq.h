@@ -279,7 +279,7 @@ int fpq_conv2d(const void *x, int x_is_fp32, fpq_format_t fx, float sx, const fl
  * With more than one slice the layer kernel writes partial sums to the workspace and a reduction kernel adds them.
  * For tests and benchmarks that have to state, or to cover, every launch configuration a workload uses. */
 typedef enum fpq_kernel {
-    FPQ_KERNEL_SMALL_TILE = 0, /* register-staged 128 x 128 / 64 x 64 tiles: any shape */
+    FPQ_KERNEL_SMALL_TILE = 0, /* tiles of at most 128 x 128 outputs: any shape */
     FPQ_KERNEL_256x160 = 1,    /* persistent 256 x 160 tiles, three LDS stages */
     FPQ_KERNEL_128x160 = 2,    /* persistent 128 x 160 tiles, two LDS stages, two workgroups per compute unit */
     FPQ_KERNEL_ROWS16 = 3      /* linear layers with at most 16 rows: K split over the wavefronts of a workgroup */
@@ -413,9 +413,10 @@ int fpq_int_gemm(const uint8_t *xcodes, float sx, int32_t zx, const fpq_int_para
  *                       256 bytes, then one 256-byte slot per problem with [scale, absmax] at byte 128);
  *   FPQ_X_CODES         x holds codes [M, K] with the scale sx_dev[0]; no workspace.
  * Every K must be a multiple of 16 and every x 16-byte aligned (FPQ_ERR_ALIGN).  Each y[M, N] receives exactly what
- * fpq_gemm computes for that problem with the register-staged kernel (bit for bit for shapes that fpq_gemm itself
- * gives to that kernel; the same sums in another order otherwise).  Meant for small problems: every problem runs on
- * 64 x 64 tiles (or, when all problems of a chunk of 32 have at most 16 rows, on the one-launch kernel for such layers). */
+ * fpq_gemm computes for that problem on small tiles (bit for bit for shapes that fpq_gemm itself gives to
+ * FPQ_KERNEL_SMALL_TILE with K of at most 896; the same sums, possibly in another order, otherwise).  Meant for small problems: every problem runs
+ * on tiles of at most 128 x 64 (or, when all problems of a chunk of 32 have at most 16 rows, on the one-launch kernel for
+ * such layers). */
 typedef struct fpq_gemm_problem {
     const void *x;
     const float *sx_dev;  /* FPQ_X_CODES only */

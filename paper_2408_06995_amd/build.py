@@ -13,7 +13,7 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libfpq.so")
 CALLS = os.path.join(HERE, "_fpqcall.so")
 OBJ = os.path.join(HERE, "_build")
-SOURCES = ["api.hip", "quant.hip", "search.hip", "sparsity.hip", "rounding.hip", "gemm.hip", "gemm_dma.hip", "gemm_dma_q.hip", "peaks.hip", "gemm_sparse.hip", "igemm.hip"]
+SOURCES = ["api.hip", "quant.hip", "search.hip", "sparsity.hip", "rounding.hip", "gemm.hip", "gemm_dma.hip", "gemm_dma_q.hip", "gemm_dma_s.hip", "gemm_dma_sq.hip", "gemm_wk.hip", "gemm_wk_q.hip", "peaks.hip", "gemm_sparse.hip", "igemm.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
@@ -38,7 +38,7 @@ def build_calls():
 def build():
     os.makedirs(OBJ, exist_ok=True)
     build_calls()
-    with ThreadPoolExecutor(max_workers=7) as ex:
+    with ThreadPoolExecutor(max_workers=8) as ex:
         objs = list(ex.map(_compile, SOURCES))
     subprocess.check_call(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", OUT])
     return OUT

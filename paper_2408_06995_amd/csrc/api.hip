@@ -444,9 +444,9 @@ size_t fpq_conv2d_workspace_size(int64_t B, int64_t Cin, int64_t H, int64_t W, i
 
 static void fill_plan(const GemmPlan& p, int64_t M, bool linear, fpq_plan_t* out)
 {
-    out->kernel = p.tile == TILE_256x160_S3 ? FPQ_KERNEL_256x160
+    out->kernel = (linear && M <= 16)         ? FPQ_KERNEL_ROWS16
+                  : p.tile == TILE_256x160_S3 ? FPQ_KERNEL_256x160
                   : p.tile == TILE_128x160_S2 ? FPQ_KERNEL_128x160
-                  : (linear && M <= 16)       ? FPQ_KERNEL_ROWS16
                                               : FPQ_KERNEL_SMALL_TILE;
     out->k_slices = p.splits;
 }
@@ -769,6 +769,7 @@ int fpq_gemm_grouped(const fpq_gemm_problem_t* problems, int count, int x_is_fp3
             d.bias = q.bias;
             d.y = q.y;
             d.M = (int)q.M; d.N = (int)q.N; d.K = (int)q.K; d.Kpad = (int)padded_k(q.K, 1);
+            d.w_bytes = (uint32_t)((is_four_bit(fw) ? d.Kpad / 2 : d.Kpad) * q.N);
             if (dyn) {
                 d.x32 = static_cast<const float*>(q.x);
                 d.xcodes = codes_at;

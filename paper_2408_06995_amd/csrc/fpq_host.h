@@ -121,6 +121,7 @@ struct GroupedProblem {
     float* y;               // [M, N]
     float* partials;        // dynamic-scale form: kGroupAbsmaxParts partial maxima
     int M, N, K, Kpad;      // K = codes per row of x (a multiple of 16), Kpad = packed row length in codes
+    uint32_t w_bytes;       // size of the packed weight rows
 };
 struct GroupedArgs {
     GroupedProblem p[kGroupMax];
@@ -131,37 +132,91 @@ static_assert(sizeof(GroupedArgs) <= 4096, "kernel arguments are limited to 4 KB
 
 // Kernel family / tile for a problem, and how many K slices share an output tile.
 enum GemmTile : int {
-    TILE_GENERIC = 0,    // register-staged 128x128 / 64x64 kernels: any shape
+    TILE_GENERIC = 0,    // register-staged 128x128 / 64x64 kernels: any shape, any operand kinds
     TILE_256x160_S3 = 1, // LDS-DMA kernel, three stages: deep K
-    TILE_128x160_S2 = 2  // LDS-DMA kernel, two stages, two workgroups per compute unit
+    TILE_128x160_S2 = 2, // LDS-DMA kernel, two stages, two workgroups per compute unit
+    TILE_128x64 = 3,     // the same pipeline on smaller tiles, two workgroups per compute unit
+    TILE_128x128 = 4,
+    TILE_WAVE_K4 = 5,    // 64 x 64 tiles, K split over the wavefronts (gemm_wk_kernel.h): four stages, one workgroup per compute unit
+    TILE_WAVE_K2 = 6     // two stages, two workgroups
 };
 struct GemmPlan {
     int tile;
     int splits;
 };
 
-// The large-tile kernels need N to be a multiple of 160 (every U-Net width, a multiple of 320, is) and pay off
-// from a few hundred thousand outputs on.
-// Deep K with enough 256-row tiles to fill the compute units takes the 256 x 160 tile with three
-// stages (one workgroup per compute unit); everything else takes the 128 x 160 tile with two stages,
-// of which two workgroups fit on a compute unit.  When the tile grid alone would leave compute units
-// idle and K is deep, K is cut into slices (each split costs a reduction launch and a round trip of
-// the partial sums, which only a deep K pays back): 2 to 4 slices of the 256-row tile when that gives
-// about one work item per compute unit with at least 32 K steps each, otherwise one work item per compute
-// unit of the 128-row tile (two when each keeps 20 K steps), with at least 8 K steps each.  Problems of a few tiles and a
-// short K are bound by the length of their serial K loop and are sliced as well.  At most 256 MB of
-// partial sums.
+// Which tile, from sweeps of tile x slices over the U-Net's layers and 60 shapes of other widths.
+//
+// Widths that are multiples of 160 (every U-Net width, a multiple of 320, is): deep K with enough 256-row tiles to fill the
+// compute units takes the 256 x 160 tile with three stages (one workgroup per compute unit), everything else the 128 x 160 tile
+// with two stages, of which two workgroups fit on a compute unit.  When the tile grid alone would leave compute units idle and K
+// is deep, K is cut into slices (each split costs a reduction launch and a round trip of the partial sums, which only a deep K
+// pays back): 2 to 4 slices of the 256-row tile when that gives about one work item per compute unit with at least 32 K steps
+// each, otherwise one work item per compute unit of the 128-row tile (two when each keeps 20 K steps), with at least 8 K steps
+// each.  At most 256 MB of partial sums.  Exceptions:
+//   - small outputs with a short K (M N <= 2 Mi, at most 20 steps of 128 codes), at most three columns of 160-wide tiles with a
+//     grid of at most 512 64 x 64 tiles, and grids of less than 32 tiles of 128 x 160: plan_small (4096 x 2880 -> 320: 27 us
+//     sliced, 19 us with K over the wavefronts; 40 x 5120 -> 1280: 18.9 and 9.8 us; 256 x 11520 -> 1280: 24.4 and 18.8 us);
+//   - a grid of less than 192 tiles of 128 x 160 that is not sliced, K of at least 8 steps: 128 x 64 tiles
+//     (2048 x 1280 -> 1280: 18.3 -> 13.7 us).
+//
+// Small problems and other widths, with K of at least 8 steps of 128 codes: grids of at most 256 tiles of 64 x 64 split K over the
+// wavefronts of a workgroup with four stages, and K over workgroups too as far as that leaves every compute unit at most one and
+// every slice 8 steps (slices need more than 20 steps to pay for their launch: 512 x 1280 -> 320 7.2 us whole, 8.6 us in two);
+// grids of at most 512 do so with two stages while K has at most 40 steps (beyond that 128 x 64 tiles in slices are faster:
+// 1024 x 9216 -> 1100 37.7 and 32.3 us).  A shorter K takes the register-staged kernel, which starts faster (616 x 768 -> 320:
+// 6.1 us against 6.3 us).  Larger grids take the 128 x 64, 128 x 128 or 128 x 160 tile and the slices that a model of the time
+// prefers: a step of 128 codes over 128 rows costs 6 ns per column of the tile (times 1.15 / 1 / 0.97 for the three) and per work
+// item on the busiest compute unit, 1.4 times that where a compute unit has one work item only; slices cost 3 us and their partial
+// sums at 5 TB/s (2048 x 11520 -> 1100: 79 us whole, 61 us in three).
+static inline GemmPlan plan_tiled(int64_t M, int64_t N, int64_t nk)
+{
+    const int bw[3] = {64, 128, 160};
+    const double per[3] = {1.15, 1.0, 0.97};
+    const int tile[3] = {TILE_128x64, TILE_128x128, TILE_128x160_S2};
+    GemmPlan best{TILE_128x64, 1};
+    double least = 1e30;
+    for (int i = 0; i < 3; ++i)
+        for (int s = 1; s == 1 || (s <= 4 && nk >= 16 * s); ++s) {
+            const int64_t items = ((M + 127) / 128) * ((N + bw[i] - 1) / bw[i]) * s;
+            const double busiest = items <= 256 ? 1.4 : (double)((items + 255) / 256);
+            double us = busiest * bw[i] * per[i] * 0.006 * (double)((nk + s - 1) / s);
+            if (s > 1) us += 3.0 + (double)s * (double)M * (double)N * 8.0 / 5e6;
+            if (us < least) { least = us; best = GemmPlan{tile[i], s}; }
+        }
+    return best;
+}
+static inline GemmPlan plan_small(int64_t M, int64_t N, int64_t nk)
+{
+    const int64_t t64 = ((M + 63) / 64) * ((N + 63) / 64);
+    if (t64 > 512 || (t64 > 256 && nk > 40)) return plan_tiled(M, N, nk);
+    if (nk < 8) return GemmPlan{TILE_GENERIC, 1};
+    if (t64 > 256) return GemmPlan{TILE_WAVE_K2, 1};
+    int64_t s = 256 / t64;
+    if (s > nk / 8) s = nk / 8;
+    if (s > 32) s = 32;
+    if (nk <= 20) s = 1;
+    return GemmPlan{TILE_WAVE_K4, (int)s};
+}
 static inline GemmPlan plan_gemm(int64_t M, int64_t N, int64_t Kpad)
 {
     GemmPlan p{TILE_GENERIC, 1};
-    if (N % 160 != 0 || M < 1) return p;
-    if (M <= 16) return p;   // at most 16 rows: the register-staged kernels (linear layers: one that splits K over its waves)
+    if (M < 1) return p;
     const int64_t nk = Kpad / 128;
-    // Small outputs with a short K: the register-staged kernel with its 64 x 64 tiles spreads them over more
-    // workgroups and has a shorter serial K loop (M = 616, K = 768: 6.5 us against 12 us).
-    if (M * N <= ((int64_t)2 << 20) && nk <= 20) return p;
+    if (M <= 16) {           // (linear layers of at most 16 rows have a kernel of their own)
+        p = plan_small(M, N, nk);
+        p.splits = 1;
+        return p;
+    }
+    const int64_t t64 = ((M + 63) / 64) * ((N + 63) / 64);
+    const int64_t tiles = ((M + 127) / 128) * ((N + 159) / 160);
+    if (N % 160 != 0 || (M * N <= ((int64_t)2 << 20) && nk <= 20) || (N <= 480 && t64 <= 512 && nk >= 8) ||
+        (tiles < 32 && nk <= 128)) {
+        p = plan_small(M, N, nk);
+        while (p.splits > 1 && p.splits * M * N * 4 > ((int64_t)256 << 20)) --p.splits;
+        return p;
+    }
     const int64_t tiles256 = ((M + 255) / 256) * (N / 160);
-    const int64_t tiles = ((M + 127) / 128) * (N / 160);
     int64_t s = 1;
     if (nk >= 16 && tiles256 >= 192) {
         p.tile = TILE_256x160_S3;
@@ -176,11 +231,10 @@ static inline GemmPlan plan_gemm(int64_t M, int64_t N, int64_t Kpad)
         if (nk / (2 * s) >= 20) s *= 2;             // ... two when each still has 20 K steps
         if (s > nk / 8) s = nk / 8;
         if (s > 32) s = 32;
-    } else if (tiles <= 16 && nk >= 4) {
-        s = nk / 2 < 8 ? nk / 2 : 8;
     }
     while (s > 1 && s * M * N * 4 > ((int64_t)256 << 20)) --s;
     if (s < 1) s = 1;
+    if (s == 1 && tiles < 192 && nk >= 8) p.tile = TILE_128x64;
     p.splits = (int)s;
     return p;
 }
@@ -248,7 +302,13 @@ int launch_gemm(const GemmArgs& a, hipStream_t st);
 int launch_gemm_skinny_dynamic(const GemmArgs& a, const float* x, const QParams& qx, float maxval, uint8_t* codes,
                                float* publish, hipStream_t st);
 // Grouped forms (gemm.hip, quant.hip): one launch each over all problems of g.
-int launch_gemm_grouped(const GroupedArgs& g, hipStream_t st);                 // register-staged 64 x 64 tiles, any shape
+int launch_gemm_grouped(const GroupedArgs& g, hipStream_t st);                 // small tiles, any shape
+int launch_wk_grouped(const GroupedArgs& g, hipStream_t st);                   // 64 x 64 tiles, K split over the wavefronts
+static inline bool grouped_wk_applicable(const GemmArgs& a)                    // operand kinds of that one
+{
+    if (a.acc_mode == FPQ_ACC_FP8_MFMA) return a.xkind == OPK_FP8 && (a.wkind == OPK_FP8 || a.wkind == OPK_FP4);
+    return (a.xkind == OPK_FP8 && (a.wkind == OPK_FP8 || a.wkind == OPK_FP4)) || a.xkind == OPK_HALF8;
+}
 bool skinny_grouped_applicable(const GroupedArgs& g);                           // all problems: at most 16 rows, <= 16 Ki activations
 int launch_gemm_skinny_dynamic_grouped(const GroupedArgs& g, const QParams& qx, float maxval, hipStream_t st);
 int launch_quantize_dynamic_grouped(const GroupedArgs& g, const QParams& qx, float maxval, hipStream_t st);
@@ -272,5 +332,9 @@ int launch_probe(int kind, int iters, const void* src, void* dst, size_t bytes, 
 bool gemm_dma_applicable(const GemmArgs& a);
 int launch_gemm_dma(const GemmArgs& a, hipStream_t st);
 int launch_gemm_dma_q(const GemmArgs& a, hipStream_t st);   // the same with the result as codes (a.yq)
+int launch_gemm_dma_s(const GemmArgs& a, hipStream_t st);   // small tiles
+int launch_gemm_dma_sq(const GemmArgs& a, hipStream_t st);
+int launch_gemm_wk(const GemmArgs& a, hipStream_t st);      // K split over the wavefronts
+int launch_gemm_wk_q(const GemmArgs& a, hipStream_t st);
 
 }  // namespace fpq

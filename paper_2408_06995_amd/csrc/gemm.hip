@@ -393,23 +393,6 @@ __global__ __launch_bounds__(256) void gemm_kernel(const GemmArgs a)
     gemm_tile<BX, BW, WGX, WGW, XKIND, WKIND, ACC, CONV>(a, blockIdx.x, smem);
 }
 
-// Grouped linear layers: blockIdx.y picks the problem, blockIdx.x the output tile within it (the grid is as wide as
-// the problem with the most tiles; workgroups beyond a problem's own tile count leave at once).
-__device__ __forceinline__ GemmArgs grouped_problem_args(const GroupedArgs& g, int pi)
-{
-    GemmArgs a = g.common;
-    const GroupedProblem& q = g.p[pi];
-    a.x = q.xcodes;
-    a.wrows = q.wrows;
-    a.sw = q.sw;
-    a.bias = q.bias;
-    a.sx_dev = q.sx_dev;
-    a.y = q.y;
-    a.M = q.M; a.N = q.N; a.Kpad = q.Kpad; a.Kreal = q.K;
-    a.B = q.M; a.H = 1; a.W = 1; a.Cp = q.K; a.Ho = 1; a.Wo = 1;
-    return a;
-}
-
 template <int XKIND, int WKIND, int ACC>
 __global__ __launch_bounds__(256) void gemm_grouped_kernel(const GroupedArgs g)
 {
@@ -712,10 +695,9 @@ static int launch_grouped_one(const GroupedArgs& g, hipStream_t st)
     return hipGetLastError() == hipSuccess ? FPQ_OK : FPQ_ERR_LAUNCH;
 }
 
-int launch_gemm_grouped(const GroupedArgs& g, hipStream_t st)
+static int launch_gemm_grouped_tiles(const GroupedArgs& g, hipStream_t st)
 {
     const GemmArgs& a = g.common;
-    if (g.count <= 0) return FPQ_OK;
     if (a.acc_mode == FPQ_ACC_FP8_MFMA) {
         if (a.xkind == OPK_FP8 && a.wkind == OPK_FP8) return launch_grouped_one<OPK_FP8, OPK_FP8, FPQ_ACC_FP8_MFMA>(g, st);
         if (a.xkind == OPK_FP8 && a.wkind == OPK_FP4) return launch_grouped_one<OPK_FP8, OPK_FP4, FPQ_ACC_FP8_MFMA>(g, st);
@@ -728,6 +710,33 @@ int launch_gemm_grouped(const GroupedArgs& g, hipStream_t st)
                                      : launch_grouped_one<OPK_HALF8, OPK_HALF8, FPQ_ACC_FP32>(g, st);
     if (kind_is_4bit(a.wkind)) return launch_grouped_one<OPK_GENERIC8, OPK_GENERIC4, FPQ_ACC_FP32>(g, st);
     return launch_grouped_one<OPK_GENERIC8, OPK_GENERIC8, FPQ_ACC_FP32>(g, st);
+}
+
+// The problems that fpq_gemm would give to the kernel with K split over the wavefronts go to that kernel (its sums have their
+// own order) while their tiles fit on the chip at once; the register-staged kernel, of which more workgroups fit on a compute
+// unit, is the faster one for more (30 x 1013 x 1264 -> 432: 113 us, 170 us on 128 x 64 tiles of the LDS-DMA kernel).
+int launch_gemm_grouped(const GroupedArgs& g, hipStream_t st)
+{
+    if (g.count <= 0) return FPQ_OK;
+    GroupedArgs part[2];
+    int which[kGroupMax];
+    int tiles = 0;
+    const bool wk = grouped_wk_applicable(g.common);
+    for (int i = 0; i < g.count; ++i) {
+        const GemmPlan plan = plan_gemm(g.p[i].M, g.p[i].N, g.p[i].Kpad);
+        which[i] = wk && (plan.tile == TILE_WAVE_K4 || plan.tile == TILE_WAVE_K2) ? 1 : 0;
+        if (which[i]) tiles += ((g.p[i].M + 63) / 64) * ((g.p[i].N + 63) / 64);
+    }
+    part[0].count = part[1].count = 0;
+    part[0].common = part[1].common = g.common;
+    for (int i = 0; i < g.count; ++i) {
+        GroupedArgs& to = part[tiles <= 512 ? which[i] : 0];
+        to.p[to.count++] = g.p[i];
+    }
+    int rc = FPQ_OK;
+    if (part[0].count) rc = launch_gemm_grouped_tiles(part[0], st);
+    if (rc == FPQ_OK && part[1].count) rc = launch_wk_grouped(part[1], st);
+    return rc;
 }
 
 int launch_gemm(const GemmArgs& a, hipStream_t st)

@@ -148,6 +148,25 @@ __device__ __forceinline__ v8bf decode8(uint32_t lo, uint32_t hi, const GenFmt& 
     return o.v;
 }
 
+// Grouped linear layers: blockIdx.y picks the problem, blockIdx.x the output tile within it (the grid is as wide as
+// the problem with the most tiles; workgroups beyond a problem's own tile count leave at once).
+__device__ __forceinline__ GemmArgs grouped_problem_args(const GroupedArgs& g, int pi)
+{
+    GemmArgs a = g.common;
+    const GroupedProblem& q = g.p[pi];
+    a.x = q.xcodes;
+    a.wrows = q.wrows;
+    a.sw = q.sw;
+    a.bias = q.bias;
+    a.sx_dev = q.sx_dev;
+    a.y = q.y;
+    a.M = q.M; a.N = q.N; a.Kpad = q.Kpad; a.Kreal = q.K;
+    a.B = q.M; a.H = 1; a.W = 1; a.Cp = q.K; a.Ho = 1; a.Wo = 1;
+    a.x_bytes = (uint32_t)q.M * (uint32_t)q.K;              // below 2^31
+    a.w_bytes = q.w_bytes;
+    return a;
+}
+
 constexpr bool kind_is_4bit(int k) { return k == OPK_FP4 || k == OPK_GENERIC4 || k == OPK_HALF4; }
 
 // One 32 x 32 x 16 step of the fp32-accumulate mode on fragments of decode8 (both operands are halves or both bf16).

@@ -118,16 +118,17 @@ template <int XKIND, int WKIND, int ACC>
 static int launch_dma_shape(const GemmArgs& a, hipStream_t st)
 {
     if (a.tile == TILE_128x160_S2)
-        return a.conv_out ? launch_dma_one<128, 160, 2, XKIND, WKIND, ACC, true, false>(a, st)
-                          : launch_dma_one<128, 160, 2, XKIND, WKIND, ACC, false, false>(a, st);
-    return a.conv_out ? launch_dma_one<256, 160, 3, XKIND, WKIND, ACC, true, false>(a, st)
-                      : launch_dma_one<256, 160, 3, XKIND, WKIND, ACC, false, false>(a, st);
+        return a.conv_out ? launch_dma_one<128, 160, 2, 1, XKIND, WKIND, ACC, true, false>(a, st)
+                          : launch_dma_one<128, 160, 2, 1, XKIND, WKIND, ACC, false, false>(a, st);
+    return a.conv_out ? launch_dma_one<256, 160, 3, 1, XKIND, WKIND, ACC, true, false>(a, st)
+                      : launch_dma_one<256, 160, 3, 1, XKIND, WKIND, ACC, false, false>(a, st);
 }
 
 // Operand kinds the large-tile kernels are instantiated for.
 bool gemm_dma_applicable(const GemmArgs& a)
 {
     if (a.tile == TILE_GENERIC || a.kh * a.kw > 31) return false;   // tap-validity masks are 31 bits
+    if (a.tile >= TILE_128x64 && (a.xkind == OPK_GENERIC8 || a.wkind == OPK_GENERIC8)) return false;
     if (a.yq) return a.xkind == OPK_FP8 && (a.wkind == OPK_FP8 || a.wkind == OPK_FP4);   // codes out: see gemm_dma_q.hip
     if (a.acc_mode == FPQ_ACC_FP8_MFMA) return a.xkind == OPK_FP8 && (a.wkind == OPK_FP8 || a.wkind == OPK_FP4);
     return (a.xkind == OPK_FP8 && (a.wkind == OPK_FP8 || a.wkind == OPK_FP4)) ||
@@ -137,6 +138,8 @@ bool gemm_dma_applicable(const GemmArgs& a)
 
 int launch_gemm_dma(const GemmArgs& a, hipStream_t st)
 {
+    if (a.tile == TILE_WAVE_K4 || a.tile == TILE_WAVE_K2) return a.yq ? launch_gemm_wk_q(a, st) : launch_gemm_wk(a, st);
+    if (a.tile == TILE_128x64 || a.tile == TILE_128x128) return a.yq ? launch_gemm_dma_sq(a, st) : launch_gemm_dma_s(a, st);
     if (a.yq) return launch_gemm_dma_q(a, st);
     if (a.acc_mode == FPQ_ACC_FP8_MFMA) {
         if (a.xkind == OPK_FP8 && a.wkind == OPK_FP8) return launch_dma_shape<OPK_FP8, OPK_FP8, FPQ_ACC_FP8_MFMA>(a, st);

@@ -1,8 +1,9 @@
 // Quantized linear / convolution layer on ExMy codes for gfx950: the large-tile kernel (template and its launcher;
-// gemm_dma.hip instantiates it for fp32 results, gemm_dma_q.hip for results that leave as codes).
+// gemm_dma.hip and gemm_dma_s.hip instantiate it for fp32 results, gemm_dma_q.hip and gemm_dma_sq.hip for results that leave as
+// codes).
 //
-// A workgroup of four wavefronts owns a BX x BW tile (BX activation rows, BW weight rows; the
-// wavefronts split the activation rows) and walks its K range in steps of 128 codes through an LDS
+// A workgroup of four wavefronts owns a BX x BW tile (BX activation rows, BW weight rows; WGW of the
+// wavefronts along the weight rows, 4 / WGW along the activation rows) and walks its K range in steps of 128 codes through an LDS
 // ring of two or three stages.  Codes travel global memory -> LDS without touching registers:
 // buffer_load_dwordx4 ... lds writes 64 lanes x 16 bytes to consecutive LDS addresses, and a lane
 // whose element does not exist (row beyond M or N, padding pixel of the convolution, K beyond the
@@ -45,6 +46,19 @@ __device__ __forceinline__ void dma16(v4i rsrc, unsigned voff, unsigned lds_addr
                  : "memory");
 }
 
+// The same for a wavefront that may have nothing left to load: live = all ones, or zero, and then no lane takes part.  The load
+// still counts in vmcnt, so the waits stay as they are, but nothing is moved; out-of-range offsets in its place would write
+// zeros to LDS at the rate of a real load (about 50 bytes per clock), 0.5 to 1 us at the end of every launch.
+// All 64 lanes of the calling wavefronts are active.
+__device__ __forceinline__ void dma16_live(v4i rsrc, unsigned voff, unsigned lds_addr, int live)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_mov_b32 exec_lo, %3\n\ts_mov_b32 exec_hi, %3\n\t"
+                 "buffer_load_dwordx4 %1, %2, 0 offen lds\n\ts_mov_b64 exec, -1"
+                 :
+                 : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(voff), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane(live))
+                 : "memory");
+}
+
 // Raw buffer descriptor: base address, no stride, size in bytes, 32-bit untyped data.
 __device__ __forceinline__ v4i make_rsrc(const void* base, unsigned bytes)
 {
@@ -62,6 +76,7 @@ __device__ __forceinline__ v4i make_rsrc(const void* base, unsigned bytes)
 constexpr int vmcnt_imm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
 
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));   // a 16-byte store at any 4-byte address
 // Results leave with streaming (non-temporal) stores: an output is far larger than the L2 and would
 // otherwise push out the operand tiles that other workgroups are about to re-read.
 __device__ __forceinline__ void store_out(float* p, float v) { __builtin_nontemporal_store(v, p); }
@@ -146,8 +161,8 @@ __device__ __forceinline__ void quad_transpose(float (&v)[4], bool b0, bool b1)
     }
 }
 
-template <int BX, int BW, int NSTAGE, int XKIND, int WKIND, int ACC, bool CONV, bool QOUT>
-__global__ __launch_bounds__(256, ((BX <= 128 && NSTAGE <= 2) ? 2 : 1)) void gemm_dma_kernel(const GemmArgs a)
+template <int BX, int BW, int NSTAGE, int WGW, int XKIND, int WKIND, int ACC, bool CONV, bool QOUT>
+__global__ __launch_bounds__(256, (BX <= 128 ? 2 : 1)) void gemm_dma_kernel(const GemmArgs a)
 {
     constexpr bool W4 = kind_is_4bit(WKIND);
     constexpr int XROWB = 128;
@@ -164,10 +179,12 @@ __global__ __launch_bounds__(256, ((BX <= 128 && NSTAGE <= 2) ? 2 : 1)) void gem
     // P = operand indexed by the accumulator registers, Q = operand indexed by the lane.
     // P = activations, Q = weights (see the epilogue for what that means for the stores).
     constexpr bool P_IS_W = false;
-    constexpr int TX = BX / 4;                 // activation rows per wave
-    constexpr int TP = P_IS_W ? BW : TX, TQ = P_IS_W ? TX : BW;
+    // the four wavefronts: 4 / WGW along the activation rows, WGW along the weight rows
+    constexpr int TX = BX * WGW / 4;           // activation rows per wave
+    constexpr int TW = BW / WGW;               // weight rows per wave
+    constexpr int TP = P_IS_W ? TW : TX, TQ = P_IS_W ? TX : TW;
     constexpr int MI = TP / 32, NI = TQ / 32;
-    static_assert(BW % 32 == 0 && TX % 32 == 0, "tile shape");
+    static_assert(TW % 32 == 0 && TX % 32 == 0, "tile shape");
     constexpr int PKIND = P_IS_W ? WKIND : XKIND, QKIND = P_IS_W ? XKIND : WKIND;
     constexpr int PROWB = P_IS_W ? WROWB : XROWB, QROWB = P_IS_W ? XROWB : WROWB;
     constexpr bool P4 = kind_is_4bit(PKIND), Q4 = kind_is_4bit(QKIND);
@@ -218,8 +235,13 @@ __global__ __launch_bounds__(256, ((BX <= 128 && NSTAGE <= 2) ? 2 : 1)) void gem
     unsigned wbase[WLD];
 
     bool ihas = true;                          // false once this workgroup has no more loads to issue
+    // How the loads after the last work item are kept from moving anything: by masking the lanes off (dma16_live), or by offsets
+    // out of range.  The masks cost scalar instructions at every load, which the 160-wide tiles have no free issue slots for
+    // (8 x 640 x 64 x 64 -> 320, 3 x 3: 93.4 us masked, 89.2 us not).
+    constexpr bool MASKED = BW < 160;
+    int live = -1;                             // what dma16_live wants
     auto x_refresh = [&]() {
-        x_sel = (ihas && x_k < a.Kreal) ? x_tap : 31;
+        x_sel = ((MASKED || ihas) && x_k < a.Kreal) ? x_tap : 31;
         x_delta = CONV ? (unsigned)((x_kh * a.W + x_kw) * a.Cp + x_ci) : (unsigned)x_k;
     };
 
@@ -288,9 +310,17 @@ __global__ __launch_bounds__(256, ((BX <= 128 && NSTAGE <= 2) ? 2 : 1)) void gem
         const unsigned xs = lds0 + stage * STAGE;
         if (idx < XLD) {
             const unsigned off = ((xmask[idx] >> x_sel) & 1u) ? xbase[idx] + x_delta : OOB;
-            dma16(xrsrc, off, xs + (4 * idx + wave) * 1024);
+            const unsigned to = xs + (4 * idx + wave) * 1024;
+            if constexpr (MASKED)
+                dma16_live(xrsrc, off, to, live);
+            else
+                dma16(xrsrc, off, to);
         } else {
-            dma16(wrsrc, wbase[idx - XLD], xs + XTILE + (4 * (idx - XLD) + wave) * 1024);
+            const unsigned to = xs + XTILE + (4 * (idx - XLD) + wave) * 1024;
+            if constexpr (MASKED)
+                dma16_live(wrsrc, wbase[idx - XLD], to, live);
+            else
+                dma16(wrsrc, wbase[idx - XLD], to);
         }
     };
     // After the LOADS loads of a step: move this lane's K position on by 128 codes.
@@ -319,9 +349,11 @@ __global__ __launch_bounds__(256, ((BX <= 128 && NSTAGE <= 2) ? 2 : 1)) void gem
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
-    const int xrow0 = wave * TX + l32;         // this lane's first activation row in the tile
-    const int prow0 = P_IS_W ? l32 : xrow0;
-    const int qrow0 = P_IS_W ? xrow0 : l32;
+    const int wave_x = wave / WGW, wave_w = wave % WGW;
+    const int xrow0 = wave_x * TX + l32;       // this lane's first activation row in the tile
+    const int wrow0 = wave_w * TW + l32;       // and weight row
+    const int prow0 = P_IS_W ? wrow0 : xrow0;
+    const int qrow0 = P_IS_W ? xrow0 : wrow0;
     const GenFmt wfm{a.we, a.wm, a.wb}, xfm{a.xe, a.xm, a.xb};
     const GenFmt pf = P_IS_W ? wfm : xfm, qf = P_IS_W ? xfm : wfm;
 
@@ -400,6 +432,7 @@ __global__ __launch_bounds__(256, ((BX <= 128 && NSTAGE <= 2) ? 2 : 1)) void gem
         asm volatile("" ::: "memory");
     };
 
+    constexpr int LSLOT = 3 * LOADS <= 6 * NM ? 3 : (2 * LOADS <= 6 * NM ? 2 : 1);   // slots per load
     auto compute = [&](int stage, int next_stage, int to_stage, int mode) {
 #pragma unroll
         for (int st = 0; st < 8; ++st) {
@@ -418,12 +451,12 @@ __global__ __launch_bounds__(256, ((BX <= 128 && NSTAGE <= 2) ? 2 : 1)) void gem
                     }
                     frag[(st + 1) & 1][f] = dec((st + 1) & 7, f);
                 }
-                // the loads of the step NSTAGE - 1 ahead: one every third slot
-                if ((st * NM + k) % 3 == 2 && (st * NM + k) / 3 < LOADS) issue_one((st * NM + k) / 3, to_stage);
+                // the loads of the step NSTAGE - 1 ahead: one every third slot (every one or two in small tiles)
+                if ((st * NM + k) % LSLOT == LSLOT - 1 && (st * NM + k) / LSLOT < LOADS) issue_one((st * NM + k) / LSLOT, to_stage);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        static_assert(3 * LOADS <= 6 * NM, "the loads of a step must be issued before its tail_sync");
+        static_assert(LSLOT * LOADS <= 6 * NM, "the loads of a step must be issued before its tail_sync");
     };
 
     // ---- FPQ_ACC_FP8_MFMA: codes feed the 8-bit / 4-bit MFMA directly, two 64-code MFMA steps per K step.  The
@@ -478,13 +511,14 @@ __global__ __launch_bounds__(256, ((BX <= 128 && NSTAGE <= 2) ? 2 : 1)) void gem
                 for (int f = k; f < NF; f += NM)
                     frag8[st ^ 1][f] = st == 0 ? lds_read8(stage, 1, f) : lds_read8(next_stage, 0, f);
                 if (st == 0) {
-                    if (2 * k < LOADS) issue_one(2 * k, to_stage);
-                    if (2 * k + 1 < LOADS) issue_one(2 * k + 1, to_stage);
+                    constexpr int PER = LOADS <= 2 * NM ? 2 : (LOADS + NM - 1) / NM;
+#pragma unroll
+                    for (int u = 0; u < PER; ++u)
+                        if (PER * k + u < LOADS) issue_one(PER * k + u, to_stage);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        static_assert(LOADS <= 2 * NM, "the loads of a step must be issued before its tail_sync");
     };
 
     // ---- epilogue of one work item: acc * (sx * alpha * sw[n]) + bias[n].
@@ -516,9 +550,10 @@ __global__ __launch_bounds__(256, ((BX <= 128 && NSTAGE <= 2) ? 2 : 1)) void gem
     const QParams qy{a.ym, a.yb, a.yem, a.yc};
     const float ry = QOUT ? inv_scale(a.sy, a.sy_dev) : 0.0f;
     auto epilogue = [&](int m0, int n0, int sl, int par) -> int {
-        const float* stab = reinterpret_cast<const float*>(smem + RING + par * 2048);
+        const float* stab = reinterpret_cast<const float*>(smem + RING + par * 2048) + wave_w * TW;
         const bool full = (m0 + BX <= a.M) && (n0 + BW <= a.N);   // whole tile inside the output
-        const int mw = m0 + wave * TX;                           // first row of this wave
+        const int mw = m0 + wave_x * TX;                         // first row of this wave
+        n0 += wave_w * TW;                                       // and first column
         const int qa = l32 >> 2, qb = l32 & 3;
         const bool b0 = qb & 1, b1 = qb & 2;
         if (QOUT && a.splits == 1) {
@@ -690,7 +725,51 @@ __global__ __launch_bounds__(256, ((BX <= 128 && NSTAGE <= 2) ? 2 : 1)) void gem
                 return W_AFTER_STORES;
             }
         }
-        // tiles that cross the edge of the output, or an output that does not allow 16-byte stores
+        if constexpr (CONV && !QOUT && BX <= 128) {
+            if (!accum && hw >= 4) {
+                // images whose size is no multiple of four pixels, or a tile that crosses the edge: the same transpose, but the
+                // four pixels of a lane can lie in two images or beyond the last one, and 16-byte stores are not aligned
+                unsigned plane = (unsigned)hw;             // per lane: uniform, the offsets of all planes would be kept in (spilled)
+                asm volatile("" : "+v"(plane));            // scalar registers, also through the main loop
+#pragma unroll
+                for (int i = 0; i < MI; ++i) {
+                    const int m = mw + 32 * i + 8 * qb + 4 * g;
+                    const int bi = m / hw;
+                    const int pix = m - bi * hw;
+                    const bool together = m + 3 < a.M && pix + 3 < hw;
+                    float* mp = yout + ((size_t)bi * a.N + n0 + 4 * qa) * plane + pix;
+                    const size_t next_image = (size_t)(a.N - 1) * plane;
+#pragma unroll
+                    for (int j = 0; j < NI; ++j) {
+                        float v[4][4];   // [pixel e][group q]
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+#pragma unroll
+                            for (int q4 = 0; q4 < 4; ++q4) v[e][q4] = acc[i][j][4 * q4 + e];
+                            quad_transpose(v[e], b0, b1);
+                        }
+#pragma unroll
+                        for (int q4 = 0; q4 < 4; ++q4) {
+                            if (n0 + 32 * j + 4 * qa + q4 >= a.N) continue;
+                            const float s1 = stab[32 * j + 4 * qa + q4] * sxa, b1v = stab[256 + 32 * j + 4 * qa + q4];
+                            float* yp = mp + (size_t)(32 * j + q4) * plane;
+                            if (together) {
+                                const v4f o = {v[0][q4] * s1 + b1v, v[1][q4] * s1 + b1v, v[2][q4] * s1 + b1v, v[3][q4] * s1 + b1v};
+                                __builtin_nontemporal_store(o, reinterpret_cast<v4f_any*>(yp));
+                            } else {
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) {
+                                    if (m + e >= a.M) break;
+                                    yp[pix + e < hw ? (size_t)e : (size_t)e + next_image] = v[e][q4] * s1 + b1v;
+                                }
+                            }
+                        }
+                    }
+                }
+                return W_DRAIN;
+            }
+        }
+        // tiles that cross the edge of the output, results that are added to y
         float sc[NI], bv[NI];
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
@@ -740,9 +819,17 @@ __global__ __launch_bounds__(256, ((BX <= 128 && NSTAGE <= 2) ? 2 : 1)) void gem
     // ---- main loop over the K steps of all work items of this workgroup.  Each wave issues LOADS buffer
     // loads per step and they complete in order.  The loads run NSTAGE - 1 steps ahead of the MFMAs,
     // across item boundaries.  Every step issues one group of LOADS loads; once the work items run out
-    // the group is a dummy (every offset out of range: zeros into a free ring slot, no memory traffic),
-    // which keeps the control flow and the vmcnt arithmetic uniform.
+    // the group moves nothing (no lane takes part, or every offset is out of range: zeros into a free ring slot), which
+    // keeps the control flow and the vmcnt arithmetic uniform.
     int istage = 0;
+    auto issue_nothing = [&]() {
+        live = 0;
+        if constexpr (!MASKED) {
+            x_sel = 31;
+#pragma unroll
+            for (int i = 0; i < WLD; ++i) wbase[i] = OOB;
+        }
+    };
     ihas = i_item < nitems;
     if (ihas) issue_setup();
     auto issued = [&]() {
@@ -751,20 +838,13 @@ __global__ __launch_bounds__(256, ((BX <= 128 && NSTAGE <= 2) ? 2 : 1)) void gem
         if (ihas && --i_rem == 0) {
             i_item += G;
             ihas = i_item < nitems;
-            if (ihas) {
+            if (ihas)
                 issue_setup();
-            } else {
-                x_sel = 31;
-#pragma unroll
-                for (int i = 0; i < WLD; ++i) wbase[i] = OOB;
-            }
+            else
+                issue_nothing();
         }
     };
-    if (!ihas) {
-        x_sel = 31;
-#pragma unroll
-        for (int i = 0; i < WLD; ++i) wbase[i] = OOB;
-    }
+    if (!ihas) issue_nothing();
 #pragma unroll
     for (int s = 0; s < NSTAGE - 1; ++s) {
 #pragma unroll
@@ -822,16 +902,21 @@ __global__ __launch_bounds__(256, ((BX <= 128 && NSTAGE <= 2) ? 2 : 1)) void gem
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // no load may land in LDS after the workgroup has gone
 }
 
+// LDS of one workgroup: ring + scale / bias slots
+constexpr int dma_lds_bytes(int bx, int bw, int nstage, bool w4)
+{
+    return nstage * (bx * 128 + (bw * (w4 ? 64 : 128) + 4095) / 4096 * 4096) + 4096;
+}
+
 // Adds up the K slices in the workspace (gemm_dma.hip): into y, or quantized into the code matrix.
 int launch_splitk_reduce(const GemmArgs& a, hipStream_t st);
 
-template <int BX, int BW, int NSTAGE, int XKIND, int WKIND, int ACC, bool CONV, bool QOUT>
+template <int BX, int BW, int NSTAGE, int WGW, int XKIND, int WKIND, int ACC, bool CONV, bool QOUT>
 static int launch_dma_one(const GemmArgs& a, hipStream_t st)
 {
-    constexpr int WROWB = kind_is_4bit(WKIND) ? 64 : 128;
-    constexpr int smem = NSTAGE * (BX * 128 + (BW * WROWB + 4095) / 4096 * 4096) + 4096;   // ring + scale / bias slots
+    constexpr int smem = dma_lds_bytes(BX, BW, NSTAGE, kind_is_4bit(WKIND));
     const int tiles = ((a.M + BX - 1) / BX) * ((a.N + BW - 1) / BW);
-    auto kern = gemm_dma_kernel<BX, BW, NSTAGE, XKIND, WKIND, ACC, CONV, QOUT>;
+    auto kern = gemm_dma_kernel<BX, BW, NSTAGE, WGW, XKIND, WKIND, ACC, CONV, QOUT>;
     static std::atomic<uint64_t> allowed{0};   // per instantiation
     if (!allow_dynamic_lds(reinterpret_cast<const void*>(kern), smem, allowed)) return FPQ_ERR_LAUNCH;
     const int nitems = tiles * a.splits;

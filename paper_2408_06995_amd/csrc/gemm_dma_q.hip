@@ -9,10 +9,10 @@ template <int XKIND, int WKIND, int ACC>
 static int launch_dma_q_shape(const GemmArgs& a, hipStream_t st)
 {
     if (a.tile == TILE_128x160_S2)
-        return a.conv_out ? launch_dma_one<128, 160, 2, XKIND, WKIND, ACC, true, true>(a, st)
-                          : launch_dma_one<128, 160, 2, XKIND, WKIND, ACC, false, true>(a, st);
-    return a.conv_out ? launch_dma_one<256, 160, 3, XKIND, WKIND, ACC, true, true>(a, st)
-                      : launch_dma_one<256, 160, 3, XKIND, WKIND, ACC, false, true>(a, st);
+        return a.conv_out ? launch_dma_one<128, 160, 2, 1, XKIND, WKIND, ACC, true, true>(a, st)
+                          : launch_dma_one<128, 160, 2, 1, XKIND, WKIND, ACC, false, true>(a, st);
+    return a.conv_out ? launch_dma_one<256, 160, 3, 1, XKIND, WKIND, ACC, true, true>(a, st)
+                      : launch_dma_one<256, 160, 3, 1, XKIND, WKIND, ACC, false, true>(a, st);
 }
 
 int launch_gemm_dma_q(const GemmArgs& a, hipStream_t st)

@@ -27,8 +27,10 @@ struct Args {
     PyObject* const* a;
     bool bad = false;
 
+    // (after a failure the remaining arguments are not looked at: the first error is the one reported)
     long long integer(int i)
     {
+        if (bad) return 0;
         PyObject* o = a[i];
         if (PyLong_CheckExact(o)) {
             const long long v = PyLong_AsLongLong(o);
@@ -43,9 +45,21 @@ struct Args {
         return v;
     }
     int i(int k) { return (int)integer(k); }
-    int64_t l(int k) { return (int64_t)integer(k); }
+    // a size: whole numbers only, no conversion
+    int64_t l(int k)
+    {
+        if (bad) return 0;
+        if (!PyLong_Check(a[k])) {
+            PyErr_Format(PyExc_TypeError, "sizes are ints, not %s", Py_TYPE(a[k])->tp_name);
+            bad = true;
+            return 0;
+        }
+        return (int64_t)integer(k);
+    }
+    int d(int k) { return (int)l(k); }
     float f(int k)
     {
+        if (bad) return 0.0f;
         const double v = PyFloat_AsDouble(a[k]);
         if (v == -1.0 && PyErr_Occurred()) bad = true;
         return (float)v;
@@ -53,7 +67,7 @@ struct Args {
     // data_ptr() of a tensor; None: null
     void* ptr_of(PyObject* o)
     {
-        if (o == Py_None) return nullptr;
+        if (bad || o == Py_None) return nullptr;
         PyObject* r = PyObject_CallMethodNoArgs(o, s_data_ptr);
         if (!r) { bad = true; return nullptr; }
         void* p = PyLong_AsVoidPtr(r);
@@ -66,6 +80,7 @@ struct Args {
     uint8_t* bp(int k) { return static_cast<uint8_t*>(p(k)); }
     size_t method(PyObject* o, PyObject* name)
     {
+        if (bad) return 0;
         PyObject* r = PyObject_CallMethodNoArgs(o, name);
         if (!r) { bad = true; return 0; }
         const size_t v = PyLong_AsSize_t(r);
@@ -75,10 +90,19 @@ struct Args {
     }
     size_t numel(int k) { return method(a[k], s_numel); }
     size_t bytes(int k) { return a[k] == Py_None ? 0 : method(a[k], s_numel) * method(a[k], s_element_size); }
-    int64_t size(int k, int dim)
+    // dimension `dim` of a tensor that must have `ndim` (0: any number)
+    int64_t size(int k, int dim, int ndim)
     {
+        if (bad) return 0;
         PyObject* sh = PyObject_GetAttr(a[k], s_shape);
         if (!sh) { bad = true; return 0; }
+        const Py_ssize_t have = PySequence_Size(sh);
+        if (have < 0 || (ndim && have != ndim)) {
+            if (have >= 0) PyErr_Format(PyExc_ValueError, "a tensor of %d dimensions expected, not %zd", ndim, have);
+            Py_DECREF(sh);
+            bad = true;
+            return 0;
+        }
         PyObject* d = PySequence_GetItem(sh, dim);
         Py_DECREF(sh);
         if (!d) { bad = true; return 0; }
@@ -92,6 +116,7 @@ struct Args {
     {
         fpq_format_t r;
         memset(&r, 0, sizeof r);
+        if (bad) return r;
         PyObject* o = a[k];
         if (PyTuple_CheckExact(o) && PyTuple_GET_SIZE(o) == 4) {
             Args t{&PyTuple_GET_ITEM(o, 0)};
@@ -123,6 +148,7 @@ struct Args {
     // the current torch stream of the current device
     void* stream()
     {
+        if (bad) return nullptr;
         if (!g_get_stream) {
             PyObject* m = PyImport_ImportModule("torch._C");
             if (!m) { bad = true; return nullptr; }
@@ -189,7 +215,7 @@ int do_conv2d(Args& A)
 {
     FN(fpq_conv2d);
     return invoke(A, fn, A.p(0), A.i(1), A.fmt(2), A.f(3), A.fp(4), A.p(5), A.fmt(6), A.fp(7), A.fp(8), A.fp(9), A.l(10), A.l(11),
-                  A.l(12), A.l(13), A.l(14), A.i(15), A.i(16), A.i(17), A.i(18), A.i(19), A.p(20), A.bytes(20), A.stream());
+                  A.l(12), A.l(13), A.l(14), A.d(15), A.d(16), A.d(17), A.d(18), A.i(19), A.p(20), A.bytes(20), A.stream());
 }
 int do_gemm_codes_out(Args& A)
 {
@@ -201,7 +227,7 @@ int do_conv2d_codes_out(Args& A)
 {
     FN(fpq_conv2d_codes_out);
     return invoke(A, fn, A.p(0), A.i(1), A.fmt(2), A.f(3), A.fp(4), A.p(5), A.fmt(6), A.fp(7), A.fp(8), A.fmt(9), A.f(10), A.fp(11),
-                  A.bp(12), A.l(13), A.l(14), A.l(15), A.l(16), A.l(17), A.i(18), A.i(19), A.i(20), A.i(21), A.i(22), A.p(23),
+                  A.bp(12), A.l(13), A.l(14), A.l(15), A.l(16), A.l(17), A.d(18), A.d(19), A.d(20), A.d(21), A.i(22), A.p(23),
                   A.bytes(23), A.stream());
 }
 int do_gemm_sparse(Args& A)
@@ -214,7 +240,7 @@ int do_conv2d_sparse(Args& A)
 {
     FN(fpq_conv2d_sparse);
     return invoke(A, fn, A.p(0), A.i(1), A.fmt(2), A.f(3), A.fp(4), A.p(5), A.fmt(6), A.fp(7), A.fp(8), A.fp(9), A.l(10), A.l(11),
-                  A.l(12), A.l(13), A.l(14), A.i(15), A.i(16), A.i(17), A.i(18), A.p(19), A.bytes(19), A.stream());
+                  A.l(12), A.l(13), A.l(14), A.d(15), A.d(16), A.d(17), A.d(18), A.p(19), A.bytes(19), A.stream());
 }
 int do_gemm_grouped(Args& A)
 {
@@ -239,7 +265,8 @@ int do_quantize(Args& A)
 int do_quantize_nhwc(Args& A)
 {
     FN(fpq_quantize_nhwc);
-    return invoke(A, fn, A.fp(0), A.size(0, 0), A.size(0, 1), A.size(0, 2), A.size(0, 3), A.fmt(1), A.f(2), A.fp(3), A.bp(4), A.stream());
+    return invoke(A, fn, A.fp(0), A.size(0, 0, 4), A.size(0, 1, 4), A.size(0, 2, 4), A.size(0, 3, 4),
+                  A.fmt(1), A.f(2), A.fp(3), A.bp(4), A.stream());
 }
 int do_int_calibrate(Args& A)
 {
@@ -261,7 +288,7 @@ int do_int_gemm(Args& A)
 int do_rl_step(Args& A)
 {
     FN(fpq_rl_step);
-    return invoke(A, fn, A.fp(0), A.fp(1), A.size(0, 0), A.size(0, 1), A.fmt(2), A.fp(3), A.fp(4), A.size(4, 0), A.f(5), A.f(6), A.fp(7),
+    return invoke(A, fn, A.fp(0), A.fp(1), A.size(0, 0, 2), A.size(0, 1, 2), A.fmt(2), A.fp(3), A.fp(4), A.size(4, 0, 0), A.f(5), A.f(6), A.fp(7),
                   A.fp(8), A.p(9), A.bytes(9), A.stream());
 }
 int do_search_format(Args& A)

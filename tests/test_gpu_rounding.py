@@ -193,3 +193,16 @@ def test_argument_checks():
 def test_step_at_tile_edges(M, N, K):
     """Shapes either side of the tiles (64, 128 rows), of the steps of 16 k and of the loads' four elements, in both products."""
     check_step(N, K, M, E2M1, 9700 + M)
+
+
+def test_weights_of_a_convolution_are_refused():
+    """The step takes weights as a matrix; a four-dimensional tensor is an error of the caller, not its first two sizes."""
+    w = torch.zeros((4, 8, 3, 3), dtype=torch.float32, device=DEV)
+    sw, loss, a = (torch.ones(n, dtype=torch.float32, device=DEV) for n in (4, 2, 72))
+    ws = torch.empty(4096, dtype=torch.uint8, device=DEV)
+    with pytest.raises(ValueError):
+        B.fpq_rl_step(w, sw, synth.E4M3, w, a, 1e-2, 1e-3, loss, None, ws)
+    with pytest.raises(ValueError):
+        B.fpq_quantize_nhwc(w.reshape(1, 4, 8, 3, 3), synth.E4M3, 1.0, None, ws)
+    with pytest.raises(TypeError):
+        B.fpq_gemm(a, B.FPQ_X_FP32, synth.E4M3, 1.0, None, ws, synth.E4M3, sw, None, loss, 1.5, 1, 16, workspace=ws)

@@ -461,7 +461,8 @@ int fpq_probe_peak(int kind, int iterations, const void *src, void *dst, size_t 
  * maxima and scale of the dynamic-scale form) lives in a static device array of FPQ_NOALLOC_SCRATCH_BYTES inside
  * the library, of which every GPU the library runs on holds its own copy until the process ends.  The call
  * allocates nothing and frees nothing.  The first call on a device looks the array's address up (make it outside
- * a graph capture).  A shape whose fpq_gemm_workspace_size exceeds FPQ_NOALLOC_SCRATCH_BYTES returns
+ * a graph capture).  A shape whose fpq_gemm_workspace_size exceeds FPQ_NOALLOC_SCRATCH_BYTES runs in one K slice if it
+ * takes FPQ_KERNEL_SMALL_TILE or a width that is no multiple of 160 and fits without partial sums; any other returns
  * FPQ_ERR_WORKSPACE and launches nothing.  All calls on one GPU share that GPU's array: nothing in it has to
  * start at zero and every call overwrites what it uses, but two calls that overlap in time on one GPU (different
  * streams, or different host threads on unordered streams) race; order them on one stream. */

@@ -489,7 +489,8 @@ static size_t sparse_pos_offset(int64_t N, int64_t kpad, fpq_format_t f)
 static int run_layer(const CodesOut* out, const void* x, int x_is_fp32, fpq_format_t fx, float sx, const float* sx_dev,
                      const void* packed_w, fpq_format_t fw, const float* sw, const float* bias, float* y, int64_t B,
                      int64_t Cin, int64_t H, int64_t W, int64_t Cout, int kh, int kw, int stride, int pad,
-                     int conv_out, int acc_mode, void* workspace, size_t workspace_bytes, void* stream, bool sparse = false)
+                     int conv_out, int acc_mode, void* workspace, size_t workspace_bytes, void* stream, bool sparse = false,
+                     bool sliced = true)
 {
     const int accumulate = (acc_mode & FPQ_OUT_ACCUMULATE) ? 1 : 0;
     const int act = acc_mode & (FPQ_ACT_SILU | FPQ_ACT_GEGLU);
@@ -541,6 +542,7 @@ static int run_layer(const CodesOut* out, const void* x, int x_is_fp32, fpq_form
             return FPQ_ERR_UNSUPPORTED;
         plan = GemmPlan{TILE_GENERIC, 1};
     }
+    if (!sliced) plan.splits = 1;
     const size_t codes_bytes = x_is_fp32 ? align_up((size_t)B * H * W * (size_t)Cp, 256) : 0;
     const size_t part_bytes = align_up(split_workspace_bytes(plan, M, Cout), 256);
     if (workspace && (reinterpret_cast<uintptr_t>(workspace) & 255)) return FPQ_ERR_ALIGN;
@@ -972,13 +974,22 @@ int fpq_gemm_noalloc(const void* x, int x_is_fp32, fpq_format_t fx, float sx, co
 {
     if (M == 0 && N > 0 && K > 0) return FPQ_OK;
     if (M < 0 || N <= 0 || K <= 0) return FPQ_ERR_SHAPE;
-    // the scratch a call of this shape needs is what fpq_gemm would ask of its caller
-    if (fpq_gemm_workspace_size(M, N, K, x_is_fp32) > kStaticScratchBytes) return FPQ_ERR_WORKSPACE;
+    // The scratch a call of this shape needs is what fpq_gemm would ask of its caller.  K slices of the small tiles are a matter of
+    // speed only: a call that fits without their partial sums runs in one slice.
+    bool sliced = true;
+    if (fpq_gemm_workspace_size(M, N, K, x_is_fp32) > kStaticScratchBytes) {
+        sliced = false;
+        const int64_t kpad = padded_k(K, 1);
+        const size_t part_bytes = align_up(split_workspace_bytes(plan_gemm(M, N, kpad), M, N), 256);
+        if (!takes_plan_small(M, N, kpad / 128) ||
+            fpq_gemm_workspace_size(M, N, K, x_is_fp32) - part_bytes > kStaticScratchBytes)
+            return FPQ_ERR_WORKSPACE;
+    }
     void* ws = nullptr;
     const int st = scratch_on_current_device(&ws);
     if (st) return st;
     return run_layer(nullptr, x, x_is_fp32, fx, sx, sx_dev, packed_w, fw, sw, bias, y, M, K, 1, 1, N, 1, 1, 1, 0, 0, acc_mode,
-                     ws, kStaticScratchBytes, stream);
+                     ws, kStaticScratchBytes, stream, false, sliced);
 }
 
 }  // extern "C"

@@ -198,6 +198,12 @@ static inline GemmPlan plan_small(int64_t M, int64_t N, int64_t nk)
     if (nk <= 20) s = 1;
     return GemmPlan{TILE_WAVE_K4, (int)s};
 }
+static inline bool takes_plan_small(int64_t M, int64_t N, int64_t nk)
+{
+    const int64_t t64 = ((M + 63) / 64) * ((N + 63) / 64), tiles = ((M + 127) / 128) * ((N + 159) / 160);
+    return M <= 16 || N % 160 != 0 || (M * N <= ((int64_t)2 << 20) && nk <= 20) || (N <= 480 && t64 <= 512 && nk >= 8) ||
+           (tiles < 32 && nk <= 128);
+}
 static inline GemmPlan plan_gemm(int64_t M, int64_t N, int64_t Kpad)
 {
     GemmPlan p{TILE_GENERIC, 1};
@@ -208,10 +214,8 @@ static inline GemmPlan plan_gemm(int64_t M, int64_t N, int64_t Kpad)
         p.splits = 1;
         return p;
     }
-    const int64_t t64 = ((M + 63) / 64) * ((N + 63) / 64);
     const int64_t tiles = ((M + 127) / 128) * ((N + 159) / 160);
-    if (N % 160 != 0 || (M * N <= ((int64_t)2 << 20) && nk <= 20) || (N <= 480 && t64 <= 512 && nk >= 8) ||
-        (tiles < 32 && nk <= 128)) {
+    if (takes_plan_small(M, N, nk)) {
         p = plan_small(M, N, nk);
         while (p.splits > 1 && p.splits * M * N * 4 > ((int64_t)256 << 20)) --p.splits;
         return p;

@@ -255,6 +255,7 @@ __global__ __launch_bounds__(256) void rl_im2col_kernel(const float* __restrict_
 // largest go to the matrix unit (bf16 products are exact in fp32, sums are fp32): hh, hm, mh, mm, hl, lh.  The three left out
 // are below 2^-26 of |x y| together, less than the rounding of one fp32 multiplication, so nothing is lost against the fp32
 // matrix instruction, whose rate is 1/16 of the bf16 one: six bf16 steps take 3/8 of the time of an fp32 one.
+// Operands have to be finite and below bf16's largest value (3.39e38): the differences of an infinite part are NaN.
 //
 // A workgroup of four wavefronts (2 x 2) owns a T x T tile of C (T = 128 or 64) and walks k in steps of 16 through three LDS
 // buffers; the split happens in registers between the global load and the LDS store.  Per step and wavefront at T = 128:

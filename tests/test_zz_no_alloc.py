@@ -59,3 +59,21 @@ def test_noalloc_rejects_what_does_not_fit():
     M, K, N = 1 << 20, 4096, 320
     assert B.fpq_gemm_workspace_size(M, N, K, 1) > B.FPQ_NOALLOC_SCRATCH_BYTES
     assert L.fpq_gemm_noalloc(p, 1, f, 1.0, None, p, f, p, None, p, M, N, K, 0, None) == -6
+
+
+def test_noalloc_takes_in_one_slice_what_fits_without_partial_sums():
+    # codes of 40.5 MB and the partial sums of three slices exceed the scratch together, the codes alone do not
+    M, K, N = 6912, 6144, 300
+    assert B.fpq_gemm_workspace_size(M, N, K, B.FPQ_X_FP32_DYNAMIC) > B.FPQ_NOALLOC_SCRATCH_BYTES > M * K + 8192
+    x = synth.activations((M, K), 41)
+    w = synth.weights((N, K), 42)
+    sx = oracle.scale_from_absmax(oracle.absmax(x), synth.E4M3[3])
+    rows = np.r_[0:64, 3450:3470, M - 64:M]
+    wq, sw = oracle.pack_weights(w, synth.E4M3)
+    Y, T = oracle.gemm(oracle.quantize(np.ascontiguousarray(x[rows]), synth.E4M3, sx), synth.E4M3, sx, wq, synth.E4M3, sw, None)
+    packed, sw_t, _ = gpu_pack(w, synth.E4M3, None, want_codes=False)
+    y = torch.full((M, N), float("nan"), dtype=torch.float32, device=DEV)
+    B.fpq_gemm_noalloc(dev(x), B.FPQ_X_FP32_DYNAMIC, synth.E4M3, 0.0, None, packed, synth.E4M3, sw_t, None, y, M, N, K,
+                       B.FPQ_ACC_FP32)
+    assert not torch.isnan(y).any()
+    check_close(y.cpu().numpy()[rows], Y, T, what="fpq_gemm_noalloc in one slice")

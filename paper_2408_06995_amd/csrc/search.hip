@@ -27,6 +27,7 @@
 // single-workgroup reduction (506).  20 K elements: 17 us against 205.
 #include "fpq_dev.h"
 #include "fpq_host.h"
+#include "search_split.h"
 
 namespace fpq {
 
@@ -45,7 +46,7 @@ constexpr int kGroupBins = kBins / kBinGroups;
 constexpr int kBinBlocks = kBins / 64;              // workgroups of the interval kernel, 64 neighbouring intervals each
 static_assert(kBins % (64 * kBinGroups) == 0 && kGroupBins * 16 <= 160 * 1024, "interval table");
 constexpr int kTailCap = 65536;
-constexpr int kCountShift = 39;                     // packed moment word: count above, sum of the low bits below
+static_assert(kFineShift <= kSearchLowBits && kCoarseShift <= kSearchLowBits, "moment word");
 
 // A boundary inside an interval: an element l units below the upper end adds slope * (l - t) to its candidate's error if
 // l < t.  `where` = t in 1/256 units << 10 | candidate (an element at the boundary adds nothing, so t may be rounded).
@@ -60,18 +61,13 @@ struct BinnedLayout {
     size_t table, cursors, starts, cuts, tail, sums_i, sums_c, total;
 };
 __host__ __device__ inline size_t up256(size_t v) { return (v + 255) / 256 * 256; }
-inline int binned_parts(size_t n)                   // copies of the interval table: a multiple of 8 (one per XCD)
-{
-    size_t p = n / 49152 / 8 * 8;
-    return (int)(p < 8 ? 8 : (p > 64 ? 64 : p));
-}
 constexpr int kCutBlocks = 1024;
 inline BinnedLayout binned_layout(size_t n, int nc)
 {
     BinnedLayout l;
     size_t at = 0;
     auto take = [&](size_t bytes) { const size_t was = at; at += up256(bytes); return was; };
-    l.table = take((size_t)binned_parts(n) * kBins * 16);
+    l.table = take((size_t)search_parts(n) * kBins * 16);
     l.cursors = take(256);
     l.starts = take((size_t)kBins * 4);
     l.cuts = take((kMaxCuts + 1) * sizeof(Cut));
@@ -220,8 +216,7 @@ __device__ __forceinline__ void for_elements(const float* __restrict__ x, size_t
 {
     if ((reinterpret_cast<uintptr_t>(x) & 15) == 0) {
         const size_t n4 = n >> 2;
-        const size_t per = (n4 + parts - 1) / parts;
-        const size_t lo = (size_t)part * per, hi = lo + per < n4 ? lo + per : n4;
+        const auto [lo, hi] = search_range(n4, part, parts);
         const uint4* x4 = reinterpret_cast<const uint4*>(x);
         for (size_t i = lo + threadIdx.x; i < hi; i += 4 * THREADS) {
             uint4 v[4];
@@ -234,8 +229,7 @@ __device__ __forceinline__ void for_elements(const float* __restrict__ x, size_t
         if (part == 0 && threadIdx.x < (n & 3))
             f4(make_uint4(__float_as_uint(x[(n4 << 2) + threadIdx.x]) & 0x7fffffffu, 0u, 0u, 0u));
     } else {
-        const size_t per = (n + parts - 1) / parts;
-        const size_t lo = (size_t)part * per, hi = lo + per < n ? lo + per : n;
+        const auto [lo, hi] = search_range(n, part, parts);
         for (size_t i = lo + threadIdx.x; i < hi; i += 4 * THREADS) {
             uint32_t v[4];
 #pragma unroll
@@ -245,7 +239,7 @@ __device__ __forceinline__ void for_elements(const float* __restrict__ x, size_t
     }
 }
 
-// Moments of the intervals of one group over one part of the tensor: {count << 39 | sum of low, sum of low^2}.  A part is
+// Moments of the intervals of one group over one part of the tensor: {search_moment of all, sum of low^2}.  A part is
 // read by one workgroup per group, all on the same XCD (workgroup ids go round-robin over the eight).
 __global__ __launch_bounds__(1024) void search_bins_kernel(const float* __restrict__ x, size_t n,
                                                            const float* __restrict__ absmax_parts_, int nparts, int parts,
@@ -264,7 +258,7 @@ __global__ __launch_bounds__(1024) void search_bins_kernel(const float* __restri
         uint32_t low;
         if (locate(b, top, bin, low) && ((bin >> 6) & (kBinGroups - 1)) == group) {
             const int at = ((bin >> 8) << 6) | (bin & 63);
-            atomicAdd(&packed[at], ((unsigned long long)1 << kCountShift) | low);
+            atomicAdd(&packed[at], (unsigned long long)search_moment(low));
             atomicAdd(&squares[at], (unsigned long long)low * low);
         }
     };
@@ -301,8 +295,8 @@ __global__ __launch_bounds__(512) void search_intervals_kernel(const ulonglong2*
         const ulonglong2* t = table + (size_t)group * parts * kGroupBins + lb * 64 + i;
         for (int q = p; q < parts; q += 8) {
             const ulonglong2 v = t[(size_t)q * kGroupBins];
-            n += v.x >> kCountShift;
-            s1 += v.x & (((unsigned long long)1 << kCountShift) - 1);
+            n += search_moment_count(v.x);
+            s1 += search_moment_sum(v.x);
             s2 += v.y;
         }
         red[p][i][0] = n; red[p][i][1] = s1; red[p][i][2] = s2;
@@ -550,9 +544,9 @@ __global__ __launch_bounds__(1024) void search_select_kernel(const double* __res
 }
 
 // The binned form has a cost of its own (about 55 us: the interval tables are written and read once whatever n is); the
-// direct form takes 0.13 us per 1024 elements at 444 candidates.  Beyond 2^31 elements the packed counts could overflow.
+// direct form takes 0.13 us per 1024 elements at 444 candidates.
 constexpr size_t kSearchBinnedWork = (size_t)400000 * 444;   // elements x candidates
-bool binned_pays(size_t n, int nc) { return n * (size_t)nc >= kSearchBinnedWork && n >= 131072 && n <= ((size_t)1 << 31); }
+bool binned_pays(size_t n, int nc) { return n * (size_t)nc >= kSearchBinnedWork && n >= 131072 && n <= kSearchMaxBinned; }
 
 }  // namespace
 
@@ -576,7 +570,7 @@ int launch_search(const float* x, size_t n, const SearchArgs& a, const float* ma
         double* sums_i = reinterpret_cast<double*>(ws + l.sums_i);
         double* sums_c = reinterpret_cast<double*>(ws + l.sums_c);
         double* mse_w = reinterpret_cast<double*>(ws + l.total);
-        const int parts = binned_parts(n);
+        const int parts = search_parts(n);
         constexpr int lds = kGroupBins * 16;
         static std::atomic<uint64_t> allowed{0};
         if (!allow_dynamic_lds(reinterpret_cast<const void*>(search_bins_kernel), lds, allowed)) return FPQ_ERR_LAUNCH;

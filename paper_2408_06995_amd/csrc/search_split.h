@@ -1,0 +1,38 @@
+// How the search divides a tensor over workgroups and packs what it counts: plain arithmetic, for host and device.
+#pragma once
+#include <stddef.h>
+#include <stdint.h>
+
+namespace fpq {
+
+// A moment word holds the count of an interval above, the sum of its low bits (at most 14 each) below.  Neither overflows while
+// fewer than 2^25 elements are counted into one word.
+constexpr int kSearchLowBits = 14;
+constexpr int kSearchCountShift = 39;
+constexpr uint64_t search_moment(uint32_t low) { return ((uint64_t)1 << kSearchCountShift) | low; }
+constexpr uint64_t search_moment_count(uint64_t word) { return word >> kSearchCountShift; }
+constexpr uint64_t search_moment_sum(uint64_t word) { return word & (((uint64_t)1 << kSearchCountShift) - 1); }
+
+// Units [lo, hi) of part `part` of `parts`.
+struct SearchRange {
+    size_t lo, hi;
+};
+constexpr SearchRange search_range(size_t units, size_t part, size_t parts)
+{
+    const size_t per = (units + parts - 1) / parts;
+    const size_t lo = part * per < units ? part * per : units;
+    return SearchRange{lo, lo + per < units ? lo + per : units};
+}
+
+// Copies of the interval table, one per part of the tensor: a multiple of 8 (one per XCD), 64 when that leaves a part 49152
+// elements (fewer do not pay for a table), and as many more as keep a part near 2^24 elements, below what a moment word counts.
+constexpr int search_parts(size_t n)
+{
+    const size_t p = n / 49152 / 8 * 8, least = (n / ((size_t)1 << 24) + 7) / 8 * 8;
+    const size_t q = p < 8 ? 8 : (p > 64 ? 64 : p);
+    return (int)(q < least ? least : q);
+}
+// Largest tensor of the binned form.
+constexpr size_t kSearchMaxBinned = (size_t)1 << 31;
+
+}  // namespace fpq

@@ -20,8 +20,9 @@
 //   3. search_cuts_kernel       every element adds, for each candidate that cuts its interval, what the upper side changes:
 //                               (x - q2)^2 - (x - q1)^2 = -2 g (x - mid), g = q2 - q1, if x > mid, else nothing (the error is
 //                               continuous at the boundary, so which side a tie takes does not matter).
-// About five such terms per element instead of 444 evaluations.  Elements more than 32 binades below the maximum, and
-// subnormal ones, go to a list that step 4 (search_reduce_kernel) evaluates directly.
+// About five such terms per element instead of 444 evaluations.  A workgroup of step 3 that meets elements more than 32 binades
+// below the maximum, or subnormal ones, reads its share again and evaluates those directly (add_outside); with such elements
+// only, that costs what the direct form costs.
 // Measured, 10.5 M elements x 444 candidates: 172 us (absmax 8, intervals' moments 37, closed forms 25, cuts 87: one cache
 // line per element and list access, sums 15) against 1758 us of the direct form (1244, bound by vector ALU work) with its
 // single-workgroup reduction (506).  20 K elements: 17 us against 205.
@@ -45,7 +46,6 @@ constexpr int kBinGroups = 4;                       // LDS holds a quarter of th
 constexpr int kGroupBins = kBins / kBinGroups;
 constexpr int kBinBlocks = kBins / 64;              // workgroups of the interval kernel, 64 neighbouring intervals each
 static_assert(kBins % (64 * kBinGroups) == 0 && kGroupBins * 16 <= 160 * 1024, "interval table");
-constexpr int kTailCap = 65536;
 static_assert(kFineShift <= kSearchLowBits && kCoarseShift <= kSearchLowBits, "moment word");
 
 // A boundary inside an interval: an element l units below the upper end adds slope * (l - t) to its candidate's error if
@@ -58,7 +58,7 @@ struct Cut {
 constexpr size_t kMaxCuts = (size_t)kSearchMaxCandidates * 127;
 
 struct BinnedLayout {
-    size_t table, cursors, starts, cuts, tail, sums_i, sums_c, total;
+    size_t table, cursors, starts, cuts, sums_i, sums_c, total;
 };
 __host__ __device__ inline size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 constexpr int kCutBlocks = 1024;
@@ -71,7 +71,6 @@ inline BinnedLayout binned_layout(size_t n, int nc)
     l.cursors = take(256);
     l.starts = take((size_t)kBins * 4);
     l.cuts = take((kMaxCuts + 1) * sizeof(Cut));
-    l.tail = take((size_t)kTailCap * 4);
     l.sums_i = take((size_t)kBinBlocks * nc * 8);
     l.sums_c = take((size_t)kCutBlocks * nc * 8);
     l.total = at;
@@ -195,7 +194,7 @@ __global__ __launch_bounds__(256) void search_direct_kernel(const float* __restr
 
 __device__ __forceinline__ uint32_t top_bits(float am) { return (__float_as_uint(am) | 0x7fffffu) & 0x7fffffffu; }
 
-// Interval and position below its upper end of a magnitude; false for one that takes the list (or is NaN).
+// Interval and position below its upper end of a magnitude; false for one outside all intervals (or NaN).
 __device__ __forceinline__ bool locate(uint32_t b, uint32_t top, int& bin, uint32_t& low)
 {
     const uint32_t rel = top - b;
@@ -251,7 +250,7 @@ __global__ __launch_bounds__(1024) void search_bins_kernel(const float* __restri
     const int group = (blockIdx.x >> 3) & (kBinGroups - 1);
     const int part = (blockIdx.x >> 5) * 8 + (blockIdx.x & 7);
     for (int i = threadIdx.x; i < 2 * kGroupBins; i += 1024) bins[i] = 0;
-    if (blockIdx.x == 0 && threadIdx.x < 2) cursors[threadIdx.x] = 0;            // cuts and listed elements, for the next kernels
+    if (blockIdx.x == 0 && threadIdx.x == 0) cursors[0] = 0;                     // cuts, for the next kernel
     const uint32_t top = top_bits(fold_absmax(absmax_parts_, nparts, 16));       // its barrier also closes the clearing
     auto count = [&](uint32_t b) {
         int bin;
@@ -376,16 +375,87 @@ __global__ __launch_bounds__(512) void search_intervals_kernel(const ulonglong2*
     }
 }
 
-// What the upper sides of the cut intervals change, per candidate; elements outside all intervals go to the list.
+constexpr int kOutsideRound = 4;                     // elements per thread and round of add_outside
+
+// Squared errors of the elements of this workgroup's share that lie outside all intervals, of candidate threadIdx.x + 512 h in
+// sum[h] (all 512 threads call this): the elements of a round are gathered in LDS, in the order of the tensor, and every thread
+// walks them with its candidates.
+__device__ void add_outside(const float* __restrict__ x, size_t n, int part, int parts, uint32_t top, float am,
+                            const SearchArgs& a, int NC, double (&sum)[kSearchMaxCandidates / 512])
+{
+    __shared__ float found[512 * kOutsideRound];
+    __shared__ int counts[kOutsideRound * 8];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // the elements that for_elements gives this part: a range, and the last n % 4 in part 0
+    const size_t v = (reinterpret_cast<uintptr_t>(x) & 15) == 0 ? 4 : 1;
+    const SearchRange range = search_range(n / v, part, parts);
+    const size_t inside = (range.hi - range.lo) * v, total = inside + (part == 0 ? n % v : 0);
+    // magnitudes here are below 2^(e + 1 - 32), e the exponent of the maximum's binade: scaled to below 2^60, the squares of
+    // values up to 120 binades smaller stay normal numbers
+    const int shift = 60 + 31 - ((int)(top >> 23) - 127);
+    Cand k[kSearchMaxCandidates / 512];
+#pragma unroll
+    for (int h = 0; h < kSearchMaxCandidates / 512; ++h) k[h] = candidate(a, am, min(tid + 512 * h, NC - 1));
+    for (size_t base = 0; base < total; base += 512 * kOutsideRound) {
+        float value[kOutsideRound];
+        unsigned long long mask[kOutsideRound];
+#pragma unroll
+        for (int u = 0; u < kOutsideRound; ++u) {
+            const size_t j = base + (size_t)u * 512 + tid;
+            const size_t i = j < inside ? range.lo * v + j : n / v * v + (j - inside);
+            const uint32_t b = j < total ? __float_as_uint(x[i]) & 0x7fffffffu : 0u;
+            int bin;
+            uint32_t low;
+            const bool take = b && !locate(b, top, bin, low);
+            mask[u] = __ballot(take);
+            value[u] = take ? __uint_as_float(b) : -1.0f;
+            if (lane == 0) counts[u * 8 + wave] = __popcll(mask[u]);
+        }
+        __syncthreads();
+        int at[kOutsideRound], count = 0;
+#pragma unroll
+        for (int u = 0; u < kOutsideRound; ++u)
+            for (int w = 0; w < 8; ++w) {
+                if (w == wave) at[u] = count;
+                count += counts[u * 8 + w];
+            }
+#pragma unroll
+        for (int u = 0; u < kOutsideRound; ++u)
+            if ((mask[u] >> lane) & 1) found[at[u] + __popcll(mask[u] & ((1ull << lane) - 1))] = value[u];
+        __syncthreads();
+        for (int i = 0; i < count; i += 4) {
+#pragma unroll
+            for (int h = 0; h < kSearchMaxCandidates / 512; ++h) {
+                if (512 * h >= NC) continue;
+                float four = 0.0f;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    if (i + u >= count) continue;
+                    const float e = found[i + u];
+                    const float d = ldexpf(__fmaf_rn(-grid_value(e, k[h].r, k[h].c0, k[h].m, k[h].b0), k[h].sc, e), shift);
+                    four = __fmaf_rn(d, d, four);
+                }
+                sum[h] += (double)four;
+            }
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int h = 0; h < kSearchMaxCandidates / 512; ++h) sum[h] = ldexp(sum[h], -2 * shift);
+}
+
+// What the upper sides of the cut intervals change, per candidate, and the errors of the elements outside all intervals.
 __global__ __launch_bounds__(512) void search_cuts_kernel(const float* __restrict__ x, size_t n,
-                                                          const float* __restrict__ absmax_parts_, int nparts, int NC,
+                                                          const float* __restrict__ absmax_parts_, int nparts, SearchArgs a,
                                                           const uint32_t* __restrict__ starts, const Cut* __restrict__ cuts,
-                                                          uint32_t* __restrict__ cursors, float* __restrict__ tail,
                                                           double* __restrict__ sums)
 {
     __shared__ double acc[kSearchMaxCandidates];
+    const int NC = a.n_enc * a.J;
     for (int c = threadIdx.x; c < NC; c += 512) acc[c] = 0.0;
-    const uint32_t top = top_bits(fold_absmax(absmax_parts_, nparts, 8));                // its barrier also closes the clearing
+    const float am = fold_absmax(absmax_parts_, nparts, 8);                              // its barrier also closes the clearing
+    const uint32_t top = top_bits(am);
+    int outside = 0;
     // four elements side by side: the loads of a step (first the lists' places, then their next entries) are independent
     for_elements<512>(x, n, blockIdx.x, gridDim.x, [&](uint4 b4) {
         const uint32_t b[4] = {b4.x, b4.y, b4.z, b4.w};
@@ -401,10 +471,7 @@ __global__ __launch_bounds__(512) void search_cuts_kernel(const float* __restric
             left[k] = s & 2047u;
             l[k] = (float)low;
             most = max(most, left[k]);
-            if (!in && b[k]) {
-                const uint32_t p = atomicAdd(&cursors[1], 1u);
-                if (p < (uint32_t)kTailCap) tail[p] = __uint_as_float(b[k]);
-            }
+            outside |= !in && b[k];
         }
         auto add = [&](uint32_t slope, uint32_t where, float low) {
             const float v = __uint_as_float(slope) * (low - (float)(where >> 10) * 0.00390625f);
@@ -424,8 +491,13 @@ __global__ __launch_bounds__(512) void search_cuts_kernel(const float* __restric
             }
         }
     });
-    __syncthreads();
-    for (int c = threadIdx.x; c < NC; c += 512) sums[(size_t)blockIdx.x * NC + c] = acc[c];
+    double sum[kSearchMaxCandidates / 512] = {};
+    if (__syncthreads_or(outside)) add_outside(x, n, blockIdx.x, gridDim.x, top, am, a, NC, sum);
+#pragma unroll
+    for (int h = 0; h < kSearchMaxCandidates / 512; ++h) {
+        const int c = threadIdx.x + 512 * h;
+        if (c < NC) sums[(size_t)blockIdx.x * NC + c] = acc[c] + sum[h];
+    }
 }
 
 // ---------------------------------------------------------------------------------- sums over workgroups, the choice
@@ -433,42 +505,16 @@ __global__ __launch_bounds__(512) void search_cuts_kernel(const float* __restric
 // Mean squared errors: one wavefront-row of 16 candidates, 64 rows of partial sums at a time.
 __global__ __launch_bounds__(1024) void search_reduce_kernel(const float* __restrict__ direct, int rows0,
                                                              const double* __restrict__ s1, int rows1,
-                                                             const double* __restrict__ s2, int rows2,
-                                                             const float* __restrict__ x, size_t n,
-                                                             const float* __restrict__ absmax_parts_, int nparts, SearchArgs a,
-                                                             const uint32_t* __restrict__ cursors, const float* __restrict__ tail,
+                                                             const double* __restrict__ s2, int rows2, size_t n, int NC,
                                                              double* __restrict__ mse)
 {
     __shared__ double red[64][16];
-    const int NC = a.n_enc * a.J;
     const int c = blockIdx.x * 16 + (threadIdx.x & 15), row = threadIdx.x >> 4;
     double s = 0.0;
-    const uint32_t listed = cursors ? cursors[1] : 0u;
     if (c < NC) {
         for (int r = row; r < rows0; r += 64) s += (double)direct[(size_t)r * NC + c];
         for (int r = row; r < rows1; r += 64) s += s1[(size_t)r * NC + c];
         for (int r = row; r < rows2; r += 64) s += s2[(size_t)r * NC + c];
-    }
-    if (listed) {                                    // the same for the whole grid
-        const float am = fold_absmax(absmax_parts_, nparts, 16);
-        const uint32_t top = top_bits(am);
-        if (c < NC) {
-            const Cand k = candidate(a, am, c);
-            auto add = [&](float v) {
-                const float d = __fmaf_rn(-grid_value(v, k.r, k.c0, k.m, k.b0), k.sc, v);
-                s += (double)d * (double)d;
-            };
-            if (listed <= (uint32_t)kTailCap) {
-                for (uint32_t i = row; i < listed; i += 64) add(tail[i]);
-            } else {                                 // more than the list holds: find them in the tensor again
-                for (size_t i = row; i < n; i += 64) {
-                    const uint32_t b = __float_as_uint(x[i]) & 0x7fffffffu;
-                    int bin;
-                    uint32_t low;
-                    if (b && !locate(b, top, bin, low)) add(__uint_as_float(b));
-                }
-            }
-        }
     }
     red[row][threadIdx.x & 15] = s;
     __syncthreads();
@@ -566,7 +612,6 @@ int launch_search(const float* x, size_t n, const SearchArgs& a, const float* ma
         uint32_t* cursors = reinterpret_cast<uint32_t*>(ws + l.cursors);
         uint32_t* starts = reinterpret_cast<uint32_t*>(ws + l.starts);
         Cut* cuts = reinterpret_cast<Cut*>(ws + l.cuts);
-        float* tail = reinterpret_cast<float*>(ws + l.tail);
         double* sums_i = reinterpret_cast<double*>(ws + l.sums_i);
         double* sums_c = reinterpret_cast<double*>(ws + l.sums_c);
         double* mse_w = reinterpret_cast<double*>(ws + l.total);
@@ -579,10 +624,9 @@ int launch_search(const float* x, size_t n, const SearchArgs& a, const float* ma
         hipLaunchKernelGGL(search_intervals_kernel, dim3(kBinBlocks), dim3(512), 0, st, table, parts, maxparts, nparts, a, cursors,
                            starts, cuts, sums_i);
         const int cb = (int)(n / 4096 < kCutBlocks ? (n / 4096 > 0 ? n / 4096 : 1) : kCutBlocks);
-        hipLaunchKernelGGL(search_cuts_kernel, dim3(cb), dim3(512), 0, st, x, n, maxparts, nparts, NC, starts, cuts, cursors, tail,
-                           sums_c);
-        hipLaunchKernelGGL(search_reduce_kernel, dim3((NC + 15) / 16), dim3(1024), 0, st, nullptr, 0, sums_i, kBinBlocks, sums_c, cb, x, n,
-                           maxparts, nparts, a, cursors, tail, mse_w);
+        hipLaunchKernelGGL(search_cuts_kernel, dim3(cb), dim3(512), 0, st, x, n, maxparts, nparts, a, starts, cuts, sums_c);
+        hipLaunchKernelGGL(search_reduce_kernel, dim3((NC + 15) / 16), dim3(1024), 0, st, nullptr, 0, sums_i, kBinBlocks, sums_c, cb, n, NC,
+                           mse_w);
         mse = mse_w;
     } else if (rows > 0) {
         // few elements: split the candidates, at least 16 for a workgroup (the lane sums that end each candidate weigh more
@@ -594,8 +638,8 @@ int launch_search(const float* x, size_t n, const SearchArgs& a, const float* ma
         const size_t used = up256((size_t)rows * NC * 4);
         if (rows > 48 && partial_bytes >= used + up256((size_t)NC * 8)) {   // more rows than one workgroup adds in the time of a launch
             double* mse_w = reinterpret_cast<double*>(reinterpret_cast<uint8_t*>(partial) + used);
-            hipLaunchKernelGGL(search_reduce_kernel, dim3((NC + 15) / 16), dim3(1024), 0, st, partial, rows, nullptr, 0, nullptr, 0, x,
-                               n, maxparts, nparts, a, nullptr, nullptr, mse_w);
+            hipLaunchKernelGGL(search_reduce_kernel, dim3((NC + 15) / 16), dim3(1024), 0, st, partial, rows, nullptr, 0, nullptr, 0,
+                               n, NC, mse_w);
             mse = mse_w;
         }
     }

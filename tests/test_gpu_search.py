@@ -127,3 +127,34 @@ def test_search_large_tensors_of_unusual_values():
     assert (r.encoding, r.bias_index, r.mse) == (1, 127, 0.0)       # exactly zero, as with the direct evaluation
     r = check(np.zeros(BINNED, np.float32), FP8, 111)
     assert (r.encoding, r.bias_index, r.mse) == (0, 0, 0.0)
+
+
+def _time(xd, encodings, J):
+    from paper_2408_06995_amd import binding as B
+    mse = torch.empty(len(encodings) * J, dtype=torch.float32, device="cuda")
+    res = torch.zeros(40, dtype=torch.uint8, device="cuda")
+    ws = torch.empty(B.fpq_search_workspace_size(xd.numel(), len(encodings), J), dtype=torch.uint8, device="cuda")
+    t = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    for i in range(3):
+        if i == 1:
+            t[0].record()
+        B.fpq_search_format(xd, encodings, J, mse, res, ws)
+    t[1].record()
+    torch.cuda.synchronize()
+    return t[0].elapsed_time(t[1]) / 2
+
+
+@pytest.mark.parametrize("offset", [0, 1])
+def test_search_with_an_outlier_is_no_cliff(offset):
+    """One value 2^60 times the rest of a large tensor: no element lies in an interval, every one is evaluated directly.
+    That may cost what direct evaluation costs (some ten times the ordinary search), not a walk of the whole tensor by a
+    few workgroups (hundreds of times)."""
+    n = 1 << 22
+    x = synth.activations((n + offset,), 31)
+    ordinary = _time(torch.from_numpy(x).cuda()[offset:], FP8, 111)
+    x[offset + 77] = np.float32(2.0 ** 60)
+    xd = torch.from_numpy(x).cuda()[offset:]
+    assert _time(xd, FP8, 111) < 40 * ordinary
+    # the same values, few enough per call for the oracle, a workgroup's share at a time
+    part = np.concatenate([x[offset:offset + (1 << 19) + 5]])
+    check(part, FP8 + [(6, 1)], 111)

@@ -50,6 +50,8 @@ static_assert(kFineShift <= kSearchLowBits && kCoarseShift <= kSearchLowBits, "m
 
 // A boundary inside an interval: an element l units below the upper end adds slope * (l - t) to its candidate's error if
 // l < t.  `where` = t in 1/256 units << 10 | candidate (an element at the boundary adds nothing, so t may be rounded).
+// Slopes are in units of 4^e, e the exponent of the maximum's binade: errors are squares, and those of a tensor of values around
+// 10^-17 or 10^20 would leave a float's range (in these units they span 2^-103 to 2^-8).
 struct Cut {
     float slope;
     uint32_t where;
@@ -193,6 +195,7 @@ __global__ __launch_bounds__(256) void search_direct_kernel(const float* __restr
 // ---------------------------------------------------------------------------------- binned form
 
 __device__ __forceinline__ uint32_t top_bits(float am) { return (__float_as_uint(am) | 0x7fffffu) & 0x7fffffffu; }
+__device__ __forceinline__ int top_exponent(uint32_t top) { return (int)(top >> 23) - 127; }
 
 // Interval and position below its upper end of a magnitude; false for one outside all intervals (or NaN).
 __device__ __forceinline__ bool locate(uint32_t b, uint32_t top, int& bin, uint32_t& low)
@@ -367,7 +370,7 @@ __global__ __launch_bounds__(512) void search_intervals_kernel(const ulonglong2*
             double t = rint(((double)xh - 0.5 * (q1 + q2)) * inv_u * 256.0);
             t = t < 0.0 ? 0.0 : (t > 4194303.0 ? 4194303.0 : t);
             Cut e;
-            e.slope = (float)(2.0 * (q2 - q1) / inv_u);
+            e.slope = (float)ldexp(2.0 * (q2 - q1), (int)(upper(i) >> 23) - 150 - 2 * top_exponent(top));
             e.where = ((uint32_t)t << 10) | (uint32_t)c;
             const int p = atomicAdd(&at[i], 1);
             if ((size_t)p < kMaxCuts) cuts[p] = e;
@@ -392,7 +395,7 @@ __device__ void add_outside(const float* __restrict__ x, size_t n, int part, int
     const size_t inside = (range.hi - range.lo) * v, total = inside + (part == 0 ? n % v : 0);
     // magnitudes here are below 2^(e + 1 - 32), e the exponent of the maximum's binade: scaled to below 2^60, the squares of
     // values up to 120 binades smaller stay normal numbers
-    const int shift = 60 + 31 - ((int)(top >> 23) - 127);
+    const int shift = 60 + 31 - top_exponent(top);
     Cand k[kSearchMaxCandidates / 512];
 #pragma unroll
     for (int h = 0; h < kSearchMaxCandidates / 512; ++h) k[h] = candidate(a, am, min(tid + 512 * h, NC - 1));
@@ -496,7 +499,7 @@ __global__ __launch_bounds__(512) void search_cuts_kernel(const float* __restric
 #pragma unroll
     for (int h = 0; h < kSearchMaxCandidates / 512; ++h) {
         const int c = threadIdx.x + 512 * h;
-        if (c < NC) sums[(size_t)blockIdx.x * NC + c] = acc[c] + sum[h];
+        if (c < NC) sums[(size_t)blockIdx.x * NC + c] = ldexp(acc[c], 2 * top_exponent(top)) + sum[h];
     }
 }
 

@@ -158,3 +158,14 @@ def test_search_with_an_outlier_is_no_cliff(offset):
     # the same values, few enough per call for the oracle, a workgroup's share at a time
     part = np.concatenate([x[offset:offset + (1 << 19) + 5]])
     check(part, FP8 + [(6, 1)], 111)
+
+
+@pytest.mark.parametrize("k", [-54, -20, 40])
+def test_search_scales_with_the_tensor(k):
+    """A power of two times the tensor has the same candidates and 4^k times their errors, also where the errors of single
+    elements are far outside the range of a float."""
+    x = synth.activations((BINNED + 3,), 55)
+    want, r0 = run_search(x, FP8 + FP4, 111)
+    got, r = run_search(np.ldexp(x, k), FP8 + FP4, 111)
+    assert np.all(np.abs(np.ldexp(got.astype(np.float64), -2 * k) - want) <= 1e-6 * want)
+    assert (r.encoding, r.bias_index) == (r0.encoding, r0.bias_index)

@@ -20,6 +20,10 @@
 //   3. search_cuts_kernel       every element adds, for each candidate that cuts its interval, what the upper side changes:
 //                               (x - q2)^2 - (x - q1)^2 = -2 g (x - mid), g = q2 - q1, if x > mid, else nothing (the error is
 //                               continuous at the boundary, so which side a tie takes does not matter).
+// The terms of step 3 arrive in any order, so they are added as integers, in units of at most 2^-60 of the candidate's sum of step
+// 2 (search_base_kernel).  No element's term is larger than its own share of that sum, so nothing overflows, and together they
+// are a small part of it (at most 2^-9 in tensors drawn or made to lie in cut intervals), so nothing is lost.  Every call gives the same bits, and candidates that quantize the tensor alike
+// have equal errors, which the choice of the first minimum rests on.
 // About five such terms per element instead of 444 evaluations.  A workgroup of step 3 that meets elements more than 32 binades
 // below the maximum, or subnormal ones, reads its share again and evaluates those directly (add_outside); with such elements
 // only, that costs what the direct form costs.
@@ -60,7 +64,7 @@ struct Cut {
 constexpr size_t kMaxCuts = (size_t)kSearchMaxCandidates * 127;
 
 struct BinnedLayout {
-    size_t table, cursors, starts, cuts, sums_i, sums_c, total;
+    size_t table, cursors, starts, cuts, sums_i, sums_c, base, shifts, total;
 };
 __host__ __device__ inline size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 constexpr int kCutBlocks = 1024;
@@ -75,6 +79,8 @@ inline BinnedLayout binned_layout(size_t n, int nc)
     l.cuts = take((kMaxCuts + 1) * sizeof(Cut));
     l.sums_i = take((size_t)kBinBlocks * nc * 8);
     l.sums_c = take((size_t)kCutBlocks * nc * 8);
+    l.base = take((size_t)nc * 8);
+    l.shifts = take((size_t)nc * 4);
     l.total = at;
     return l;
 }
@@ -447,15 +453,54 @@ __device__ void add_outside(const float* __restrict__ x, size_t n, int part, int
     for (int h = 0; h < kSearchMaxCandidates / 512; ++h) sum[h] = ldexp(sum[h], -2 * shift);
 }
 
+// Sum of a column of `rows` sums per candidate, candidate blockIdx.x * 16 + threadIdx.x % 16 of NC: 64 rows at a time, always in
+// the same order.  Valid in the first 16 of the 1024 threads; all of them call this.
+template <typename T>
+__device__ __forceinline__ double column_sum(const T* __restrict__ sums, int rows, int NC, double (&red)[64][16])
+{
+    const int col = threadIdx.x & 15, c = blockIdx.x * 16 + col, row = threadIdx.x >> 4;
+    double s = 0.0;
+    if (c < NC)
+        for (int r = row; r < rows; r += 64) s += (double)sums[(size_t)r * NC + c];
+    red[row][col] = s;
+    __syncthreads();
+    for (int off = 32; off > 0; off >>= 1) {
+        if (row < off) red[row][col] += red[row + off][col];
+        __syncthreads();
+    }
+    return red[0][col];
+}
+
+// Closed forms of all intervals per candidate, and the unit of the terms that the cuts add to it: 2^-shift of the slopes' unit,
+// the power of two that makes the sum less than 2^61.
+__global__ __launch_bounds__(1024) void search_base_kernel(const double* __restrict__ sums, int rows,
+                                                           const float* __restrict__ absmax_parts_, int nparts, int NC,
+                                                           double* __restrict__ base, int* __restrict__ shifts)
+{
+    __shared__ double red[64][16];
+    const double s = column_sum(sums, rows, NC, red);
+    const int e = top_exponent(top_bits(fold_absmax(absmax_parts_, nparts, 16)));
+    const int c = blockIdx.x * 16 + threadIdx.x;
+    if (threadIdx.x < 16 && c < NC) {
+        base[c] = s;
+        // no sum, no elements in cut intervals; an infinite one or NaN keeps whatever is added
+        shifts[c] = s > 0.0 && s < __builtin_huge_val() ? 60 - ilogb(s) + 2 * e : 0;
+    }
+}
+
 // What the upper sides of the cut intervals change, per candidate, and the errors of the elements outside all intervals.
 __global__ __launch_bounds__(512) void search_cuts_kernel(const float* __restrict__ x, size_t n,
                                                           const float* __restrict__ absmax_parts_, int nparts, SearchArgs a,
                                                           const uint32_t* __restrict__ starts, const Cut* __restrict__ cuts,
-                                                          double* __restrict__ sums)
+                                                          const int* __restrict__ shifts, double* __restrict__ sums)
 {
-    __shared__ double acc[kSearchMaxCandidates];
+    __shared__ unsigned long long acc[kSearchMaxCandidates];     // two's complement, in units of 2^-shift of the slopes' unit
+    __shared__ int shift[kSearchMaxCandidates];
     const int NC = a.n_enc * a.J;
-    for (int c = threadIdx.x; c < NC; c += 512) acc[c] = 0.0;
+    for (int c = threadIdx.x; c < NC; c += 512) {
+        acc[c] = 0;
+        shift[c] = shifts[c];
+    }
     const float am = fold_absmax(absmax_parts_, nparts, 8);                              // its barrier also closes the clearing
     const uint32_t top = top_bits(am);
     int outside = 0;
@@ -478,7 +523,7 @@ __global__ __launch_bounds__(512) void search_cuts_kernel(const float* __restric
         }
         auto add = [&](uint32_t slope, uint32_t where, float low) {
             const float v = __uint_as_float(slope) * (low - (float)(where >> 10) * 0.00390625f);
-            if (v < 0.0f) atomicAdd(&acc[where & 1023u], (double)v);
+            if (v < 0.0f) atomicAdd(&acc[where & 1023u], (unsigned long long)(long long)ldexpf(v, shift[where & 1023u]));
         };
         for (uint32_t i = 0; i < most; i += 2) {
             uint4 e[4];
@@ -499,33 +544,21 @@ __global__ __launch_bounds__(512) void search_cuts_kernel(const float* __restric
 #pragma unroll
     for (int h = 0; h < kSearchMaxCandidates / 512; ++h) {
         const int c = threadIdx.x + 512 * h;
-        if (c < NC) sums[(size_t)blockIdx.x * NC + c] = ldexp(acc[c], 2 * top_exponent(top)) + sum[h];
+        if (c < NC) sums[(size_t)blockIdx.x * NC + c] = ldexp((double)(long long)acc[c], 2 * top_exponent(top) - shift[c]) + sum[h];
     }
 }
 
 // ---------------------------------------------------------------------------------- sums over workgroups, the choice
 
-// Mean squared errors: one wavefront-row of 16 candidates, 64 rows of partial sums at a time.
-__global__ __launch_bounds__(1024) void search_reduce_kernel(const float* __restrict__ direct, int rows0,
-                                                             const double* __restrict__ s1, int rows1,
-                                                             const double* __restrict__ s2, int rows2, size_t n, int NC,
-                                                             double* __restrict__ mse)
+// Mean squared errors from the rows of partial sums of either form (base: NULL, or what they are added to).
+template <typename T>
+__global__ __launch_bounds__(1024) void search_reduce_kernel(const T* __restrict__ sums, int rows, const double* __restrict__ base,
+                                                             size_t n, int NC, double* __restrict__ mse)
 {
     __shared__ double red[64][16];
-    const int c = blockIdx.x * 16 + (threadIdx.x & 15), row = threadIdx.x >> 4;
-    double s = 0.0;
-    if (c < NC) {
-        for (int r = row; r < rows0; r += 64) s += (double)direct[(size_t)r * NC + c];
-        for (int r = row; r < rows1; r += 64) s += s1[(size_t)r * NC + c];
-        for (int r = row; r < rows2; r += 64) s += s2[(size_t)r * NC + c];
-    }
-    red[row][threadIdx.x & 15] = s;
-    __syncthreads();
-    for (int off = 32; off > 0; off >>= 1) {
-        if (row < off) red[row][threadIdx.x & 15] += red[row + off][threadIdx.x & 15];
-        __syncthreads();
-    }
-    if (row == 0 && c < NC) mse[c] = red[0][threadIdx.x & 15] / (double)n;
+    const double s = column_sum(sums, rows, NC, red);
+    const int c = blockIdx.x * 16 + threadIdx.x;
+    if (threadIdx.x < 16 && c < NC) mse[c] = (base ? base[c] + s : s) / (double)n;
 }
 
 // Every candidate's mean squared error (from `mse`, or summed here over the rows of the direct form) and the choice: the
@@ -617,6 +650,8 @@ int launch_search(const float* x, size_t n, const SearchArgs& a, const float* ma
         Cut* cuts = reinterpret_cast<Cut*>(ws + l.cuts);
         double* sums_i = reinterpret_cast<double*>(ws + l.sums_i);
         double* sums_c = reinterpret_cast<double*>(ws + l.sums_c);
+        double* base = reinterpret_cast<double*>(ws + l.base);
+        int* shifts = reinterpret_cast<int*>(ws + l.shifts);
         double* mse_w = reinterpret_cast<double*>(ws + l.total);
         const int parts = search_parts(n);
         constexpr int lds = kGroupBins * 16;
@@ -626,10 +661,12 @@ int launch_search(const float* x, size_t n, const SearchArgs& a, const float* ma
                            cursors);
         hipLaunchKernelGGL(search_intervals_kernel, dim3(kBinBlocks), dim3(512), 0, st, table, parts, maxparts, nparts, a, cursors,
                            starts, cuts, sums_i);
+        hipLaunchKernelGGL(search_base_kernel, dim3((NC + 15) / 16), dim3(1024), 0, st, sums_i, kBinBlocks, maxparts, nparts, NC, base,
+                           shifts);
         const int cb = (int)(n / 4096 < kCutBlocks ? (n / 4096 > 0 ? n / 4096 : 1) : kCutBlocks);
-        hipLaunchKernelGGL(search_cuts_kernel, dim3(cb), dim3(512), 0, st, x, n, maxparts, nparts, a, starts, cuts, sums_c);
-        hipLaunchKernelGGL(search_reduce_kernel, dim3((NC + 15) / 16), dim3(1024), 0, st, nullptr, 0, sums_i, kBinBlocks, sums_c, cb, n, NC,
-                           mse_w);
+        hipLaunchKernelGGL(search_cuts_kernel, dim3(cb), dim3(512), 0, st, x, n, maxparts, nparts, a, starts, cuts, shifts,
+                           sums_c);
+        hipLaunchKernelGGL(search_reduce_kernel<double>, dim3((NC + 15) / 16), dim3(1024), 0, st, sums_c, cb, base, n, NC, mse_w);
         mse = mse_w;
     } else if (rows > 0) {
         // few elements: split the candidates, at least 16 for a workgroup (the lane sums that end each candidate weigh more
@@ -641,8 +678,7 @@ int launch_search(const float* x, size_t n, const SearchArgs& a, const float* ma
         const size_t used = up256((size_t)rows * NC * 4);
         if (rows > 48 && partial_bytes >= used + up256((size_t)NC * 8)) {   // more rows than one workgroup adds in the time of a launch
             double* mse_w = reinterpret_cast<double*>(reinterpret_cast<uint8_t*>(partial) + used);
-            hipLaunchKernelGGL(search_reduce_kernel, dim3((NC + 15) / 16), dim3(1024), 0, st, partial, rows, nullptr, 0, nullptr, 0,
-                               n, NC, mse_w);
+            hipLaunchKernelGGL(search_reduce_kernel<float>, dim3((NC + 15) / 16), dim3(1024), 0, st, partial, rows, nullptr, n, NC, mse_w);
             mse = mse_w;
         }
     }

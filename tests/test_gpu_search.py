@@ -169,3 +169,23 @@ def test_search_scales_with_the_tensor(k):
     got, r = run_search(np.ldexp(x, k), FP8 + FP4, 111)
     assert np.all(np.abs(np.ldexp(got.astype(np.float64), -2 * k) - want) <= 1e-6 * want)
     assert (r.encoding, r.bias_index) == (r0.encoding, r0.bias_index)
+
+
+@pytest.mark.parametrize("offset,outlier", [(0, 0), (1, 0), (0, 60)])
+def test_search_has_the_same_bits_every_time(offset, outlier):
+    """Repeated calls agree in every bit, and an encoding listed twice has equal errors, of which the first is chosen."""
+    x = synth.activations((BINNED + 50001,), 91)
+    if outlier:
+        x[::3] *= np.float32(2.0 ** -40)
+        x[4] = np.float32(2.0 ** (outlier // 4))
+    x = x[offset:]
+    encodings = [(4, 3), (3, 4), (4, 3), (3, 4), (2, 5), (2, 5), (5, 2), (5, 2)]
+    first, r = run_search(x, encodings, 111)
+    for _ in range(4):
+        again, ra = run_search(x, encodings, 111)
+        assert np.array_equal(again, first)
+        assert (ra.encoding, ra.bias_index, ra.mse) == (r.encoding, r.bias_index, r.mse)
+    for i, j in ((0, 2), (1, 3), (4, 5), (6, 7)):
+        assert np.array_equal(first[i], first[j])
+    assert r.encoding in (0, 1, 4, 6)
+    check(x, encodings[:2] + [(5, 2)], 111)

@@ -497,27 +497,36 @@ int tile_of(long I, long J, int slices)
 }
 long tiles_of(long I, long J, int T) { return ((I + T - 1) / T) * ((J + T - 1) / T); }
 
+// The record of the devices that allow the kernel its LDS is one per kernel: kernels of one type share a static of a generic
+// lambda over them.
+template <int T, bool KCONTIG, bool VEC, bool SUMSQ>
+int launch_sgemm_tile(const float* p, long pstride, const float* q, long qstride, int I, int J, int Kc, float scale, float* c,
+                      long cstride, int slices, float* sq, hipStream_t st)
+{
+    constexpr int lds = 3 * 6 * 2 * (T + 8) * 16;
+    auto kern = sgemm_kernel<T, KCONTIG, VEC, SUMSQ>;
+    if (lds > 65536) {
+        static std::atomic<uint64_t> allowed{0};
+        if (!allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds, allowed)) return FPQ_ERR_LAUNCH;
+    }
+    const int kslice = ((Kc + slices - 1) / slices + 15) / 16 * 16;
+    hipLaunchKernelGGL(kern, dim3((unsigned)tiles_of(I, J, T), slices), dim3(256), lds, st, p, pstride, q, qstride, I, J, Kc, scale, c,
+                       cstride, kslice, sq);
+    return hipGetLastError() == hipSuccess ? FPQ_OK : FPQ_ERR_LAUNCH;
+}
+
 // slices > 1: the contraction is cut into that many pieces, piece z writes c + z * I * cstride (the caller adds them up)
 template <bool KCONTIG, bool SUMSQ>
-void launch_sgemm(const float* p, long pstride, const float* q, long qstride, int I, int J, int Kc, float scale, float* c,
-                  long cstride, int slices, float* sq, hipStream_t st)
+int launch_sgemm(const float* p, long pstride, const float* q, long qstride, int I, int J, int Kc, float scale, float* c,
+                 long cstride, int slices, float* sq, hipStream_t st)
 {
     // 16-byte loads: aligned bases and rows, and a multiple of 4 elements along the direction of the loads
     const bool vec = ((reinterpret_cast<uintptr_t>(p) | reinterpret_cast<uintptr_t>(q)) & 15) == 0 && pstride % 4 == 0 &&
                      qstride % 4 == 0 && (KCONTIG ? Kc % 4 == 0 : I % 4 == 0 && J % 4 == 0);
-    const int kslice = ((Kc + slices - 1) / slices + 15) / 16 * 16;
-    const int T = tile_of(I, J, slices);
-    const dim3 grid((unsigned)tiles_of(I, J, T), slices);
-    const int lds = 3 * 6 * 2 * (T + 8) * 16;
-    auto go = [&](auto kern) {
-        static std::atomic<uint64_t> allowed{0};
-        if (lds > 65536 && !allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds, allowed)) return;   // the launch then fails
-        hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, p, pstride, q, qstride, I, J, Kc, scale, c, cstride, kslice, sq);
-    };
-    if (vec)
-        T == 128 ? go(sgemm_kernel<128, KCONTIG, true, SUMSQ>) : go(sgemm_kernel<64, KCONTIG, true, SUMSQ>);
-    else
-        T == 128 ? go(sgemm_kernel<128, KCONTIG, false, SUMSQ>) : go(sgemm_kernel<64, KCONTIG, false, SUMSQ>);
+    const bool big = tile_of(I, J, slices) == 128;
+    auto run = vec ? (big ? launch_sgemm_tile<128, KCONTIG, true, SUMSQ> : launch_sgemm_tile<64, KCONTIG, true, SUMSQ>)
+                   : (big ? launch_sgemm_tile<128, KCONTIG, false, SUMSQ> : launch_sgemm_tile<64, KCONTIG, false, SUMSQ>);
+    return run(p, pstride, q, qstride, I, J, Kc, scale, c, cstride, slices, sq, st);
 }
 
 // Slices of the gradient product (its contraction runs over the M calibration rows, its output is only [N, K]): enough
@@ -597,9 +606,11 @@ int launch_rl_step(const float* w, const float* sw, int64_t N, int64_t K, const 
     auto update = v4 ? rl_update_kernel<4> : rl_update_kernel<1>;
     hipLaunchKernelGGL(soft, dim3(bw), dim3(256), 0, st, w, sw, alpha, nw, (int)K, q, d, regp);
     // R[m, n] = sum_k A[m, k] D[n, k]
-    launch_sgemm<true, true>(a, K, d, K, (int)M, (int)N, (int)K, 1.0f, r, N, 1, sqp, st);
+    int rc = launch_sgemm<true, true>(a, K, d, K, (int)M, (int)N, (int)K, 1.0f, r, N, 1, sqp, st);
+    if (rc) return rc;
     // G[n, k] = (2 / (M N)) sum_m R[m, n] A[m, k]
-    launch_sgemm<false, false>(r, N, a, K, (int)N, (int)K, (int)M, (float)(2.0 / (double)nr), g, K, slices, nullptr, st);
+    rc = launch_sgemm<false, false>(r, N, a, K, (int)N, (int)K, (int)M, (float)(2.0 / (double)nr), g, K, slices, nullptr, st);
+    if (rc) return rc;
     const LossArgs losses{sqp, nsq, (double)nr, regp, bw, (double)nw, loss_out};
     hipLaunchKernelGGL(update, dim3(bw), dim3(256), 0, st, w, sw, alpha, g, slices, nw, (int)K, q, lr,
                        (float)((double)reg_weight / (double)nw), grad_out, losses);

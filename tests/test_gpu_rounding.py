@@ -195,6 +195,12 @@ def test_step_at_tile_edges(M, N, K):
     check_step(N, K, M, E2M1, 9700 + M)
 
 
+def test_steps_of_both_loads_in_one_process():
+    """A kernel's allowance of more than 64 KB of LDS is its own: both forms run, whichever ran first."""
+    for M, N, K in [(4100, 1028, 20), (4099, 1027, 27), (4100, 1028, 20)]:
+        check_step(N, K, M, E2M1, 9760 + N)
+
+
 def test_weights_of_a_convolution_are_refused():
     """The step takes weights as a matrix; a four-dimensional tensor is an error of the caller, not its first two sizes."""
     w = torch.zeros((4, 8, 3, 3), dtype=torch.float32, device=DEV)

@@ -195,6 +195,18 @@ def test_step_at_tile_edges(M, N, K):
     check_step(N, K, M, E2M1, 9700 + M)
 
 
+# Products of at least 256 tiles of 128 x 128 (output error: M x N; gradient: N x K times the slices of M), and the loads they
+# take: 16 bytes where rows have a multiple of 4 elements, single elements otherwise.
+BIG = [((4100, 1028, 20), "output error, 16-byte loads"), ((4099, 1027, 27), "output error, single elements"),
+       ((2050, 645, 1283), "gradient, single elements"), ((2052, 644, 1284), "gradient, 16-byte loads")]
+
+
+@pytest.mark.parametrize("shape,what", BIG)
+def test_step_of_128_tiles(shape, what):
+    M, N, K = shape
+    check_step(N, K, M, E2M1, 9750 + N)
+
+
 def test_steps_of_both_loads_in_one_process():
     """A kernel's allowance of more than 64 KB of LDS is its own: both forms run, whichever ran first."""
     for M, N, K in [(4100, 1028, 20), (4099, 1027, 27), (4100, 1028, 20)]:

@@ -593,8 +593,10 @@ __global__ __launch_bounds__(1024) void search_select_kernel(const double* __res
         if (mse_out) mse_out[c] = (float)v;
         at = c;
     }
-    auto take = [&](double ov, int oi) {             // an error that is no number is never taken
-        if (oi < kSearchMaxCandidates && (at == kSearchMaxCandidates || ov < v || (ov == v && oi < at) || !(v == v))) {
+    const double own = v;
+    if (!(v == v)) v = __builtin_huge_val();         // an error that is no number is as bad as an infinite one: never less than another
+    auto take = [&](double ov, int oi) {
+        if (oi < kSearchMaxCandidates && (at == kSearchMaxCandidates || ov < v || (ov == v && oi < at))) {
             v = ov;
             at = oi;
         }
@@ -619,7 +621,7 @@ __global__ __launch_bounds__(1024) void search_select_kernel(const double* __res
         result->int_bias = a.enc[i].b0;
         result->maxval = cj;
         result->scale = (float)((double)cj / (double)a.enc[i].c0);
-        result->mse = (float)v;
+        result->mse = (float)(at == 0 ? own : v);    // thread 0's own candidate is the first one
         // Eq. (7) solved for the bias: c = (2 - 2^-m) 2^(2^e - b - 1)
         result->real_bias = (float)((double)((1 << e) - 1) - log2((double)cj / (2.0 - exp2((double)-m))));
     }

@@ -189,3 +189,16 @@ def test_search_has_the_same_bits_every_time(offset, outlier):
         assert np.array_equal(first[i], first[j])
     assert r.encoding in (0, 1, 4, 6)
     check(x, encodings[:2] + [(5, 2)], 111)
+
+
+@pytest.mark.parametrize("n", [1000, 524288])
+@pytest.mark.parametrize("bad", [[float("nan")], [float("inf")], [float("nan"), float("-inf")]])
+def test_search_without_a_finite_error_takes_the_first_candidate(n, bad):
+    """With no finite error nothing is less than the first candidate's, in the direct and the binned form; the error is reported
+    as it is."""
+    x = synth.activations((n,), 77)
+    x[n // 3:n // 3 + len(bad)] = bad
+    got, r = run_search(x, FP8, 111)
+    assert not np.isfinite(got).any()
+    assert (r.encoding, r.bias_index) == (0, 0)
+    assert r.mse == got[0, 0] or (np.isnan(r.mse) and np.isnan(got[0, 0]))

@@ -46,9 +46,10 @@ __device__ __forceinline__ void dma16(v4i rsrc, unsigned voff, unsigned lds_addr
                  : "memory");
 }
 
-// The same for a wavefront that may have nothing left to load: live = all ones, or zero, and then no lane takes part.  The load
-// still counts in vmcnt, so the waits stay as they are, but nothing is moved; out-of-range offsets in its place would write
-// zeros to LDS at the rate of a real load (about 50 bytes per clock), 0.5 to 1 us at the end of every launch.
+// The same for a wavefront that may have nothing left to load: live = all ones, or zero, and then no lane takes part and nothing
+// is moved; out-of-range offsets in its place would write zeros to LDS at the rate of a real load (about 50 bytes per clock), 0.5
+// to 1 us at the end of every launch.  No wait may rest on such a load being counted in vmcnt, or on its not being counted:
+// the kernels' waits count loads of lanes that take part only.
 // All 64 lanes of the calling wavefronts are active.
 __device__ __forceinline__ void dma16_live(v4i rsrc, unsigned voff, unsigned lds_addr, int live)
 {
@@ -820,7 +821,7 @@ __global__ __launch_bounds__(256, (BX <= 128 ? 2 : 1)) void gemm_dma_kernel(cons
     // loads per step and they complete in order.  The loads run NSTAGE - 1 steps ahead of the MFMAs,
     // across item boundaries.  Every step issues one group of LOADS loads; once the work items run out
     // the group moves nothing (no lane takes part, or every offset is out of range: zeros into a free ring slot), which
-    // keeps the control flow and the vmcnt arithmetic uniform.
+    // keeps the control flow uniform, and with the offsets the vmcnt arithmetic too.
     int istage = 0;
     auto issue_nothing = [&]() {
         live = 0;
@@ -863,8 +864,11 @@ __global__ __launch_bounds__(256, (BX <= 128 ? 2 : 1)) void gemm_dma_kernel(cons
                 for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
     };
     {
-        // the first ring slot: its group is the oldest of the NSTAGE - 1 outstanding ones
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(LOADS * (NSTAGE - 2)));
+        // the first ring slot: its group is the oldest of the NSTAGE - 1 outstanding ones (of fewer, if the loads ran out already)
+        if (MASKED && NSTAGE > 2 && !live)
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+        else
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm(LOADS * (NSTAGE - 2)));
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
@@ -881,7 +885,8 @@ __global__ __launch_bounds__(256, (BX <= 128 ? 2 : 1)) void gemm_dma_kernel(cons
             issue_scales(tw * BW, sl, par);
             for (int kt = 0; kt < nk; ++kt) {
                 const int nstage = (cstage + 1 == NSTAGE) ? 0 : cstage + 1;
-                const int mode = since < NSTAGE - 2 ? after : (int)W_NORMAL;
+                // (once the loads have run out, the wanted group is the youngest there is)
+                const int mode = MASKED && NSTAGE > 2 && !live ? (int)W_DRAIN : since < NSTAGE - 2 ? after : (int)W_NORMAL;
                 if constexpr (ACC == FPQ_ACC_FP32)
                     compute(cstage, nstage, istage, mode);
                 else
@@ -890,7 +895,7 @@ __global__ __launch_bounds__(256, (BX <= 128 ? 2 : 1)) void gemm_dma_kernel(cons
                 issued();
                 cstage = nstage;
             }
-            // the scale loads are older than the loads issued during the item's K steps (at least one group)
+            // the scale loads are older than the loads issued during the item's K steps (at least one group, or after a wait for zero)
             __builtin_amdgcn_s_waitcnt(vmcnt_imm(LOADS));
             asm volatile("" ::: "memory");
             after = epilogue(tx * BX, tw * BW, sl, par);

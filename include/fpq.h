@@ -275,7 +275,8 @@ int fpq_conv2d(const void *x, int x_is_fp32, fpq_format_t fx, float sx, const fl
 
 /* Read-only query (host, no GPU): which kernel fpq_gemm / fpq_conv2d launch for a shape and into how many K slices
  * they cut it, given a workspace of the size the *_workspace_size functions state and operands in the hardware's
- * E4M3 / E2M1 encodings (other operand pairings may take FPQ_KERNEL_SMALL_TILE, unsliced, whatever the shape).
+ * E4M3 / E2M1 encodings (other operand pairings may take another kernel or number of slices, and some of them
+ * FPQ_KERNEL_SMALL_TILE, unsliced, whatever the shape).
  * With more than one slice the layer kernel writes partial sums to the workspace and a reduction kernel adds them.
  * For tests and benchmarks that have to state, or to cover, every launch configuration a workload uses. */
 typedef enum fpq_kernel {
@@ -461,7 +462,7 @@ int fpq_probe_peak(int kind, int iterations, const void *src, void *dst, size_t 
  * maxima and scale of the dynamic-scale form) lives in a static device array of FPQ_NOALLOC_SCRATCH_BYTES inside
  * the library, of which every GPU the library runs on holds its own copy until the process ends.  The call
  * allocates nothing and frees nothing.  The first call on a device looks the array's address up (make it outside
- * a graph capture).  A shape whose fpq_gemm_workspace_size exceeds FPQ_NOALLOC_SCRATCH_BYTES runs in one K slice if it
+ * a graph capture).  A call whose codes, scale and partial sums exceed FPQ_NOALLOC_SCRATCH_BYTES runs in one K slice if it
  * takes FPQ_KERNEL_SMALL_TILE or a width that is no multiple of 160 and fits without partial sums; any other returns
  * FPQ_ERR_WORKSPACE and launches nothing.  All calls on one GPU share that GPU's array: nothing in it has to
  * start at zero and every call overwrites what it uses, but two calls that overlap in time on one GPU (different

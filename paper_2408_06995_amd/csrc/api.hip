@@ -425,8 +425,7 @@ size_t fpq_gemm_workspace_size(int64_t M, int64_t N, int64_t K, int x_is_fp32)
 {
     if (M <= 0 || K <= 0 || N <= 0) return 0;
     size_t codes = x_is_fp32 ? align_up((size_t)M * (size_t)padded_channels(K), 256) : 0;
-    return codes + align_up(split_workspace_bytes(plan_gemm(M, N, padded_k(K, 1)), M, N), 256) +
-           (x_is_fp32 == FPQ_X_FP32_DYNAMIC ? kDynScaleBytes : 0);
+    return codes + align_up(most_split_workspace_bytes(M, N, padded_k(K, 1)), 256) + (x_is_fp32 == FPQ_X_FP32_DYNAMIC ? kDynScaleBytes : 0);
 }
 
 size_t fpq_conv2d_workspace_size(int64_t B, int64_t Cin, int64_t H, int64_t W, int64_t Cout, int kh, int kw,
@@ -436,9 +435,7 @@ size_t fpq_conv2d_workspace_size(int64_t B, int64_t Cin, int64_t H, int64_t W, i
     if (H + 2 * pad < kh || W + 2 * pad < kw) return 0;
     const int64_t Ho = (H + 2 * pad - kh) / stride + 1, Wo = (W + 2 * pad - kw) / stride + 1;
     size_t codes = x_is_fp32 ? align_up((size_t)B * H * W * (size_t)padded_channels(Cin), 256) : 0;
-    return codes +
-           align_up(split_workspace_bytes(plan_gemm(B * Ho * Wo, Cout, padded_k(Cin, (int64_t)kh * kw)), B * Ho * Wo, Cout),
-                    256) +
+    return codes + align_up(most_split_workspace_bytes(B * Ho * Wo, Cout, padded_k(Cin, (int64_t)kh * kw)), 256) +
            (x_is_fp32 == FPQ_X_FP32_DYNAMIC ? kDynScaleBytes : 0);
 }
 
@@ -535,7 +532,8 @@ static int run_layer(const CodesOut* out, const void* x, int x_is_fp32, fpq_form
     const uint8_t* xcodes;
     // workspace = [activation codes when the input is fp32][split-K partial results]; a caller that passes
     // codes and no (or too small a) workspace gets the unsplit kernel
-    GemmPlan plan = plan_gemm(M, Cout, padded_k(Cin, (int64_t)kh * kw));
+    const int64_t kpad = padded_k(Cin, (int64_t)kh * kw);
+    GemmPlan plan = xkind == OPK_GENERIC8 ? plan_arithmetic(M, Cout, kpad) : plan_gemm(M, Cout, kpad);
     if (sparse) {
         // the structured-sparse form has one kernel: hardware E4M3 activations, E4M3 / E2M1 weights, exact accumulate
         if (out || accumulate || acc_mode != FPQ_ACC_FP32 || xkind != OPK_FP8 || (wkind != OPK_FP8 && wkind != OPK_FP4))
@@ -968,23 +966,31 @@ int fpq_probe_peak(int kind, int iterations, const void* src, void* dst, size_t 
     return FPQ_OK;
 }
 
+// The plan of a linear layer in these formats (formats that the call will refuse: any).
+static GemmPlan plan_for(fpq_format_t fx, fpq_format_t fw, int acc_mode, int64_t M, int64_t N, int64_t kpad)
+{
+    QParams qx, qw;
+    int xkind, wkind;
+    float alpha;
+    const bool arithmetic = resolve_format(fx, &qx) == FPQ_OK && resolve_format(fw, &qw) == FPQ_OK &&
+                            resolve_kinds(fx, qx.c, fw, qw.c, acc_mode & ~FPQ_OUT_ACCUMULATE, &xkind, &wkind, &alpha) == FPQ_OK &&
+                            xkind == OPK_GENERIC8;
+    return arithmetic ? plan_arithmetic(M, N, kpad) : plan_gemm(M, N, kpad);
+}
+
 int fpq_gemm_noalloc(const void* x, int x_is_fp32, fpq_format_t fx, float sx, const float* sx_dev, const void* packed_w,
                      fpq_format_t fw, const float* sw, const float* bias, float* y, int64_t M, int64_t N, int64_t K,
                      int acc_mode, void* stream)
 {
     if (M == 0 && N > 0 && K > 0) return FPQ_OK;
     if (M < 0 || N <= 0 || K <= 0) return FPQ_ERR_SHAPE;
-    // The scratch a call of this shape needs is what fpq_gemm would ask of its caller.  K slices of the small tiles are a matter of
-    // speed only: a call that fits without their partial sums runs in one slice.
-    bool sliced = true;
-    if (fpq_gemm_workspace_size(M, N, K, x_is_fp32) > kStaticScratchBytes) {
-        sliced = false;
-        const int64_t kpad = padded_k(K, 1);
-        const size_t part_bytes = align_up(split_workspace_bytes(plan_gemm(M, N, kpad), M, N), 256);
-        if (!takes_plan_small(M, N, kpad / 128) ||
-            fpq_gemm_workspace_size(M, N, K, x_is_fp32) - part_bytes > kStaticScratchBytes)
-            return FPQ_ERR_WORKSPACE;
-    }
+    // What the scratch has to hold: codes, scale and the partial sums of this call's plan.  K slices of the small tiles are a
+    // matter of speed only: a call that fits without their partial sums runs in one slice.
+    const int64_t kpad = padded_k(K, 1);
+    const size_t part_bytes = align_up(split_workspace_bytes(plan_for(fx, fw, acc_mode, M, N, kpad), M, N), 256);
+    const size_t rest = fpq_gemm_workspace_size(M, N, K, x_is_fp32) - align_up(most_split_workspace_bytes(M, N, kpad), 256);
+    const bool sliced = rest + part_bytes <= kStaticScratchBytes;
+    if (!sliced && (!takes_plan_small(M, N, kpad / 128) || rest > kStaticScratchBytes)) return FPQ_ERR_WORKSPACE;
     void* ws = nullptr;
     const int st = scratch_on_current_device(&ws);
     if (st) return st;

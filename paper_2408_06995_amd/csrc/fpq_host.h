@@ -204,6 +204,37 @@ static inline bool takes_plan_small(int64_t M, int64_t N, int64_t nk)
     return M <= 16 || N % 160 != 0 || (M * N <= ((int64_t)2 << 20) && nk <= 20) || (N <= 480 && t64 <= 512 && nk >= 8) ||
            (tiles < 32 && nk <= 128);
 }
+// Widths that are multiples of 160: the 256 x 160 and 128 x 160 tiles and their slices.
+static inline GemmPlan plan_wide(int64_t M, int64_t N, int64_t nk)
+{
+    GemmPlan p{TILE_128x160_S2, 1};
+    const int64_t tiles256 = ((M + 255) / 256) * (N / 160), tiles = ((M + 127) / 128) * (N / 160);
+    int64_t s = 1;
+    if (nk >= 16 && tiles256 >= 192) {
+        p.tile = TILE_256x160_S3;
+        return p;
+    }
+    if (tiles256 < 192 && tiles256 >= 48 && nk >= 32 * ((256 + tiles256 / 2) / tiles256)) {
+        p.tile = TILE_256x160_S3;
+        s = (256 + tiles256 / 2) / tiles256;
+    } else if (tiles < 192 && nk >= 16) {
+        s = (256 + tiles - 1) / tiles;              // one work item per compute unit ...
+        if (nk / (2 * s) >= 20) s *= 2;             // ... two when each still has 20 K steps
+        if (s > nk / 8) s = nk / 8;
+        if (s > 32) s = 32;
+    } else if (tiles <= 16 && nk >= 4) {
+        s = nk / 2 < 8 ? nk / 2 : 8;                // a few tiles and a short K: bound by the length of the serial K loop
+    }
+    while (s > 1 && s * M * N * 4 > ((int64_t)256 << 20)) --s;
+    p.splits = s < 1 ? 1 : (int)s;
+    return p;
+}
+// A plan of plan_wide that leaves compute units idle and is not sliced.
+static inline bool unsliced_part_grid(const GemmPlan& p, int64_t M, int64_t N, int64_t nk)
+{
+    return p.splits == 1 && p.tile == TILE_128x160_S2 && ((M + 127) / 128) * (N / 160) < 192 && nk >= 8;
+}
+// Operands with a hardware conversion or moved into halves.
 static inline GemmPlan plan_gemm(int64_t M, int64_t N, int64_t Kpad)
 {
     GemmPlan p{TILE_GENERIC, 1};
@@ -214,37 +245,36 @@ static inline GemmPlan plan_gemm(int64_t M, int64_t N, int64_t Kpad)
         p.splits = 1;
         return p;
     }
-    const int64_t tiles = ((M + 127) / 128) * ((N + 159) / 160);
     if (takes_plan_small(M, N, nk)) {
         p = plan_small(M, N, nk);
         while (p.splits > 1 && p.splits * M * N * 4 > ((int64_t)256 << 20)) --p.splits;
         return p;
     }
-    const int64_t tiles256 = ((M + 255) / 256) * (N / 160);
-    int64_t s = 1;
-    if (nk >= 16 && tiles256 >= 192) {
-        p.tile = TILE_256x160_S3;
-        return p;
-    }
-    p.tile = TILE_128x160_S2;
-    if (tiles256 < 192 && tiles256 >= 48 && nk >= 32 * ((256 + tiles256 / 2) / tiles256)) {
-        p.tile = TILE_256x160_S3;
-        s = (256 + tiles256 / 2) / tiles256;
-    } else if (tiles < 192 && nk >= 16) {
-        s = (256 + tiles - 1) / tiles;              // one work item per compute unit ...
-        if (nk / (2 * s) >= 20) s *= 2;             // ... two when each still has 20 K steps
-        if (s > nk / 8) s = nk / 8;
-        if (s > 32) s = 32;
-    }
-    while (s > 1 && s * M * N * 4 > ((int64_t)256 << 20)) --s;
-    if (s < 1) s = 1;
-    if (s == 1 && tiles < 192 && nk >= 8) p.tile = TILE_128x64;
-    p.splits = (int)s;
+    p = plan_wide(M, N, nk);
+    if (unsliced_part_grid(p, M, N, nk)) p.tile = TILE_128x64;
     return p;
 }
+// Operands decoded arithmetically (five exponent bits and more): the small tiles are not built for them, so widths that are
+// multiples of 160 keep the 160-wide tiles and their slices (E5M2, 256 x 11520 -> 1280: 70 us, 209 us on the register-staged
+// kernel; 40 x 5120 -> 1280: 60 and 92 us; 4096 x 2880 -> 320: 86 and 98 us).  The register-staged kernel serves small outputs with
+// a short K, and grids of less than 192 tiles that are not sliced (2048 x 1280 -> 1280: 63 us, 69 us on 128 x 160 tiles).
+static inline GemmPlan plan_arithmetic(int64_t M, int64_t N, int64_t Kpad)
+{
+    const int64_t nk = Kpad / 128;
+    if (N % 160 != 0 || M <= 16 || (M * N <= ((int64_t)2 << 20) && nk <= 20)) return GemmPlan{TILE_GENERIC, 1};
+    const GemmPlan p = plan_wide(M, N, nk);
+    return unsliced_part_grid(p, M, N, nk) ? GemmPlan{TILE_GENERIC, 1} : p;
+}
+
 static inline size_t split_workspace_bytes(const GemmPlan& p, int64_t M, int64_t N)
 {
     return p.splits > 1 ? (size_t)p.splits * (size_t)M * (size_t)N * sizeof(float) : 0;
+}
+// Partial sums that a layer of any operand kinds may want.
+static inline size_t most_split_workspace_bytes(int64_t M, int64_t N, int64_t Kpad)
+{
+    const size_t a = split_workspace_bytes(plan_gemm(M, N, Kpad), M, N), b = split_workspace_bytes(plan_arithmetic(M, N, Kpad), M, N);
+    return a > b ? a : b;
 }
 
 // Encoding / bias search (Section V-A): at most 8 encodings x 128 bias candidates.

@@ -154,6 +154,15 @@ def test_plan_query_and_format_range():
     assert B.fpq_format_check((5, 2, -64, 0.0)) == 0 and B.fpq_format_check((4, 3, -64, 0.0)) == 0
 
 
+def test_workspace_holds_the_partial_sums_of_any_operands():
+    """Formats of five exponent bits are not built on the small tiles: on widths of 160 they keep the 160-wide tiles and their
+    slices, also where the hardware's formats take small tiles in fewer slices, or whole."""
+    for M, N, K, slices in [(256, 1280, 11520, 11), (4096, 320, 2880, 2), (40, 1280, 5120, 5), (2048, 1280, 1280, 1),
+                            (616, 320, 768, 1), (8, 1280, 11520, 1)]:
+        most = max(slices, B.fpq_gemm_plan(M, N, K)[1])
+        assert B.fpq_gemm_workspace_size(M, N, K, 0) == (most * M * N * 4 if most > 1 else 0), (M, N, K)
+
+
 def test_noalloc_entry_validates_before_touching_the_gpu():
     L = B.lib()
     f = B.fmt(synth.E4M3)

@@ -133,3 +133,12 @@ def test_grouped_call_has_the_bits_of_single_calls(fx, fw, acc):
         B.fpq_gemm(xq, 0, fx, 0.0, sx, packed, fw, sw_t, bias, y1, M, N, K, acc, ws)
         torch.cuda.synchronize()
         assert torch.equal(y, y1), (M, K, N)
+
+
+# Operands that are decoded arithmetically on widths that are multiples of 160: the 128 x 160 tile in 11, 5, 2 and one slices, the
+# 256 x 160 tile, and the register-staged kernel for a small output or a small grid with a short K.
+@pytest.mark.parametrize("fx,fw", [(synth.E5M2, synth.E5M2), (E4M3, synth.E5M2), (synth.E5M2, E2M1)])
+@pytest.mark.parametrize("M,K,N", [(256, 11520, 1280), (40, 5120, 1280), (4096, 2880, 320), (2048, 1280, 1280), (4096, 640, 640),
+                                   (3072, 2048, 2560), (616, 768, 320)])
+def test_arithmetic_operands(M, K, N, fx, fw):
+    test_linear(M, K, N, fx, fw, 0)

@@ -712,25 +712,22 @@ static int launch_gemm_grouped_tiles(const GroupedArgs& g, hipStream_t st)
     return launch_grouped_one<OPK_GENERIC8, OPK_GENERIC8, FPQ_ACC_FP32>(g, st);
 }
 
-// The problems that fpq_gemm would give to the kernel with K split over the wavefronts go to that kernel (its sums have their
-// own order) while their tiles fit on the chip at once; the register-staged kernel, of which more workgroups fit on a compute
-// unit, is the faster one for more (30 x 1013 x 1264 -> 432: 113 us, 170 us on 128 x 64 tiles of the LDS-DMA kernel).
+// Problems of a few tiles that fpq_gemm would give to the kernel with K split over the wavefronts go to that kernel (its sums have
+// their own order).  The rule looks at the problem alone, so that its bits do not depend on the others of the call; 32 problems
+// of at most 16 tiles are on the chip at once with any others' share, and with more tiles the register-staged kernel, of which more
+// workgroups fit on a compute unit, is as fast or faster: 8 x 616 x 1024 -> 320 10.2 us, 10.9 us over the wavefronts;
+// 30 x 1013 x 1264 -> 432 58 and 72 us; 32 x 100 x 1040 -> 100 8.0 us either way; 8 x 154 x 2048 -> 640 13.6 and 12.7 us.
 int launch_gemm_grouped(const GroupedArgs& g, hipStream_t st)
 {
     if (g.count <= 0) return FPQ_OK;
     GroupedArgs part[2];
-    int which[kGroupMax];
-    int tiles = 0;
     const bool wk = grouped_wk_applicable(g.common);
-    for (int i = 0; i < g.count; ++i) {
-        const GemmPlan plan = plan_gemm(g.p[i].M, g.p[i].N, g.p[i].Kpad);
-        which[i] = wk && (plan.tile == TILE_WAVE_K4 || plan.tile == TILE_WAVE_K2) ? 1 : 0;
-        if (which[i]) tiles += ((g.p[i].M + 63) / 64) * ((g.p[i].N + 63) / 64);
-    }
     part[0].count = part[1].count = 0;
     part[0].common = part[1].common = g.common;
     for (int i = 0; i < g.count; ++i) {
-        GroupedArgs& to = part[tiles <= 512 ? which[i] : 0];
+        const GemmPlan plan = plan_gemm(g.p[i].M, g.p[i].N, g.p[i].Kpad);
+        const int tiles = ((g.p[i].M + 63) / 64) * ((g.p[i].N + 63) / 64);
+        GroupedArgs& to = part[wk && (plan.tile == TILE_WAVE_K4 || plan.tile == TILE_WAVE_K2) && tiles <= 16 ? 1 : 0];
         to.p[to.count++] = g.p[i];
     }
     int rc = FPQ_OK;

@@ -142,3 +142,24 @@ def test_grouped_call_has_the_bits_of_single_calls(fx, fw, acc):
                                    (3072, 2048, 2560), (616, 768, 320)])
 def test_arithmetic_operands(M, K, N, fx, fw):
     test_linear(M, K, N, fx, fw, 0)
+
+
+@pytest.mark.parametrize("M,K,N", [(200, 1040, 256), (200, 1040, 257), (616, 1024, 320), (1407, 3312, 100)])
+def test_grouped_bits_do_not_depend_on_the_other_problems(M, K, N):
+    """At and beyond the 16 tiles up to which a problem has its K split over the wavefronts; alone, and among problems that fill the
+    chip."""
+    def problem(M, K, N, seed):
+        x = synth.activations((M, K), seed)
+        sx = oracle.scale_from_absmax(oracle.absmax(x), E4M3[3])
+        packed, sw_t, _ = gpu_pack(synth.weights((N, K), seed + 1), E4M3, None, want_codes=False)
+        return [dev(oracle.quantize(x, E4M3, sx)), dev(np.array([sx], dtype=np.float32)), packed, sw_t, None,
+                torch.full((M, N), float("nan"), device=DEV), M, N, K]
+    one, other = problem(M, K, N, 950), problem(616, 1024, 320, 960)
+    B.fpq_gemm_grouped(B.gemm_problems([one]), B.FPQ_X_CODES, E4M3, E4M3, 0, None)
+    torch.cuda.synchronize()
+    alone = one[5].clone()
+    one[5].fill_(float("nan"))
+    others = [other[:5] + [torch.empty_like(other[5])] + other[6:] for _ in range(20)]
+    B.fpq_gemm_grouped(B.gemm_problems(others[:7] + [one] + others[7:]), B.FPQ_X_CODES, E4M3, E4M3, 0, None)
+    torch.cuda.synchronize()
+    assert torch.equal(one[5], alone)

@@ -414,5 +414,5 @@ try:
 except ImportError:
     globals().update((_n, _not_built(_n)) for _n in NATIVE)
 else:
-    _fpqcall.setup(_resolve, _check)
+    _fpqcall.setup(_resolve, _check, fpq_format_t, fpq_gemm_problem_t, C.Array)
     globals().update((_n, getattr(_fpqcall, _n)) for _n in NATIVE)

@@ -18,7 +18,8 @@ namespace {
 
 PyObject* g_resolve = nullptr;      // resolver(name) -> address of the C function
 PyObject* g_check = nullptr;        // checker(status, name): raises
-PyObject *s_data_ptr, *s_numel, *s_element_size, *s_shape;
+PyObject *g_format = nullptr, *g_problem = nullptr, *g_array = nullptr;   // fpq_format_t, fpq_gemm_problem_t, ctypes.Array
+PyObject *s_type, *s_data_ptr, *s_numel, *s_element_size, *s_shape;
 PyObject *g_get_device = nullptr, *g_get_stream = nullptr;
 
 constexpr int kBad = 1;             // a Python error is set (statuses of the library are <= 0)
@@ -111,7 +112,7 @@ struct Args {
         if (v == -1 && PyErr_Occurred()) bad = true;
         return v;
     }
-    // (e, m, b, c) or the ctypes structure
+    // the ctypes structure, or anything with four elements (e, m, b, c)
     fpq_format_t fmt(int k)
     {
         fpq_format_t r;
@@ -124,11 +125,12 @@ struct Args {
             bad |= t.bad;
             return r;
         }
-        if (PyObject_CheckBuffer(o)) {
+        const int is = PyObject_IsInstance(o, g_format);
+        if (is < 0) { bad = true; return r; }
+        if (is) {
             Py_buffer b;
             if (PyObject_GetBuffer(o, &b, PyBUF_SIMPLE)) { bad = true; return r; }
-            if (b.len == (Py_ssize_t)sizeof r) memcpy(&r, b.buf, sizeof r);
-            else { PyErr_SetString(PyExc_TypeError, "a format is (e, m, b, c)"); bad = true; }
+            memcpy(&r, b.buf, sizeof r);
             PyBuffer_Release(&b);
             return r;
         }
@@ -245,7 +247,15 @@ int do_conv2d_sparse(Args& A)
 int do_gemm_grouped(Args& A)
 {
     FN(fpq_gemm_grouped);
-    Py_buffer b;                                 // the array of gemm_problems()
+    // the array of gemm_problems() and nothing else that has a buffer: the library reads addresses from it
+    PyObject* of = PyObject_IsInstance(A.a[0], g_array) == 1 ? PyObject_GetAttr(A.a[0], s_type) : nullptr;
+    const bool problems = of == g_problem;
+    Py_XDECREF(of);
+    if (!problems) {
+        if (!PyErr_Occurred()) PyErr_Format(PyExc_TypeError, "problems: the array of gemm_problems(), not %s", Py_TYPE(A.a[0])->tp_name);
+        return kBad;
+    }
+    Py_buffer b;
     if (PyObject_GetBuffer(A.a[0], &b, PyBUF_SIMPLE)) return kBad;
     const int st = invoke(A, fn, static_cast<const fpq_gemm_problem_t*>(b.buf), (int)(b.len / (Py_ssize_t)sizeof(fpq_gemm_problem_t)),
                           A.i(1), A.fmt(2), A.fmt(3), A.i(4), A.p(5), A.bytes(5), A.stream());
@@ -385,12 +395,14 @@ PyObject* trampoline(PyObject*, PyObject* const* args, Py_ssize_t nargs, PyObjec
 
 PyObject* setup(PyObject*, PyObject* args)
 {
-    PyObject *r, *c;
-    if (!PyArg_ParseTuple(args, "OO", &r, &c)) return nullptr;
-    Py_INCREF(r);
-    Py_INCREF(c);
-    Py_XSETREF(g_resolve, r);
-    Py_XSETREF(g_check, c);
+    PyObject *r, *c, *f, *p, *a;
+    if (!PyArg_ParseTuple(args, "OOOOO", &r, &c, &f, &p, &a)) return nullptr;
+    PyObject** const to[] = {&g_resolve, &g_check, &g_format, &g_problem, &g_array};
+    PyObject* const from[] = {r, c, f, p, a};
+    for (int i = 0; i < 5; ++i) {
+        Py_INCREF(from[i]);
+        Py_XSETREF(*to[i], from[i]);
+    }
     Py_RETURN_NONE;
 }
 
@@ -413,6 +425,7 @@ PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_fpqcall", "Native argument mars
 
 PyMODINIT_FUNC PyInit__fpqcall(void)
 {
+    s_type = PyUnicode_InternFromString("_type_");
     s_data_ptr = PyUnicode_InternFromString("data_ptr");
     s_numel = PyUnicode_InternFromString("numel");
     s_element_size = PyUnicode_InternFromString("element_size");
@@ -434,7 +447,7 @@ PyMODINIT_FUNC PyInit__fpqcall(void)
         }
     }
     fill_methods<0>();
-    g_methods[kEntries] = PyMethodDef{"setup", setup, METH_VARARGS, "setup(resolver, checker)"};
+    g_methods[kEntries] = PyMethodDef{"setup", setup, METH_VARARGS, "setup(resolver, checker, fpq_format_t, fpq_gemm_problem_t, ctypes.Array)"};
     g_methods[kEntries + 1] = PyMethodDef{nullptr, nullptr, 0, nullptr};
     return PyModule_Create(&g_module);
 }

@@ -171,3 +171,15 @@ def test_noalloc_entry_validates_before_touching_the_gpu():
     assert L.fpq_gemm_noalloc(p, 0, f, 1.0, None, p, f, p, None, p, 0, 8, 32, 0, None) == 0
     assert L.fpq_gemm_noalloc(p, 0, f, 1.0, None, p, f, p, None, p, 8, 0, 32, 0, None) == -4
     assert L.fpq_strerror(-9).decode().startswith("packed weights")
+
+
+def test_grouped_call_takes_the_problem_array_only():
+    """The library reads device addresses from the array: other objects with a buffer are refused before that."""
+    array = B.gemm_problems([])
+    for other in (b"\0" * 72, bytearray(72), (C.c_int64 * 9)(), None, [1, 2], C.pointer((B.fpq_gemm_problem_t * 1)())):
+        with pytest.raises(TypeError, match="gemm_problems"):
+            B.fpq_gemm_grouped(other, 0, synth.E4M3, synth.E4M3)
+    with pytest.raises(Exception) as e:                       # (what the CPU has instead of a stream, or no error on a GPU)
+        B.fpq_gemm_grouped(array, 7, synth.E4M3, synth.E4M3)
+        raise RuntimeError("taken")
+    assert "gemm_problems" not in str(e.value)

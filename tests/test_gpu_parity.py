@@ -718,3 +718,16 @@ def test_fp8_mfma_mode_misses_the_layer_tolerance_on_the_synthetic_workload():
     worst = float((np.abs(y8 - Y) / tol).max())
     print("FP8-MFMA mode: %.2f %% of outputs outside 1e-5 T + 1e-6, worst err/tol %.1f" % (100 * miss, worst))
     assert 0.001 < miss < 0.2 and worst < 85.0      # 7 * 2^-13 / 1e-5 = 85 is the mode's own bound
+
+
+@pytest.mark.parametrize("of", [list, lambda f: B.fmt(f), lambda f: np.array(f, dtype=np.float32),
+                                lambda f: np.array(f, dtype=np.float64), lambda f: torch.tensor(f),
+                                lambda f: (np.int64(f[0]), np.int32(f[1]), f[2], np.float32(f[3]))])
+def test_a_format_is_anything_with_its_four_elements(of):
+    """Also an array whose buffer happens to have the size of the C structure."""
+    x = dev(synth.activations((1000,), 4321))
+    want, got = (torch.zeros(1000, dtype=torch.uint8, device=DEV) for _ in range(2))
+    B.fpq_quantize(x, synth.E4M3, 0.5, None, want)
+    B.fpq_quantize(x, of(synth.E4M3), 0.5, None, got)
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)

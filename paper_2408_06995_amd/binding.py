@@ -403,16 +403,19 @@ def _resolve(name):
     return C.cast(getattr(lib(), name), C.c_void_p).value
 
 
-def _not_built(name):
+def _unavailable(name, cause):
+    path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_fpqcall.so")
+    what = "does not load: %s" % cause if os.path.exists(path) else "is not built"
+
     def missing(*args, **kwargs):
-        raise ImportError("_fpqcall not built: run `python -m paper_2408_06995_amd.build` (needed by %s)" % name)
+        raise ImportError("%s needs _fpqcall.so, which %s (`python -m paper_2408_06995_amd.build` builds it)" % (name, what)) from cause
     return missing
 
 
 try:
     from . import _fpqcall
-except ImportError:
-    globals().update((_n, _not_built(_n)) for _n in NATIVE)
+except ImportError as _e:
+    globals().update((_n, _unavailable(_n, _e)) for _n in NATIVE)
 else:
     _fpqcall.setup(_resolve, _check, fpq_format_t, fpq_gemm_problem_t, C.Array)
     globals().update((_n, getattr(_fpqcall, _n)) for _n in NATIVE)

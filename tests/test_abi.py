@@ -183,3 +183,20 @@ def test_grouped_call_takes_the_problem_array_only():
         B.fpq_gemm_grouped(array, 7, synth.E4M3, synth.E4M3)
         raise RuntimeError("taken")
     assert "gemm_problems" not in str(e.value)
+
+
+def test_native_calls_that_do_not_load_name_the_cause(tmp_path):
+    import shutil
+    import subprocess
+    import sys
+    package = tmp_path / "paper_2408_06995_amd"
+    package.mkdir()
+    for f in ("__init__.py", "binding.py", "synth.py"):
+        shutil.copy(os.path.join(ROOT, "paper_2408_06995_amd", f), package / f)
+    ask = [sys.executable, "-c", "from paper_2408_06995_amd import binding as B\n"
+           "try: B.fpq_gemm()\nexcept ImportError as e: print(e, '|', type(e.__cause__).__name__)"]
+    run = lambda: subprocess.run(ask, cwd=tmp_path, capture_output=True, text=True, check=True).stdout
+    assert "is not built" in run()
+    (package / "_fpqcall.so").write_bytes(b"no library")
+    out = run()
+    assert "does not load" in out and "invalid ELF header" in out or "file too short" in out, out

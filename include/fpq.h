@@ -158,8 +158,10 @@ int fpq_search_format(const float *x, size_t n, const int32_t *ebits, const int3
  * NULL, receives the gradient used.  fpq_rl_init_alpha sets sigmoid(alpha) to each weight's fractional
  * position between its two grid neighbours (kept inside [1e-3, 1 - 1e-3]), so that learning starts from
  * the unquantized weights.  fpq_rl_mask writes the decision used at inference, 1 where
- * sigmoid(alpha) >= 0.5: the mask that fpq_pack_weights takes.  All products are fp32 on the fp32
- * matrix instruction.  workspace: fpq_rl_workspace_size bytes, 256-byte aligned, no initialisation.
+ * sigmoid(alpha) >= 0.5: the mask that fpq_pack_weights takes.  Both contractions are fp32: operands are split
+ * into three bf16 parts (all 24 bits for magnitudes from 2^-110), a product keeps six of their nine products (what is left out is at
+ * most 2^-24 of it, 2^-27.4 in the root mean square), sums are fp32; infinities and NaN come out as fp32 products give them.
+ * workspace: fpq_rl_workspace_size bytes, 256-byte aligned, no initialisation.
  * Size limits (FPQ_ERR_SHAPE beyond them): N K < 2^31, M N < 2^31, M < 2^23; lr and reg_weight finite and
  * >= 0 (FPQ_ERR_SCALE otherwise). */
 /* A convolution takes part as the linear layer on its patch matrix (Section V-B presents the method on a linear

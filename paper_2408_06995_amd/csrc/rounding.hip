@@ -251,11 +251,15 @@ __global__ __launch_bounds__(256) void rl_im2col_kernel(const float* __restrict_
 // KCONTIG = false: pi = 1 (rows of the stored matrices run along i / j: C = P'^T Q' with P' = [Kc, I], Q' = [Kc, J]).
 //
 // Every fp32 operand x is split into three bf16 parts, x = h + m + l: h = bf16(x), m = bf16(x - h), l = x - h - m, each
-// difference exact, the last one representable (24 significant bits = 8 + 8 + 8).  Of the nine products of a pair the six
-// largest go to the matrix unit (bf16 products are exact in fp32, sums are fp32): hh, hm, mh, mm, hl, lh.  The three left out
-// are below 2^-26 of |x y| together, less than the rounding of one fp32 multiplication, so nothing is lost against the fp32
-// matrix instruction, whose rate is 1/16 of the bf16 one: six bf16 steps take 3/8 of the time of an fp32 one.
-// Operands have to be finite and below bf16's largest value (3.39e38): the differences of an infinite part are NaN.
+// difference exact, the last one representable (24 significant bits = 8 + 8 + 8; the split of Henry, Tang and Heinecke,
+// "Leveraging the bfloat16 artificial intelligence datatype for higher-precision computations", ARITH 2019).  Of the nine products
+// of a pair the six largest go to the matrix unit (bf16 products are exact in fp32, sums are fp32): hh, hm, mh, mm, hl, lh.  The
+// three left out are at most 2^-24 of |x y| together, 5.5e-9 (2^-27.4) in the root mean square over normal deviates, where one fp32
+// rounding, of which every addition makes one of the whole partial sum, has 2.5e-8.  The rate of the fp32 matrix instruction is 1/16
+// of the bf16 one: six bf16 steps take 3/8 of the time of an fp32 one.
+// An operand that is infinite, or rounds to bf16's infinity, has parts that are NaN: an output that is no finite number is computed
+// once more by plain fp32 multiply-adds, so that it is what the operands themselves make it.  The last part meets bf16's smallest
+// number below 2^-110: smaller operands keep fewer than 24 bits.
 //
 // A workgroup of four wavefronts (2 x 2) owns a T x T tile of C (T = 128 or 64) and walks k in steps of 16 through three LDS
 // buffers; the split happens in registers between the global load and the LDS store.  Per step and wavefront at T = 128:
@@ -468,22 +472,43 @@ __global__ __launch_bounds__(256, 2) void sgemm_kernel(const float* __restrict__
     }
     auto of_place = [&](int at) { return KCONTIG ? at : W * (at % (T / W)) + at / (T / W); };     // row of the tile kept there
     // acc[a][b][r]: row 8 (r / 4) + 4 g + r % 4 of the block (operand P), column l32 (operand Q)
-    float sq = 0.0f;
+    auto row_of = [&](int a, int r) { return i0 + of_place(wi * (T / 2) + 32 * a + 8 * (r >> 2) + 4 * g + (r & 3)); };
+    auto col_of = [&](int b) { return j0 + of_place(wj * (T / 2) + 32 * b + l32); };
+    float sq = 0.0f, finite = 0.0f;                // finite: 0, or NaN once an output was infinite or NaN
 #pragma unroll
     for (int a = 0; a < NB; ++a)
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
-            const int j = j0 + of_place(wj * (T / 2) + 32 * b + l32);
+            const int j = col_of(b);
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int i = i0 + of_place(wi * (T / 2) + 32 * a + 8 * (r >> 2) + 4 * g + (r & 3));
+                const int i = row_of(a, r);
                 const float v = scale * acc[a][b][r];
                 if (i < I && j < J) {
+                    finite = __fmaf_rn(v, 0.0f, finite);
                     if (SUMSQ) sq += v * v;
                     c[(long)i * cstride + j] = v;
                 }
             }
         }
+    if (!(finite == 0.0f)) {
+        sq = 0.0f;
+#pragma unroll 1
+        for (int z = 0; z < NB * NB * 16; ++z) {
+            const int i = row_of(z / (16 * NB), z & 15), j = col_of((z >> 4) % NB);
+            if (i >= I || j >= J) continue;
+            float v = c[(long)i * cstride + j];
+            if (!(fabsf(v) < __builtin_huge_valf())) {
+                float sum = 0.0f;
+                for (int k = kbeg; k < kend && sum == sum; ++k)
+                    sum = KCONTIG ? __fmaf_rn(p[(long)i * pstride + k], qm[(long)j * qstride + k], sum)
+                                  : __fmaf_rn(p[(long)k * pstride + i], qm[(long)k * qstride + j], sum);
+                v = scale * sum;
+                c[(long)i * cstride + j] = v;
+            }
+            if (SUMSQ) sq += v * v;
+        }
+    }
     if (SUMSQ) {
         sq = block_sum(sq);
         if (tid == 0) sq_partial[blockIdx.x] = sq;

@@ -224,3 +224,34 @@ def test_weights_of_a_convolution_are_refused():
         B.fpq_quantize_nhwc(w.reshape(1, 4, 8, 3, 3), synth.E4M3, 1.0, None, ws)
     with pytest.raises(TypeError):
         B.fpq_gemm(a, B.FPQ_X_FP32, synth.E4M3, 1.0, None, ws, synth.E4M3, sw, None, loss, 1.5, 1, 16, workspace=ws)
+
+
+@pytest.mark.parametrize("M,N,K", [(70, 33, 40), (4100, 1028, 20), (4099, 1027, 27)])
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_activations_that_are_not_finite(M, N, K, bad):
+    """An infinite activation makes the outputs of its row, the loss and the gradient infinite, with the signs of the products; a NaN
+    makes them NaN.  (Not against R.loss, which subtracts the two outputs: both are infinite.)"""
+    W, sw, A, alpha = layer(N, K, M, 9900 + N, E2M1)
+    m, k = M // 2, K // 3
+    A[m, k] = bad
+    _, loss, grad = gpu_step(W, sw, alpha, A, E2M1, 1.0, 0.3)
+    Wq, dWq = R.soft_weights(W, sw, alpha, E2M1)
+    D = Wq[:, k] - W[:, k].astype(np.float64)
+    sure = np.abs(D) > 1e-5 * np.abs(W[:, k])                      # the sign of an error of a few ulps is the rounding's
+    assert sure.sum() > N // 2
+    with np.errstate(all="ignore"):
+        want = (bad * D)[:, None] * A[m].astype(np.float64) * dWq    # what the row adds to d mse / d alpha, up to 2 / (M N)
+    got, want = grad[sure], want[sure]
+    assert loss[0] == bad or np.isnan(loss[0]) and (np.isnan(bad) or not sure.all())      # an error of 0 times infinity
+    assert np.isfinite(loss[1])
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isposinf(got), np.isposinf(want))
+
+
+def test_activations_near_the_largest_float():
+    """Above the largest bf16 number and still finite: the output error of weights around 1e-30 is as well."""
+    W, sw, A, alpha = layer(40, 48, 70, 9950, E2M1)
+    W, sw = W * np.float32(2.0 ** -100), sw * np.float32(2.0 ** -100)
+    A[5, 7] = np.float32(3.395e38)
+    _, loss, _ = gpu_step(W, sw, alpha, A, E2M1, 1.0, 0.3)
+    mse, _ = R.loss(W, sw, alpha, A, E2M1, 0.3)
+    assert loss[0] == pytest.approx(mse, rel=1e-4)

@@ -544,6 +544,9 @@ static int run_layer(const CodesOut* out, const void* x, int x_is_fp32, fpq_form
     if (!sliced) plan.splits = 1;
     const size_t codes_bytes = x_is_fp32 ? align_up((size_t)B * H * W * (size_t)Cp, 256) : 0;
     const size_t part_bytes = align_up(split_workspace_bytes(plan, M, Cout), 256);
+    // partial maxima and scale of the dynamic form: at the end of a workspace of the stated size, which holds any plan's partial sums
+    const size_t stated = codes_bytes + align_up(most_split_workspace_bytes(M, Cout, kpad), 256);
+    const size_t dyn_at = !sparse && workspace_bytes >= stated + kDynScaleBytes ? stated : codes_bytes + part_bytes;
     if (workspace && (reinterpret_cast<uintptr_t>(workspace) & 255)) return FPQ_ERR_ALIGN;
     if (x_is_fp32 && (!workspace || workspace_bytes < codes_bytes + part_bytes + (dyn ? kDynScaleBytes : 0)))
         return FPQ_ERR_WORKSPACE;
@@ -597,12 +600,12 @@ static int run_layer(const CodesOut* out, const void* x, int x_is_fp32, fpq_form
         if (dyn && !conv_out && Cp == Cin && M <= 16 && !sparse) {
             // at most 16 rows: maximum, scale, codes and the layer itself in one launch
             st = launch_gemm_skinny_dynamic(a, static_cast<const float*>(x), qx, qx.c, buf,
-                                            reinterpret_cast<float*>(buf + codes_bytes + part_bytes) + 1024, s);
+                                            reinterpret_cast<float*>(buf + dyn_at) + 1024, s);
             if (st != FPQ_ERR_UNSUPPORTED) return st;
         }
         if (dyn && !conv_out && Cp == Cin) {
             // a tensor of a few thousand elements: maximum, scale and codes by one workgroup in one launch
-            float* dynbuf = reinterpret_cast<float*>(buf + codes_bytes + part_bytes);
+            float* dynbuf = reinterpret_cast<float*>(buf + dyn_at);
             st = launch_quantize_dynamic_small(static_cast<const float*>(x), (size_t)M * Cin, qx, qx.c, dynbuf + 1024, buf, s);
             if (st == FPQ_OK) {
                 quantized = true;
@@ -614,7 +617,7 @@ static int run_layer(const CodesOut* out, const void* x, int x_is_fp32, fpq_form
         if (dyn && !quantized) {
             // per-tensor scale = absmax(x) / maxval found here: one reduction launch leaves per-block maxima,
             // the quantize kernel folds them and publishes the scale the layer kernel reads
-            float* dynbuf = reinterpret_cast<float*>(buf + codes_bytes + part_bytes);
+            float* dynbuf = reinterpret_cast<float*>(buf + dyn_at);
             const size_t nx = (size_t)B * Cin * H * W;
             st = launch_absmax_partials(static_cast<const float*>(x), nx, dynbuf, s);
             if (st) return st;

@@ -27,9 +27,10 @@
 // About five such terms per element instead of 444 evaluations.  A workgroup of step 3 that meets elements more than 32 binades
 // below the maximum, or subnormal ones, reads its share again and evaluates those directly (add_outside); with such elements
 // only, that costs what the direct form costs.
-// Measured, 10.5 M elements x 444 candidates: 172 us (absmax 8, intervals' moments 37, closed forms 25, cuts 87: one cache
-// line per element and list access, sums 15) against 1758 us of the direct form (1244, bound by vector ALU work) with its
-// single-workgroup reduction (506).  20 K elements: 17 us against 205.
+// Measured, 10.5 M elements x 444 candidates: 182 us (moments of the intervals 37, closed forms 25, their sums 6, cuts 102: one
+// cache line per element and list access, and the terms' way into integers; sums 7, choice 5, the rest the maximum) against 1758 us
+// of the direct form (1244, bound by vector ALU work) with its single-workgroup reduction (506).  The same tensor with one value 2^60
+// times the rest, so that every element is evaluated directly: 1754 us.  20 K elements: 17 us against 205.
 #include "fpq_dev.h"
 #include "fpq_host.h"
 #include "search_split.h"
@@ -627,9 +628,9 @@ __global__ __launch_bounds__(1024) void search_select_kernel(const double* __res
     }
 }
 
-// The binned form has a cost of its own (about 55 us: the interval tables are written and read once whatever n is); the
-// direct form takes 0.13 us per 1024 elements at 444 candidates.
-constexpr size_t kSearchBinnedWork = (size_t)400000 * 444;   // elements x candidates
+// The binned form has a cost of its own (about 73 us: the interval tables are written and read once whatever n is); the
+// direct form takes 0.13 us per 1024 elements at 444 candidates.  400000 elements: 73 us binned, 64 direct; 500000: 75 and 78.
+constexpr size_t kSearchBinnedWork = (size_t)480000 * 444;   // elements x candidates
 bool binned_pays(size_t n, int nc) { return n * (size_t)nc >= kSearchBinnedWork && n >= 131072 && n <= kSearchMaxBinned; }
 
 }  // namespace

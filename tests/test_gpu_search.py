@@ -105,7 +105,7 @@ def _outliers_and_tiny(n):
     return x
 
 
-BINNED = 400000   # from here on (at 444 candidates) the errors come from interval moments
+BINNED = 480000   # from here on (at 444 candidates) the errors come from interval moments
 
 
 @pytest.mark.parametrize("n", [BINNED - 1, BINNED, (1 << 19) + 3])

@@ -94,9 +94,10 @@ int resolve_kinds(fpq_format_t fx, float cx, fpq_format_t fw, float cw, int acc_
         if (xk == OPK_GENERIC8 || wk == OPK_GENERIC8 || wk == OPK_GENERIC4) return FPQ_ERR_UNSUPPORTED;
     } else if (acc_mode == FPQ_ACC_FP32) {
         if (!(xk == OPK_FP8 && (wk == OPK_FP8 || wk == OPK_FP4))) {
-            // exponents of at most 4 bits fit a half's 5 without meeting its infinities; biases so far out that the factor
-            // 2^(15 - b) of the two operands could leave fp32 take the arithmetic decode, as wider exponents do
-            const bool half = fx.ebits <= 4 && fw.ebits <= 4 && abs(fx.bias) <= 48 && abs(fw.bias) <= 48;
+            // exponents of at most 4 bits fit a half's 5 without meeting its infinities; biases far out, whose factors 2^(15 - b) could
+            // take the activations' scale out of fp32 before the weights' scale brings it back (common ones are 2^(e - 1), 1 to
+            // 8: factors of 2^-2 to 2^62 are left), take the arithmetic decode, as wider exponents do
+            const bool half = fx.ebits <= 4 && fw.ebits <= 4 && abs(fx.bias) <= 16 && abs(fw.bias) <= 16;
             xk = half ? OPK_HALF8 : OPK_GENERIC8;
             wk = is_four_bit(fw) ? (half ? OPK_HALF4 : OPK_GENERIC4) : (half ? OPK_HALF8 : OPK_GENERIC8);
             ax = half ? (float)ldexp(1.0, 15 - fx.bias) : 1.0f;

@@ -731,3 +731,23 @@ def test_a_format_is_anything_with_its_four_elements(of):
     B.fpq_quantize(x, of(synth.E4M3), 0.5, None, got)
     torch.cuda.synchronize()
     assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("fx,fw", [((3, 4, 3, 0.0), (2, 5, -48, 0.0)), ((3, 4, -40, 0.0), (3, 0, 4, 0.0)), ((2, 5, 48, 0.0), (2, 5, 48, 0.0)),
+                                   ((3, 4, 16, 0.0), (2, 5, -16, 0.0))])
+def test_formats_of_far_out_biases_on_far_out_scales(fx, fw):
+    """Large activations on small weights: the scales make up for each other, and for what the formats' biases add to them."""
+    fx, fw = resolved(fx), resolved(fw)
+    M, K, N = 70, 256, 48
+    x = synth.activations((M, K), 5000) * np.float32(2.0 ** 60)
+    w = synth.weights((N, K), 5001) * np.float32(2.0 ** -60)
+    sx = oracle.scale_from_absmax(oracle.absmax(x), fx[3])
+    xq = oracle.quantize(x, fx, sx)
+    wq, sw = oracle.pack_weights(w, fw, None)
+    Y, T = oracle.gemm(xq, fx, sx, wq, fw, sw)
+    packed, sw_t, _ = gpu_pack(w, fw, None)
+    y = torch.full((M, N), float("nan"), dtype=torch.float32, device=DEV)
+    ws = torch.empty(max(256, B.fpq_gemm_workspace_size(M, N, K, 0)), dtype=torch.uint8, device=DEV)
+    B.fpq_gemm(dev(xq), 0, fx, sx, None, packed, fw, sw_t, None, y, M, N, K, 0, ws)
+    torch.cuda.synchronize()
+    check_close(y.cpu().numpy(), Y, T, what="%s %s" % (fx, fw))

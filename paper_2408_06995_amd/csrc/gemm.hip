@@ -424,13 +424,9 @@ template <int XKIND, int WKIND, int ACC, bool CONV>
 static int launch_tiles(const GemmArgs& a, hipStream_t st)
 {
     // Tile choice: the large tile when it still yields at least two waves of workgroups over the 256
-    // compute units, otherwise the small one.  Linear layers in the hardware's encodings come here with grids of at most 512
-    // small tiles only (plan_small).
-    constexpr bool small_only = !CONV && XKIND == OPK_FP8 && (WKIND == OPK_FP8 || WKIND == OPK_FP4);
-    if constexpr (!small_only) {
-        const long big = (long)((a.M + 127) / 128) * ((a.N + 127) / 128);
-        if (big >= 512) return launch_one<128, 128, 2, 2, XKIND, WKIND, ACC, CONV>(a, st);
-    }
+    // compute units, otherwise the small one.
+    const long big = (long)((a.M + 127) / 128) * ((a.N + 127) / 128);
+    if (big >= 512) return launch_one<128, 128, 2, 2, XKIND, WKIND, ACC, CONV>(a, st);
     return launch_one<64, 64, 2, 2, XKIND, WKIND, ACC, CONV>(a, st);
 }
 

@@ -126,6 +126,7 @@ struct GroupedProblem {
 struct GroupedArgs {
     GroupedProblem p[kGroupMax];
     int count;
+    uint32_t over_waves;    // bit i: problem i has its K split over the wavefronts (launch_gemm_grouped)
     GemmArgs common;        // formats, operand kinds, alpha, accumulate mode; the per-problem fields are filled in the kernel
 };
 static_assert(sizeof(GroupedArgs) <= 4096, "kernel arguments are limited to 4 KB");
@@ -337,7 +338,6 @@ int launch_gemm_skinny_dynamic(const GemmArgs& a, const float* x, const QParams&
                                float* publish, hipStream_t st);
 // Grouped forms (gemm.hip, quant.hip): one launch each over all problems of g.
 int launch_gemm_grouped(const GroupedArgs& g, hipStream_t st);                 // small tiles, any shape
-int launch_wk_grouped(const GroupedArgs& g, hipStream_t st);                   // 64 x 64 tiles, K split over the wavefronts
 static inline bool grouped_wk_applicable(const GemmArgs& a)                    // operand kinds of that one
 {
     if (a.acc_mode == FPQ_ACC_FP8_MFMA) return a.xkind == OPK_FP8 && (a.wkind == OPK_FP8 || a.wkind == OPK_FP4);

@@ -20,6 +20,7 @@
 #include <type_traits>
 
 #include "gemm_common.h"
+#include "gemm_wk_kernel.h"
 
 namespace fpq {
 
@@ -403,6 +404,20 @@ __global__ __launch_bounds__(256) void gemm_grouped_kernel(const GroupedArgs g)
     gemm_tile<64, 64, 2, 2, XKIND, WKIND, ACC, false>(a, blockIdx.x, smem);
 }
 
+// The same for a group in which some problems have their K split over the wavefronts: either tile, by problem.
+template <int XKIND, int WKIND, int ACC>
+__global__ __launch_bounds__(256, 2) void gemm_grouped_mixed_kernel(const GroupedArgs g)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    const GemmArgs a = grouped_problem_args(g, blockIdx.y);
+    const int tiles = ((a.M + 63) / 64) * ((a.N + 63) / 64);
+    if ((int)blockIdx.x >= tiles) return;
+    if ((g.over_waves >> blockIdx.y) & 1)
+        gemm_wk_tile<2, XKIND, WKIND, ACC, false, false>(a, blockIdx.x, smem);
+    else
+        gemm_tile<64, 64, 2, 2, XKIND, WKIND, ACC, false>(a, blockIdx.x, smem);
+}
+
 // ---------------------------------------------------------------------------------- dispatch
 
 template <int BX, int BW, int WGX, int WGW, int XKIND, int WKIND, int ACC, bool CONV>
@@ -691,6 +706,17 @@ static int launch_grouped_one(const GroupedArgs& g, hipStream_t st)
         const int t = ((g.p[i].M + 63) / 64) * ((g.p[i].N + 63) / 64);
         maxt = t > maxt ? t : maxt;
     }
+    if constexpr (XKIND == OPK_FP8 || XKIND == OPK_HALF8) {
+        if (g.over_waves) {
+            constexpr int mixed = 4 * wk_wave_lds(2, kind_is_4bit(WKIND)) + 1024;
+            static_assert(mixed >= smem, "either tile");
+            auto kern = gemm_grouped_mixed_kernel<XKIND, WKIND, ACC>;
+            static std::atomic<uint64_t> allowed{0};   // per instantiation
+            if (!allow_dynamic_lds(reinterpret_cast<const void*>(kern), mixed, allowed)) return FPQ_ERR_LAUNCH;
+            hipLaunchKernelGGL(kern, dim3((unsigned)maxt, (unsigned)g.count), dim3(256), mixed, st, g);
+            return hipGetLastError() == hipSuccess ? FPQ_OK : FPQ_ERR_LAUNCH;
+        }
+    }
     hipLaunchKernelGGL((gemm_grouped_kernel<XKIND, WKIND, ACC>), dim3((unsigned)maxt, (unsigned)g.count), dim3(256), smem, st, g);
     return hipGetLastError() == hipSuccess ? FPQ_OK : FPQ_ERR_LAUNCH;
 }
@@ -712,28 +738,24 @@ static int launch_gemm_grouped_tiles(const GroupedArgs& g, hipStream_t st)
     return launch_grouped_one<OPK_GENERIC8, OPK_GENERIC8, FPQ_ACC_FP32>(g, st);
 }
 
-// Problems of a few tiles that fpq_gemm would give to the kernel with K split over the wavefronts go to that kernel (its sums have
-// their own order).  The rule looks at the problem alone, so that its bits do not depend on the others of the call; 32 problems
-// of at most 16 tiles are on the chip at once with any others' share, and with more tiles the register-staged kernel, of which more
-// workgroups fit on a compute unit, is as fast or faster: 8 x 616 x 1024 -> 320 10.2 us, 10.9 us over the wavefronts;
-// 30 x 1013 x 1264 -> 432 58 and 72 us; 32 x 100 x 1040 -> 100 8.0 us either way; 8 x 154 x 2048 -> 640 13.6 and 12.7 us.
+// Problems of at most 12 tiles with a K of more than 8 steps that fpq_gemm would give to the kernel with K split over the wavefronts
+// have it split here too, so that single and grouped calls give the same sums (such sums have their own order).  The rule looks
+// at the problem alone: its bits do not depend on the others of the call.  It buys no time (32 x 100 x 1040 -> 100: 8.0 us either way),
+// and larger problems lose by it, since more workgroups of the register-staged tile fit on a compute unit: 8 x 616 x 1024 -> 320
+// 10.2 us, 10.9 us over the wavefronts; 30 x 1013 x 1264 -> 432 58 and 72 us.  Both kinds go out in one launch: as two, a call of 39
+// problems (36 x 1040 -> 512, 1024, 2048) took 51 us where the register-staged tile alone takes 37 and one launch of both 41.
 int launch_gemm_grouped(const GroupedArgs& g, hipStream_t st)
 {
     if (g.count <= 0) return FPQ_OK;
-    GroupedArgs part[2];
-    const bool wk = grouped_wk_applicable(g.common);
-    part[0].count = part[1].count = 0;
-    part[0].common = part[1].common = g.common;
-    for (int i = 0; i < g.count; ++i) {
-        const GemmPlan plan = plan_gemm(g.p[i].M, g.p[i].N, g.p[i].Kpad);
-        const int tiles = ((g.p[i].M + 63) / 64) * ((g.p[i].N + 63) / 64);
-        GroupedArgs& to = part[wk && (plan.tile == TILE_WAVE_K4 || plan.tile == TILE_WAVE_K2) && tiles <= 16 ? 1 : 0];
-        to.p[to.count++] = g.p[i];
-    }
-    int rc = FPQ_OK;
-    if (part[0].count) rc = launch_gemm_grouped_tiles(part[0], st);
-    if (rc == FPQ_OK && part[1].count) rc = launch_wk_grouped(part[1], st);
-    return rc;
+    GroupedArgs all = g;
+    all.over_waves = 0;
+    if (grouped_wk_applicable(g.common))
+        for (int i = 0; i < g.count; ++i) {
+            const GemmPlan plan = plan_gemm(g.p[i].M, g.p[i].N, g.p[i].Kpad);
+            const int tiles = ((g.p[i].M + 63) / 64) * ((g.p[i].N + 63) / 64);
+            if ((plan.tile == TILE_WAVE_K4 || plan.tile == TILE_WAVE_K2) && tiles <= 12 && g.p[i].Kpad > 1024) all.over_waves |= 1u << i;
+        }
+    return launch_gemm_grouped_tiles(all, st);
 }
 
 int launch_gemm(const GemmArgs& a, hipStream_t st)

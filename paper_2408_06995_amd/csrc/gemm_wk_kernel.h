@@ -385,16 +385,6 @@ __global__ __launch_bounds__(256, (NST <= 2 ? 2 : 1)) void gemm_wk_kernel(const 
     gemm_wk_tile<NST, XKIND, WKIND, ACC, CONV, QOUT>(a, blockIdx.x, smem);
 }
 
-// A group of linear layers: blockIdx.y picks the problem.
-template <int NST, int XKIND, int WKIND, int ACC>
-__global__ __launch_bounds__(256, (NST <= 2 ? 2 : 1)) void gemm_wk_grouped_kernel(const GroupedArgs g)
-{
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    const GemmArgs a = grouped_problem_args(g, blockIdx.y);
-    if ((int)blockIdx.x >= ((a.M + 63) / 64) * ((a.N + 63) / 64)) return;
-    gemm_wk_tile<NST, XKIND, WKIND, ACC, false, false>(a, blockIdx.x, smem);
-}
-
 template <int NST, int XKIND, int WKIND, int ACC, bool CONV, bool QOUT>
 static int launch_wk_one(const GemmArgs& a, hipStream_t st)
 {

@@ -453,7 +453,7 @@ int fpq_gemm_plan(int64_t M, int64_t N, int64_t K, fpq_plan_t* plan)
 {
     if (!plan) return FPQ_ERR_NULL;
     if (M <= 0 || K <= 0 || N <= 0) return FPQ_ERR_SHAPE;
-    fill_plan(plan_gemm(M, N, padded_k(K, 1)), M, true, plan);
+    fill_plan(plan_gemm(M, N, padded_k(K, 1), PLAN_LINEAR), M, true, plan);
     return FPQ_OK;
 }
 
@@ -465,7 +465,7 @@ int fpq_conv2d_plan(int64_t B, int64_t Cin, int64_t H, int64_t W, int64_t Cout, 
         return FPQ_ERR_SHAPE;
     if (H + 2 * pad < kh || W + 2 * pad < kw) return FPQ_ERR_SHAPE;
     const int64_t Ho = (H + 2 * pad - kh) / stride + 1, Wo = (W + 2 * pad - kw) / stride + 1;
-    fill_plan(plan_gemm(B * Ho * Wo, Cout, padded_k(Cin, (int64_t)kh * kw)), B * Ho * Wo, false, plan);
+    fill_plan(plan_gemm(B * Ho * Wo, Cout, padded_k(Cin, (int64_t)kh * kw), PLAN_CONV), B * Ho * Wo, false, plan);
     return FPQ_OK;
 }
 
@@ -534,7 +534,10 @@ static int run_layer(const CodesOut* out, const void* x, int x_is_fp32, fpq_form
     // workspace = [activation codes when the input is fp32][split-K partial results]; a caller that passes
     // codes and no (or too small a) workspace gets the unsplit kernel
     const int64_t kpad = padded_k(Cin, (int64_t)kh * kw);
-    GemmPlan plan = xkind == OPK_GENERIC8 ? plan_arithmetic(M, Cout, kpad) : plan_gemm(M, Cout, kpad);
+    GemmPlan plan = xkind == OPK_GENERIC8 ? plan_arithmetic(M, Cout, kpad)
+                                          : plan_gemm(M, Cout, kpad, xkind == OPK_HALF8 ? PLAN_HALF
+                                                                     : conv_out         ? (out ? PLAN_CONV_CODES : PLAN_CONV)
+                                                                                        : (out ? PLAN_LINEAR_CODES : PLAN_LINEAR));
     if (sparse) {
         // the structured-sparse form has one kernel: hardware E4M3 activations, E4M3 / E2M1 weights, exact accumulate
         if (out || accumulate || acc_mode != FPQ_ACC_FP32 || xkind != OPK_FP8 || (wkind != OPK_FP8 && wkind != OPK_FP4))
@@ -976,10 +979,10 @@ static GemmPlan plan_for(fpq_format_t fx, fpq_format_t fw, int acc_mode, int64_t
     QParams qx, qw;
     int xkind, wkind;
     float alpha;
-    const bool arithmetic = resolve_format(fx, &qx) == FPQ_OK && resolve_format(fw, &qw) == FPQ_OK &&
-                            resolve_kinds(fx, qx.c, fw, qw.c, acc_mode & ~FPQ_OUT_ACCUMULATE, &xkind, &wkind, &alpha) == FPQ_OK &&
-                            xkind == OPK_GENERIC8;
-    return arithmetic ? plan_arithmetic(M, N, kpad) : plan_gemm(M, N, kpad);
+    const bool known = resolve_format(fx, &qx) == FPQ_OK && resolve_format(fw, &qw) == FPQ_OK &&
+                       resolve_kinds(fx, qx.c, fw, qw.c, acc_mode & ~FPQ_OUT_ACCUMULATE, &xkind, &wkind, &alpha) == FPQ_OK;
+    if (known && xkind == OPK_GENERIC8) return plan_arithmetic(M, N, kpad);
+    return plan_gemm(M, N, kpad, known && xkind == OPK_HALF8 ? PLAN_HALF : PLAN_LINEAR);
 }
 
 int fpq_gemm_noalloc(const void* x, int x_is_fp32, fpq_format_t fx, float sx, const float* sx_dev, const void* packed_w,

@@ -166,10 +166,49 @@ struct GemmPlan {
 // every slice 8 steps (slices need more than 20 steps to pay for their launch: 512 x 1280 -> 320 7.2 us whole, 8.6 us in two);
 // grids of at most 512 do so with two stages while K has at most 40 steps (beyond that 128 x 64 tiles in slices are faster:
 // 1024 x 9216 -> 1100 37.7 and 32.3 us).  A shorter K takes the register-staged kernel, which starts faster (616 x 768 -> 320:
-// 6.1 us against 6.3 us).  Larger grids take the 128 x 64, 128 x 128 or 128 x 160 tile and the slices that a model of the time
-// prefers: a step of 128 codes over 128 rows costs 6 ns per column of the tile (times 1.15 / 1 / 0.97 for the three) and per work
-// item on the busiest compute unit, 1.4 times that where a compute unit has one work item only; slices cost 3 us and their partial
-// sums at 5 TB/s (2048 x 11520 -> 1100: 79 us whole, 61 us in three).
+// 6.1 us against 6.3 us).  Larger grids: plan_unsliced with a K of less than 32 steps, plan_tiled beyond.
+enum PlanForm : int {
+    PLAN_LINEAR = 0,        // hardware encodings, fp32 results
+    PLAN_CONV = 1,
+    PLAN_LINEAR_CODES = 2,  // results that leave as codes
+    PLAN_CONV_CODES = 3,
+    PLAN_HALF = 4           // operands moved into halves, fp32 results
+};
+// The register-staged 64 x 64 tile or one of the three larger tiles of the load-to-LDS pipeline, as a model of the time prefers:
+// t[0] + w (t[1] + t[2] nk) us for launch, epilogue and steps of 128 codes, with w = tiles per compute unit (of the large tiles, of
+// which few fit at once, half way between that and the next whole number, and 1.1 for at most one each).  The constants were fitted to
+// 1060 shapes of random sizes x tiles; the tiles that the model chooses take 1.02 to 1.05 times the time of the best one in the geometric
+// mean.  A choice by K steps times columns among the large tiles alone took 1.17 to 1.31 times, the register-staged kernel with
+// 128 x 128 tiles from 512 of them on 1.14 to 1.27 times: its epilogue, an activation ahead of codes above all, runs on one or two
+// workgroups per compute unit (1477 x 384 -> 3072, gated GELU, codes out: 14 us in 64 x 64 tiles, 30 us in 128 x 160).  A large tile has
+// to be 5 % faster by the model: where the two are close, it errs for either.
+static inline GemmPlan plan_unsliced(int64_t M, int64_t N, int64_t nk, PlanForm form)
+{
+    static const float us_of[5][4][3] = {
+        {{3.72f, 0.37f, 0.34f}, {4.47f, 1.04f, 0.53f}, {4.06f, 2.10f, 0.87f}, {3.69f, 2.71f, 1.05f}},
+        {{5.87f, 0.68f, 0.38f}, {5.17f, 2.24f, 0.58f}, {4.54f, 3.64f, 0.92f}, {3.82f, 4.32f, 1.14f}},
+        {{4.37f, 0.79f, 0.36f}, {8.13f, 1.32f, 0.51f}, {9.92f, 2.34f, 0.86f}, {10.0f, 3.70f, 1.08f}},
+        {{7.76f, 1.23f, 0.39f}, {8.20f, 2.10f, 0.58f}, {9.89f, 4.05f, 0.81f}, {10.0f, 5.07f, 1.08f}},
+        {{4.98f, 0.19f, 0.68f}, {6.66f, 0.77f, 0.99f}, {6.72f, 1.61f, 1.33f}, {6.18f, 2.09f, 1.77f}},
+    };
+    const int bx[4] = {64, 128, 128, 128}, bw[4] = {64, 64, 128, 160};
+    const int tile[4] = {TILE_GENERIC, TILE_128x64, TILE_128x128, TILE_128x160_S2};
+    int best = 0;
+    double least = 1e30;
+    for (int i = 0; i < 4; ++i) {
+        const int64_t tiles = ((M + bx[i] - 1) / bx[i]) * ((N + bw[i] - 1) / bw[i]);
+        const double per = (double)tiles / 256.0;
+        const double w = i == 0 ? (per > 1.0 ? per : 1.0) : tiles <= 256 ? 1.1 : 0.5 * ((double)((tiles + 255) / 256) + per);
+        const float* t = us_of[form][i];
+        const double us = (t[0] + w * (t[1] + t[2] * (double)nk)) * (i == 0 ? 0.95 : 1.0);
+        if (us < least) { least = us; best = i; }
+    }
+    return GemmPlan{tile[best], 1};
+}
+// A deep K: the 128 x 64, 128 x 128 or 128 x 160 tile and the slices that a model of the time prefers: a step of 128 codes over 128 rows
+// costs 6 ns per column of the tile (times 1.15 / 1 / 0.97 for the three) and per work item on the busiest compute unit, 1.4 times that
+// where a compute unit has one work item only; slices cost 3 us and their partial sums at 5 TB/s (2048 x 11520 -> 1100: 79 us whole, 61 us
+// in three).
 static inline GemmPlan plan_tiled(int64_t M, int64_t N, int64_t nk)
 {
     const int bw[3] = {64, 128, 160};
@@ -187,9 +226,10 @@ static inline GemmPlan plan_tiled(int64_t M, int64_t N, int64_t nk)
         }
     return best;
 }
-static inline GemmPlan plan_small(int64_t M, int64_t N, int64_t nk)
+static inline GemmPlan plan_small(int64_t M, int64_t N, int64_t nk, PlanForm form)
 {
     const int64_t t64 = ((M + 63) / 64) * ((N + 63) / 64);
+    if (t64 > 512 && nk < 32) return plan_unsliced(M, N, nk, form);
     if (t64 > 512 || (t64 > 256 && nk > 40)) return plan_tiled(M, N, nk);
     if (nk < 8) return GemmPlan{TILE_GENERIC, 1};
     if (t64 > 256) return GemmPlan{TILE_WAVE_K2, 1};
@@ -236,18 +276,18 @@ static inline bool unsliced_part_grid(const GemmPlan& p, int64_t M, int64_t N, i
     return p.splits == 1 && p.tile == TILE_128x160_S2 && ((M + 127) / 128) * (N / 160) < 192 && nk >= 8;
 }
 // Operands with a hardware conversion or moved into halves.
-static inline GemmPlan plan_gemm(int64_t M, int64_t N, int64_t Kpad)
+static inline GemmPlan plan_gemm(int64_t M, int64_t N, int64_t Kpad, PlanForm form)
 {
     GemmPlan p{TILE_GENERIC, 1};
     if (M < 1) return p;
     const int64_t nk = Kpad / 128;
     if (M <= 16) {           // (linear layers of at most 16 rows have a kernel of their own)
-        p = plan_small(M, N, nk);
+        p = plan_small(M, N, nk, form);
         p.splits = 1;
         return p;
     }
     if (takes_plan_small(M, N, nk)) {
-        p = plan_small(M, N, nk);
+        p = plan_small(M, N, nk, form);
         while (p.splits > 1 && p.splits * M * N * 4 > ((int64_t)256 << 20)) --p.splits;
         return p;
     }
@@ -271,10 +311,11 @@ static inline size_t split_workspace_bytes(const GemmPlan& p, int64_t M, int64_t
 {
     return p.splits > 1 ? (size_t)p.splits * (size_t)M * (size_t)N * sizeof(float) : 0;
 }
-// Partial sums that a layer of any operand kinds may want.
+// Partial sums that a layer of any operand kinds may want (slices do not depend on the form).
 static inline size_t most_split_workspace_bytes(int64_t M, int64_t N, int64_t Kpad)
 {
-    const size_t a = split_workspace_bytes(plan_gemm(M, N, Kpad), M, N), b = split_workspace_bytes(plan_arithmetic(M, N, Kpad), M, N);
+    const size_t a = split_workspace_bytes(plan_gemm(M, N, Kpad, PLAN_LINEAR), M, N);
+    const size_t b = split_workspace_bytes(plan_arithmetic(M, N, Kpad), M, N);
     return a > b ? a : b;
 }
 

@@ -23,7 +23,11 @@ LINEAR = [(17, 1024, 1), (64, 1040, 64), (65, 1152, 66), (200, 2048, 333),      
           (1407, 3312, 749), (2049, 1024, 516),                                      # ... two stages
           (4097, 336, 700), (9000, 16, 300), (8961, 144, 300), (9000, 400, 301),     # 128 x 64
           (4918, 1040, 896), (4864, 272, 895),                                       # 128 x 128
-          (8193, 144, 1116)]                                                         # 128 x 160, ragged last column
+          (8193, 144, 1116),                                                         # 128 x 160, ragged last column
+          # larger grids, by results and operands: 128 x 64 / 128 x 128 / 128 x 160 for fp32 results of hardware encodings ...
+          (9772, 1040, 516), (19112, 1024, 301), (9772, 272, 1116), (12222, 272, 895), (7812, 272, 1100), (12222, 336, 749),
+          # ... and of halves
+          (12222, 1024, 301), (9772, 144, 749), (9772, 144, 895)]
 
 
 @pytest.mark.parametrize("fx,fw,acc", FORMS)
@@ -63,7 +67,8 @@ CONV = [(2, 128, 19, 19, 36, 3, 1, 1), (1, 128, 3, 3, 70, 3, 1, 1), (5, 1040, 1,
         (2, 200, 35, 33, 72, 3, 2, 1), (1, 64, 13, 7, 50, 5, 1, 2), (1, 1440, 15, 7, 66, 3, 1, 1), (3, 130, 9, 9, 65, 3, 1, 0),
         (2, 128, 70, 71, 130, 3, 1, 1), (1, 320, 32, 64, 320, 3, 1, 1),
         (3, 36, 67, 65, 200, 3, 1, 1), (3, 20, 133, 130, 196, 3, 2, 1), (2800, 16, 2, 2, 197, 1, 1, 0),
-        (3, 20, 81, 81, 250, 3, 1, 1), (3, 16, 67, 65, 1116, 1, 1, 0), (2, 320, 32, 32, 320, 3, 1, 1)]
+        (3, 20, 81, 81, 250, 3, 1, 1), (3, 16, 67, 65, 1116, 1, 1, 0), (2, 320, 32, 32, 320, 3, 1, 1),
+        (3, 128, 64, 64, 301, 3, 1, 1), (2, 16, 70, 70, 749, 3, 1, 1), (2, 16, 63, 62, 516, 1, 1, 0)]      # 128 x 64, 128, 160
 
 
 @pytest.mark.parametrize("fx,fw,acc", FORMS)
@@ -103,13 +108,14 @@ def test_conv(case, fx, fw, acc):
 @pytest.mark.parametrize("fw,fy,acc", [(E4M3, E4M3, 0), (E2M1, E3M4, 0), (E4M3, E4M3, 1)])
 @pytest.mark.parametrize("act", ["silu", "geglu"])
 @pytest.mark.parametrize("M,K,N", [(65, 1152, 96), (40, 5120, 128), (1407, 3312, 736), (4097, 336, 704), (4918, 1024, 896),
-                                   (8193, 144, 1088)])
+                                   (8193, 144, 1088), (4990, 400, 2048), (12222, 400, 896), (4990, 1024, 2048)])
 def test_linear_codes_out(M, K, N, fw, fy, acc, act):
     linear_activation_case(M, K, N, fw, fy, acc, act)
 
 
 @pytest.mark.parametrize("case", [(2, 128, 19, 19, 36, 3, 1, 1), (1, 1440, 15, 7, 66, 3, 1, 1), (2, 128, 70, 71, 130, 3, 1, 1),
-                                  (3, 36, 67, 65, 200, 3, 1, 1), (3, 20, 81, 81, 250, 3, 1, 1)])
+                                  (3, 36, 67, 65, 200, 3, 1, 1), (3, 20, 81, 81, 250, 3, 1, 1), (2, 16, 63, 62, 749, 1, 1, 0),
+                                  (2, 16, 70, 70, 1100, 3, 1, 1), (2, 16, 63, 62, 1116, 3, 1, 1)])
 def test_conv_codes_out(case):
     conv_silu_case(case)
 

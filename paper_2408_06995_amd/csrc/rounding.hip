@@ -608,8 +608,9 @@ int launch_rl_mask(const float* alpha, size_t n, uint8_t* mask, hipStream_t st)
     return hipGetLastError() == hipSuccess ? FPQ_OK : FPQ_ERR_LAUNCH;
 }
 
-// 8192 rows, 1280 x 1280 weights: 726 us with the fp32 matrix instruction (its two products 320 and 363), 320 us with the
-// split operands (154 and 150; matrix unit busy half of the time, the rest is the operand loads: 60 us without them).
+// 8192 rows, 1280 x 1280 weights: 726 us with the fp32 matrix instruction (its two products 320 and 363), 323 us with the
+// split operands (155 and 173 in the profiler's trace; matrix unit busy 0.64 and 0.55 of the time, the rest is operand loads and the
+// split).
 int launch_rl_step(const float* w, const float* sw, int64_t N, int64_t K, const QParams& q, float* alpha, const float* a,
                    int64_t M, float lr, float reg_weight, float* loss_out, float* grad_out, void* workspace, hipStream_t st)
 {

@@ -46,17 +46,18 @@ __device__ __forceinline__ void dma16(v4i rsrc, unsigned voff, unsigned lds_addr
                  : "memory");
 }
 
-// The same for a wavefront that may have nothing left to load: live = all ones, or zero, and then no lane takes part and nothing
-// is moved; out-of-range offsets in its place would write zeros to LDS at the rate of a real load (about 50 bytes per clock), 0.5
-// to 1 us at the end of every launch.  No wait may rest on such a load being counted in vmcnt, or on its not being counted:
-// the kernels' waits count loads of lanes that take part only.
+// The same for a wavefront that may have nothing left to load: live = -1, or 1, and then the first lane takes part alone.  That load
+// counts in vmcnt like any other (whether one without lanes would is not relied on), so the waits stay as they are, and it moves 16
+// bytes into a ring slot that nothing reads any more; out-of-range offsets of all lanes would write zeros to LDS at the rate of a
+// real load (about 50 bytes per clock), 0.5 to 1 us at the end of every launch.
 // All 64 lanes of the calling wavefronts are active.
 __device__ __forceinline__ void dma16_live(v4i rsrc, unsigned voff, unsigned lds_addr, int live)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_mov_b32 exec_lo, %3\n\ts_mov_b32 exec_hi, %3\n\t"
+    asm volatile("s_mov_b32 m0, %0\n\ts_mov_b32 exec_lo, %3\n\ts_mov_b32 exec_hi, %4\n\t"
                  "buffer_load_dwordx4 %1, %2, 0 offen lds\n\ts_mov_b64 exec, -1"
                  :
-                 : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(voff), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane(live))
+                 : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(voff), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane(live)),
+                   "s"(__builtin_amdgcn_readfirstlane(live >> 1))
                  : "memory");
 }
 
@@ -820,11 +821,11 @@ __global__ __launch_bounds__(256, (BX <= 128 ? 2 : 1)) void gemm_dma_kernel(cons
     // ---- main loop over the K steps of all work items of this workgroup.  Each wave issues LOADS buffer
     // loads per step and they complete in order.  The loads run NSTAGE - 1 steps ahead of the MFMAs,
     // across item boundaries.  Every step issues one group of LOADS loads; once the work items run out
-    // the group moves nothing (no lane takes part, or every offset is out of range: zeros into a free ring slot), which
-    // keeps the control flow uniform, and with the offsets the vmcnt arithmetic too.
+    // the group moves next to nothing (one lane takes part, or every offset is out of range: zeros into a free ring slot), which
+    // keeps the control flow and the vmcnt arithmetic uniform.
     int istage = 0;
     auto issue_nothing = [&]() {
-        live = 0;
+        live = 1;
         if constexpr (!MASKED) {
             x_sel = 31;
 #pragma unroll
@@ -864,11 +865,8 @@ __global__ __launch_bounds__(256, (BX <= 128 ? 2 : 1)) void gemm_dma_kernel(cons
                 for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
     };
     {
-        // the first ring slot: its group is the oldest of the NSTAGE - 1 outstanding ones (of fewer, if the loads ran out already)
-        if (MASKED && NSTAGE > 2 && !live)
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-        else
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(LOADS * (NSTAGE - 2)));
+        // the first ring slot: its group is the oldest of the NSTAGE - 1 outstanding ones
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(LOADS * (NSTAGE - 2)));
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
@@ -885,8 +883,7 @@ __global__ __launch_bounds__(256, (BX <= 128 ? 2 : 1)) void gemm_dma_kernel(cons
             issue_scales(tw * BW, sl, par);
             for (int kt = 0; kt < nk; ++kt) {
                 const int nstage = (cstage + 1 == NSTAGE) ? 0 : cstage + 1;
-                // (once the loads have run out, the wanted group is the youngest there is)
-                const int mode = MASKED && NSTAGE > 2 && !live ? (int)W_DRAIN : since < NSTAGE - 2 ? after : (int)W_NORMAL;
+                const int mode = since < NSTAGE - 2 ? after : (int)W_NORMAL;
                 if constexpr (ACC == FPQ_ACC_FP32)
                     compute(cstage, nstage, istage, mode);
                 else
@@ -895,7 +892,7 @@ __global__ __launch_bounds__(256, (BX <= 128 ? 2 : 1)) void gemm_dma_kernel(cons
                 issued();
                 cstage = nstage;
             }
-            // the scale loads are older than the loads issued during the item's K steps (at least one group, or after a wait for zero)
+            // the scale loads are older than the loads issued during the item's K steps (at least one group)
             __builtin_amdgcn_s_waitcnt(vmcnt_imm(LOADS));
             asm volatile("" ::: "memory");
             after = epilogue(tx * BX, tw * BW, sl, par);

@@ -106,7 +106,7 @@ __device__ __forceinline__ void gemm_wk_tile(const GemmArgs& a, int item, uint8_
         }
     }
     int todo = nk;                                                 // steps whose loads have not gone out
-    int live = nk > 0 ? -1 : 0;
+    int live = nk > 0 ? -1 : 1;                                       // what dma16_live wants
     // scale and bias of the column (NCHW: of channel l32 of the block) that this lane finishes: fetched ahead of the K loop
     const float sxa = (a.sx_dev ? a.sx_dev[0] : a.sx) * a.alpha;
     float my_scale = 0.0f, my_bias = 0.0f;
@@ -132,7 +132,7 @@ __device__ __forceinline__ void gemm_wk_tile(const GemmArgs& a, int item, uint8_
         }
     };
     auto issue_advance = [&]() {
-        if (--todo <= 0) live = 0;
+        if (--todo <= 0) live = 1;
 #pragma unroll
         for (int i = 0; i < WLD; ++i)
             if (wbase[i] != OOB) wbase[i] += W4 ? 32 : 64;
@@ -169,19 +169,12 @@ __device__ __forceinline__ void gemm_wk_tile(const GemmArgs& a, int item, uint8_
     constexpr int PFMT = mfma_fmt(PKIND), QFMT = mfma_fmt(QKIND);   // immediates of the MFMA
     auto is_w = [](int f) { return P_IS_W ? f < 2 : f >= 2; };
     auto w4_off = [](int row, int chunk) { return row * 32 + ((chunk ^ ((row >> 3) & 1)) << 4); };
-    // A slot's loads have landed when at most the NST - 2 younger groups are outstanding, or as many fewer as the steps have run
-    // out of (left: steps whose loads have not gone out once the youngest of the NST - 2 has).
-    static_assert(NST == 2 || NST == 4, "the cases below");
-    auto wait_slot = [&](int left) {
-        if (NST == 2 || left < -1)
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-        else if (left < 0)
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(LOADS));
-        else
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * LOADS));
+    // the next slot's loads have landed when at most the NST - 2 younger groups are outstanding
+    auto wait_next = [&]() {
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm((NST - 2) * LOADS));
         asm volatile("" ::: "memory");
     };
-    wait_slot(todo);
+    wait_next();
     int slot = 0, to = NST - 1;
     if constexpr (ACC == FPQ_ACC_FP32) {
         // 64 codes = two rounds of LDS reads (lane half g: codes 32 j + 16 g .. + 15) x two MFMA steps; the slots as in
@@ -218,7 +211,7 @@ __device__ __forceinline__ void gemm_wk_tile(const GemmArgs& a, int item, uint8_
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     acc[k >> 1][k & 1] = mfma_exact<PKIND>(frag[st & 1][k >> 1], frag[st & 1][2 + (k & 1)], acc[k >> 1][k & 1]);
-                    if (st == 2 && k == 0) wait_slot(todo - 1);
+                    if (st == 2 && k == 0) wait_next();
                     if (st == 0) raw[1][k] = lds_read(slot, 1, k);
                     if (st == 2) raw[0][k] = lds_read(next, 0, k);
                     frag[(st + 1) & 1][k] = dec((st + 1) & 3, k);
@@ -254,7 +247,7 @@ __device__ __forceinline__ void gemm_wk_tile(const GemmArgs& a, int item, uint8_
 #pragma unroll
             for (int idx = 0; idx < LOADS; ++idx) issue_one(idx, to);
             issue_advance();
-            wait_slot(todo);
+            wait_next();
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 acc[k >> 1][k & 1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(

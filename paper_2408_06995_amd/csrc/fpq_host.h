@@ -411,5 +411,9 @@ int launch_gemm_dma_s(const GemmArgs& a, hipStream_t st);   // small tiles
 int launch_gemm_dma_sq(const GemmArgs& a, hipStream_t st);
 int launch_gemm_wk(const GemmArgs& a, hipStream_t st);      // K split over the wavefronts
 int launch_gemm_wk_q(const GemmArgs& a, hipStream_t st);
+bool gemm_strip_applicable(const GemmArgs& a);              // weights in registers: a short K (gemm_strip_kernel.h)
+int launch_gemm_strip(const GemmArgs& a, hipStream_t st);
+int launch_gemm_strip_h(const GemmArgs& a, hipStream_t st);
+int launch_gemm_strip_q(const GemmArgs& a, hipStream_t st);
 
 }  // namespace fpq

@@ -773,6 +773,7 @@ int launch_gemm(const GemmArgs& a, hipStream_t st)
             hipLaunchKernelGGL(gemm_skinny_kernel<OPK_FP4>, grid, dim3(256), 0, st, a);
         return hipGetLastError() == hipSuccess ? FPQ_OK : FPQ_ERR_LAUNCH;
     }
+    if (gemm_strip_applicable(a)) return launch_gemm_strip(a, st);
     if (gemm_dma_applicable(a)) return launch_gemm_dma(a, st);
     if (a.splits > 1) return FPQ_ERR_UNSUPPORTED;   // plan_gemm only splits for the large-tile kernels
     if (a.acc_mode == FPQ_ACC_FP8_MFMA) {

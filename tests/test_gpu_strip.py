@@ -1,0 +1,47 @@
+"""The kernel that keeps the weights of a short K in registers (a K of at most 320 codes, every output from one row of
+activations), at its edges, against the oracle: every number of 64-code steps, rows and columns that fill no block or
+strip, images that end inside a block, output rows that share cache lines, and results as codes."""
+import pytest
+
+from paper_2408_06995_amd import synth
+from test_gpu_codes_out import test_linear_activation_then_codes as linear_activation_case
+from test_gpu_codes_out import test_conv_silu_then_codes as conv_silu_case
+from test_gpu_tiles import FORMS
+from test_gpu_tiles import test_conv as conv_case
+from test_gpu_tiles import test_linear as linear_case
+
+pytestmark = pytest.mark.gpu
+
+E4M3, E2M1, E3M4 = synth.E4M3, synth.E2M1, synth.E3M4
+
+# results in rows: from 144 pairs of 128 rows and 64 columns on; 16 .. 320 codes, all remainders of the 64-code steps' chunks
+LINEAR = [(17, 320, 9200), (33, 64, 9217), (128, 80, 9248), (129, 128, 4640), (2311, 144, 512), (3000, 192, 448),
+          (4640, 208, 200), (9217, 256, 65), (9300, 272, 127), (18500, 304, 64), (4700, 320, 256), (18433, 16, 96),
+          (70000, 320, 64)]
+
+
+@pytest.mark.parametrize("fx,fw,acc", FORMS)
+@pytest.mark.parametrize("M,K,N", LINEAR)
+def test_rows(M, K, N, fx, fw, acc):
+    linear_case(M, K, N, fx, fw, acc)
+
+
+@pytest.mark.parametrize("fx,fw,acc", FORMS)
+@pytest.mark.parametrize("case", [(1, 320, 5, 5, 32, 1, 1, 0), (3, 64, 9, 7, 64, 1, 1, 0), (2, 100, 16, 16, 65, 1, 1, 0),
+                                  (5, 3, 11, 13, 130, 1, 1, 0), (2, 160, 64, 32, 320, 1, 1, 0), (9, 250, 33, 31, 72, 1, 1, 0),
+                                  (4, 300, 32, 64, 127, 1, 1, 0), (40, 20, 3, 3, 100, 1, 1, 0), (17, 48, 1, 1, 40, 1, 1, 0)])
+def test_nchw(case, fx, fw, acc):
+    conv_case(case, fx, fw, acc)
+
+
+@pytest.mark.parametrize("fw,fy,acc", [(E4M3, E4M3, 0), (E2M1, E4M3, 0), (E4M3, E3M4, 0), (E4M3, E4M3, 1), (E2M1, E4M3, 1)])
+@pytest.mark.parametrize("act", ["silu", "geglu"])
+@pytest.mark.parametrize("M,K,N", [(17, 320, 32), (33, 64, 96), (100, 80, 2560), (1500, 192, 160), (4097, 256, 64), (3000, 304, 544)])
+def test_linear_codes_out(M, K, N, fw, fy, acc, act):
+    linear_activation_case(M, K, N, fw, fy, acc, act)
+
+
+@pytest.mark.parametrize("case", [(2, 128, 5, 5, 36, 1, 1, 0), (1, 320, 15, 7, 66, 1, 1, 0), (2, 20, 31, 33, 130, 1, 1, 0),
+                                  (3, 200, 20, 20, 16, 1, 1, 0), (2, 256, 32, 32, 320, 1, 1, 0)])
+def test_conv_codes_out(case):
+    conv_silu_case(case)

@@ -946,7 +946,7 @@ int fpq_int_gemm(const uint8_t* xcodes, float sx, int32_t zx, const fpq_int_para
     const uint8_t* base = static_cast<const uint8_t*>(packed_w);
     const int32_t* rowsum = reinterpret_cast<const int32_t*>(base + kPackedRowsOffset + align_up(int_rows_bytes(N, K, wbits), 256));
     return launch_int_gemm(xcodes, sx, zx, px_dev, base + kPackedRowsOffset, rowsum, wbits, sw, zw, bias, y, M, N, K,
-                           static_cast<int32_t*>(workspace), static_cast<hipStream_t>(stream));
+                           static_cast<hipStream_t>(stream));
 }
 
 int fpq_probe_peak(int kind, int iterations, const void* src, void* dst, size_t bytes, double* work_out, void* stream)

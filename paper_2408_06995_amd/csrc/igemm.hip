@@ -7,14 +7,14 @@
 // 4-bit weights as b' = q (0 .. 15 fits a signed byte).  With za = zx - 128 and zb = zw - 128 (or zw):
 //   sum_k (qx - zx)(qw - zw) = sum_k a' b'  -  zb * sum_k a'  -  za * sum_k b'  +  K * za * zb,
 // all in 32-bit integers (K <= 32768 keeps the result below 2^31; intermediate wrap-around cancels).  The row sums of b'
-// are computed when the weights are packed, those of a' by a small kernel before the layer.
+// are computed when the weights are packed, those of a' by the layer kernel on its way through the codes.
 #include "fpq_dev.h"
 #include "fpq_host.h"
-#include "gemm_common.h"
+#include "gemm_dma_kernel.h"
 
 namespace fpq {
 
-typedef int v4i32 __attribute__((ext_vector_type(4)));
+typedef v4i v4i32;
 typedef int v16i32 __attribute__((ext_vector_type(16)));
 
 // ---------------------------------------------------------------------------------- min / max -> (s, z)
@@ -46,11 +46,25 @@ __device__ __forceinline__ void int_params_of(float lo, float hi, int levels, fl
 __global__ __launch_bounds__(256) void int_minmax_partial_kernel(const float* __restrict__ x, size_t n, float* __restrict__ partial)
 {
     float lo = INFINITY, hi = -INFINITY;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
-        const float v = x[i];
+    const size_t nthreads = (size_t)gridDim.x * 256, tid = (size_t)blockIdx.x * 256 + threadIdx.x;
+    auto take = [&](float v) {
         lo = fminf(lo, v);
         hi = fmaxf(hi, v);
+    };
+    auto take4 = [&](const float4& v) { take(v.x), take(v.y), take(v.z), take(v.w); };
+    // 16 bytes per lane, four loads in flight; a start that is not 16-byte aligned leaves up to three elements to single loads
+    size_t head = (16 - (reinterpret_cast<uintptr_t>(x) & 15)) / 4 & 3;
+    if (head > n) head = n;
+    const float4* x4 = reinterpret_cast<const float4*>(x + head);
+    const size_t n4 = (n - head) >> 2;
+    size_t i = tid;
+    for (; i + 3 * nthreads < n4; i += 4 * nthreads) {
+        const float4 a = x4[i], b = x4[i + nthreads], c = x4[i + 2 * nthreads], d = x4[i + 3 * nthreads];
+        take4(a), take4(b), take4(c), take4(d);
     }
+    for (; i < n4; i += nthreads) take4(x4[i]);
+    if (tid < head) take(x[tid]);
+    if (head + 4 * n4 + tid < n) take(x[head + 4 * n4 + tid]);
     block_minmax(lo, hi);
     if (threadIdx.x == 0) { partial[2 * blockIdx.x] = lo; partial[2 * blockIdx.x + 1] = hi; }
 }
@@ -208,28 +222,6 @@ int launch_int_pack_weights(const float* w, int64_t N, int64_t K, int bits, uint
     return hipGetLastError() == hipSuccess ? FPQ_OK : FPQ_ERR_LAUNCH;
 }
 
-// ---------------------------------------------------------------------------------- row sums of the activation codes
-
-// rowsum[m] = sum_k (q[m, k] - 128): one wavefront per row, 16 bytes per lane and step.
-__global__ __launch_bounds__(256) void int_rowsum_kernel(const uint8_t* __restrict__ codes, int M, int K, int32_t* __restrict__ rowsum)
-{
-    const int lane = threadIdx.x & 63;
-    const int m = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (m >= M) return;
-    const uint8_t* row = codes + (size_t)m * K;
-    int sum = 0;
-    for (int k = lane * 16; k < K; k += 64 * 16) {            // K % 16 == 0
-        const uint4 v = *reinterpret_cast<const uint4*>(row + k);
-        const uint32_t wds[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            sum += (int)(wds[i] & 0xff) + (int)((wds[i] >> 8) & 0xff) + (int)((wds[i] >> 16) & 0xff) + (int)(wds[i] >> 24) - 512;
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-    if (lane == 0) rowsum[m] = sum;
-}
-
 // ---------------------------------------------------------------------------------- the layer
 
 struct IGemmArgs {
@@ -239,7 +231,6 @@ struct IGemmArgs {
     const float* sw;         // [N]
     const int32_t* zw;       // [N]
     const float* bias;       // [N] or null
-    const int32_t* xsum;     // [M] row sums of a'
     const fpq_int_params* px_dev;   // activation scale / zero point on the device, or null
     float sx;
     int zx;
@@ -247,58 +238,72 @@ struct IGemmArgs {
     int M, N, K, Kpad;
 };
 
-// A workgroup of four wavefronts (2 x 2) owns a BX x BW tile; K in steps of 128 codes through two LDS stages,
-// register-staged loads, four 32-code integer MFMA steps per K step.  Activations are the row operand (accumulator
-// registers run along m), weights the lane operand, so a half-wave stores 128 consecutive bytes of an output row.
-template <int BX, int BW, bool W4>
-__global__ __launch_bounds__(256) void igemm_kernel(const IGemmArgs a)
+// A workgroup of four wavefronts (2 x 2) owns a BX x BW tile and walks K in steps of 128 codes through NST LDS stages that buffer loads
+// fill without registers (dma16; codes beyond the rows or K arrive as 0).  A step's loads go out NST - 1 steps ahead, behind the
+// barrier that frees its stage, and there is one barrier per step; two to five workgroups share a compute unit, so that one
+// stores while another multiplies.  Activations are the row operand (accumulator registers run along m), weights the lane operand, so a
+// half-wave stores 128 consecutive bytes of an output row.
+// The row sums of the activation codes, which the zero points need, are taken from the fragments as they pass (one dot4 per four
+// codes, in the shadow of the matrix instructions) instead of by a kernel of their own.
+// Bound by LDS (64 x 64 outputs per wavefront read as many bytes per clock as LDS gives at the full matrix rate, and the loads write
+// theirs beside it) and by the stores, which the other workgroup's steps overlap.  2048 x 1280 -> 10240: 77 us staged through registers
+// with single workgroups walking along the columns, 41 us (8-bit weights; 35 us with 4-bit ones).
+template <int BX, int BW, int NST, bool W4>
+__global__ __launch_bounds__(256, (BX <= 128 ? 2 : 1)) void igemm_kernel(const IGemmArgs a)
 {
     constexpr int XROWB = 128, WROWB = W4 ? 64 : 128;
     constexpr int XTILE = BX * XROWB, WTILE = BW * WROWB, STAGE = XTILE + WTILE;
-    constexpr int XLD = BX / 32;
-    constexpr int WCPR = WROWB / 16, WROWS_PER_PASS = 256 / WCPR, WLD = (BW + WROWS_PER_PASS - 1) / WROWS_PER_PASS;
+    constexpr int XLD = XTILE / 4096, WLD = WTILE / 4096, LOADS = XLD + WLD;     // loads per wavefront and step
     constexpr int TP = BX / 2, TQ = BW / 2, MI = TP / 32, NI = TQ / 32;
+    static_assert(XTILE % 4096 == 0 && WTILE % 4096 == 0, "a tile splits evenly over the wavefronts' loads");
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, g = lane >> 5;
+    const int lane = threadIdx.x & 63, l32 = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int tiles_w = (a.N + BW - 1) / BW;
-    const int tx = blockIdx.x / tiles_w, tw = blockIdx.x - tx * tiles_w;
+    // ids go round-robin over the 8 XCDs: each takes a contiguous run of tiles, which share activation rows
+    int tile = blockIdx.x;
+    {
+        const int per = gridDim.x >> 3;
+        if (tile < (per << 3)) tile = (tile & 7) * per + (tile >> 3);
+    }
+    // bands of eight tile rows, rows innermost: the workgroups that run together on an XCD then share weights as well as activations
+    // (columns innermost, each of 64 workgroups would fetch weights of its own)
+    const int tiles_x = (a.M + BX - 1) / BX;
+    const int band = tile / (8 * tiles_w), rows = tiles_x - 8 * band < 8 ? tiles_x - 8 * band : 8;
+    const int at = tile - band * 8 * tiles_w;
+    const int tw = at / rows, tx = 8 * band + at - tw * rows;
     const int m0 = tx * BX, n0 = tw * BW;
-    const int xc = tid & 7, xr0 = tid >> 3;
-    const int wc = tid % WCPR, wr0 = tid / WCPR;
-    const size_t wrow_bytes = W4 ? (size_t)a.Kpad / 2 : (size_t)a.Kpad;
-    uint4 xreg[XLD], wreg[WLD];
-    auto load_global = [&](int kt) {
+
+    // buffers of this tile's rows alone: rows beyond M or N are beyond the buffer
+    const unsigned wrow_bytes = W4 ? (unsigned)a.Kpad / 2 : (unsigned)a.Kpad;
+    const v4i xrsrc = make_rsrc(a.x + (size_t)m0 * a.K, (unsigned)(a.M - m0 < BX ? a.M - m0 : BX) * (unsigned)a.K);
+    const v4i wrsrc = make_rsrc(a.wrows + (size_t)n0 * wrow_bytes, (unsigned)(a.N - n0 < BW ? a.N - n0 : BW) * wrow_bytes);
+    const unsigned lds0 = (unsigned)(size_t)((__attribute__((address_space(3))) void*)smem);
+    constexpr unsigned OOB = 0x80000000u;
+    // load i covers rows 8 (4 i + wave) .. + 7 of 128 bytes (weights of 64 bytes: 16 rows); the swizzle of lds_off is applied by
+    // choosing the chunk that a lane fetches
+    const int xc = (lane & 7) ^ ((wave * 4 + (lane >> 4)) & 7);
+    unsigned xoff[XLD], woff[WLD];
 #pragma unroll
-        for (int i = 0; i < XLD; ++i) {
-            const int m = m0 + xr0 + 32 * i;
-            const int k = kt * 128 + xc * 16;
-            // rows and k beyond the tensor read as a' = 0, i.e. the byte 0x80 before the sign flip below
-            xreg[i] = (m < a.M && k < a.K) ? *reinterpret_cast<const uint4*>(a.x + (size_t)m * a.K + k)
-                                           : make_uint4(0x80808080u, 0x80808080u, 0x80808080u, 0x80808080u);
-        }
+    for (int i = 0; i < XLD; ++i) xoff[i] = (unsigned)((4 * i + wave) * 8 + (lane >> 3)) * (unsigned)a.K + 16u * xc;
 #pragma unroll
-        for (int i = 0; i < WLD; ++i) {
-            const int row = wr0 + WROWS_PER_PASS * i;
-            wreg[i] = (row < BW && n0 + row < a.N)
-                          ? *reinterpret_cast<const uint4*>(a.wrows + (size_t)(n0 + row) * wrow_bytes + (size_t)kt * WROWB + wc * 16)
-                          : make_uint4(0, 0, 0, 0);
-        }
+    for (int i = 0; i < WLD; ++i)
+        woff[i] = W4 ? (unsigned)((4 * i + wave) * 16 + (lane >> 2)) * wrow_bytes + 16u * ((lane & 3) ^ ((lane >> 4) & 3))
+                     : (unsigned)((4 * i + wave) * 8 + (lane >> 3)) * wrow_bytes + 16u * xc;
+    const int nk = a.Kpad / 128;
+    auto issue = [&](int kt, int stage) {
+        const int live = kt < nk ? -1 : 1;                    // beyond the last step one lane keeps the counts of the waits
+        const bool in_row = kt * 128 + xc * 16 < a.K;
+#pragma unroll
+        for (int i = 0; i < XLD; ++i)
+            dma16_live(xrsrc, in_row ? xoff[i] + kt * 128 : OOB, lds0 + stage * STAGE + (4 * i + wave) * 1024, live);
+#pragma unroll
+        for (int i = 0; i < WLD; ++i)
+            dma16_live(wrsrc, kt < nk ? woff[i] + kt * WROWB : OOB, lds0 + stage * STAGE + XTILE + (4 * i + wave) * 1024, live);
     };
-    auto store_lds = [&](int stage) {
-        uint8_t* xs = smem + stage * STAGE;
-        uint8_t* ws = xs + XTILE;
 #pragma unroll
-        for (int i = 0; i < XLD; ++i) {
-            uint4 v = xreg[i];                     // unsigned code -> signed a' = q - 128: flip the top bit of every byte
-            v.x ^= 0x80808080u; v.y ^= 0x80808080u; v.z ^= 0x80808080u; v.w ^= 0x80808080u;
-            *reinterpret_cast<uint4*>(xs + lds_off<XROWB>(xr0 + 32 * i, xc)) = v;
-        }
-#pragma unroll
-        for (int i = 0; i < WLD; ++i) {
-            const int row = wr0 + WROWS_PER_PASS * i;
-            if (row < BW) *reinterpret_cast<uint4*>(ws + lds_off<WROWB>(row, wc)) = wreg[i];
-        }
-    };
+    for (int s = 0; s < NST - 1; ++s) issue(s, s);
+
     v16i32 acc[MI][NI];
 #pragma unroll
     for (int i = 0; i < MI; ++i)
@@ -306,98 +311,161 @@ __global__ __launch_bounds__(256) void igemm_kernel(const IGemmArgs a)
         for (int j = 0; j < NI; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
+    unsigned xs[MI];                                          // sums of the codes this lane has read of row l32 of block i
+#pragma unroll
+    for (int i = 0; i < MI; ++i) xs[i] = 0;
     const int wp = wave >> 1, wq = wave & 1;
     const int prow0 = wp * TP + l32, qrow0 = wq * TQ + l32;
-    auto compute = [&](int stage) {
-        const uint8_t* xs = smem + stage * STAGE;
-        const uint8_t* ws = xs + XTILE;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {               // four chunks of 32 codes; lane half g takes codes 16 g .. 16 g + 15 of a chunk
-            v4i32 af[MI], bf_[NI];
+
+    int stage = 0, to = NST - 1;
+    for (int kt = 0; kt < nk; ++kt) {
+        // this step's loads have landed (younger: those of the NST - 2 steps after it); behind the barrier that holds for all
+        // wavefronts, and all have read the stage of the step before, which the loads issued next overwrite
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm((NST - 2) * LOADS));
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        issue(kt + NST - 1, to);
+        const uint8_t* xt = smem + stage * STAGE;
+        const uint8_t* wt = xt + XTILE;
+        // four chunks of 32 codes; lane half g takes 16 codes of a chunk, the same ones of both operands
+        v4i32 af[2][MI], bf[2][NI];
+        auto read = [&](int c) {
 #pragma unroll
             for (int i = 0; i < MI; ++i) {
-                const uint4 v = *reinterpret_cast<const uint4*>(xs + lds_off<XROWB>(prow0 + 32 * i, 2 * c + g));
-                af[i] = v4i32{(int)v.x, (int)v.y, (int)v.z, (int)v.w};
+                // two chunks of 4-bit weights are one 16-byte piece: their halves are 32 codes apart
+                const int k = W4 ? 4 * (c >> 1) + 2 * g + (c & 1) : 2 * c + g;
+                const uint4 v = *reinterpret_cast<const uint4*>(xt + lds_off<XROWB>(prow0 + 32 * i, k));
+                af[c & 1][i] = v4i32{(int)v.x, (int)v.y, (int)v.z, (int)v.w};
             }
 #pragma unroll
             for (int j = 0; j < NI; ++j) {
                 const int row = qrow0 + 32 * j;
                 if (W4) {
-                    // 16 codes = 8 bytes = words 2 h, 2 h + 1 of the row's step (h = 2 c + g): low nibbles, then high nibbles
-                    const uint2 v = *reinterpret_cast<const uint2*>(ws + lds_off<WROWB>(row, c) + g * 8);
-                    bf_[j] = v4i32{(int)(v.x & 0x0f0f0f0fu), (int)((v.x >> 4) & 0x0f0f0f0fu), (int)(v.y & 0x0f0f0f0fu),
-                                   (int)((v.y >> 4) & 0x0f0f0f0fu)};
+                    // 16 codes = 8 bytes = two words: low nibbles, then high nibbles of each
+                    const uint2 v = *reinterpret_cast<const uint2*>(wt + lds_off<WROWB>(row, 2 * (c >> 1) + g) + 8 * (c & 1));
+                    bf[c & 1][j] = v4i32{(int)(v.x & 0x0f0f0f0fu), (int)((v.x >> 4) & 0x0f0f0f0fu), (int)(v.y & 0x0f0f0f0fu),
+                                         (int)((v.y >> 4) & 0x0f0f0f0fu)};
                 } else {
-                    const uint4 v = *reinterpret_cast<const uint4*>(ws + lds_off<WROWB>(row, 2 * c + g));
-                    bf_[j] = v4i32{(int)v.x, (int)v.y, (int)v.z, (int)v.w};
+                    const uint4 v = *reinterpret_cast<const uint4*>(wt + lds_off<WROWB>(row, 2 * c + g));
+                    bf[c & 1][j] = v4i32{(int)v.x, (int)v.y, (int)v.z, (int)v.w};
                 }
             }
+        };
+        read(0);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            if (c + 1 < 4) read(c + 1);
 #pragma unroll
             for (int i = 0; i < MI; ++i)
 #pragma unroll
-                for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[i], bf_[j], acc[i][j], 0, 0, 0);
+                for (int w = 0; w < 4; ++w) {
+                    const unsigned q = (unsigned)af[c & 1][i][w];
+                    xs[i] = __builtin_amdgcn_udot4(q, 0x01010101u, xs[i], false);
+                    af[c & 1][i][w] = (int)(q ^ 0x80808080u);  // unsigned code -> signed a' = q - 128
+                }
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[c & 1][i], bf[c & 1][j], acc[i][j], 0, 0, 0);
         }
-    };
-    const int nk = a.Kpad / 128;
-    load_global(0);
-    store_lds(0);
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-        const int cur = kt & 1;
-        if (kt + 1 < nk) load_global(kt + 1);
-        compute(cur);
-        if (kt + 1 < nk) store_lds(cur ^ 1);
-        __syncthreads();
+        to = stage;
+        stage = stage + 1 == NST ? 0 : stage + 1;
     }
-    // ---- epilogue: fold the zero points out with the row sums, scale, store
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));                 // no load may land in LDS from here on
+    asm volatile("" ::: "memory");
+    __syncthreads();
+
+    // ---- epilogue: fold the zero points out with the row sums, scale, store.  The row sums cross from lanes to registers in LDS.
+    unsigned* sums = reinterpret_cast<unsigned*>(smem) + wave * TP;
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+        const unsigned both = xs[i] + (unsigned)__shfl_xor((int)xs[i], 32, 64);
+        if (g == 0) sums[32 * i + l32] = both - 128u * (unsigned)a.K;          // sum of a'
+    }
+    __syncthreads();
     const float sx = a.px_dev ? a.px_dev->scale : a.sx;
     const int za = (a.px_dev ? a.px_dev->zero_point : a.zx) - 128;
+    float sc[NI], bv[NI];
+    unsigned zb[NI], colterm[NI];
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
         const int n = n0 + wq * TQ + 32 * j + l32;
-        if (n >= a.N) continue;
-        const int zb = a.zw[n] - (W4 ? 0 : 128);
-        const int colterm = (int)((uint32_t)a.K * (uint32_t)za * (uint32_t)zb - (uint32_t)za * (uint32_t)a.wsum[n]);
-        const float sc = sx * a.sw[n];
-        const float bv = a.bias ? a.bias[n] : 0.0f;
+        const bool in = n < a.N;
+        zb[j] = in ? (unsigned)(a.zw[n] - (W4 ? 0 : 128)) : 0u;
+        colterm[j] = in ? (unsigned)a.K * (unsigned)za * zb[j] - (unsigned)za * (unsigned)a.wsum[n] : 0u;
+        sc[j] = in ? sx * a.sw[n] : 0.0f;
+        bv[j] = in && a.bias ? a.bias[n] : 0.0f;
+    }
+    const int mw = m0 + wp * TP, nw = n0 + wq * TQ;
+    auto store_all = [&](auto whole, auto streaming) {
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int m = m0 + wp * TP + 32 * i + 8 * (r >> 2) + 4 * g + (r & 3);
-                if (m < a.M) {
-                    // unsigned arithmetic: intermediate values may wrap, the result fits (K <= 32768)
-                    const int total = (int)((uint32_t)acc[i][j][r] - (uint32_t)zb * (uint32_t)a.xsum[m] + (uint32_t)colterm);
-                    a.y[(size_t)m * a.N + n] = (float)total * sc + bv;
+            for (int q = 0; q < 4; ++q) {
+                const uint4 s4 = *reinterpret_cast<const uint4*>(sums + 32 * i + 8 * q + 4 * g);
+                const unsigned s[4] = {s4.x, s4.y, s4.z, s4.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int m = mw + 32 * i + 8 * q + 4 * g + e;
+#pragma unroll
+                    for (int j = 0; j < NI; ++j) {
+                        // unsigned arithmetic: intermediate values may wrap, the result fits (K <= 32768)
+                        const int total = (int)((unsigned)acc[i][j][4 * q + e] - zb[j] * s[e] + colterm[j]);
+                        const float v = (float)total * sc[j] + bv[j];
+                        float* at = a.y + (size_t)m * a.N + nw + 32 * j + l32;
+                        if constexpr (decltype(streaming)::value)
+                            store_out(at, v);
+                        else if (decltype(whole)::value || (m < a.M && nw + 32 * j + l32 < a.N))
+                            *at = v;
+                    }
                 }
             }
-    }
+    };
+    // streaming stores where rows are whole cache lines; lines shared by two rows are put together in the L2
+    const bool whole_tile = m0 + BX <= a.M && n0 + BW <= a.N;
+    if (whole_tile && (a.N & 31) == 0)
+        store_all(std::true_type{}, std::true_type{});
+    else if (whole_tile)
+        store_all(std::true_type{}, std::false_type{});
+    else
+        store_all(std::false_type{}, std::false_type{});
 }
 
-template <int BX, int BW, bool W4>
+template <int BX, int BW, int NST, bool W4>
 static int launch_igemm_one(const IGemmArgs& a, hipStream_t st)
 {
-    constexpr int smem = 2 * (BX * 128 + BW * (W4 ? 64 : 128));
-    const int tiles = ((a.M + BX - 1) / BX) * ((a.N + BW - 1) / BW);
-    auto kern = igemm_kernel<BX, BW, W4>;
+    constexpr int smem = NST * (BX * 128 + BW * (W4 ? 64 : 128));
+    const int64_t tiles = (int64_t)((a.M + BX - 1) / BX) * ((a.N + BW - 1) / BW);
+    auto kern = igemm_kernel<BX, BW, NST, W4>;
     if (smem > 64 * 1024) {
         static std::atomic<uint64_t> allowed{0};
         if (!allow_dynamic_lds(reinterpret_cast<const void*>(kern), smem, allowed)) return FPQ_ERR_LAUNCH;
     }
-    hipLaunchKernelGGL(kern, dim3(tiles), dim3(256), smem, st, a);
+    hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(256), smem, st, a);
     return hipGetLastError() == hipSuccess ? FPQ_OK : FPQ_ERR_LAUNCH;
 }
 
 int launch_int_gemm(const uint8_t* x, float sx, int zx, const fpq_int_params* px_dev, const uint8_t* wrows, const int32_t* wsum,
                     int wbits, const float* sw, const int32_t* zw, const float* bias, float* y, int64_t M, int64_t N, int64_t K,
-                    int32_t* xsum, hipStream_t st)
+                    hipStream_t st)
 {
     if (M <= 0 || N <= 0) return FPQ_OK;
-    hipLaunchKernelGGL(int_rowsum_kernel, dim3((unsigned)((M + 3) / 4)), dim3(256), 0, st, x, (int)M, (int)K, xsum);
-    IGemmArgs a{x, wrows, wsum, sw, zw, bias, xsum, px_dev, sx, zx, y, (int)M, (int)N, (int)K, (int)padded_k(K, 1)};
-    const long big = (long)((M + 127) / 128) * ((N + 127) / 128);
-    if (wbits == 4) return big >= 256 ? launch_igemm_one<128, 128, true>(a, st) : launch_igemm_one<64, 64, true>(a, st);
-    return big >= 256 ? launch_igemm_one<128, 128, false>(a, st) : launch_igemm_one<64, 64, false>(a, st);
+    IGemmArgs a{x, wrows, wsum, sw, zw, bias, px_dev, sx, zx, y, (int)M, (int)N, (int)K, (int)padded_k(K, 1)};
+    // 128 x 128 tiles where they fill the compute units and cover few columns beyond N (calibration, quantizer and layer, 8-bit weights,
+    // against 64 x 64: 2048 x 1280 -> 10240 50 and 64 us, 8192 x 640 -> 2560 41 and 46; 4000 x 1024 -> 1000, 256 tiles, 33 and 29;
+    // 32768 x 320 -> 320 45 and 36); 64 x 64 tiles with a third stage where a deep K has to hide its loads with few workgroups per
+    // compute unit (2000 x 5120 -> 640: 45 us, 52 with two), which otherwise costs the room for five of them (30000 x 64 -> 1001: 56
+    // and 47).
+    const int64_t tiles128 = ((M + 127) / 128) * ((N + 127) / 128), tiles64 = ((M + 63) / 64) * ((N + 63) / 64);
+    const bool large = tiles128 >= 320 && (N + 127) / 128 * 128 * 10 <= N * 11;
+    const bool third = a.Kpad >= 2048 && tiles64 <= 768;
+    if (wbits == 4)
+        return large ? launch_igemm_one<128, 128, 2, true>(a, st)
+                     : third ? launch_igemm_one<64, 64, 3, true>(a, st) : launch_igemm_one<64, 64, 2, true>(a, st);
+    return large ? launch_igemm_one<128, 128, 2, false>(a, st)
+                 : third ? launch_igemm_one<64, 64, 3, false>(a, st) : launch_igemm_one<64, 64, 2, false>(a, st);
 }
 
 }  // namespace fpq

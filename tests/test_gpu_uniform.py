@@ -135,3 +135,21 @@ def test_integer_entry_points_validate():
     assert L.fpq_int_gemm(p, 1.0, 0, None, p, 8, p, p, None, p, 0, 8, 32, p, 16, None) == 0
     assert B.fpq_int_packed_size(320, 320, 8) == 256 + 320 * 384 + 320 * 4
     assert B.fpq_int_packed_size(320, 320, 4) == 256 + 320 * 192 + 320 * 4
+
+
+@pytest.mark.parametrize("M,K,N", [(4099, 144, 1285), (5100, 272, 1024), (3000, 1040, 1793),      # 128 x 128 tiles
+                                   (70, 2064, 129), (1, 32752, 65), (513, 4112, 66),              # 64 x 64, three stages
+                                   (1100, 64, 33), (65, 2032, 64)])                               # two
+@pytest.mark.parametrize("wbits", [8, 4])
+def test_tiles_of_the_integer_layer(M, K, N, wbits):
+    test_integer_layer(M, K, N, wbits)
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 7, 1023, 100003])
+@pytest.mark.parametrize("offset", [0, 1, 2, 3])
+def test_calibration_of_unaligned_tensors(n, offset):
+    x = synth.activations((n + 8,), 40 + n)
+    x[offset], x[offset + n - 1] = -70.0, 90.0
+    x[:offset], x[offset + n:] = 1e6, -1e6                      # neighbours that must not count
+    _, p = gpu_calibrate(dev(x)[offset:offset + n], 8)
+    assert (p.min, p.max) == ((-70.0 if n > 1 else 90.0), 90.0)

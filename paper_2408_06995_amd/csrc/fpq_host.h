@@ -33,11 +33,12 @@ static inline bool allow_dynamic_lds(const void* kernel, int bytes, std::atomic<
 // Length of a packed weight row: taps * Cp rounded up to the 128-code K step of the kernels.
 static inline int64_t padded_k(int64_t Cin, int64_t taps) { return (taps * padded_channels(Cin) + 127) / 128 * 128; }
 
-// Blocks of the first absmax pass (each folds >= 4096 elements; at most 1024 partials).
+// Blocks of the first absmax pass (each folds >= 4096 elements; at most kAbsmaxParts partials).
+constexpr int kAbsmaxParts = 1024;
 static inline int absmax_parts(size_t n)
 {
     size_t g = (n + 4095) / 4096;
-    return (int)(g > 1024 ? 1024 : g);
+    return (int)(g > kAbsmaxParts ? kAbsmaxParts : g);
 }
 
 // Header in front of the packed rows.  The rows start kPackedRowsOffset bytes into the buffer so that, for a

@@ -26,12 +26,29 @@ __device__ __forceinline__ float block_max(float v)
     return v;
 }
 
-// r = fl32(1 / scale) for a quantize kernel (all threads of the block call this).
-__device__ __forceinline__ float block_inv_scale(const ScaleSrc& s)
+// r = fl32(1 / scale) for a quantize kernel, in two halves (all threads of the block call both): the partial maxima go out first, the
+// caller's own first loads right behind them, and the wait for the partials, the barriers and the division then run while those are
+// on their way.  (One after the other, a block spent half of its life on the fold: its loads, four in a row, and nothing else.)
+// Loads ahead of fold_end are not conditional (an index beyond the end becomes the last one): behind a branch, the compiler's wait for
+// the partials would be one for all loads.
+struct Fold {
+    float part[kAbsmaxParts / 256];
+};
+__device__ __forceinline__ Fold fold_begin(const ScaleSrc& s)
+{
+    Fold f;
+#pragma unroll
+    for (int u = 0; u < kAbsmaxParts / 256; ++u) {
+        f.part[u] = s.partials != nullptr ? s.partials[min((int)threadIdx.x + 256 * u, s.nparts - 1)] : 0.0f;
+    }
+    return f;
+}
+__device__ __forceinline__ float fold_end(const ScaleSrc& s, const Fold& f)
 {
     if (s.partials == nullptr) return inv_scale(s.host, s.dev);
-    float v = 0.0f;
-    for (int i = threadIdx.x; i < s.nparts; i += 256) v = fmaxf(v, s.partials[i]);
+    float v = f.part[0];
+#pragma unroll
+    for (int u = 1; u < kAbsmaxParts / 256; ++u) v = fmaxf(v, f.part[u]);
     v = block_max(v);
     const float sc = (v == 0.0f) ? 1.0f : __fdiv_rn(v, s.maxval);
     if (s.publish && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0) {
@@ -39,6 +56,40 @@ __device__ __forceinline__ float block_inv_scale(const ScaleSrc& s)
         s.publish[1] = v;
     }
     return __fdiv_rn(1.0f, sc);
+}
+
+// Four codes in one word, byte e = value e.  The formats that the hardware converts (YKIND 1: (4, 3, 7), 2: (5, 2, 15), see hw_kind)
+// take one conversion per pair after the clip, the same rounding on the same grid, signs of zeros included: 14 vector instructions
+// for four values against about 60 of the arithmetic encoder, which at 10 M elements take as long as half of the reads.
+template <int YKIND>
+__device__ __forceinline__ uint32_t quantize4(float v0, float v1, float v2, float v3, float r, const QParams& q)
+{
+    if constexpr (YKIND == 0) {
+        return quantize_nearest(v0, r, q) | (quantize_nearest(v1, r, q) << 8) | (quantize_nearest(v2, r, q) << 16) |
+               (quantize_nearest(v3, r, q) << 24);
+    } else {
+        auto clip = [&](float x) {
+            const float y = __fmul_rn(x, r);
+            return copysignf(fminf(fabsf(y), q.c), y);
+        };
+        int w;
+        if constexpr (YKIND == 1) {
+            w = __builtin_amdgcn_cvt_pk_fp8_f32(clip(v0), clip(v1), 0, false);
+            w = __builtin_amdgcn_cvt_pk_fp8_f32(clip(v2), clip(v3), w, true);
+        } else {
+            w = __builtin_amdgcn_cvt_pk_bf8_f32(clip(v0), clip(v1), 0, false);
+            w = __builtin_amdgcn_cvt_pk_bf8_f32(clip(v2), clip(v3), w, true);
+        }
+        return (uint32_t)w;
+    }
+}
+
+// The format's conversion instruction, if there is one (any max value up to the hardware's own: the clip comes first).
+int hw_kind(const QParams& q)
+{
+    if (q.em == 7 && q.m == 3 && q.b == 7 && q.c <= 448.0f) return 1;
+    if (q.em == 7 && q.m == 2 && q.b == 15 && q.c <= 57344.0f) return 2;
+    return 0;
 }
 
 // Tensors from this many elements (64 MB of fp32) on take the contiguous-share / streaming-load kernels.
@@ -61,7 +112,8 @@ __device__ __forceinline__ float max4(float v, const float4& a)
 }
 
 // Pass 1: each block folds one contiguous share of x into one partial maximum of |x| (contiguous shares
-// and eight 16-byte loads in flight per lane measured fastest: ~6.6 TB/s against ~5.3 grid-strided).
+// and eight 16-byte loads in flight per lane measured fastest: ~6.6 TB/s against ~5.3 grid-strided; 168 MB 35.4 us, 38.7 us with
+// loads behind conditions).
 __global__ __launch_bounds__(256) void absmax_partial_kernel(const float* __restrict__ x, size_t n,
                                                              float* __restrict__ partial)
 {
@@ -72,12 +124,12 @@ __global__ __launch_bounds__(256) void absmax_partial_kernel(const float* __rest
         const size_t per = (n4 + gridDim.x - 1) / gridDim.x;
         const size_t b0 = (size_t)blockIdx.x * per;
         const size_t e = b0 + per < n4 ? b0 + per : n4;
-        // eight loads in flight per lane whatever the length of the share (the last round is predicated)
+        // eight loads in flight per lane whatever the length of the share (beyond its end the last element again: a load behind a
+        // condition would be waited for before the next); plain loads: the quantize pass that follows re-reads x
         for (size_t base = b0 + threadIdx.x; base < e; base += 8 * 256) {
             float4 a[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                a[u] = (base + u * 256 < e) ? x4[base + u * 256] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);   // plain loads: the quantize pass that follows re-reads x
+            for (int u = 0; u < 8; ++u) a[u] = x4[base + u * 256 < e ? base + u * 256 : e - 1];
 #pragma unroll
             for (int u = 0; u < 8; ++u) v = max4(v, a[u]);
         }
@@ -163,61 +215,61 @@ int launch_absmax_partials(const float* x, size_t n, float* partial, hipStream_t
 
 // ------------------------------------------------------------------------------ quantize (flat)
 
+template <bool FOUR_BIT, int YKIND>
+__device__ __forceinline__ void store_codes(uint8_t* codes, size_t i, const float4& v, float r, const QParams& q)
+{
+    if (FOUR_BIT) {
+        const uint32_t c = quantize4<0>(v.x, v.y, v.z, v.w, r, q);
+        reinterpret_cast<uint16_t*>(codes)[i] = (uint16_t)((c & 0xfu) | (c >> 4 & 0xf0u) | (c >> 8 & 0xf00u) | (c >> 12 & 0xf000u));
+    } else {
+        reinterpret_cast<uint32_t*>(codes)[i] = quantize4<YKIND>(v.x, v.y, v.z, v.w, r, q);
+    }
+}
+
 // Four elements per lane and step: one 16-byte streaming load, four encodes, one 4-byte (8-bit codes) or
 // 2-byte (4-bit codes) store.  Each block walks one contiguous share with four loads in flight per lane.
-template <bool FOUR_BIT>
+template <bool FOUR_BIT, int YKIND>
 __global__ __launch_bounds__(256) void quantize_vec_kernel(const float4* __restrict__ x4, size_t n4, QParams q,
                                                            ScaleSrc ss, uint8_t* __restrict__ codes)
 {
-    const float r = block_inv_scale(ss);
+    const Fold f = fold_begin(ss);
     const size_t per = (n4 + gridDim.x - 1) / gridDim.x;
     const size_t b0 = (size_t)blockIdx.x * per;
     const size_t e = b0 + per < n4 ? b0 + per : n4;
     size_t i = b0 + threadIdx.x;
-    auto emit = [&](size_t idx, const float4& v) {
-        uint32_t c0 = quantize_nearest(v.x, r, q), c1 = quantize_nearest(v.y, r, q);
-        uint32_t c2 = quantize_nearest(v.z, r, q), c3 = quantize_nearest(v.w, r, q);
-        if (FOUR_BIT)
-            reinterpret_cast<uint16_t*>(codes)[idx] = (uint16_t)(c0 | (c1 << 4) | (c2 << 8) | (c3 << 12));
-        else
-            reinterpret_cast<uint32_t*>(codes)[idx] = c0 | (c1 << 8) | (c2 << 16) | (c3 << 24);
+    float4 a[4];
+    auto load = [&]() {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) a[u] = load_stream(x4 + (i + u * 256 < e ? i + u * 256 : e - 1));
     };
-    for (; i < e; i += 4 * 256) {   // four loads in flight per lane; the last round is predicated
-        float4 a[4];
+    load();
+    const float r = fold_end(ss, f);
+    while (i < e) {   // four loads in flight per lane
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            if (i + u * 256 < e) a[u] = load_stream(x4 + i + u * 256);
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (i + u * 256 < e) emit(i + u * 256, a[u]);
+            if (i + u * 256 < e) store_codes<FOUR_BIT, YKIND>(codes, i + u * 256, a[u], r, q);
+        i += 4 * 256;
+        if (i < e) load();
     }
 }
 
-// The same for tensors below kStreamElems, grid-strided with plain loads: one 16-byte load, four encodes, one 4-byte (8-bit codes) or
-// 2-byte (4-bit codes) store.  Four independent loads are kept in flight per lane.
-template <bool FOUR_BIT>
+// The same for tensors below kStreamElems, grid-strided with plain loads, one round of four loads per lane: the grid covers the
+// tensor.  32768 x 320: 11.3 us with the fold in front of the loads and the arithmetic
+// encoder, 7.9 us.
+template <bool FOUR_BIT, int YKIND>
 __global__ __launch_bounds__(256) void quantize_vec_strided_kernel(const float4* __restrict__ x4, size_t n4, QParams q,
                                                            ScaleSrc ss, uint8_t* __restrict__ codes)
 {
-    const float r = block_inv_scale(ss);
+    const Fold f = fold_begin(ss);
     const size_t nthreads = (size_t)gridDim.x * 256;
-    size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    auto emit = [&](size_t idx, const float4& v) {
-        uint32_t c0 = quantize_nearest(v.x, r, q), c1 = quantize_nearest(v.y, r, q);
-        uint32_t c2 = quantize_nearest(v.z, r, q), c3 = quantize_nearest(v.w, r, q);
-        if (FOUR_BIT)
-            reinterpret_cast<uint16_t*>(codes)[idx] = (uint16_t)(c0 | (c1 << 4) | (c2 << 8) | (c3 << 12));
-        else
-            reinterpret_cast<uint32_t*>(codes)[idx] = c0 | (c1 << 8) | (c2 << 16) | (c3 << 24);
-    };
-    for (; i + 3 * nthreads < n4; i += 4 * nthreads) {
-        float4 a = x4[i], b = x4[i + nthreads], c = x4[i + 2 * nthreads], d = x4[i + 3 * nthreads];
-        emit(i, a);
-        emit(i + nthreads, b);
-        emit(i + 2 * nthreads, c);
-        emit(i + 3 * nthreads, d);
-    }
-    for (; i < n4; i += nthreads) emit(i, x4[i]);
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    float4 a[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) a[u] = x4[i + u * nthreads < n4 ? i + u * nthreads : n4 - 1];
+    const float r = fold_end(ss, f);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (i + u * nthreads < n4) store_codes<FOUR_BIT, YKIND>(codes, i + u * nthreads, a[u], r, q);
 }
 
 // One output byte per lane: any alignment, tails.  first = index of the first element handled.
@@ -226,7 +278,7 @@ __global__ __launch_bounds__(256) void quantize_scalar_kernel(const float* __res
                                                               QParams q, ScaleSrc ss,
                                                               uint8_t* __restrict__ codes)
 {
-    const float r = block_inv_scale(ss);
+    const float r = fold_end(ss, fold_begin(ss));
     const size_t per = FOUR_BIT ? 2 : 1;
     size_t j = first / per + (size_t)blockIdx.x * 256 + threadIdx.x;  // output byte
     const size_t nbytes = (n + per - 1) / per;
@@ -257,19 +309,15 @@ int launch_quantize(const float* x, size_t n, const QParams& q, bool four_bit, c
     bool aligned = (reinterpret_cast<uintptr_t>(x) & 15) == 0 && (reinterpret_cast<uintptr_t>(codes) & 3) == 0;
     size_t n4 = aligned ? (n >> 2) : 0;
     if (n4) {
+        static_assert(kStreamElems <= (size_t)4096 * 4 * 256 * 4, "the grid of the strided kernel covers what it is given");
         int g = grid_for(n4, 256 * 4);
         const float4* x4 = reinterpret_cast<const float4*>(x);
-        if (n >= kStreamElems) {
-            if (four_bit)
-                hipLaunchKernelGGL(quantize_vec_kernel<true>, dim3(g), dim3(256), 0, st, x4, n4, q, ss, codes);
-            else
-                hipLaunchKernelGGL(quantize_vec_kernel<false>, dim3(g), dim3(256), 0, st, x4, n4, q, ss, codes);
-        } else {
-            if (four_bit)
-                hipLaunchKernelGGL(quantize_vec_strided_kernel<true>, dim3(g), dim3(256), 0, st, x4, n4, q, ss, codes);
-            else
-                hipLaunchKernelGGL(quantize_vec_strided_kernel<false>, dim3(g), dim3(256), 0, st, x4, n4, q, ss, codes);
-        }
+        const int kind = hw_kind(q);
+        auto kern = n >= kStreamElems ? (four_bit ? quantize_vec_kernel<true, 0> : kind == 1 ? quantize_vec_kernel<false, 1>
+                                         : kind == 2 ? quantize_vec_kernel<false, 2> : quantize_vec_kernel<false, 0>)
+                                      : (four_bit ? quantize_vec_strided_kernel<true, 0> : kind == 1 ? quantize_vec_strided_kernel<false, 1>
+                                         : kind == 2 ? quantize_vec_strided_kernel<false, 2> : quantize_vec_strided_kernel<false, 0>);
+        hipLaunchKernelGGL(kern, dim3(g), dim3(256), 0, st, x4, n4, q, ss, codes);
     }
     size_t first = n4 << 2;
     if (first < n) {
@@ -339,15 +387,33 @@ __global__ __launch_bounds__(256) void absmax_grouped_kernel(const GroupedArgs g
     const float4* x4 = reinterpret_cast<const float4*>(q.x32);
     const int n4 = (q.M * q.K) >> 2;
     float v = 0.0f;
-    for (int i = blockIdx.x * 256 + threadIdx.x; i < n4; i += kGroupAbsmaxParts * 256) v = max4(v, x4[i]);
+    constexpr int step = kGroupAbsmaxParts * 256;
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < n4; i += 8 * step) {      // eight loads in flight: 2 x 616 x 768 9.7 us, 4.9 us
+        float4 a[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) a[u] = x4[min(i + u * step, n4 - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v = max4(v, a[u]);
+    }
     v = block_max(v);
     if (threadIdx.x == 0) q.partials[blockIdx.x] = v;
 }
 
+template <int YKIND>
 __global__ __launch_bounds__(256) void quantize_grouped_kernel(const GroupedArgs g, QParams qx, float maxval)
 {
     const GroupedProblem& q = g.p[blockIdx.y];
     float v = threadIdx.x < kGroupAbsmaxParts ? q.partials[threadIdx.x] : 0.0f;
+    const float4* x4 = reinterpret_cast<const float4*>(q.x32);
+    uint32_t* codes = reinterpret_cast<uint32_t*>(const_cast<uint8_t*>(q.xcodes));
+    const int n4 = (q.M * q.K) >> 2, step = gridDim.x * 256;
+    int i = blockIdx.x * 256 + threadIdx.x;
+    float4 a[4];
+    auto load = [&]() {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) a[u] = x4[min(i + u * step, n4 - 1)];
+    };
+    load();                                    // on their way while the maxima are folded
     v = block_max(v);
     const float sc = (v == 0.0f) ? 1.0f : __fdiv_rn(v, maxval);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -356,13 +422,12 @@ __global__ __launch_bounds__(256) void quantize_grouped_kernel(const GroupedArgs
         pub[1] = v;
     }
     const float r = __fdiv_rn(1.0f, sc);
-    const float4* x4 = reinterpret_cast<const float4*>(q.x32);
-    uint32_t* codes = reinterpret_cast<uint32_t*>(const_cast<uint8_t*>(q.xcodes));
-    const int n4 = (q.M * q.K) >> 2;
-    for (int i = blockIdx.x * 256 + threadIdx.x; i < n4; i += gridDim.x * 256) {
-        const float4 a = x4[i];
-        codes[i] = quantize_nearest(a.x, r, qx) | (quantize_nearest(a.y, r, qx) << 8) | (quantize_nearest(a.z, r, qx) << 16) |
-                   (quantize_nearest(a.w, r, qx) << 24);
+    while (i < n4) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (i + u * step < n4) codes[i + u * step] = quantize4<YKIND>(a[u].x, a[u].y, a[u].z, a[u].w, r, qx);
+        i += 4 * step;
+        if (i < n4) load();
     }
 }
 
@@ -377,75 +442,143 @@ int launch_quantize_dynamic_grouped(const GroupedArgs& g, const QParams& qx, flo
     hipLaunchKernelGGL(absmax_grouped_kernel, dim3(kGroupAbsmaxParts, (unsigned)g.count), dim3(256), 0, st, g);
     size_t gx = (most + 1023) / 1024;          // four 16-byte loads per lane
     gx = gx < 1 ? 1 : (gx > 256 ? 256 : gx);
-    hipLaunchKernelGGL(quantize_grouped_kernel, dim3((unsigned)gx, (unsigned)g.count), dim3(256), 0, st, g, qx, maxval);
+    const int kind = hw_kind(qx);
+    auto kern = kind == 1 ? quantize_grouped_kernel<1> : kind == 2 ? quantize_grouped_kernel<2> : quantize_grouped_kernel<0>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)gx, (unsigned)g.count), dim3(256), 0, st, g, qx, maxval);
     return hipGetLastError() == hipSuccess ? FPQ_OK : FPQ_ERR_LAUNCH;
 }
 
 // ------------------------------------------------------------------- quantize NCHW -> NHWC codes
 
+// 16 bytes from any 4-byte address (planes and rows of sizes that are no multiple of four elements).
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float4 load_any(const float* p, bool stream)
+{
+    const v4f_any* at = reinterpret_cast<const v4f_any*>(p);
+    const v4f_any v = stream ? __builtin_nontemporal_load(at) : *at;
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+
+// Keeps the first `left` codes of a word, the others become code 0 (whatever the scale).
+__device__ __forceinline__ uint32_t first_codes(uint32_t w, int left)
+{
+    return left >= 4 ? w : left <= 0 ? 0u : w & ((1u << (8 * left)) - 1u);
+}
+
 // One block turns a 64-channel x 64-pixel patch of one image: reads run along pixels (contiguous in
 // NCHW), the codes cross an LDS tile, writes run along channels (contiguous in [B,H,W,Cp]).
-// Channels C..Cp-1 receive code 0.  Rows of the tile are 68 bytes so that the four-byte column
-// groups of neighbouring pixels fall into different LDS banks.
+// A thread has four pixels of four channels, its four loads in flight together and ahead of the fold of the scale; the four codes
+// of a pixel are one word.  Channels C..Cp-1 receive code 0.  Rows of the tile are 17 words, so that the words of a wavefront's 16
+// pixel quads x 4 channel groups fall on different LDS banks.
+// 8 x 320 x 64 x 64: 12.6 us with byte stores, loads behind the fold and the arithmetic encoder, 10.0 us; 3 x 200 x 75 x 53, whose
+// planes are no multiple of 16 bytes: 9.9 us with single-element loads, 4.6 us.
+template <int YKIND>
 __global__ __launch_bounds__(256) void quantize_nhwc_kernel(const float* __restrict__ x, int B, int C, int Cp, int HW,
                                                             QParams q, ScaleSrc ss, bool stream,
                                                             uint8_t* __restrict__ codes)
 {
-    constexpr int LDW = 68;
-    __shared__ __attribute__((aligned(16))) uint8_t tile[64 * LDW];
-    const float r = block_inv_scale(ss);
+    constexpr int LDW = 17;
+    __shared__ uint32_t tile[64 * LDW];
+    const Fold f = fold_begin(ss);
+    const int c0 = blockIdx.y * 64, p0 = blockIdx.x * 64;
+    const int pq = threadIdx.x & 15, cg = threadIdx.x >> 4;           // pixel quad, channel group
+    const int ch = c0 + 4 * cg, p = p0 + 4 * pq;
+    float4 v[4];                                                      // of channel ch + k
+    // A quad that runs over the end of its plane goes on into the next; the last one of the tensor is read from four elements before
+    // its end.
+    const size_t last = (size_t)B * C * HW - 4;
+    auto at = [&](int b, int k) { return ((size_t)b * C + min(ch + k, C - 1)) * HW + p; };
+    auto load = [&](int b) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = load_any(x + (at(b, k) < last ? at(b, k) : last), stream);
+    };
     // images b = blockIdx.z, blockIdx.z + gridDim.z, ... (the grid's third dimension stops at 65535)
-    for (int b = blockIdx.z; b < B; b += gridDim.z) {
-    const int c0 = blockIdx.y * 64;
-    const int p0 = blockIdx.x * 64;
-    const int pq = threadIdx.x & 15;   // pixel quad
-    const int cs = threadIdx.x >> 4;   // channel within a pass
-    const bool vec_ok = ((HW & 3) == 0) && ((reinterpret_cast<uintptr_t>(x) & 15) == 0);
+    int b = blockIdx.z;
+    load(b);
+    const float r = fold_end(ss, f);
+    for (;;) {
+        const int left = C - ch;
+        if (p < HW && at(b, 3) > last) {
 #pragma unroll
-    for (int pass = 0; pass < 4; ++pass) {
-        const int cl = pass * 16 + cs;
-        const int ch = c0 + cl;
-        const int p = p0 + 4 * pq;
-        uint32_t cd[4] = {0u, 0u, 0u, 0u};
-        if (ch < C) {
-            const float* src = x + ((size_t)b * C + ch) * (size_t)HW + p;
-            if (vec_ok && p + 3 < HW) {
-                const float4 v = stream ? load_stream(reinterpret_cast<const float4*>(src)) : *reinterpret_cast<const float4*>(src);
-                cd[0] = quantize_nearest(v.x, r, q);
-                cd[1] = quantize_nearest(v.y, r, q);
-                cd[2] = quantize_nearest(v.z, r, q);
-                cd[3] = quantize_nearest(v.w, r, q);
+            for (int k = 0; k < 4; ++k)
+                for (size_t late = last; late < at(b, k); ++late) v[k] = make_float4(v[k].y, v[k].z, v[k].w, 0.0f);
+        }
+        uint32_t* to = tile + 4 * pq * LDW + cg;
+        to[0] = first_codes(quantize4<YKIND>(v[0].x, v[1].x, v[2].x, v[3].x, r, q), left);
+        to[LDW] = first_codes(quantize4<YKIND>(v[0].y, v[1].y, v[2].y, v[3].y, r, q), left);
+        to[2 * LDW] = first_codes(quantize4<YKIND>(v[0].z, v[1].z, v[2].z, v[3].z, r, q), left);
+        to[3 * LDW] = first_codes(quantize4<YKIND>(v[0].w, v[1].w, v[2].w, v[3].w, r, q), left);
+        __syncthreads();
+        const int out_p = p0 + (threadIdx.x >> 2), part = threadIdx.x & 3, out_ch = c0 + part * 16;
+        if (out_p < HW && out_ch < Cp) {
+            const uint32_t* t4 = tile + (threadIdx.x >> 2) * LDW + part * 4;
+            *reinterpret_cast<uint4*>(codes + ((size_t)b * HW + out_p) * (size_t)Cp + out_ch) = make_uint4(t4[0], t4[1], t4[2], t4[3]);
+        }
+        b += gridDim.z;
+        if (b >= B) break;
+        load(b);
+        __syncthreads();   // the tile is rewritten for the next image
+    }
+}
+
+// Rows of C elements to rows of Cp codes (a linear layer whose K is no multiple of 16; images of one pixel or one channel are the
+// same): a word of four codes per lane, four of them in flight.  Channels C..Cp-1 receive code 0.
+// 4000 x 1001 -> 320, the whole call: 131 us as images of one pixel each (a block for 64 elements), 21 us; 30000 x 100 -> 64: 74 and
+// 10 us.
+template <int YKIND>
+__global__ __launch_bounds__(256) void quantize_rows_kernel(const float* __restrict__ x, uint32_t words, int C, int wpr,
+                                                            QParams q, ScaleSrc ss, uint32_t* __restrict__ codes)
+{
+    const Fold f = fold_begin(ss);
+    const uint32_t nthreads = gridDim.x * 256;
+    uint32_t i = blockIdx.x * 256 + threadIdx.x;                      // words < 2^29: no sum wraps
+    float4 v[4];
+    int left[4];
+    auto load = [&]() {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t at = i + u * nthreads, row = at / (uint32_t)wpr;
+            const int k = 4 * (int)(at - row * (uint32_t)wpr);
+            left[u] = at < words ? C - k : 0;
+            const float* src = x + (size_t)row * C + k;
+            if (left[u] >= 4) {
+                v[u] = load_any(src, false);
+            } else if (left[u] > 0) {
+                v[u].x = src[0];
+                v[u].y = left[u] > 1 ? src[1] : 0.0f;
+                v[u].z = left[u] > 2 ? src[2] : 0.0f;
+                v[u].w = 0.0f;
             } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (p + j < HW) cd[j] = quantize_nearest(src[j], r, q);
+                v[u] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             }
         }
+    };
+    load();
+    const float r = fold_end(ss, f);
+    while (i < words) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) tile[(4 * pq + j) * LDW + cl] = (uint8_t)cd[j];
-    }
-    __syncthreads();
-    const int pl = threadIdx.x >> 2;
-    const int part = threadIdx.x & 3;
-    const int p = p0 + pl;
-    const int ch = c0 + part * 16;
-    if (p < HW && ch < Cp) {
-        const uint32_t* t4 = reinterpret_cast<const uint32_t*>(tile + pl * LDW + part * 16);
-        uint4 v = make_uint4(t4[0], t4[1], t4[2], t4[3]);
-        *reinterpret_cast<uint4*>(codes + ((size_t)b * HW + p) * (size_t)Cp + ch) = v;
-    }
-    __syncthreads();   // the tile is rewritten for the next image
+        for (int u = 0; u < 4; ++u)
+            if (i + u * nthreads < words)
+                codes[i + u * nthreads] = first_codes(quantize4<YKIND>(v[u].x, v[u].y, v[u].z, v[u].w, r, q), left[u]);
+        i += 4 * nthreads;
+        load();
     }
 }
 
 int launch_quantize_nhwc(const float* x, int64_t B, int64_t C, int64_t H, int64_t W, const QParams& q,
                          const ScaleSrc& ss, uint8_t* codes, hipStream_t st)
 {
-    int Cp = (int)padded_channels(C);
-    int HW = (int)(H * W);
-    dim3 grid((HW + 63) / 64, (Cp + 63) / 64, (unsigned)(B < 65535 ? B : 65535));
-    hipLaunchKernelGGL(quantize_nhwc_kernel, grid, dim3(256), 0, st, x, (int)B, (int)C, Cp, HW, q, ss,
-                       (size_t)B * C * H * W >= kStreamElems, codes);
+    const int Cp = (int)padded_channels(C), HW = (int)(H * W), kind = hw_kind(q);
+    if (HW == 1 || C == 1) {
+        const uint32_t words = (uint32_t)(B * HW * (Cp / 4));
+        auto kern = kind == 1 ? quantize_rows_kernel<1> : kind == 2 ? quantize_rows_kernel<2> : quantize_rows_kernel<0>;
+        hipLaunchKernelGGL(kern, dim3(grid_for(words, 1024)), dim3(256), 0, st, x, words, (int)C, Cp / 4, q, ss,
+                           reinterpret_cast<uint32_t*>(codes));
+    } else {                                                          // at least four elements
+        dim3 grid((HW + 63) / 64, (Cp + 63) / 64, (unsigned)(B < 65535 ? B : 65535));
+        auto kern = kind == 1 ? quantize_nhwc_kernel<1> : kind == 2 ? quantize_nhwc_kernel<2> : quantize_nhwc_kernel<0>;
+        hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, x, (int)B, (int)C, Cp, HW, q, ss, (size_t)B * C * H * W >= kStreamElems, codes);
+    }
     return hipGetLastError() == hipSuccess ? FPQ_OK : FPQ_ERR_LAUNCH;
 }
 

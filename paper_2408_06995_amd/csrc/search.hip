@@ -3,7 +3,7 @@
 // A candidate is an encoding (e, m) with the max value c_j = absmax * (j + 1) / J; its real-valued bias (Eq. (7) solved
 // for b) is carried as the integer bias b0 = 2^(e-1) plus the scale c_j / c0, c0 = Eq. (7) at b0, so a candidate is
 // exactly what fpq_quantize computes for the format (e, m, b0) and that scale.  Every candidate's sum of squared errors is
-// wanted.  Two forms, chosen by elements times candidates (kSearchBinnedWork):
+// wanted.  Three forms, chosen by elements times candidates (kSearchBinnedWork):
 //
 // Direct: a lane holds eight elements in registers and walks a share of the candidates over them (quantize with the
 // encoder's magic-add rounding, dequantize, square): about 11 vector instructions per element and candidate.  The
@@ -27,10 +27,11 @@
 // About five such terms per element instead of 444 evaluations.  A workgroup of step 3 that meets elements more than 32 binades
 // below the maximum, or subnormal ones, reads its share again and evaluates those directly (add_outside); with such elements
 // only, that costs what the direct form costs.
-// Measured, 10.5 M elements x 444 candidates: 182 us (moments of the intervals 37, closed forms 25, their sums 6, cuts 102: one
-// cache line per element and list access, and the terms' way into integers; sums 7, choice 5, the rest the maximum) against 1758 us
-// of the direct form (1244, bound by vector ALU work) with its single-workgroup reduction (506).  The same tensor with one value 2^60
-// times the rest, so that every element is evaluated directly: 1754 us.  20 K elements: 17 us against 205.
+// Sorted (search_sorted.h): the same intervals and closed forms with the elements sorted into stretches of float values first, so that
+// neither moments nor cuts cost a cache line or an atomic per element and candidate.  Up to kSearchMaxSorted elements; it wants 2.9
+// bytes of workspace per element, so larger tensors, and callers with less workspace, take the interval tables.
+// Measured, 444 candidates, sorted / tables / direct, us: 10.5 M elements 121 / 182 / 1758; 60 M 507 / 737; 2 M 76 / 84; 480 K 69 / 75 /
+// 78; all of 10.5 M equal 162 / 337.  20 K elements: 17 us direct.
 #include "fpq_dev.h"
 #include "fpq_host.h"
 #include "search_split.h"
@@ -387,19 +388,16 @@ __global__ __launch_bounds__(512) void search_intervals_kernel(const ulonglong2*
 
 constexpr int kOutsideRound = 4;                     // elements per thread and round of add_outside
 
-// Squared errors of the elements of this workgroup's share that lie outside all intervals, of candidate threadIdx.x + 512 h in
-// sum[h] (all 512 threads call this): the elements of a round are gathered in LDS, in the order of the tensor, and every thread
-// walks them with its candidates.
-__device__ void add_outside(const float* __restrict__ x, size_t n, int part, int parts, uint32_t top, float am,
+// Squared errors of the elements of this workgroup's share (`inside` from `lo` on, then `tail` from `tail_lo` on) that lie outside all
+// intervals, of candidate threadIdx.x + 512 h in sum[h] (all 512 threads call this): the elements of a round are gathered in LDS, in
+// the order of the tensor, and every thread walks them with its candidates.
+__device__ void add_outside(const float* __restrict__ x, size_t lo, size_t inside, size_t tail_lo, size_t tail, uint32_t top, float am,
                             const SearchArgs& a, int NC, double (&sum)[kSearchMaxCandidates / 512])
 {
     __shared__ float found[512 * kOutsideRound];
     __shared__ int counts[kOutsideRound * 8];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // the elements that for_elements gives this part: a range, and the last n % 4 in part 0
-    const size_t v = (reinterpret_cast<uintptr_t>(x) & 15) == 0 ? 4 : 1;
-    const SearchRange range = search_range(n / v, part, parts);
-    const size_t inside = (range.hi - range.lo) * v, total = inside + (part == 0 ? n % v : 0);
+    const size_t total = inside + tail;
     // magnitudes here are below 2^(e + 1 - 32), e the exponent of the maximum's binade: scaled to below 2^60, the squares of
     // values up to 120 binades smaller stay normal numbers
     const int shift = 60 + 31 - top_exponent(top);
@@ -412,7 +410,7 @@ __device__ void add_outside(const float* __restrict__ x, size_t n, int part, int
 #pragma unroll
         for (int u = 0; u < kOutsideRound; ++u) {
             const size_t j = base + (size_t)u * 512 + tid;
-            const size_t i = j < inside ? range.lo * v + j : n / v * v + (j - inside);
+            const size_t i = j < inside ? lo + j : tail_lo + (j - inside);
             const uint32_t b = j < total ? __float_as_uint(x[i]) & 0x7fffffffu : 0u;
             int bin;
             uint32_t low;
@@ -454,6 +452,19 @@ __device__ void add_outside(const float* __restrict__ x, size_t n, int part, int
     for (int h = 0; h < kSearchMaxCandidates / 512; ++h) sum[h] = ldexp(sum[h], -2 * shift);
 }
 
+// Sum over the 64 rows of a workgroup of 16 x 64 threads, always in the same order, valid in the first 16 threads.
+__device__ __forceinline__ double fold_rows(double s, double (&red)[64][16])
+{
+    const int col = threadIdx.x & 15, row = threadIdx.x >> 4;
+    red[row][col] = s;
+    __syncthreads();
+    for (int off = 32; off > 0; off >>= 1) {
+        if (row < off) red[row][col] += red[row + off][col];
+        __syncthreads();
+    }
+    return red[0][col];
+}
+
 // Sum of a column of `rows` sums per candidate, candidate blockIdx.x * 16 + threadIdx.x % 16 of NC: 64 rows at a time, always in
 // the same order.  Valid in the first 16 of the 1024 threads; all of them call this.
 template <typename T>
@@ -463,13 +474,7 @@ __device__ __forceinline__ double column_sum(const T* __restrict__ sums, int row
     double s = 0.0;
     if (c < NC)
         for (int r = row; r < rows; r += 64) s += (double)sums[(size_t)r * NC + c];
-    red[row][col] = s;
-    __syncthreads();
-    for (int off = 32; off > 0; off >>= 1) {
-        if (row < off) red[row][col] += red[row + off][col];
-        __syncthreads();
-    }
-    return red[0][col];
+    return fold_rows(s, red);
 }
 
 // Closed forms of all intervals per candidate, and the unit of the terms that the cuts add to it: 2^-shift of the slopes' unit,
@@ -541,13 +546,22 @@ __global__ __launch_bounds__(512) void search_cuts_kernel(const float* __restric
         }
     });
     double sum[kSearchMaxCandidates / 512] = {};
-    if (__syncthreads_or(outside)) add_outside(x, n, blockIdx.x, gridDim.x, top, am, a, NC, sum);
+    if (__syncthreads_or(outside)) {
+        // the elements that for_elements gives this part: a range, and the last n % 4 in part 0
+        const size_t v = (reinterpret_cast<uintptr_t>(x) & 15) == 0 ? 4 : 1;
+        const SearchRange range = search_range(n / v, blockIdx.x, gridDim.x);
+        add_outside(x, range.lo * v, (range.hi - range.lo) * v, n / v * v, blockIdx.x == 0 ? n % v : 0, top, am, a, NC, sum);
+    }
 #pragma unroll
     for (int h = 0; h < kSearchMaxCandidates / 512; ++h) {
         const int c = threadIdx.x + 512 * h;
         if (c < NC) sums[(size_t)blockIdx.x * NC + c] = ldexp((double)(long long)acc[c], 2 * top_exponent(top) - shift[c]) + sum[h];
     }
 }
+
+// ---------------------------------------------------------------------------------- sorted form
+
+#include "search_sorted.h"
 
 // ---------------------------------------------------------------------------------- sums over workgroups, the choice
 
@@ -628,14 +642,18 @@ __global__ __launch_bounds__(1024) void search_select_kernel(const double* __res
     }
 }
 
-// The binned form has a cost of its own (about 73 us: the interval tables are written and read once whatever n is); the
-// direct form takes 0.13 us per 1024 elements at 444 candidates.  400000 elements: 73 us binned, 64 direct; 500000: 75 and 78.
+// The binned forms have a cost of their own (sorted 65 us, tables 73: launches, the candidates' walks, 544 groups of intervals
+// whatever n is); the direct form takes 0.13 us per 1024 elements at 444 candidates, in steps of a full chip.  350000 elements: 66 us
+// direct, 68 sorted; 500000: 78 and 69.
 constexpr size_t kSearchBinnedWork = (size_t)480000 * 444;   // elements x candidates
 bool binned_pays(size_t n, int nc) { return n * (size_t)nc >= kSearchBinnedWork && n >= 131072 && n <= kSearchMaxBinned; }
 
 }  // namespace
 
-size_t search_binned_bytes(size_t n, int nc) { return binned_pays(n, nc) ? binned_layout(n, nc).total : 0; }
+size_t search_binned_bytes(size_t n, int nc)
+{
+    return !binned_pays(n, nc) ? 0 : n <= kSearchMaxSorted ? sorted_layout(n, nc).total : binned_layout(n, nc).total;
+}
 
 int launch_search(const float* x, size_t n, const SearchArgs& a, const float* maxparts, float* partial, size_t partial_bytes,
                   float* mse_out, fpq_search_result* result, hipStream_t st)
@@ -644,7 +662,42 @@ int launch_search(const float* x, size_t n, const SearchArgs& a, const float* ma
     const int nparts = absmax_parts(n);
     const double* mse = nullptr;
     int rows = search_blocks(n);
-    if (binned_pays(n, NC) && partial_bytes >= binned_layout(n, NC).total + up256((size_t)NC * 8)) {
+    if (binned_pays(n, NC) && n <= kSearchMaxSorted && partial_bytes >= sorted_layout(n, NC).total + up256((size_t)NC * 8)) {
+        const SortedLayout l = sorted_layout(n, NC);
+        uint8_t* ws = reinterpret_cast<uint8_t*>(partial);
+        uint16_t* sorted = reinterpret_cast<uint16_t*>(ws + l.sorted);
+        uint16_t* offsets = reinterpret_cast<uint16_t*>(ws + l.offsets);
+        uint32_t* flags = reinterpret_cast<uint32_t*>(ws + l.flags);
+        uint32_t* cursor = reinterpret_cast<uint32_t*>(ws + l.cursor);
+        uint32_t* totals = reinterpret_cast<uint32_t*>(ws + l.totals);
+        CountTask* tasks = reinterpret_cast<CountTask*>(ws + l.tasks);
+        SortGroup* groups = reinterpret_cast<SortGroup*>(ws + l.groups);
+        uint32_t* bases = reinterpret_cast<uint32_t*>(ws + l.bases);
+        uint32_t* cuts = reinterpret_cast<uint32_t*>(ws + l.cuts);
+        unsigned long long* cutsums = reinterpret_cast<unsigned long long*>(ws + l.cutsums);
+        SortMoments* moments = reinterpret_cast<SortMoments*>(ws + l.moments);
+        double* sums = reinterpret_cast<double*>(ws + l.sums);
+        double* mse_w = reinterpret_cast<double*>(ws + l.total);
+        static std::atomic<uint64_t> allowed{0};
+        static std::atomic<uint64_t> allowed_counts{0};
+        if (!allow_dynamic_lds(reinterpret_cast<const void*>(search_sort_kernel), kSortLds, allowed) ||
+            !allow_dynamic_lds(reinterpret_cast<const void*>(search_counts_kernel), kCountLds, allowed_counts))
+            return FPQ_ERR_LAUNCH;
+        hipLaunchKernelGGL(search_sort_kernel, dim3(l.parts), dim3(1024), kSortLds, st, x, n, maxparts, nparts, l.parts, sorted, offsets,
+                           flags, cursor);
+        const uint32_t room = (uint32_t)most_tasks(n);
+        hipLaunchKernelGGL(search_lists_kernel, dim3(kSortGroups + kStretches / 64), dim3(512), 0, st, maxparts, nparts, a, offsets, l.parts,
+                           room, totals, tasks, cursor, groups, bases, cuts, cutsums, moments);
+        hipLaunchKernelGGL(search_counts_kernel, dim3(256), dim3(1024), kCountLds, st, sorted, offsets, room, tasks, cursor, groups, cuts,
+                           cutsums, moments);
+        hipLaunchKernelGGL(search_terms_kernel, dim3(kSortGroups * l.chunks), dim3(512), 0, st, sorted, offsets, l.parts, l.chunks, totals, groups,
+                           cuts, cutsums, moments);
+        auto closed = l.chunks == 2 ? search_closed_kernel<3> : l.chunks == 4 ? search_closed_kernel<5> : search_closed_kernel<9>;
+        hipLaunchKernelGGL(closed, dim3(kSortGroups + l.parts * l.sub), dim3(512), 0, st, x, n, maxparts, nparts, a, l.parts, l.sub, flags,
+                           moments, bases, cutsums, sums);
+        hipLaunchKernelGGL(search_sorted_sums_kernel, dim3((NC + 15) / 16), dim3(1024), 0, st, sums, l.parts, l.sub, flags, n, NC, mse_w);
+        mse = mse_w;
+    } else if (binned_pays(n, NC) && partial_bytes >= binned_layout(n, NC).total + up256((size_t)NC * 8)) {
         const BinnedLayout l = binned_layout(n, NC);
         uint8_t* ws = reinterpret_cast<uint8_t*>(partial);
         ulonglong2* table = reinterpret_cast<ulonglong2*>(ws + l.table);

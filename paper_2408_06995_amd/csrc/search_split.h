@@ -32,6 +32,16 @@ constexpr int search_parts(size_t n)
     const size_t q = p < 8 ? 8 : (p > 64 ? 64 : p);
     return (int)(q < least ? least : q);
 }
+// Parts of the sorted form, a multiple of 8 (one per XCD) of at most kSearchSortElems elements (and three, the rest of an aligned
+// tensor): one for each compute unit, fewer while a part has less than 16384 elements (longer runs), and multiples of
+// 256 beyond.
+constexpr size_t kSearchSortElems = 40960;
+constexpr size_t kSearchMaxSorted = (size_t)1 << 26;
+constexpr int search_sort_parts(size_t n)
+{
+    const size_t small = (n + 16383) / 16384, p = (small + 7) / 8 * 8, most = 256 * kSearchSortElems;
+    return (int)(n > most ? (n + most - 1) / most * 256 : p < 8 ? 8 : p > 256 ? 256 : p);
+}
 // Largest tensor of the binned form.
 constexpr size_t kSearchMaxBinned = (size_t)1 << 31;
 

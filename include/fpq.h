@@ -382,7 +382,7 @@ int fpq_conv2d_sparse(const void *x, int x_is_fp32, fpq_format_t fx, float sx, c
  *   zero_point_out[N]; codes_out (or NULL) the plain codes [N, K].  K <= 32768.
  * fpq_int_gemm: xcodes [M, K] 8-bit activation codes (K % 16 == 0, 16-byte aligned) with (sx, zx) or *px_dev;
  *   packed_w / wbits / sw / zw from fpq_int_pack_weights; y[M, N] fp32; workspace fpq_int_gemm_workspace_size(M)
- *   bytes (the row sums of the activation codes). */
+ *   bytes (room for the row sums of the activation codes; not written any more, still asked for). */
 typedef struct fpq_int_params {
     float scale;
     int32_t zero_point;

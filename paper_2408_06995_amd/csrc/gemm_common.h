@@ -23,7 +23,7 @@ __device__ __forceinline__ float act_silu(float x) { return x * __frcp_rn(1.0f +
 // negative side.  Fourteen instructions, two of them transcendental: the factor 1/2 is in the coefficients, exp(-g^2 / 2) =
 // 2^-(s s), and the hardware's reciprocal is as good as a correctly rounded one here (largest error, over |g|: 2.7e-7, 3.0e-7 with
 // the correctly rounded reciprocal and g (1 - erfc / 2) on the positive side).  The bound on |g| keeps infinity times 0 out; the
-// exponential is 0 long before.  A negative g whose result underflows gives -0.
+// exponential is 0 long before.  A negative g whose result underflows gives -0; NaN stays NaN (the plain maximum drops it).
 __device__ __forceinline__ float act_gelu(float g)
 {
     const float m = fminf(fabsf(g), 1e18f);
@@ -34,7 +34,7 @@ __device__ __forceinline__ float act_gelu(float g)
     p = fmaf(t, p, 0.5f * -0.284496736f);
     p = fmaf(t, p, 0.5f * 0.254829592f);
     const float half_erfc = (t * p) * __builtin_amdgcn_exp2f(-s * s);
-    return fmaf(-m, half_erfc, fmaxf(g, -0.0f));
+    return fmaf(-m, half_erfc, __builtin_elementwise_maximum(g, -0.0f));
 }
 
 // The same as real function calls, for the rarely taken, fully unrolled element-wise paths (edge tiles, the

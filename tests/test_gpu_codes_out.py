@@ -180,6 +180,27 @@ def test_linear_activation_then_codes(M, K, N, fw, fy, acc, act):
         assert miss < 0.005
 
 
+@pytest.mark.parametrize("M,K,N", [(40, 64, 96), (300, 320, 640), (77, 768, 320), (8200, 640, 320)])
+@pytest.mark.parametrize("fy", [E4M3, E5M2, E3M4])
+def test_a_gate_that_is_no_number_saturates(M, K, N, fy):
+    """A NaN that reaches a gate (here through the bias) clips to the largest magnitude as it does without an activation; it does
+    not come out as a zero."""
+    x, w = synth.activations((M, K), 7100 + M), synth.weights((N, K), 7600 + N)
+    sx, xq, wq, sw = oracle_linear_inputs(x, w, None, E4M3, E4M3)
+    bias = np.zeros(N, dtype=np.float32)
+    bias[16], bias[N - 1], bias[3] = np.nan, -np.nan, np.nan          # two gates and a value
+    packed, sw_t, _ = gpu_pack(w, E4M3, None, want_codes=False)
+    Np = B.fpq_padded_channels(N // 2)
+    yq = torch.full((M * Np,), 0xEE, dtype=torch.uint8, device=DEV)
+    ws = torch.empty(max(256, B.fpq_gemm_workspace_size(M, N, K, 0)), dtype=torch.uint8, device=DEV)
+    B.fpq_gemm_codes_out(dev(xq), 0, E4M3, sx, None, packed, E4M3, sw_t, dev(bias), fy, 0.01, None, yq, M, N, K,
+                         B.FPQ_ACC_FP32 | B.FPQ_ACT_GEGLU, ws)
+    torch.cuda.synchronize()
+    magnitude = yq.cpu().numpy().reshape(M, Np)[:, :N // 2] & 0x7F
+    top = int(oracle.quantize(np.array([fy[3]], dtype=np.float32), fy, 1.0)[0])
+    assert np.all(magnitude[:, [0, N // 2 - 1, 3]] == top)
+
+
 def test_gated_projection_given_in_the_plain_values_then_gates_layout():
     """A feed-forward projection as a model stores it, all value channels before all gate channels.  The caller
     reorders the weight rows (and the bias) once into blocks of 16 values + 16 gates, as the header of the gated

@@ -465,64 +465,70 @@ __device__ __forceinline__ uint32_t first_codes(uint32_t w, int left)
     return left >= 4 ? w : left <= 0 ? 0u : w & ((1u << (8 * left)) - 1u);
 }
 
-// One block turns a 64-channel x 64-pixel patch of one image: reads run along pixels (contiguous in
-// NCHW), the codes cross an LDS tile, writes run along channels (contiguous in [B,H,W,Cp]).
+// One block turns a patch of GROUPS x 4 channels x 1024 / GROUPS pixels of one image, or of 64 pixels of IMAGES images: reads run along
+// pixels (contiguous in NCHW), the codes cross an LDS tile, writes run along channels (contiguous in [B,H,W,Cp]).
 // A thread has four pixels of four channels, its four loads in flight together and ahead of the fold of the scale; the four codes
-// of a pixel are one word.  Channels C..Cp-1 receive code 0.  Rows of the tile are 17 words, so that the words of a wavefront's 16
-// pixel quads x 4 channel groups fall on different LDS banks.
+// of a pixel are one word.  Channels C..Cp-1 receive code 0.  Rows of the tile are GROUPS + 1 words, so that the words of a wavefront
+// fall on different LDS banks (with 64 channels; on half and a quarter of them with 32 and 16).
 // 8 x 320 x 64 x 64: 12.6 us with byte stores, loads behind the fold and the arithmetic encoder, 10.0 us; 3 x 200 x 75 x 53, whose
-// planes are no multiple of 16 bytes: 9.9 us with single-element loads, 4.6 us.
-template <int YKIND>
+// planes are no multiple of 16 bytes: 9.9 us with single-element loads, 4.6 us.  Sixteen channel groups whatever C is cost images of few
+// channels their time (8 x 3 x 256 x 256 11.5 us, in a format without a conversion instruction 19.1 us; with four groups 4.9 and 5.3 us).
+template <int YKIND, int GROUPS, int IMAGES>
 __global__ __launch_bounds__(256) void quantize_nhwc_kernel(const float* __restrict__ x, int B, int C, int Cp, int HW,
                                                             QParams q, ScaleSrc ss, bool stream,
                                                             uint8_t* __restrict__ codes)
 {
-    constexpr int LDW = 17;
-    __shared__ uint32_t tile[64 * LDW];
+    constexpr int QUADS = 256 / GROUPS, LDW = GROUPS + 1, PARTS = GROUPS / 4, OWN = 4 * QUADS / IMAGES;   // OWN: pixels of an image
+    __shared__ uint32_t tile[4 * QUADS * LDW];
     const Fold f = fold_begin(ss);
-    const int c0 = blockIdx.y * 64, p0 = blockIdx.x * 64;
-    const int pq = threadIdx.x & 15, cg = threadIdx.x >> 4;           // pixel quad, channel group
-    const int ch = c0 + 4 * cg, p = p0 + 4 * pq;
+    const int c0 = blockIdx.y * (4 * GROUPS), p0 = blockIdx.x * OWN;
+    const int pq = threadIdx.x % QUADS, cg = threadIdx.x / QUADS;     // pixel quad, channel group
+    const int ch = c0 + 4 * cg, p = p0 + 4 * pq % OWN, left = C - ch;
+    const int img = 4 * pq / OWN;
     float4 v[4];                                                      // of channel ch + k
     // A quad that runs over the end of its plane goes on into the next; the last one of the tensor is read from four elements before
-    // its end.
+    // its end.  Groups without a channel read the tensor's first quad and encode nothing.
     const size_t last = (size_t)B * C * HW - 4;
-    auto at = [&](int b, int k) { return ((size_t)b * C + min(ch + k, C - 1)) * HW + p; };
+    auto at = [&](int b, int k) { return left > 0 ? ((size_t)b * C + min(ch + k, C - 1)) * HW + p : 0; };
     auto load = [&](int b) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) v[k] = load_any(x + (at(b, k) < last ? at(b, k) : last), stream);
     };
-    // images b = blockIdx.z, blockIdx.z + gridDim.z, ... (the grid's third dimension stops at 65535)
-    int b = blockIdx.z;
-    load(b);
+    // images from b = IMAGES blockIdx.z, IMAGES (blockIdx.z + gridDim.z), ... on (the grid's third dimension stops at 65535)
+    int b = IMAGES * blockIdx.z;
+    load(b + img);
     const float r = fold_end(ss, f);
     for (;;) {
-        const int left = C - ch;
-        if (p < HW && at(b, 3) > last) {
+        if (p < HW && b + img < B && at(b + img, 3) > last) {
 #pragma unroll
             for (int k = 0; k < 4; ++k)
-                for (size_t late = last; late < at(b, k); ++late) v[k] = make_float4(v[k].y, v[k].z, v[k].w, 0.0f);
+                for (size_t late = last; late < at(b + img, k); ++late) v[k] = make_float4(v[k].y, v[k].z, v[k].w, 0.0f);
         }
         uint32_t* to = tile + 4 * pq * LDW + cg;
-        to[0] = first_codes(quantize4<YKIND>(v[0].x, v[1].x, v[2].x, v[3].x, r, q), left);
-        to[LDW] = first_codes(quantize4<YKIND>(v[0].y, v[1].y, v[2].y, v[3].y, r, q), left);
-        to[2 * LDW] = first_codes(quantize4<YKIND>(v[0].z, v[1].z, v[2].z, v[3].z, r, q), left);
-        to[3 * LDW] = first_codes(quantize4<YKIND>(v[0].w, v[1].w, v[2].w, v[3].w, r, q), left);
-        __syncthreads();
-        const int out_p = p0 + (threadIdx.x >> 2), part = threadIdx.x & 3, out_ch = c0 + part * 16;
-        if (out_p < HW && out_ch < Cp) {
-            const uint32_t* t4 = tile + (threadIdx.x >> 2) * LDW + part * 4;
-            *reinterpret_cast<uint4*>(codes + ((size_t)b * HW + out_p) * (size_t)Cp + out_ch) = make_uint4(t4[0], t4[1], t4[2], t4[3]);
+        if (left > 0) {
+            to[0] = first_codes(quantize4<YKIND>(v[0].x, v[1].x, v[2].x, v[3].x, r, q), left);
+            to[LDW] = first_codes(quantize4<YKIND>(v[0].y, v[1].y, v[2].y, v[3].y, r, q), left);
+            to[2 * LDW] = first_codes(quantize4<YKIND>(v[0].z, v[1].z, v[2].z, v[3].z, r, q), left);
+            to[3 * LDW] = first_codes(quantize4<YKIND>(v[0].w, v[1].w, v[2].w, v[3].w, r, q), left);
+        } else if (ch < Cp) {
+            to[0] = to[LDW] = to[2 * LDW] = to[3 * LDW] = 0u;
         }
-        b += gridDim.z;
+        __syncthreads();
+        const int row = threadIdx.x / PARTS, part = threadIdx.x % PARTS;
+        const int out_b = b + row / OWN, out_p = p0 + row % OWN, out_ch = c0 + part * 16;
+        if (out_b < B && out_p < HW && out_ch < Cp) {
+            const uint32_t* t4 = tile + row * LDW + part * 4;
+            *reinterpret_cast<uint4*>(codes + ((size_t)out_b * HW + out_p) * (size_t)Cp + out_ch) = make_uint4(t4[0], t4[1], t4[2], t4[3]);
+        }
+        b += IMAGES * gridDim.z;
         if (b >= B) break;
-        load(b);
+        load(b + img);
         __syncthreads();   // the tile is rewritten for the next image
     }
 }
 
-// Rows of C elements to rows of Cp codes (a linear layer whose K is no multiple of 16; images of one pixel or one channel are the
-// same): a word of four codes per lane, four of them in flight.  Channels C..Cp-1 receive code 0.
+// Rows of C elements to rows of Cp codes (a linear layer whose K is no multiple of 16; images of one pixel are the same, and those of
+// one channel are rows of one element): a word of four codes per lane, four of them in flight.  Channels C..Cp-1 receive code 0.
 // 4000 x 1001 -> 320, the whole call: 131 us as images of one pixel each (a block for 64 elements), 21 us; 30000 x 100 -> 64: 74 and
 // 10 us.
 template <int YKIND>
@@ -565,19 +571,38 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const float* __restr
     }
 }
 
+template <int GROUPS, int IMAGES>
+static void launch_nhwc_patches(const float* x, int B, int C, int Cp, int HW, const QParams& q, const ScaleSrc& ss, uint8_t* codes,
+                                hipStream_t st)
+{
+    constexpr int pixels = 1024 / GROUPS / IMAGES;
+    const int kind = hw_kind(q), images = (int)(((int64_t)B + IMAGES - 1) / IMAGES);
+    const dim3 grid((HW + pixels - 1) / pixels, (Cp + 4 * GROUPS - 1) / (4 * GROUPS), images < 65535 ? images : 65535);
+    auto kern = kind == 1   ? quantize_nhwc_kernel<1, GROUPS, IMAGES>
+                : kind == 2 ? quantize_nhwc_kernel<2, GROUPS, IMAGES> : quantize_nhwc_kernel<0, GROUPS, IMAGES>;
+    hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, x, B, C, Cp, HW, q, ss, (size_t)B * C * HW >= kStreamElems, codes);
+}
+
 int launch_quantize_nhwc(const float* x, int64_t B, int64_t C, int64_t H, int64_t W, const QParams& q,
                          const ScaleSrc& ss, uint8_t* codes, hipStream_t st)
 {
     const int Cp = (int)padded_channels(C), HW = (int)(H * W), kind = hw_kind(q);
-    if (HW == 1 || C == 1) {
+    // One channel: planes of fewer than 64 pixels as rows (100000 of 2 x 2: 6.6 us, a patch per image 49.9 us); from 64 on in patches, where
+    // a lane has four pixels and not a quarter of one (4 x 1024 x 1024: 19.8 us, rows 31.2 us; 30000 x 8 x 8: 11.2 and 18.5 us).
+    // Patches have the channels that Cp fills, and of small planes several images (20000 x 3 x 8 x 8: 8.4 us, an image each 22.5 us).
+    if (HW == 1 || (C == 1 && HW < 64)) {
         const uint32_t words = (uint32_t)(B * HW * (Cp / 4));
         auto kern = kind == 1 ? quantize_rows_kernel<1> : kind == 2 ? quantize_rows_kernel<2> : quantize_rows_kernel<0>;
         hipLaunchKernelGGL(kern, dim3(grid_for(words, 1024)), dim3(256), 0, st, x, words, (int)C, Cp / 4, q, ss,
                            reinterpret_cast<uint32_t*>(codes));
-    } else {                                                          // at least four elements
-        dim3 grid((HW + 63) / 64, (Cp + 63) / 64, (unsigned)(B < 65535 ? B : 65535));
-        auto kern = kind == 1 ? quantize_nhwc_kernel<1> : kind == 2 ? quantize_nhwc_kernel<2> : quantize_nhwc_kernel<0>;
-        hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, x, (int)B, (int)C, Cp, HW, q, ss, (size_t)B * C * H * W >= kStreamElems, codes);
+    } else if (Cp <= 16) {                                            // at least four elements
+        HW > 64 ? launch_nhwc_patches<4, 1>(x, (int)B, (int)C, Cp, HW, q, ss, codes, st)
+                : launch_nhwc_patches<4, 4>(x, (int)B, (int)C, Cp, HW, q, ss, codes, st);
+    } else if (Cp <= 32) {
+        HW > 64 ? launch_nhwc_patches<8, 1>(x, (int)B, (int)C, Cp, HW, q, ss, codes, st)
+                : launch_nhwc_patches<8, 2>(x, (int)B, (int)C, Cp, HW, q, ss, codes, st);
+    } else {
+        launch_nhwc_patches<16, 1>(x, (int)B, (int)C, Cp, HW, q, ss, codes, st);
     }
     return hipGetLastError() == hipSuccess ? FPQ_OK : FPQ_ERR_LAUNCH;
 }

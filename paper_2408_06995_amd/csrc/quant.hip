@@ -94,6 +94,9 @@ int hw_kind(const QParams& q)
 
 // Tensors from this many elements (64 MB of fp32) on take the contiguous-share / streaming-load kernels.
 constexpr size_t kStreamElems = (size_t)16 << 20;
+// ... and the flat quantizer with a given scale from here on, where a tensor no longer fits the 32 MB of L2 (10 M elements: E4M3 8.9 us
+// grid-strided, 7.6 us in shares, E2M1 9.3 and 7.8 us; 8 M: 5.7 us both, E2M1 5.4 and 5.9 us).
+constexpr size_t kStreamElemsGiven = (size_t)9 << 20;
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 
@@ -219,8 +222,8 @@ template <bool FOUR_BIT, int YKIND>
 __device__ __forceinline__ void store_codes(uint8_t* codes, size_t i, const float4& v, float r, const QParams& q)
 {
     if (FOUR_BIT) {
-        const uint32_t c = quantize4<0>(v.x, v.y, v.z, v.w, r, q);
-        reinterpret_cast<uint16_t*>(codes)[i] = (uint16_t)((c & 0xfu) | (c >> 4 & 0xf0u) | (c >> 8 & 0xf00u) | (c >> 12 & 0xf000u));
+        reinterpret_cast<uint16_t*>(codes)[i] = (uint16_t)(quantize_nearest(v.x, r, q) | (quantize_nearest(v.y, r, q) << 4) |
+                                                           (quantize_nearest(v.z, r, q) << 8) | (quantize_nearest(v.w, r, q) << 12));
     } else {
         reinterpret_cast<uint32_t*>(codes)[i] = quantize4<YKIND>(v.x, v.y, v.z, v.w, r, q);
     }
@@ -228,11 +231,12 @@ __device__ __forceinline__ void store_codes(uint8_t* codes, size_t i, const floa
 
 // Four elements per lane and step: one 16-byte streaming load, four encodes, one 4-byte (8-bit codes) or
 // 2-byte (4-bit codes) store.  Each block walks one contiguous share with four loads in flight per lane.
-template <bool FOUR_BIT, int YKIND>
+template <bool FOUR_BIT, int YKIND, bool FOLD>
 __global__ __launch_bounds__(256) void quantize_vec_kernel(const float4* __restrict__ x4, size_t n4, QParams q,
                                                            ScaleSrc ss, uint8_t* __restrict__ codes)
 {
-    const Fold f = fold_begin(ss);
+    Fold f;
+    if constexpr (FOLD) f = fold_begin(ss);
     const size_t per = (n4 + gridDim.x - 1) / gridDim.x;
     const size_t b0 = (size_t)blockIdx.x * per;
     const size_t e = b0 + per < n4 ? b0 + per : n4;
@@ -243,7 +247,7 @@ __global__ __launch_bounds__(256) void quantize_vec_kernel(const float4* __restr
         for (int u = 0; u < 4; ++u) a[u] = load_stream(x4 + (i + u * 256 < e ? i + u * 256 : e - 1));
     };
     load();
-    const float r = fold_end(ss, f);
+    const float r = FOLD ? fold_end(ss, f) : inv_scale(ss.host, ss.dev);
     while (i < e) {   // four loads in flight per lane
 #pragma unroll
         for (int u = 0; u < 4; ++u)
@@ -253,20 +257,20 @@ __global__ __launch_bounds__(256) void quantize_vec_kernel(const float4* __restr
     }
 }
 
-// The same for tensors below kStreamElems, grid-strided with plain loads, one round of four loads per lane: the grid covers the
-// tensor.  32768 x 320: 11.3 us with the fold in front of the loads and the arithmetic
-// encoder, 7.9 us.
-template <bool FOUR_BIT, int YKIND>
+// The same for smaller tensors, grid-strided with plain loads, one round of four loads per lane: the grid covers the tensor.
+// 32768 x 320: 11.3 us with the fold in front of the loads and the arithmetic encoder, 7.9 us.
+template <bool FOUR_BIT, int YKIND, bool FOLD>
 __global__ __launch_bounds__(256) void quantize_vec_strided_kernel(const float4* __restrict__ x4, size_t n4, QParams q,
                                                            ScaleSrc ss, uint8_t* __restrict__ codes)
 {
-    const Fold f = fold_begin(ss);
+    Fold f;
+    if constexpr (FOLD) f = fold_begin(ss);
     const size_t nthreads = (size_t)gridDim.x * 256;
     const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
     float4 a[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) a[u] = x4[i + u * nthreads < n4 ? i + u * nthreads : n4 - 1];
-    const float r = fold_end(ss, f);
+    const float r = FOLD ? fold_end(ss, f) : inv_scale(ss.host, ss.dev);
 #pragma unroll
     for (int u = 0; u < 4; ++u)
         if (i + u * nthreads < n4) store_codes<FOUR_BIT, YKIND>(codes, i + u * nthreads, a[u], r, q);
@@ -312,11 +316,20 @@ int launch_quantize(const float* x, size_t n, const QParams& q, bool four_bit, c
         static_assert(kStreamElems <= (size_t)4096 * 4 * 256 * 4, "the grid of the strided kernel covers what it is given");
         int g = grid_for(n4, 256 * 4);
         const float4* x4 = reinterpret_cast<const float4*>(x);
-        const int kind = hw_kind(q);
-        auto kern = n >= kStreamElems ? (four_bit ? quantize_vec_kernel<true, 0> : kind == 1 ? quantize_vec_kernel<false, 1>
-                                         : kind == 2 ? quantize_vec_kernel<false, 2> : quantize_vec_kernel<false, 0>)
-                                      : (four_bit ? quantize_vec_strided_kernel<true, 0> : kind == 1 ? quantize_vec_strided_kernel<false, 1>
-                                         : kind == 2 ? quantize_vec_strided_kernel<false, 2> : quantize_vec_strided_kernel<false, 0>);
+        // a given scale leaves nothing to fold, and its branches ahead of the first load cost formats without a conversion instruction 3 to
+        // 8 % (E2M1, 5 M elements: 4.4 us, 3.9 us)
+        const int kind = four_bit ? 4 : hw_kind(q);
+        auto pick = [&](auto fold) {
+            constexpr bool F = decltype(fold)::value;
+            if (n >= (F ? kStreamElems : kStreamElemsGiven))
+                return kind == 4   ? quantize_vec_kernel<true, 0, F>
+                       : kind == 1 ? quantize_vec_kernel<false, 1, F>
+                       : kind == 2 ? quantize_vec_kernel<false, 2, F> : quantize_vec_kernel<false, 0, F>;
+            return kind == 4   ? quantize_vec_strided_kernel<true, 0, F>
+                   : kind == 1 ? quantize_vec_strided_kernel<false, 1, F>
+                   : kind == 2 ? quantize_vec_strided_kernel<false, 2, F> : quantize_vec_strided_kernel<false, 0, F>;
+        };
+        auto kern = ss.partials ? pick(std::true_type{}) : pick(std::false_type{});
         hipLaunchKernelGGL(kern, dim3(g), dim3(256), 0, st, x4, n4, q, ss, codes);
     }
     size_t first = n4 << 2;

@@ -63,3 +63,21 @@ def test_rows_with_a_scale_found_by_the_layer(M, K):
     torch.cuda.synchronize()
     want = padded(oracle.quantize(x, synth.E4M3, sx), K)
     assert np.array_equal(ws.cpu().numpy()[:want.size].reshape(want.shape), want)
+
+
+@pytest.mark.parametrize("n", [5, 4096 * 3 + 2, (9 << 20) - 3, 9 << 20, (9 << 20) + 1026, (16 << 20) - 1, (16 << 20) + 4099])
+@pytest.mark.parametrize("fmt", [synth.E4M3, synth.E5M2, synth.E3M4, synth.E2M1])
+def test_flat_codes_of_a_given_scale(n, fmt):
+    """Either side of the sizes at which the kernel changes, in shares that end inside a round; host and device scale."""
+    x = synth.activations((n,), n)
+    scale = float(np.float32(0.0371))
+    want = oracle.quantize(x, fmt, scale)
+    if 1 + fmt[0] + fmt[1] <= 4:
+        pairs = np.concatenate([want, np.zeros(n % 2, dtype=np.uint8)])
+        want = pairs[0::2] | (pairs[1::2] << 4)
+    for dev_scale in (None, dev(np.array([scale], dtype=np.float32))):
+        codes = torch.full((want.size + 16,), 0xEE, dtype=torch.uint8, device=DEV)
+        B.fpq_quantize(dev(x), fmt, 0.0 if dev_scale is not None else scale, dev_scale, codes)
+        torch.cuda.synchronize()
+        got = codes.cpu().numpy()
+        assert np.array_equal(got[:want.size], want) and np.all(got[want.size:] == 0xEE)

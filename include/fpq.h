@@ -276,16 +276,18 @@ int fpq_conv2d(const void *x, int x_is_fp32, fpq_format_t fx, float sx, const fl
                int pad, int acc_mode, void *workspace, size_t workspace_bytes, void *stream);
 
 /* Read-only query (host, no GPU): which kernel fpq_gemm / fpq_conv2d launch for a shape and into how many K slices
- * they cut it, given a workspace of the size the *_workspace_size functions state and operands in the hardware's
- * E4M3 / E2M1 encodings (other operand pairings may take another kernel or number of slices, and some of them
- * FPQ_KERNEL_SMALL_TILE, unsliced, whatever the shape).
+ * they cut it, given a workspace of the size the *_workspace_size functions state, operands in the hardware's
+ * E4M3 / E2M1 encodings and a result that is stored (other operand pairings may take another kernel or number of slices,
+ * and some of them FPQ_KERNEL_SMALL_TILE, unsliced, whatever the shape; with FPQ_OUT_ACCUMULATE a shape of
+ * FPQ_KERNEL_STRIP takes one of the tiles).
  * With more than one slice the layer kernel writes partial sums to the workspace and a reduction kernel adds them.
  * For tests and benchmarks that have to state, or to cover, every launch configuration a workload uses. */
 typedef enum fpq_kernel {
     FPQ_KERNEL_SMALL_TILE = 0, /* tiles of at most 128 x 128 outputs: any shape */
     FPQ_KERNEL_256x160 = 1,    /* persistent 256 x 160 tiles, three LDS stages */
     FPQ_KERNEL_128x160 = 2,    /* persistent 128 x 160 tiles, two LDS stages, two workgroups per compute unit */
-    FPQ_KERNEL_ROWS16 = 3      /* linear layers with at most 16 rows: K split over the wavefronts of a workgroup */
+    FPQ_KERNEL_ROWS16 = 3,     /* linear layers with at most 16 rows: K split over the wavefronts of a workgroup */
+    FPQ_KERNEL_STRIP = 4       /* linear layers and 1 x 1 convolutions of at most 320 codes: weights of 64 columns in registers */
 } fpq_kernel;
 typedef struct fpq_plan {
     int32_t kernel;   /* fpq_kernel */

@@ -33,7 +33,7 @@ class fpq_plan_t(C.Structure):
     _fields_ = [("kernel", C.c_int32), ("k_slices", C.c_int32)]
 
 
-FPQ_KERNEL_SMALL_TILE, FPQ_KERNEL_256x160, FPQ_KERNEL_128x160, FPQ_KERNEL_ROWS16 = 0, 1, 2, 3
+FPQ_KERNEL_SMALL_TILE, FPQ_KERNEL_256x160, FPQ_KERNEL_128x160, FPQ_KERNEL_ROWS16, FPQ_KERNEL_STRIP = 0, 1, 2, 3, 4
 FPQ_NOALLOC_SCRATCH_BYTES = 64 << 20
 
 

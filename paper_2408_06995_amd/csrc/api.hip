@@ -440,9 +440,21 @@ size_t fpq_conv2d_workspace_size(int64_t B, int64_t Cin, int64_t H, int64_t W, i
            (x_is_fp32 == FPQ_X_FP32_DYNAMIC ? kDynScaleBytes : 0);
 }
 
-static void fill_plan(const GemmPlan& p, int64_t M, bool linear, fpq_plan_t* out)
+// Hardware E4M3 operands, fp32 results that are stored.
+static void fill_plan(const GemmPlan& p, int64_t M, int64_t N, int64_t Cin, int kh, int kw, int stride, int pad, bool linear, fpq_plan_t* out)
 {
+    auto capped = [](int64_t v) { return (int)(v < INT32_MAX ? v : INT32_MAX); };   // (larger sizes the layers refuse)
+    GemmArgs a;
+    memset(&a, 0, sizeof a);
+    a.M = capped(M); a.N = capped(N);
+    a.Kreal = capped(padded_channels(Cin) * kh * kw);
+    a.kh = kh; a.kw = kw; a.stride = stride; a.pad = pad;
+    a.conv_out = !linear;
+    a.xkind = a.wkind = OPK_FP8;
+    a.acc_mode = FPQ_ACC_FP32;
+    a.splits = p.splits;
     out->kernel = (linear && M <= 16)         ? FPQ_KERNEL_ROWS16
+                  : gemm_strip_applicable(a)  ? FPQ_KERNEL_STRIP
                   : p.tile == TILE_256x160_S3 ? FPQ_KERNEL_256x160
                   : p.tile == TILE_128x160_S2 ? FPQ_KERNEL_128x160
                                               : FPQ_KERNEL_SMALL_TILE;
@@ -453,7 +465,7 @@ int fpq_gemm_plan(int64_t M, int64_t N, int64_t K, fpq_plan_t* plan)
 {
     if (!plan) return FPQ_ERR_NULL;
     if (M <= 0 || K <= 0 || N <= 0) return FPQ_ERR_SHAPE;
-    fill_plan(plan_gemm(M, N, padded_k(K, 1), PLAN_LINEAR), M, true, plan);
+    fill_plan(plan_gemm(M, N, padded_k(K, 1), PLAN_LINEAR), M, N, K, 1, 1, 1, 0, true, plan);
     return FPQ_OK;
 }
 
@@ -465,7 +477,8 @@ int fpq_conv2d_plan(int64_t B, int64_t Cin, int64_t H, int64_t W, int64_t Cout, 
         return FPQ_ERR_SHAPE;
     if (H + 2 * pad < kh || W + 2 * pad < kw) return FPQ_ERR_SHAPE;
     const int64_t Ho = (H + 2 * pad - kh) / stride + 1, Wo = (W + 2 * pad - kw) / stride + 1;
-    fill_plan(plan_gemm(B * Ho * Wo, Cout, padded_k(Cin, (int64_t)kh * kw), PLAN_CONV), B * Ho * Wo, false, plan);
+    fill_plan(plan_gemm(B * Ho * Wo, Cout, padded_k(Cin, (int64_t)kh * kw), PLAN_CONV), B * Ho * Wo, Cout, Cin, kh, kw, stride, pad, false,
+              plan);
     return FPQ_OK;
 }
 

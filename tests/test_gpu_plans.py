@@ -1,5 +1,5 @@
 """Every launch configuration the planner of the layer calls can produce -- kernel (small register-staged tiles,
-128 x 160 tiles, 256 x 160 tiles, the at-most-16-rows kernel) x number of K slices -- compared with the oracle:
+128 x 160 tiles, 256 x 160 tiles, the at-most-16-rows kernel, the short-K kernel) x number of K slices -- compared with the oracle:
 linear layers and convolutions, E4M3 and E2M1 weights, fp32 results and results as codes.  Each case first asserts,
 through the library's read-only plan query, that its shape still takes the configuration it is meant to cover."""
 import numpy as np
@@ -16,6 +16,7 @@ pytestmark = pytest.mark.gpu
 
 E4M3, E2M1 = synth.E4M3, synth.E2M1
 SMALL, T256, T128, ROWS16 = B.FPQ_KERNEL_SMALL_TILE, B.FPQ_KERNEL_256x160, B.FPQ_KERNEL_128x160, B.FPQ_KERNEL_ROWS16
+STRIP = B.FPQ_KERNEL_STRIP
 
 
 def rows_to_check(M, seed, tile=128, n_tiles=12, n_random=24):
@@ -34,6 +35,7 @@ LINEAR_PLANS = [
     (8, 1280, 1280, ROWS16, 1),
     (616, 768, 320, SMALL, 1),
     (4096, 640, 640, T128, 1),
+    (16384, 320, 960, STRIP, 1),
     (3072, 2048, 2560, T256, 1),
     (2048, 8192, 2080, T256, 2),
     (1280, 12288, 2720, T256, 3),
@@ -94,7 +96,8 @@ def test_linear_every_plan(M, K, N, kernel, slices):
 # (B, Cin, H, W, Cout, k, stride, kernel, K slices)
 CONV_PLANS = [
     (2, 64, 24, 24, 320, 3, 1, SMALL, 1),
-    (8, 320, 64, 64, 320, 1, 1, T128, 1),
+    (8, 320, 64, 64, 320, 1, 1, STRIP, 1),
+    (8, 160, 32, 32, 640, 3, 1, T128, 1),
     (8, 320, 32, 32, 320, 3, 1, T128, 2),
     (8, 320, 64, 64, 320, 3, 1, T256, 1),
     (8, 960, 32, 32, 640, 3, 1, T256, 2),

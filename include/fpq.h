@@ -278,8 +278,8 @@ int fpq_conv2d(const void *x, int x_is_fp32, fpq_format_t fx, float sx, const fl
 /* Read-only query (host, no GPU): which kernel fpq_gemm / fpq_conv2d launch for a shape and into how many K slices
  * they cut it, given a workspace of the size the *_workspace_size functions state, operands in the hardware's
  * E4M3 / E2M1 encodings and a result that is stored (other operand pairings may take another kernel or number of slices,
- * and some of them FPQ_KERNEL_SMALL_TILE, unsliced, whatever the shape; with FPQ_OUT_ACCUMULATE a shape of
- * FPQ_KERNEL_STRIP takes one of the tiles).
+ * and some of them FPQ_KERNEL_SMALL_TILE, unsliced, whatever the shape; with FPQ_OUT_ACCUMULATE, and with E2M1 weights
+ * for some K of at most 128, a shape of FPQ_KERNEL_STRIP takes one of the tiles).
  * With more than one slice the layer kernel writes partial sums to the workspace and a reduction kernel adds them.
  * For tests and benchmarks that have to state, or to cover, every launch configuration a workload uses. */
 typedef enum fpq_kernel {

@@ -156,12 +156,13 @@ def test_plan_query_and_format_range():
 
 def test_plan_query_of_a_short_k():
     """Every output from one row of at most 320 codes: the kernel that keeps the weights in registers, from 144 pairs of 128 rows and
-    64 columns on (NCHW results: from 32 channels on)."""
+    64 columns on (NCHW results: from 32 channels on); with more than 64 and at most 128 codes, one step of the tiles, from 4 M values on."""
     strip = (B.FPQ_KERNEL_STRIP, 1)
     assert B.fpq_conv2d_plan(8, 320, 64, 64, 320, 1, 1, 1, 0) == strip
     assert B.fpq_gemm_plan(16384, 960, 320) == strip and B.fpq_gemm_plan(18432, 64, 16) == strip
     assert B.fpq_gemm_plan(17, 9216, 320) == strip and B.fpq_conv2d_plan(1, 3, 5, 5, 32, 1, 1, 1, 0) == strip
-    for plan in (B.fpq_gemm_plan(17, 9215, 320), B.fpq_gemm_plan(16384, 960, 336), B.fpq_gemm_plan(16, 9216, 320),
+    assert B.fpq_gemm_plan(6250, 640, 128) == strip and B.fpq_gemm_plan(40000, 640, 128) == strip
+    for plan in (B.fpq_gemm_plan(6249, 640, 128), B.fpq_gemm_plan(6249, 640, 80), B.fpq_gemm_plan(17, 9215, 320), B.fpq_gemm_plan(16384, 960, 336), B.fpq_gemm_plan(16, 9216, 320),
                  B.fpq_gemm_plan(18304, 64, 16), B.fpq_gemm_plan(18432, 63, 16), B.fpq_gemm_plan(16384, 1001, 320),
                  B.fpq_gemm_plan(1 << 20, 640, (1 << 32) + 320), B.fpq_conv2d_plan(1, 3, 5, 5, 31, 1, 1, 1, 0),
                  B.fpq_conv2d_plan(1, 3, 4, 4, 32, 1, 1, 1, 0), B.fpq_conv2d_plan(8, 16, 64, 64, 320, 3, 3, 1, 1),

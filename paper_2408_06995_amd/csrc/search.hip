@@ -678,19 +678,23 @@ int launch_search(const float* x, size_t n, const SearchArgs& a, const float* ma
         SortMoments* moments = reinterpret_cast<SortMoments*>(ws + l.moments);
         double* sums = reinterpret_cast<double*>(ws + l.sums);
         double* mse_w = reinterpret_cast<double*>(ws + l.total);
-        static std::atomic<uint64_t> allowed{0};
-        static std::atomic<uint64_t> allowed_counts{0};
-        if (!allow_dynamic_lds(reinterpret_cast<const void*>(search_sort_kernel), kSortLds, allowed) ||
-            !allow_dynamic_lds(reinterpret_cast<const void*>(search_counts_kernel), kCountLds, allowed_counts))
+        constexpr int narrow = kSearchSortMost * 2 / 3;
+        const bool two_thirds = l.width == narrow;
+        auto sort = two_thirds ? search_sort_kernel<narrow> : search_sort_kernel<kSearchSortMost>;
+        auto counts = two_thirds ? search_counts_kernel<narrow> : search_counts_kernel<kSearchSortMost>;
+        auto terms = two_thirds ? search_terms_kernel<narrow> : search_terms_kernel<kSearchSortMost>;
+        static std::atomic<uint64_t> allowed_sort[2]{}, allowed_counts[2]{};      // per instantiation
+        if (!allow_dynamic_lds(reinterpret_cast<const void*>(sort), sort_lds_bytes(l.width), allowed_sort[two_thirds]) ||
+            !allow_dynamic_lds(reinterpret_cast<const void*>(counts), kCountLds, allowed_counts[two_thirds]))
             return FPQ_ERR_LAUNCH;
-        hipLaunchKernelGGL(search_sort_kernel, dim3(l.parts), dim3(1024), kSortLds, st, x, n, maxparts, nparts, l.parts, sorted, offsets,
+        hipLaunchKernelGGL(sort, dim3(l.parts), dim3(1024), sort_lds_bytes(l.width), st, x, n, maxparts, nparts, l.parts, sorted, offsets,
                            flags, cursor);
         const uint32_t room = (uint32_t)most_tasks(n);
         hipLaunchKernelGGL(search_lists_kernel, dim3(kSortGroups + kStretches / 64), dim3(512), 0, st, maxparts, nparts, a, offsets, l.parts,
                            room, totals, tasks, cursor, groups, bases, cuts, cutsums, moments);
-        hipLaunchKernelGGL(search_counts_kernel, dim3(256), dim3(1024), kCountLds, st, sorted, offsets, room, tasks, cursor, groups, cuts,
+        hipLaunchKernelGGL(counts, dim3(256), dim3(1024), kCountLds, st, sorted, offsets, room, tasks, cursor, groups, cuts,
                            cutsums, moments);
-        hipLaunchKernelGGL(search_terms_kernel, dim3(kSortGroups * l.chunks), dim3(512), 0, st, sorted, offsets, l.parts, l.chunks, totals, groups,
+        hipLaunchKernelGGL(terms, dim3(kSortGroups * l.chunks), dim3(512), 0, st, sorted, offsets, l.parts, l.chunks, totals, groups,
                            cuts, cutsums, moments);
         auto closed = l.chunks == 2 ? search_closed_kernel<3> : l.chunks == 4 ? search_closed_kernel<5> : search_closed_kernel<9>;
         hipLaunchKernelGGL(closed, dim3(kSortGroups + l.parts * l.sub), dim3(512), 0, st, x, n, maxparts, nparts, a, l.parts, l.sub, flags,

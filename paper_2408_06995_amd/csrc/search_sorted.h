@@ -3,7 +3,7 @@
 // A cut needs the elements of one interval, and the tensor has them anywhere: walking the tensor, every element looked its interval
 // up, read the list of its cuts and added each term to another candidate's sum, a cache line and an integer atomic per element and
 // cut (102 of 182 us for 10.5 M elements x 444 candidates).  Here the elements come to the cuts:
-//   1. search_sort_kernel     one workgroup takes a part of at most 40960 elements into registers, counts them per stretch of 2^16
+//   1. search_sort_kernel     one workgroup takes a part of at most 61440 elements into registers, counts them per stretch of 2^16
 //                             float values in LDS, and writes their positions inside the stretches (16 bits each) in the order of the
 //                             stretches, with the stretches' offsets: x is read once, everything written goes out in whole lines;
 //   2. search_lists_kernel    the cuts of 64 neighbouring intervals (4 or 16 stretches), from the candidates alone, and the work for 3;
@@ -20,10 +20,10 @@
 
 constexpr int kSortGroups = kBins / 64;                       // 64 neighbouring intervals each
 constexpr int kStretches = (int)(kSpan >> 16);
-constexpr int kSortStride = kSearchSortElems + 8;             // 16-bit positions of a part, whole 16 bytes
+constexpr int sort_stride(int width) { return width * 1024 + 8; }   // 16-bit positions of a part, whole 16 bytes
 constexpr int kOffStride = kStretches + 8;                    // 16-bit offsets of a part
-constexpr int kSortLds = kStretches * 4 + kSortStride * 2;
 constexpr int kSums = 1 + 8;                                  // copies of moments and sums of cuts: search_counts_kernel's, search_terms_kernel's
+constexpr int sort_lds_bytes(int width) { return kStretches * 4 + sort_stride(width) * 2; }
 // elements from which a stretch is counted by position (a task takes about 12 us of a compute unit, search_terms_kernel 1 us per 1024),
 // and the most of a task (16-bit counters)
 constexpr uint32_t kCountFrom = 4096, kCountMost = 65535;
@@ -52,7 +52,7 @@ inline size_t most_tasks(size_t n)
 }
 struct SortedLayout {
     size_t sorted, offsets, flags, cursor, totals, tasks, groups, bases, cuts, cutsums, moments, sums, total;
-    int parts, chunks;                                        // chunks: workgroups of search_terms_kernel per group
+    int parts, width, chunks;                                 // chunks: workgroups of search_terms_kernel per group
     int sub;                                                  // workgroups per part for the elements outside all intervals
 };
 inline SortedLayout sorted_layout(size_t n, int nc)
@@ -61,10 +61,11 @@ inline SortedLayout sorted_layout(size_t n, int nc)
     size_t at = 0;
     auto take = [&](size_t bytes) { const size_t was = at; at += up256(bytes); return was; };
     l.parts = search_sort_parts(n);
+    l.width = search_sort_width(n);
     // a workgroup of search_terms_kernel wants 32 parts at least (2 M elements: 76 us with four, 88 with eight)
     l.chunks = l.parts < 64 ? 2 : l.parts < 256 ? 4 : 8;
     l.sub = l.parts <= 256 ? 4 : 2;
-    l.sorted = take((size_t)l.parts * kSortStride * 2);
+    l.sorted = take((size_t)l.parts * sort_stride(l.width) * 2);
     l.offsets = take((size_t)l.parts * kOffStride * 2);
     l.flags = take((size_t)l.parts * 4);
     l.cursor = take(256);
@@ -94,6 +95,7 @@ __device__ __forceinline__ SortShare sort_share(const float* x, size_t n, int pa
 
 // 22 us for 42 MB.  Bound by its phases in a row (load, count, scan, place, write out), one workgroup per compute unit: two of 40960 elements do not fit
 // into LDS, and smaller parts make shorter runs for the kernel that reads them.
+template <int E>   // elements per thread
 __global__ __launch_bounds__(1024) void search_sort_kernel(const float* __restrict__ x, size_t n,
                                                            const float* __restrict__ absmax_parts_, int nparts, int parts,
                                                            uint16_t* __restrict__ sorted, uint16_t* __restrict__ offsets,
@@ -105,7 +107,6 @@ __global__ __launch_bounds__(1024) void search_sort_kernel(const float* __restri
     uint16_t* place = reinterpret_cast<uint16_t*>(sort_lds + kStretches);
     const int tid = threadIdx.x, part = blockIdx.x;
     const SortShare share = sort_share(x, n, part, parts);
-    constexpr int E = kSearchSortElems / 1024;
     uint32_t b[E + 1];
     if ((reinterpret_cast<uintptr_t>(x) & 15) == 0) {
         const uint4* x4 = reinterpret_cast<const uint4*>(x);
@@ -169,7 +170,7 @@ __global__ __launch_bounds__(1024) void search_sort_kernel(const float* __restri
         if (rel < kSpan && b[u] >= 0x00800000u) place[atomicAdd(&counters[rel >> 16], 1u)] = (uint16_t)rel;
     }
     __syncthreads();
-    uint4* out = reinterpret_cast<uint4*>(sorted + (size_t)part * kSortStride);
+    uint4* out = reinterpret_cast<uint4*>(sorted + (size_t)part * sort_stride(E));
     const uint4* in = reinterpret_cast<const uint4*>(place);
     for (uint32_t i = tid; i < (total + 7) / 8; i += 1024) out[i] = in[i];
 }
@@ -373,6 +374,7 @@ __device__ __forceinline__ uint32_t dot2(uint32_t a, uint32_t b, uint32_t c)
 
 // A stretch's elements per position, 16 bits each.  A thread then owns 64 positions, a wavefront 4096: a fine interval, or a quarter of
 // a coarse one.  Bound by its phases in a row (clear, count, scan, cuts), one workgroup per compute unit: the counters take 128 KB.
+template <int WIDTH>
 __global__ __launch_bounds__(1024) void search_counts_kernel(const uint16_t* __restrict__ sorted, const uint16_t* __restrict__ offsets,
                                                              uint32_t task_room, const CountTask* __restrict__ tasks,
                                                              const uint32_t* __restrict__ cursor, const SortGroup* __restrict__ groups,
@@ -417,7 +419,7 @@ __global__ __launch_bounds__(1024) void search_counts_kernel(const uint16_t* __r
             const int slots = min(np, 16), sharing = 16 / slots, share = wave / slots;
             for (int p = task.from + wave % slots; p < task.to && share < sharing; p += slots) {
                 const uint16_t* o = offsets + (size_t)p * kOffStride + s;
-                const uint32_t* run = reinterpret_cast<const uint32_t*>(sorted + (size_t)p * kSortStride);
+                const uint32_t* run = reinterpret_cast<const uint32_t*>(sorted + (size_t)p * sort_stride(WIDTH));
                 const uint32_t lo = o[0], hi = o[1], step = 64u * (uint32_t)sharing;
                 for (uint32_t word = (lo >> 1) + 64u * (uint32_t)share + lane; 2 * word < hi; word += 8 * step) {
                     uint32_t two[8];
@@ -444,7 +446,7 @@ __global__ __launch_bounds__(1024) void search_counts_kernel(const uint16_t* __r
                         for (int u = 0; u < 16; ++u) {
                             const uint32_t lo = __builtin_amdgcn_readlane(o0, j + u), hi = __builtin_amdgcn_readlane(o1, j + u);
                             const uint32_t word = (lo >> 1) + from + lane;
-                            const uint32_t* run = reinterpret_cast<const uint32_t*>(sorted + (size_t)(pb + wave + 16 * (j + u)) * kSortStride);
+                            const uint32_t* run = reinterpret_cast<const uint32_t*>(sorted + (size_t)(pb + wave + 16 * (j + u)) * sort_stride(WIDTH));
                             two[u] = lo < hi && 2 * word < hi ? run[word] : 0u;
                         }
                         if (!cleared) {
@@ -542,6 +544,7 @@ __global__ __launch_bounds__(1024) void search_counts_kernel(const uint16_t* __r
 // Element by element, 24 us where it has one tenth of 10.5 M elements (all of them: 75).  Bound by set-up and latencies of its 4352
 // workgroups, then by vector instructions and LDS accesses of the loop over an element's cuts (1.8 on average with four encodings of eight bits x
 // 111 biases; a wavefront goes round as often as the element with the most).
+template <int WIDTH>
 __global__ __launch_bounds__(512) void search_terms_kernel(const uint16_t* __restrict__ sorted, const uint16_t* __restrict__ offsets,
                                                            int parts, int chunks, const uint32_t* __restrict__ totals,
                                                            const SortGroup* __restrict__ groups, const uint32_t* __restrict__ cuts,
@@ -605,7 +608,7 @@ __global__ __launch_bounds__(512) void search_terms_kernel(const uint16_t* __res
             __syncthreads();
             for (int j = tid >> 4; j < 64; j += 32) {
                 const uint32_t lo = offs[j][0], hi = offs[j][stretches];
-                const uint32_t* run = reinterpret_cast<const uint32_t*>(sorted + (size_t)(p0 + j * chunks) * kSortStride);
+                const uint32_t* run = reinterpret_cast<const uint32_t*>(sorted + (size_t)(p0 + j * chunks) * sort_stride(WIDTH));
                 for (uint32_t word = (lo >> 1) + (lane & 15); lo < hi && 2 * word < hi; word += 16) {
                     const uint32_t two = run[word];
                     uint32_t pos[2] = {two & 0xffffu, two >> 16}, list[2], at[2], most = 0;

@@ -34,13 +34,22 @@ constexpr int search_parts(size_t n)
 }
 // Parts of the sorted form, a multiple of 8 (one per XCD) of at most kSearchSortElems elements (and three, the rest of an aligned
 // tensor): one for each compute unit, fewer while a part has less than 16384 elements (longer runs), and multiples of
-// 256 beyond.
-constexpr size_t kSearchSortElems = 40960;
+// 256 beyond.  A part's positions are counted in 16 bits, which 60 elements per thread and the rest are just below, and with the
+// counters of the stretches take 136 of the 160 KB of LDS.
+constexpr int kSearchSortMost = 60;
+constexpr size_t kSearchSortElems = (size_t)kSearchSortMost * 1024;
 constexpr size_t kSearchMaxSorted = (size_t)1 << 26;
 constexpr int search_sort_parts(size_t n)
 {
     const size_t small = (n + 16383) / 16384, p = (small + 7) / 8 * 8, most = 256 * kSearchSortElems;
     return (int)(n > most ? (n + most - 1) / most * 256 : p < 8 ? 8 : p > 256 ? 256 : p);
+}
+// Elements per thread that a part is sorted with: all of them, or two thirds where those hold a part, which asks for fewer registers and
+// less LDS (10.5 M elements 120.8 and 123.9 us; with two thirds alone twice as many parts from there on, 10.6 M 143 and 124 us).
+constexpr int search_sort_width(size_t n)
+{
+    const size_t parts = (size_t)search_sort_parts(n), one = (n + parts - 1) / parts, four = (n / 4 + parts - 1) / parts * 4;
+    return (one > four ? one : four) <= kSearchSortElems * 2 / 3 ? kSearchSortMost * 2 / 3 : kSearchSortMost;
 }
 // Largest tensor of the binned form.
 constexpr size_t kSearchMaxBinned = (size_t)1 << 31;

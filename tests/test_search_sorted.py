@@ -15,16 +15,19 @@ PROGRAM = r"""
 using namespace fpq;
 int main()
 {
-    const size_t sizes[] = {131072, 480000, 480003, 4194303, 256 * kSearchSortElems - 1, 256 * kSearchSortElems,
-                            256 * kSearchSortElems + 1, 512 * kSearchSortElems + 3, kSearchMaxSorted - 1, kSearchMaxSorted};
+    const size_t full = 256 * kSearchSortElems, third = full / 3;
+    const size_t sizes[] = {131072, 480000, 480003, 4194303, 2 * third - 1, 2 * third, 2 * third + 1, 2 * third + 4, 4 * third + 3, full - 1,
+                            full, full + 1, 2 * full + 3, kSearchMaxSorted - 1, kSearchMaxSorted};
+    static_assert(kSearchSortElems + 3 <= 65535, "positions of a part in 16 bits");
     for (size_t n : sizes)
         for (size_t v : {(size_t)1, (size_t)4}) {
-            const int parts = search_sort_parts(n);
+            const int parts = search_sort_parts(n), width = search_sort_width(n);
             size_t next = 0;
             if (parts % 8 || parts > 65535) return printf("parts %zu\n", n), 1;
+            if (width != kSearchSortMost && width != kSearchSortMost * 2 / 3) return printf("width %zu\n", n), 1;
             for (int p = 0; p < parts; ++p) {
                 const SearchRange r = search_range(n / v, p, parts);
-                if (r.lo != next || (r.hi - r.lo) * v > kSearchSortElems) return printf("share %zu\n", n), 1;
+                if (r.lo != next || (r.hi - r.lo) * v > (size_t)width * 1024) return printf("share %zu\n", n), 1;
                 next = r.hi;
             }
             if (next != n / v) return printf("rest %zu\n", n), 1;
@@ -63,7 +66,8 @@ def _tensor(kind, n):
 @pytest.mark.parametrize("kind", ["normal", "saturated", "two", "levels", "wide"])
 @pytest.mark.parametrize("n,offset,encodings,J", [(480001, 1, FP8, 111), ((1 << 20) + 3, 0, FP8 * 2, 128),
                                                   ((1 << 20) + 3, 0, [(1, 2), (2, 1)], 128), (256 * 40960 + 5, 0, FP8, 111),
-                                                  (256 * 40960 - 2, 1, FP8, 111)])
+                                                  (256 * 40960 - 2, 1, FP8, 111), (256 * 40960, 0, FP8, 48), (256 * 61440 + 5, 0, FP8, 111),
+                                                  (256 * 61440 - 2, 1, FP8, 111), (33000001, 0, [(4, 3), (3, 4)], 111)])
 def test_the_three_forms_agree(kind, n, offset, encodings, J):
     import torch
     from paper_2408_06995_amd import binding as B

@@ -28,9 +28,10 @@
 // below the maximum, or subnormal ones, reads its share again and evaluates those directly (add_outside); with such elements
 // only, that costs what the direct form costs.
 // Sorted (search_sorted.h): the same intervals and closed forms with the elements sorted into stretches of float values first, so that
-// neither moments nor cuts cost a cache line or an atomic per element and candidate.  Up to kSearchMaxSorted elements; it wants 2.9
-// bytes of workspace per element, so larger tensors, and callers with less workspace, take the interval tables.
-// Measured, 444 candidates, sorted / tables / direct, us: 10.5 M elements 121 / 182 / 1758; 60 M 507 / 737; 2 M 76 / 84; 480 K 69 / 75 /
+// neither moments nor cuts cost a cache line or an atomic per element and candidate.  From kSearchSortedWork elements x candidates to
+// kSearchMaxSorted elements; other tensors, and callers with less workspace than the stated size, take the interval tables, or the
+// direct form where those do not fit either.
+// Measured, 444 candidates, sorted / tables / direct, us: 10.5 M elements 121 / 186 / 1758; 67 M 498 / 848; 2 M 77 / 86; 480 K - / 75 /
 // 78; all of 10.5 M equal 162 / 337.  20 K elements: 17 us direct.
 #include "fpq_dev.h"
 #include "fpq_host.h"
@@ -642,9 +643,9 @@ __global__ __launch_bounds__(1024) void search_select_kernel(const double* __res
     }
 }
 
-// The binned forms have a cost of their own (sorted 65 us, tables 73: launches, the candidates' walks, 544 groups of intervals
-// whatever n is); the direct form takes 0.13 us per 1024 elements at 444 candidates, in steps of a full chip.  350000 elements: 66 us
-// direct, 68 sorted; 500000: 78 and 69.
+// The interval tables have a cost of their own (about 73 us: launches, the candidates' walks, the tables written and read once, whatever
+// n is); the direct form takes 0.13 us per 1024 elements at 444 candidates, in steps of a full chip.  450000 elements: 78 us direct, 73
+// tables; 500000: 78 and 75.
 constexpr size_t kSearchBinnedWork = (size_t)480000 * 444;   // elements x candidates
 bool binned_pays(size_t n, int nc) { return n * (size_t)nc >= kSearchBinnedWork && n >= 131072 && n <= kSearchMaxBinned; }
 
@@ -652,7 +653,7 @@ bool binned_pays(size_t n, int nc) { return n * (size_t)nc >= kSearchBinnedWork 
 
 size_t search_binned_bytes(size_t n, int nc)
 {
-    return !binned_pays(n, nc) ? 0 : n <= kSearchMaxSorted ? sorted_layout(n, nc).total : binned_layout(n, nc).total;
+    return !binned_pays(n, nc) ? 0 : search_sorted_pays(n, nc) ? sorted_layout(n, nc).total : binned_layout(n, nc).total;
 }
 
 int launch_search(const float* x, size_t n, const SearchArgs& a, const float* maxparts, float* partial, size_t partial_bytes,
@@ -662,7 +663,7 @@ int launch_search(const float* x, size_t n, const SearchArgs& a, const float* ma
     const int nparts = absmax_parts(n);
     const double* mse = nullptr;
     int rows = search_blocks(n);
-    if (binned_pays(n, NC) && n <= kSearchMaxSorted && partial_bytes >= sorted_layout(n, NC).total + up256((size_t)NC * 8)) {
+    if (binned_pays(n, NC) && search_sorted_pays(n, NC) && partial_bytes >= sorted_layout(n, NC).total + up256((size_t)NC * 8)) {
         const SortedLayout l = sorted_layout(n, NC);
         uint8_t* ws = reinterpret_cast<uint8_t*>(partial);
         uint16_t* sorted = reinterpret_cast<uint16_t*>(ws + l.sorted);
@@ -689,12 +690,12 @@ int launch_search(const float* x, size_t n, const SearchArgs& a, const float* ma
             return FPQ_ERR_LAUNCH;
         hipLaunchKernelGGL(sort, dim3(l.parts), dim3(1024), sort_lds_bytes(l.width), st, x, n, maxparts, nparts, l.parts, sorted, offsets,
                            flags, cursor);
-        const uint32_t room = (uint32_t)most_tasks(n);
+        const uint32_t room = (uint32_t)most_tasks(n), from = search_count_from(n);
         hipLaunchKernelGGL(search_lists_kernel, dim3(kSortGroups + kStretches / 64), dim3(512), 0, st, maxparts, nparts, a, offsets, l.parts,
-                           room, totals, tasks, cursor, groups, bases, cuts, cutsums, moments);
+                           room, from, totals, tasks, cursor, groups, bases, cuts, cutsums, moments);
         hipLaunchKernelGGL(counts, dim3(256), dim3(1024), kCountLds, st, sorted, offsets, room, tasks, cursor, groups, cuts,
                            cutsums, moments);
-        hipLaunchKernelGGL(terms, dim3(kSortGroups * l.chunks), dim3(512), 0, st, sorted, offsets, l.parts, l.chunks, totals, groups,
+        hipLaunchKernelGGL(terms, dim3(kSortGroups * l.chunks), dim3(512), 0, st, sorted, offsets, l.parts, l.chunks, from, totals, groups,
                            cuts, cutsums, moments);
         auto closed = l.chunks == 2 ? search_closed_kernel<3> : l.chunks == 4 ? search_closed_kernel<5> : search_closed_kernel<9>;
         hipLaunchKernelGGL(closed, dim3(kSortGroups + l.parts * l.sub), dim3(512), 0, st, x, n, maxparts, nparts, a, l.parts, l.sub, flags,

@@ -24,9 +24,7 @@ constexpr int sort_stride(int width) { return width * 1024 + 8; }   // 16-bit po
 constexpr int kOffStride = kStretches + 8;                    // 16-bit offsets of a part
 constexpr int kSums = 1 + 8;                                  // copies of moments and sums of cuts: search_counts_kernel's, search_terms_kernel's
 constexpr int sort_lds_bytes(int width) { return kStretches * 4 + sort_stride(width) * 2; }
-// elements from which a stretch is counted by position (a task takes about 12 us of a compute unit, search_terms_kernel 1 us per 1024),
-// and the most of a task (16-bit counters)
-constexpr uint32_t kCountFrom = 4096, kCountMost = 65535;
+constexpr uint32_t kCountMost = 65535;                        // elements of a task (16-bit counters)
 constexpr int kCountLds = 65536 * 2 + 2 * 1024 * 4;
 constexpr int kTaskSlices = 8;
 constexpr int kWindowCuts = 1024;                             // cuts of a group that lie in LDS at a time
@@ -48,7 +46,7 @@ struct CountTask {
 // fit into one have more than kCountMost elements together.
 inline size_t most_tasks(size_t n)
 {
-    return n / kCountFrom + n / kCountMost * (kTaskSlices + 2) + 64;
+    return n / search_count_from(n) + n / kCountMost * (kTaskSlices + 2) + 64;
 }
 struct SortedLayout {
     size_t sorted, offsets, flags, cursor, totals, tasks, groups, bases, cuts, cutsums, moments, sums, total;
@@ -222,7 +220,7 @@ __device__ __forceinline__ void walk_group(const Cand& k, const GroupBits& b, S 
 
 // Elements per stretch, and the tasks of search_counts_kernel; 64 stretches per workgroup.
 __device__ void make_tasks(int block, const uint16_t* __restrict__ offsets, int parts, uint32_t most, uint32_t* __restrict__ totals,
-                           CountTask* __restrict__ tasks, uint32_t* __restrict__ cursor)
+                           CountTask* __restrict__ tasks, uint32_t* __restrict__ cursor, uint32_t count_from)
 {
     __shared__ uint32_t slices[kTaskSlices][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, s = block * 64 + lane;
@@ -239,7 +237,7 @@ __device__ void make_tasks(int block, const uint16_t* __restrict__ offsets, int 
     uint32_t total = 0;
     for (int i = 0; i < kTaskSlices; ++i) total += slices[i][lane];
     if (wave == 0) totals[s] = total;
-    if (total < kCountFrom) return;
+    if (total < count_from) return;
     auto add = [&](int from, int to, uint32_t count) {
         const uint32_t at = atomicAdd(cursor, 1u);
         if (at < most) tasks[at] = CountTask{(uint16_t)s, (uint16_t)from, (uint16_t)to, (uint16_t)count};
@@ -279,7 +277,7 @@ __device__ void make_tasks(int block, const uint16_t* __restrict__ offsets, int 
 // bases[group][candidate]; and the copies of sums that search_counts_kernel adds to, cleared.  The rest: make_tasks.
 __global__ __launch_bounds__(512) void search_lists_kernel(const float* __restrict__ absmax_parts_, int nparts, SearchArgs a,
                                                            const uint16_t* __restrict__ offsets, int parts, uint32_t task_room,
-                                                           uint32_t* __restrict__ totals, CountTask* __restrict__ tasks,
+                                                           uint32_t count_from, uint32_t* __restrict__ totals, CountTask* __restrict__ tasks,
                                                            uint32_t* __restrict__ cursor, SortGroup* __restrict__ groups,
                                                            uint32_t* __restrict__ bases, uint32_t* __restrict__ cuts,
                                                            unsigned long long* __restrict__ cutsums, SortMoments* __restrict__ moments)
@@ -287,7 +285,7 @@ __global__ __launch_bounds__(512) void search_lists_kernel(const float* __restri
     __shared__ uint32_t wave_sum[8], start;
     const int tid = threadIdx.x, g = blockIdx.x;
     if (g >= kSortGroups) {
-        make_tasks(g - kSortGroups, offsets, parts, task_room, totals, tasks, cursor + 1);
+        make_tasks(g - kSortGroups, offsets, parts, task_room, totals, tasks, cursor + 1, count_from);
         return;
     }
     const int NC = a.n_enc * a.J;
@@ -546,7 +544,7 @@ __global__ __launch_bounds__(1024) void search_counts_kernel(const uint16_t* __r
 // 111 biases; a wavefront goes round as often as the element with the most).
 template <int WIDTH>
 __global__ __launch_bounds__(512) void search_terms_kernel(const uint16_t* __restrict__ sorted, const uint16_t* __restrict__ offsets,
-                                                           int parts, int chunks, const uint32_t* __restrict__ totals,
+                                                           int parts, int chunks, uint32_t count_from, const uint32_t* __restrict__ totals,
                                                            const SortGroup* __restrict__ groups, const uint32_t* __restrict__ cuts,
                                                            unsigned long long* __restrict__ cutsums, SortMoments* __restrict__ moments)
 {
@@ -560,7 +558,7 @@ __global__ __launch_bounds__(512) void search_terms_kernel(const uint16_t* __res
     const int stretches = gs.count, shift = gs.shift;
     const uint32_t mask = (1u << shift) - 1u;
     const uint32_t mine = lane < stretches ? totals[gs.first + lane] : 0u;
-    const uint32_t light = (uint32_t)__ballot(mine > 0 && mine < kCountFrom);    // the other stretches are search_counts_kernel's
+    const uint32_t light = (uint32_t)__ballot(mine > 0 && mine < count_from);    // the other stretches are search_counts_kernel's
     const SortGroup grp = groups[g];
     unsigned long long* sums = cutsums + (size_t)(1 + chunk) * kMaxCuts;
     SortMoments* bins = moments + (size_t)(1 + chunk) * kBins + g * 64;

@@ -51,6 +51,18 @@ constexpr int search_sort_width(size_t n)
     const size_t parts = (size_t)search_sort_parts(n), one = (n + parts - 1) / parts, four = (n / 4 + parts - 1) / parts * 4;
     return (one > four ? one : four) <= kSearchSortElems * 2 / 3 ? kSearchSortMost * 2 / 3 : kSearchSortMost;
 }
+// Where the sorted form is used among the tensors that are large enough for either.  It saves the interval tables' time per element and
+// candidate and costs more per element, most for tensors whose values crowd in few intervals.  Ratios tables / sorted for normal values
+// with outliers, rectified, SiLU and GELU outputs, 444 candidates: 0.5 M elements 1.06, 1.20, 0.73, 0.80; 1 M 1.03, 1.19, 0.86,
+// 0.86; 2 M 1.14, 1.25, 0.90, 0.97; 4.2 M 1.16, 1.29, 1.01, 1.06; 222 candidates, 2 M 1.05, 1.19, 0.80, 0.89; 4.2 M 1.04, 1.14,
+// 0.90, 0.96; 8.4 M 1.24, 1.30, 1.19, 1.18.  Few candidates gain nothing that heavy-tailed tensors do not lose: 111, 33 M elements, normal
+// values 1.09, attention probabilities 0.89, quotients of normal values 0.88.
+constexpr size_t kSearchSortedWork = (size_t)3 * 524288 * 444;   // elements x candidates
+constexpr bool search_sorted_pays(size_t n, int nc) { return n <= kSearchMaxSorted && nc >= 192 && n * (size_t)nc >= kSearchSortedWork; }
+// Elements from which a stretch is counted by position: a task takes about 12 us of a compute unit whatever it holds, element by element
+// 1 us per 1024.  As many as a stretch has on average where that is more, or heavy-tailed tensors fill most stretches just above the line
+// (33 M attention probabilities x 444 candidates: 579 us from 4096 on, 534 us from 8192 on).
+constexpr uint32_t search_count_from(size_t n) { return n / 4096 > 4096 ? (uint32_t)(n / 4096) : 4096u; }
 // Largest tensor of the binned form.
 constexpr size_t kSearchMaxBinned = (size_t)1 << 31;
 

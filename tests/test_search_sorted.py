@@ -1,5 +1,5 @@
 """The sorted form of the search: how it divides a tensor (host code, compiled here), and its errors against the two forms that a
-smaller workspace selects (interval tables, then direct evaluation) where stretches change hands: few and many equal values, parts
+smaller workspace selects (interval tables, where those ask for less, then direct evaluation) where stretches change hands: few and many equal values, parts
 that do not fit a counter, ragged and unaligned tensors, more cuts of a group than lie in LDS at a time."""
 import os
 import subprocess
@@ -25,6 +25,7 @@ int main()
             size_t next = 0;
             if (parts % 8 || parts > 65535) return printf("parts %zu\n", n), 1;
             if (width != kSearchSortMost && width != kSearchSortMost * 2 / 3) return printf("width %zu\n", n), 1;
+            if (search_count_from(n) < 4096 || search_count_from(n) > 65535) return printf("line %zu\n", n), 1;
             for (int p = 0; p < parts; ++p) {
                 const SearchRange r = search_range(n / v, p, parts);
                 if (r.lo != next || (r.hi - r.lo) * v > (size_t)width * 1024) return printf("share %zu\n", n), 1;
@@ -32,6 +33,10 @@ int main()
             }
             if (next != n / v) return printf("rest %zu\n", n), 1;
         }
+    // the line between the tables and the sorted form
+    if (search_sorted_pays(1572863, 444) || !search_sorted_pays(1572864, 444) || search_sorted_pays(kSearchMaxSorted, 191) ||
+        !search_sorted_pays(3145728, 222) || !search_sorted_pays(kSearchMaxSorted, 192) || search_sorted_pays(kSearchMaxSorted + 1, 444))
+        return printf("rule\n"), 1;
     return 0;
 }
 """
@@ -64,14 +69,14 @@ def _tensor(kind, n):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("kind", ["normal", "saturated", "two", "levels", "wide"])
-@pytest.mark.parametrize("n,offset,encodings,J", [(480001, 1, FP8, 111), ((1 << 20) + 3, 0, FP8 * 2, 128),
+@pytest.mark.parametrize("n,offset,encodings,J", [(690001, 1, FP8 * 2, 128), (5000001, 1, FP8, 111), ((1 << 20) + 3, 0, FP8 * 2, 128),
                                                   ((1 << 20) + 3, 0, [(1, 2), (2, 1)], 128), (256 * 40960 + 5, 0, FP8, 111),
                                                   (256 * 40960 - 2, 1, FP8, 111), (256 * 40960, 0, FP8, 48), (256 * 61440 + 5, 0, FP8, 111),
                                                   (256 * 61440 - 2, 1, FP8, 111), (33000001, 0, [(4, 3), (3, 4)], 111)])
 def test_the_three_forms_agree(kind, n, offset, encodings, J):
     import torch
     from paper_2408_06995_amd import binding as B
-    if n * len(encodings) * J < 480000 * 444:
+    if n * len(encodings) * J < 1572864 * 444:
         encodings = encodings * 4                         # the forms meet at this many evaluations
     x = _tensor(kind, n + offset)[offset:]
     size = B.fpq_search_workspace_size(n, len(encodings), J)

@@ -30,7 +30,8 @@
 // Sorted (search_sorted.h): the same intervals and closed forms with the elements sorted into stretches of float values first, so that
 // neither moments nor cuts cost a cache line or an atomic per element and candidate.  From kSearchSortedWork elements x candidates to
 // kSearchMaxSorted elements; other tensors, and callers with less workspace than the stated size, take the interval tables, or the
-// direct form where those do not fit either.
+// direct form where those do not fit either.  Its workspace is mostly the sorted positions, two bytes per place of a part; 444 candidates
+// (the tables' in brackets): 23 MB at 1.6 M elements (25), 47 at 10.5 M (42), 58 at 10.6 M, 197 at 67 M (42).
 // Measured, 444 candidates, sorted / tables / direct, us: 10.5 M elements 121 / 186 / 1758; 67 M 498 / 848; 2 M 77 / 86; 480 K - / 75 /
 // 78; all of 10.5 M equal 162 / 337.  20 K elements: 17 us direct.
 #include "fpq_dev.h"

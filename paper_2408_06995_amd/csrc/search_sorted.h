@@ -22,7 +22,6 @@ constexpr int kSortGroups = kBins / 64;                       // 64 neighbouring
 constexpr int kStretches = (int)(kSpan >> 16);
 constexpr int sort_stride(int width) { return width * 1024 + 8; }   // 16-bit positions of a part, whole 16 bytes
 constexpr int kOffStride = kStretches + 8;                    // 16-bit offsets of a part
-constexpr int kSums = 1 + 8;                                  // copies of moments and sums of cuts: search_counts_kernel's, search_terms_kernel's
 constexpr int sort_lds_bytes(int width) { return kStretches * 4 + sort_stride(width) * 2; }
 constexpr uint32_t kCountMost = 65535;                        // elements of a task (16-bit counters)
 constexpr int kCountLds = 65536 * 2 + 2 * 1024 * 4;
@@ -72,8 +71,9 @@ inline SortedLayout sorted_layout(size_t n, int nc)
     l.groups = take((size_t)kSortGroups * sizeof(SortGroup));
     l.bases = take((size_t)kSortGroups * nc * 4);
     l.cuts = take(kMaxCuts * 4);
-    l.cutsums = take(kMaxCuts * 8 * kSums);
-    l.moments = take((size_t)kBins * kSums * sizeof(SortMoments));
+    const size_t copies = 1 + (size_t)l.chunks;               // search_counts_kernel's, search_terms_kernel's
+    l.cutsums = take(kMaxCuts * 8 * copies);
+    l.moments = take((size_t)kBins * copies * sizeof(SortMoments));
     l.sums = take((size_t)(kSortGroups + l.parts * l.sub) * nc * 8);
     l.total = at;
     return l;

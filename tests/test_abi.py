@@ -154,6 +154,13 @@ def test_plan_query_and_format_range():
     assert B.fpq_format_check((5, 2, -64, 0.0)) == 0 and B.fpq_format_check((4, 3, -64, 0.0)) == 0
 
 
+def test_search_workspace_sizes():
+    """The sizes the header states, in whole megabytes, and the least that is taken."""
+    size = lambda n, e=4, j=111: B.fpq_search_workspace_size(n, e, j)
+    assert [round(size(n) / 1e6) for n in (1572864, 8 * 320 * 64 * 64, 1 << 26, (1 << 26) + 1)] == [23, 47, 197, 42]
+    assert size(2000) == 4352 + 4 * 444 + 16                   # one workgroup's sums, to whole 256 bytes
+
+
 def test_plan_query_of_a_short_k():
     """Every output from one row of at most 320 codes: the kernel that keeps the weights in registers, from 144 pairs of 128 rows and
     64 columns on (NCHW results: from 32 channels on); with more than 64 and at most 128 codes, one step of the tiles, from 4 M values on."""

@@ -420,8 +420,8 @@ int fpq_int_gemm(const uint8_t *xcodes, float sx, int32_t zx, const fpq_int_para
  *                       256 bytes, then one 256-byte slot per problem with [scale, absmax] at byte 128);
  *   FPQ_X_CODES         x holds codes [M, K] with the scale sx_dev[0]; no workspace.
  * Every K must be a multiple of 16 and every x 16-byte aligned (FPQ_ERR_ALIGN).  Each y[M, N] receives exactly what
- * fpq_gemm computes for that problem on small tiles: bit for bit for shapes that fpq_gemm itself gives to FPQ_KERNEL_SMALL_TILE
- * with K of at most 896, or in one K slice with K above 1024 and at most 12 tiles of 64 x 64; the same sums, possibly in another
+ * fpq_gemm computes for that problem on small tiles: bit for bit for shapes that fpq_gemm itself gives to FPQ_KERNEL_STRIP, to
+ * FPQ_KERNEL_SMALL_TILE with K of at most 896, or in one K slice with K above 1024 and at most 12 tiles of 64 x 64; the same sums, possibly in another
  * order, otherwise.  The bits do not depend on the other problems of the call.  Meant for small problems: every problem runs
  * on tiles of at most 128 x 64 (or, when all problems of a chunk of 32 have at most 16 rows, on the one-launch kernel for
  * such layers, whose order of sums is its own). */

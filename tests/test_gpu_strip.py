@@ -4,9 +4,14 @@ strip, images that end inside a block, output rows that share cache lines, and r
 import os
 import subprocess
 
+import numpy as np
 import pytest
+import torch
 
+import oracle
+from paper_2408_06995_amd import binding as B
 from paper_2408_06995_amd import synth
+from gpu_util import DEV, dev, gpu_pack
 from test_gpu_codes_out import test_linear_activation_then_codes as linear_activation_case
 from test_gpu_codes_out import test_conv_silu_then_codes as conv_silu_case
 from test_gpu_tiles import FORMS
@@ -69,3 +74,52 @@ def test_linear_codes_out(M, K, N, fw, fy, acc, act):
                                   (3, 200, 20, 20, 16, 1, 1, 0), (2, 256, 32, 32, 320, 1, 1, 0)])
 def test_conv_codes_out(case):
     conv_silu_case(case)
+
+
+def _codes_and_weights(M, K, N, fx, fw, seed):
+    x = synth.activations((M, K), seed)
+    sx = oracle.scale_from_absmax(oracle.absmax(x), fx[3])
+    packed, sw_t, _ = gpu_pack(synth.weights((N, K), seed + 1), fw, None, want_codes=False)
+    return dev(oracle.quantize(x, fx, sx)), dev(np.array([sx], dtype=np.float32)), packed, sw_t
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fx,fw,acc", FORMS)
+@pytest.mark.parametrize("M,K,N", [(4700, 320, 256), (9300, 272, 127), (2311, 144, 512), (18500, 64, 64)])
+def test_single_calls_have_the_bits_of_grouped_ones(M, K, N, fx, fw, acc):
+    """The same sums in the same order as on the 64 x 64 tile of the grouped call."""
+    xq, sx, packed, sw_t = _codes_and_weights(M, K, N, fx, fw, 1000 + K)
+    bias = dev(np.linspace(-1, 1, N).astype(np.float32))
+    one, group = torch.full((M, N), float("nan"), device=DEV), torch.full((M, N), float("nan"), device=DEV)
+    B.fpq_gemm(xq, 0, fx, 0.0, sx, packed, fw, sw_t, bias, one, M, N, K, acc, None)
+    B.fpq_gemm_grouped(B.gemm_problems([(xq, sx, packed, sw_t, bias, group, M, N, K)]), B.FPQ_X_CODES, fx, fw, acc, None)
+    torch.cuda.synchronize()
+    assert torch.equal(one, group)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fw", [E4M3, E2M1])
+@pytest.mark.parametrize("form", ["rows", "nchw", "codes"])
+@pytest.mark.parametrize("M,K,N", [(4700, 320, 256), (9300, 272, 127), (9217, 48, 65)])
+def test_scales_and_bias_off_16_byte_alignment(M, K, N, form, fw):
+    """sw and bias are fetched sixteen bytes at a time: from an address that is a multiple of four, and up to their last element, which
+    may be the last of its buffer."""
+    xq, sx, packed, sw_t = _codes_and_weights(M, K, N, E4M3, fw, 1100 + K)
+    bias_t = dev(np.linspace(-1, 1, N).astype(np.float32))
+    got = []
+    for off in (0, 1, 2, 3):
+        sw, bias = torch.full((off + N,), float("nan"), device=DEV), torch.full((off + N,), float("nan"), device=DEV)
+        sw[off:], bias[off:] = sw_t, bias_t
+        y = torch.full((M * N,), float("nan"), device=DEV)
+        q = torch.full((M * B.fpq_padded_channels(N),), 0xEE, dtype=torch.uint8, device=DEV)
+        if form == "rows":
+            B.fpq_gemm(xq, 0, E4M3, 0.0, sx, packed, fw, sw[off:], bias[off:], y, M, N, K, 0, None)
+        elif form == "nchw":
+            B.fpq_conv2d(xq, 0, E4M3, 0.0, sx, packed, fw, sw[off:], bias[off:], y, 1, K, 1, M, N, 1, 1, 1, 0, 0, None)
+        else:
+            B.fpq_gemm_codes_out(xq, 0, E4M3, 0.0, sx, packed, fw, sw[off:], bias[off:], E4M3, 0.01, None, q, M, N, K, 0, None)
+        torch.cuda.synchronize()
+        got.append((y.cpu().numpy(), q.cpu().numpy()))
+        assert form == "codes" or not np.isnan(got[-1][0]).any()
+    for y, q in got[1:]:
+        assert np.array_equal(y, got[0][0], equal_nan=True) and np.array_equal(q, got[0][1])

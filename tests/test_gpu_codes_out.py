@@ -53,7 +53,7 @@ def gpu_linear_codes(xq, sx, fx, packed, fw, sw_t, bias, fy, sy, M, N, K, acc, s
     return h[16:16 + M * Np].reshape(M, Np)
 
 
-# generic kernel (small or N % 160 != 0), 128-row tile, 128-row tile with a ragged last tile, split K, 256-row tile
+# generic kernel (small or N % 160 != 0), short-K kernel (K of at most 320), split K, 256-row tile
 LINEAR = [(5, 48, 3), (77, 768, 320), (130, 128, 65), (200, 1280, 130), (8192, 320, 320), (8200, 320, 480), (300, 2880, 320),
           (512, 6400, 160), (24576, 2048, 320)]
 
@@ -136,7 +136,7 @@ def check_codes_interval(got, O, tol, fy, sy, what):
     return float((got != oracle.requantize(O, fy, sy)).mean())
 
 
-# generic kernel, 128-row tile (whole and ragged), split K, 256-row tile; N % 32 == 0 for the gated form
+# generic kernel, short-K kernel (whole and ragged rows), split K, 256-row tile; N % 32 == 0 for the gated form
 ACT_SHAPES = [(77, 768, 320), (130, 128, 64), (8192, 320, 320), (8200, 320, 640), (300, 2880, 320), (24576, 2048, 320)]
 
 
@@ -315,7 +315,7 @@ def test_conv_silu_then_codes(case):
     check_codes_interval(got[:, :Cout], O, tol, fy, sy, "conv silu then codes %s" % (case,))
 
 
-CONVS = [  # B, Cin, H, W, Cout, k, stride, pad: generic kernels, large tile, large tile with split K
+CONVS = [  # B, Cin, H, W, Cout, k, stride, pad: generic kernels, short-K kernel (1 x 1), large tile, large tile with split K
     (2, 4, 9, 7, 5, 3, 1, 1), (1, 20, 6, 6, 33, 3, 2, 1), (2, 32, 5, 5, 64, 1, 1, 0), (1, 48, 12, 10, 130, 3, 1, 0),
     (2, 320, 64, 64, 320, 3, 1, 1), (2, 64, 65, 63, 160, 3, 2, 1), (1, 640, 16, 16, 160, 3, 1, 1), (8, 320, 32, 32, 320, 1, 1, 0),
 ]

@@ -1,6 +1,8 @@
 """The tiles for small problems and for widths that are no multiple of 160 (64 x 64 with K split over the wavefronts,
 128 x 64, 128 x 128, and 128 x 160 with a ragged last column), at their edges, against the oracle: remainders of rows,
-columns and K, images that end inside a lane's four pixels, accumulating and sliced forms, and results as codes."""
+columns and K, images that end inside a lane's four pixels, accumulating and sliced forms, and results as codes.
+Of shapes with one row of at most 320 codes per output, the accumulating call alone takes a tile: stored, and as codes, they are
+mostly the short-K kernel's (test_gpu_strip.py); test_unsliced_tiles_just_beyond_the_short_k has the tiles there."""
 import numpy as np
 import pytest
 import torch
@@ -118,6 +120,24 @@ def test_linear_codes_out(M, K, N, fw, fy, acc, act):
                                   (2, 16, 70, 70, 1100, 3, 1, 1), (2, 16, 63, 62, 1116, 3, 1, 1)])
 def test_conv_codes_out(case):
     conv_silu_case(case)
+
+
+@pytest.mark.parametrize("fx,fw,acc", FORMS)
+@pytest.mark.parametrize("M,K,N", [(8193, 400, 1116), (9772, 400, 749), (9772, 400, 895), (8200, 336, 640)])
+def test_unsliced_tiles_just_beyond_the_short_k(M, K, N, fx, fw, acc):
+    """128 x 160 with a ragged last column, 128 x 128 and 128 x 160 of halves, 128 x 160 with ragged rows."""
+    test_linear(M, K, N, fx, fw, acc)
+
+
+@pytest.mark.parametrize("fw,fy,acc", [(E4M3, E4M3, 0), (E2M1, E3M4, 0), (E4M3, E4M3, 1)])
+@pytest.mark.parametrize("act", ["silu", "geglu"])
+@pytest.mark.parametrize("M,K,N", [(8192, 400, 320), (8200, 336, 640)])
+def test_codes_of_128_x_160_tiles_just_beyond_the_short_k(M, K, N, fw, fy, acc, act):
+    linear_activation_case(M, K, N, fw, fy, acc, act)
+
+
+def test_conv_codes_of_128_x_160_tiles_just_beyond_the_short_k():
+    conv_silu_case((8, 336, 32, 32, 320, 1, 1, 0))
 
 
 @pytest.mark.parametrize("fx,fw,acc", FORMS)

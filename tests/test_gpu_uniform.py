@@ -138,8 +138,8 @@ def test_integer_entry_points_validate():
 
 
 @pytest.mark.parametrize("M,K,N", [(4099, 144, 1285), (5100, 272, 1024), (3000, 1040, 1793),      # 128 x 128 tiles
-                                   (70, 2064, 129), (1, 32752, 65), (513, 4112, 66),              # 64 x 64, three stages
-                                   (1100, 64, 33), (65, 2032, 64)])                               # two
+                                   (70, 2064, 129), (1, 32752, 65), (513, 4112, 66), (65, 2032, 64),   # 64 x 64, three stages
+                                   (1100, 64, 33), (65, 1904, 64), (24610, 2064, 65)])            # two: a shallow K, or many tiles
 @pytest.mark.parametrize("wbits", [8, 4])
 def test_tiles_of_the_integer_layer(M, K, N, wbits):
     test_integer_layer(M, K, N, wbits)

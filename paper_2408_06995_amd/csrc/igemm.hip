@@ -249,7 +249,7 @@ struct IGemmArgs {
 // theirs beside it) and by the stores, which the other workgroup's steps overlap.  2048 x 1280 -> 10240: 77 us staged through registers
 // with single workgroups walking along the columns, 41 us (8-bit weights; 35 us with 4-bit ones).
 template <int BX, int BW, int NST, bool W4>
-__global__ __launch_bounds__(256, (BX <= 128 ? 2 : 1)) void igemm_kernel(const IGemmArgs a)
+__global__ __launch_bounds__(256, 2) void igemm_kernel(const IGemmArgs a)
 {
     constexpr int XROWB = 128, WROWB = W4 ? 64 : 128;
     constexpr int XTILE = BX * XROWB, WTILE = BW * WROWB, STAGE = XTILE + WTILE;
@@ -453,14 +453,15 @@ int launch_int_gemm(const uint8_t* x, float sx, int zx, const fpq_int_params* px
 {
     if (M <= 0 || N <= 0) return FPQ_OK;
     IGemmArgs a{x, wrows, wsum, sw, zw, bias, px_dev, sx, zx, y, (int)M, (int)N, (int)K, (int)padded_k(K, 1)};
-    // 128 x 128 tiles where they fill the compute units and cover few columns beyond N (calibration, quantizer and layer, 8-bit weights,
-    // against 64 x 64: 2048 x 1280 -> 10240 50 and 64 us, 8192 x 640 -> 2560 41 and 46; 4000 x 1024 -> 1000, 256 tiles, 33 and 29;
-    // 32768 x 320 -> 320 45 and 36); 64 x 64 tiles with a third stage where a deep K has to hide its loads with few workgroups per
-    // compute unit (2000 x 5120 -> 640: 45 us, 52 with two), which otherwise costs the room for five of them (30000 x 64 -> 1001: 56
-    // and 47).
+    // 128 x 128 tiles where they fill the compute units, cover few columns beyond N and have 10 G multiply-adds or more to do: their rate
+    // is the higher one and their start and last round the longer ones (time of 64 x 64 over theirs, 456 layers of random sizes:
+    // 0.7 to 0.9 below that, 1.0 there, 1.1 to 1.3 beyond; K of at most 128 0.7 to 0.95 throughout.  2048 x 1280 -> 10240 57 and 41 us,
+    // 5200 x 528 -> 1024 11.9 and 17.0).  64 x 64 tiles with a third stage where a deep K has to hide its loads with at most two
+    // workgroups per compute unit (2000 x 5120 -> 640: 45 us, 52 with two stages; 32815 x 2672 -> 28, 513 tiles: 21.5 and 17.8), which
+    // otherwise costs the room for five of them (30000 x 64 -> 1001: 56 and 47).
     const int64_t tiles128 = ((M + 127) / 128) * ((N + 127) / 128), tiles64 = ((M + 63) / 64) * ((N + 63) / 64);
-    const bool large = tiles128 >= 320 && (N + 127) / 128 * 128 * 10 <= N * 11;
-    const bool third = a.Kpad >= 2048 && tiles64 <= 768;
+    const bool large = tiles128 >= 320 && (N + 127) / 128 * 128 * 10 <= N * 11 && K > 128 && M * N * K >= (int64_t)10000000000;
+    const bool third = a.Kpad >= 2048 && tiles64 <= 512;
     if (wbits == 4)
         return large ? launch_igemm_one<128, 128, 2, true>(a, st)
                      : third ? launch_igemm_one<64, 64, 3, true>(a, st) : launch_igemm_one<64, 64, 2, true>(a, st);

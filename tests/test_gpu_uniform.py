@@ -137,12 +137,36 @@ def test_integer_entry_points_validate():
     assert B.fpq_int_packed_size(320, 320, 4) == 256 + 320 * 192 + 320 * 4
 
 
-@pytest.mark.parametrize("M,K,N", [(4099, 144, 1285), (5100, 272, 1024), (3000, 1040, 1793),      # 128 x 128 tiles
+@pytest.mark.parametrize("M,K,N", [(2600, 560, 2050), (5200, 528, 1024), (3000, 1040, 1793),      # 64 x 64, two stages
+                                   (4099, 144, 1285), (5100, 272, 1024), (5100, 512, 1024),
                                    (70, 2064, 129), (1, 32752, 65), (513, 4112, 66), (65, 2032, 64),   # 64 x 64, three stages
-                                   (1100, 64, 33), (65, 1904, 64), (24610, 2064, 65)])            # two: a shallow K, or many tiles
+                                   (1100, 64, 33), (65, 1904, 64), (24610, 2064, 65)])            # two: few steps, or many tiles
 @pytest.mark.parametrize("wbits", [8, 4])
 def test_tiles_of_the_integer_layer(M, K, N, wbits):
     test_integer_layer(M, K, N, wbits)
+
+
+@pytest.mark.parametrize("M,K,N", [(17003, 144, 4101), (8201, 1104, 1157), (3001, 2080, 1793), (66000, 656, 256)])
+@pytest.mark.parametrize("wbits", [8, 4])
+def test_large_tiles_of_the_integer_layer(M, K, N, wbits):
+    """128 x 128 tiles: from 10 G multiply-adds on, with remainders of rows, columns and K; the same integers from torch's products in
+    double, which are exact below 2^53."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M + K)
+    codes = torch.randint(0, 256, (M, K), generator=g, device=DEV, dtype=torch.uint8)
+    packed, sw, zw, wq = gpu_int_pack(synth.weights((N, K), 660 + N), wbits)
+    sx, zx = 0.037, 117
+    y = torch.full((M * N + 8,), float("nan"), device=DEV)
+    ws = torch.empty(max(256, B.fpq_int_gemm_workspace_size(M)), dtype=torch.uint8, device=DEV)
+    B.fpq_int_gemm(codes, sx, zx, None, packed, wbits, sw, zw, None, y[4:4 + M * N].view(M, N), M, N, K, ws)
+    torch.cuda.synchronize()
+    assert torch.isnan(y[:4]).all() and torch.isnan(y[-4:]).all(), "written outside the result"
+    got = y[4:4 + M * N].view(M, N)
+    w = dev(wq).double() - zw.double()[:, None]
+    for lo in range(0, M, 8192):
+        ints = (codes[lo:lo + 8192].double() - zx) @ w.T
+        want = ints.float().double() * (sw * np.float32(sx)).double()[None, :]
+        assert bool(((got[lo:lo + 8192].double() - want).abs() <= 4e-7 * want.abs() + 1e-30).all())
 
 
 @pytest.mark.parametrize("n", [1, 2, 3, 4, 7, 1023, 100003])

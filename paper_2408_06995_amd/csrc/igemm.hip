@@ -245,9 +245,9 @@ struct IGemmArgs {
 // half-wave stores 128 consecutive bytes of an output row.
 // The row sums of the activation codes, which the zero points need, are taken from the fragments as they pass (one dot4 per four
 // codes, in the shadow of the matrix instructions) instead of by a kernel of their own.
-// Bound by LDS (64 x 64 outputs per wavefront read as many bytes per clock as LDS gives at the full matrix rate, and the loads write
-// theirs beside it) and by the stores, which the other workgroup's steps overlap.  2048 x 1280 -> 10240: 77 us staged through registers
-// with single workgroups walking along the columns, 41 us (8-bit weights; 35 us with 4-bit ones).
+// No unit is busy throughout (2048 x 1280 -> 10240, counters: matrix unit 0.31 of the cycles, vector instructions 0.43, LDS 0.17; wavefronts
+// wait for 0.35 of theirs): the two workgroups of a compute unit meet at a barrier per step, and 84 MB of results leave in 43 us.  Staged
+// through registers, with single workgroups walking along the columns, 77 us; 41 us (35 us with 4-bit weights).
 template <int BX, int BW, int NST, bool W4>
 __global__ __launch_bounds__(256, 2) void igemm_kernel(const IGemmArgs a)
 {

@@ -91,8 +91,9 @@ __device__ __forceinline__ SortShare sort_share(const float* x, size_t n, int pa
     return SortShare{r.lo * v, r.hi * v, n / v * v, part == 0 ? (int)(n % v) : 0};
 }
 
-// 22 us for 42 MB.  Bound by its phases in a row (load, count, scan, place, write out), one workgroup per compute unit: two of 40960 elements do not fit
-// into LDS, and smaller parts make shorter runs for the kernel that reads them.
+// 22 us for 42 MB (counters: LDS busy 0.35 of the cycles, 0.22 with conflicts of the counters' atomics, vector instructions 0.35).  Bound by
+// its phases in a row (load, count, scan, place, write out), one workgroup per compute unit: two of 40960 elements do not fit into
+// LDS, and smaller parts make shorter runs for the kernel that reads them.
 template <int E>   // elements per thread
 __global__ __launch_bounds__(1024) void search_sort_kernel(const float* __restrict__ x, size_t n,
                                                            const float* __restrict__ absmax_parts_, int nparts, int parts,
@@ -371,7 +372,8 @@ __device__ __forceinline__ uint32_t dot2(uint32_t a, uint32_t b, uint32_t c)
 }
 
 // A stretch's elements per position, 16 bits each.  A thread then owns 64 positions, a wavefront 4096: a fine interval, or a quarter of
-// a coarse one.  Bound by its phases in a row (clear, count, scan, cuts), one workgroup per compute unit: the counters take 128 KB.
+// a coarse one.  Bound by its phases in a row (clear, count, scan, cuts), one workgroup per compute unit: the counters take 128 KB
+// (10.5 M elements, 34 us: vector instructions 0.46 of the cycles, LDS 0.19).
 template <int WIDTH>
 __global__ __launch_bounds__(1024) void search_counts_kernel(const uint16_t* __restrict__ sorted, const uint16_t* __restrict__ offsets,
                                                              uint32_t task_room, const CountTask* __restrict__ tasks,
@@ -539,8 +541,8 @@ __global__ __launch_bounds__(1024) void search_counts_kernel(const uint16_t* __r
     }
 }
 
-// Element by element, 24 us where it has one tenth of 10.5 M elements (all of them: 75).  Bound by set-up and latencies of its 4352
-// workgroups, then by vector instructions and LDS accesses of the loop over an element's cuts (1.8 on average with four encodings of eight bits x
+// Element by element, 24 us where it has one tenth of 10.5 M elements (all of them: 75; vector instructions 0.56 of the cycles, LDS
+// 0.25).  Bound by vector instructions, of the set-up of its 4352 workgroups and of the loop over an element's cuts (1.8 on average with four encodings of eight bits x
 // 111 biases; a wavefront goes round as often as the element with the most).
 template <int WIDTH>
 __global__ __launch_bounds__(512) void search_terms_kernel(const uint16_t* __restrict__ sorted, const uint16_t* __restrict__ offsets,

@@ -500,9 +500,10 @@ __global__ __launch_bounds__(256) void quantize_nhwc_kernel(const float* __restr
     const int img = 4 * pq / OWN;
     float4 v[4];                                                      // of channel ch + k
     // A quad that runs over the end of its plane goes on into the next; the last one of the tensor is read from four elements before
-    // its end.  Groups without a channel read the tensor's first quad and encode nothing.
+    // its end.  Narrow patches' groups without a channel read the tensor's first quad and encode nothing.
     const size_t last = (size_t)B * C * HW - 4;
-    auto at = [&](int b, int k) { return left > 0 ? ((size_t)b * C + min(ch + k, C - 1)) * HW + p : 0; };
+    const bool some = GROUPS == 16 || left > 0;                       // (few patches of 64 channels have groups without any)
+    auto at = [&](int b, int k) { return some ? ((size_t)b * C + min(ch + k, C - 1)) * HW + p : 0; };
     auto load = [&](int b) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) v[k] = load_any(x + (at(b, k) < last ? at(b, k) : last), stream);
@@ -512,13 +513,13 @@ __global__ __launch_bounds__(256) void quantize_nhwc_kernel(const float* __restr
     load(b + img);
     const float r = fold_end(ss, f);
     for (;;) {
-        if (p < HW && b + img < B && at(b + img, 3) > last) {
+        if (p < HW && (IMAGES == 1 || b + img < B) && at(b + img, 3) > last) {
 #pragma unroll
             for (int k = 0; k < 4; ++k)
                 for (size_t late = last; late < at(b + img, k); ++late) v[k] = make_float4(v[k].y, v[k].z, v[k].w, 0.0f);
         }
         uint32_t* to = tile + 4 * pq * LDW + cg;
-        if (left > 0) {
+        if (some) {
             to[0] = first_codes(quantize4<YKIND>(v[0].x, v[1].x, v[2].x, v[3].x, r, q), left);
             to[LDW] = first_codes(quantize4<YKIND>(v[0].y, v[1].y, v[2].y, v[3].y, r, q), left);
             to[2 * LDW] = first_codes(quantize4<YKIND>(v[0].z, v[1].z, v[2].z, v[3].z, r, q), left);
@@ -529,7 +530,7 @@ __global__ __launch_bounds__(256) void quantize_nhwc_kernel(const float* __restr
         __syncthreads();
         const int row = threadIdx.x / PARTS, part = threadIdx.x % PARTS;
         const int out_b = b + row / OWN, out_p = p0 + row % OWN, out_ch = c0 + part * 16;
-        if (out_b < B && out_p < HW && out_ch < Cp) {
+        if ((IMAGES == 1 || out_b < B) && out_p < HW && out_ch < Cp) {
             const uint32_t* t4 = tile + row * LDW + part * 4;
             *reinterpret_cast<uint4*>(codes + ((size_t)out_b * HW + out_p) * (size_t)Cp + out_ch) = make_uint4(t4[0], t4[1], t4[2], t4[3]);
         }

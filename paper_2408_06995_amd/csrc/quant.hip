@@ -603,16 +603,19 @@ int launch_quantize_nhwc(const float* x, int64_t B, int64_t C, int64_t H, int64_
     const int Cp = (int)padded_channels(C), HW = (int)(H * W), kind = hw_kind(q);
     // One channel: planes of fewer than 64 pixels as rows (100000 of 2 x 2: 6.6 us, a patch per image 49.9 us); from 64 on in patches, where
     // a lane has four pixels and not a quarter of one (4 x 1024 x 1024: 19.8 us, rows 31.2 us; 30000 x 8 x 8: 11.2 and 18.5 us).
-    // Patches have the channels that Cp fills, and of small planes several images (20000 x 3 x 8 x 8: 8.4 us, an image each 22.5 us).
+    // Where 64-channel patches would be more than two per compute unit, patches have the channels that Cp fills, and of small planes
+    // several images (20000 x 3 x 8 x 8: 8.4 us, an image each 22.5 us; fewer patches are one round of latencies, which the narrow
+    // ones' exchange through LDS makes longer: 8 x 32 x 32 x 32 2.22 us, narrow 2.37).
+    const bool narrow = B * ((HW + 63) / 64) > 512;
     if (HW == 1 || (C == 1 && HW < 64)) {
         const uint32_t words = (uint32_t)(B * HW * (Cp / 4));
         auto kern = kind == 1 ? quantize_rows_kernel<1> : kind == 2 ? quantize_rows_kernel<2> : quantize_rows_kernel<0>;
         hipLaunchKernelGGL(kern, dim3(grid_for(words, 1024)), dim3(256), 0, st, x, words, (int)C, Cp / 4, q, ss,
                            reinterpret_cast<uint32_t*>(codes));
-    } else if (Cp <= 16) {                                            // at least four elements
+    } else if (narrow && Cp <= 16) {                                  // at least four elements
         HW > 64 ? launch_nhwc_patches<4, 1>(x, (int)B, (int)C, Cp, HW, q, ss, codes, st)
                 : launch_nhwc_patches<4, 4>(x, (int)B, (int)C, Cp, HW, q, ss, codes, st);
-    } else if (Cp <= 32) {
+    } else if (narrow && Cp <= 32) {
         HW > 64 ? launch_nhwc_patches<8, 1>(x, (int)B, (int)C, Cp, HW, q, ss, codes, st)
                 : launch_nhwc_patches<8, 2>(x, (int)B, (int)C, Cp, HW, q, ss, codes, st);
     } else {

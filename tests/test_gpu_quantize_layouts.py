@@ -14,9 +14,10 @@ pytestmark = pytest.mark.gpu
 
 SHAPES = [(1, 1, 1, 3), (2, 1, 3, 5), (1, 2, 1, 2), (3, 3, 1, 3), (2, 5, 1, 1), (7, 17, 1, 1), (600, 33, 1, 1), (1, 15, 7, 9),
           (2, 16, 8, 8), (3, 66, 5, 13), (2, 64, 9, 7), (5, 130, 2, 2), (1, 200, 13, 53), (66000, 2, 1, 2),
-          # patches of 16 and 32 channels: several images of up to 64 pixels side by side, planes of one patch and one pixel more
-          (9, 3, 8, 8), (5, 16, 7, 9), (4, 1, 8, 8), (3, 1, 5, 13), (3, 17, 8, 8), (5, 32, 7, 9), (2, 4, 16, 16), (3, 3, 1, 257),
-          (2, 20, 8, 16), (1, 32, 3, 43), (263000, 2, 1, 2), (132000, 17, 1, 2), (66000, 33, 1, 2)]
+          # patches of 16 and 32 channels, from 513 of 64 pixels on: several images of up to 64 pixels side by side, planes of one patch
+          # and one pixel more
+          (514, 3, 8, 8), (515, 16, 7, 9), (513, 1, 8, 8), (260, 1, 5, 13), (513, 17, 8, 8), (514, 32, 7, 9), (130, 4, 16, 16), (150, 3, 1, 257),
+          (257, 20, 8, 16), (172, 32, 3, 43), (512, 3, 8, 8), (512, 32, 8, 8), (263000, 2, 1, 2), (132000, 17, 1, 2), (66000, 33, 1, 2)]
 
 
 def padded(codes, C):

@@ -283,6 +283,9 @@ int fpq_conv2d(const void *x, int x_is_fp32, fpq_format_t fx, float sx, const fl
  * and some of them FPQ_KERNEL_SMALL_TILE, unsliced, whatever the shape; with FPQ_OUT_ACCUMULATE, and with E2M1 weights
  * for some K of at most 128, a shape of FPQ_KERNEL_STRIP takes one of the tiles).
  * With more than one slice the layer kernel writes partial sums to the workspace and a reduction kernel adds them.
+ * It is the plan that the workspace is sized for.  fp32 results in FPQ_ACC_FP32 take tiles of 128 x 80 or 64 x 80 outputs in one
+ * slice in its place, with no workspace of their own, where those are faster: convolutions, and linear layers with K above 1024
+ * and more than twelve tiles of 64 x 64.
  * For tests and benchmarks that have to state, or to cover, every launch configuration a workload uses. */
 typedef enum fpq_kernel {
     FPQ_KERNEL_SMALL_TILE = 0, /* tiles of at most 128 x 128 outputs: any shape */

@@ -13,7 +13,7 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libfpq.so")
 CALLS = os.path.join(HERE, "_fpqcall.so")
 OBJ = os.path.join(HERE, "_build")
-SOURCES = ["api.hip", "quant.hip", "search.hip", "sparsity.hip", "rounding.hip", "gemm.hip", "gemm_dma.hip", "gemm_dma_q.hip", "gemm_dma_s.hip", "gemm_dma_sq.hip", "gemm_strip.hip", "gemm_strip_h.hip", "gemm_strip_q.hip", "gemm_wk.hip", "gemm_wk_q.hip", "peaks.hip", "gemm_sparse.hip", "igemm.hip"]
+SOURCES = ["api.hip", "quant.hip", "search.hip", "sparsity.hip", "rounding.hip", "gemm.hip", "gemm_dma.hip", "gemm_dma_q.hip", "gemm_dma_s.hip", "gemm_dma_sq.hip", "gemm_strip.hip", "gemm_strip_h.hip", "gemm_strip_q.hip", "gemm_wk.hip", "gemm_wk_q.hip", "gemm_wk16.hip", "gemm_wk16_h.hip", "peaks.hip", "gemm_sparse.hip", "igemm.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 

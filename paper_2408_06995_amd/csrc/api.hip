@@ -551,6 +551,14 @@ static int run_layer(const CodesOut* out, const void* x, int x_is_fp32, fpq_form
                                           : plan_gemm(M, Cout, kpad, xkind == OPK_HALF8 ? PLAN_HALF
                                                                      : conv_out         ? (out ? PLAN_CONV_CODES : PLAN_CONV)
                                                                                         : (out ? PLAN_LINEAR_CODES : PLAN_LINEAR));
+    // the tiles of 128 x 80 and 64 x 80, which need no workspace: it is sized for the other plan all the same, so that what a caller has
+    // to bring does not depend on the choice
+    const bool own_sums = conv_out || (kpad > 1024 && ((M + 63) / 64) * ((Cout + 63) / 64) > 12);   // (see plan_over_waves)
+    const GemmPlan over_waves = !out && !sparse && acc_mode == FPQ_ACC_FP32 && xkind != OPK_GENERIC8 && kh * kw <= 31 && own_sums
+                                    ? plan_over_waves(plan, M, Cout, Cp * kh * kw,
+                                                      xkind == OPK_HALF8 ? PLAN_HALF : conv_out ? PLAN_CONV : PLAN_LINEAR,
+                                                      conv_out && ((Ho * Wo) & 3) != 0)
+                                    : plan;
     if (sparse) {
         // the structured-sparse form has one kernel: hardware E4M3 activations, E4M3 / E2M1 weights, exact accumulate
         if (out || accumulate || acc_mode != FPQ_ACC_FP32 || xkind != OPK_FP8 || (wkind != OPK_FP8 && wkind != OPK_FP4))
@@ -567,6 +575,7 @@ static int run_layer(const CodesOut* out, const void* x, int x_is_fp32, fpq_form
     if (x_is_fp32 && (!workspace || workspace_bytes < codes_bytes + part_bytes + (dyn ? kDynScaleBytes : 0)))
         return FPQ_ERR_WORKSPACE;
     if (!x_is_fp32 && (!workspace || workspace_bytes < part_bytes)) plan.splits = 1;
+    if (over_waves.tile > TILE_WAVE_K2) plan = over_waves;
     float* partial = plan.splits > 1 ? reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + codes_bytes) : nullptr;
     GemmArgs a;
     memset(&a, 0, sizeof a);
@@ -583,6 +592,9 @@ static int run_layer(const CodesOut* out, const void* x, int x_is_fp32, fpq_form
     a.B = (int)B; a.H = (int)H; a.W = (int)W; a.Cp = (int)Cp;
     a.Ho = (int)Ho; a.Wo = (int)Wo;
     a.kh = kh; a.kw = kw; a.stride = stride; a.pad = pad;
+    a.by_hw = divisor(Ho * Wo); a.by_wo = divisor(Wo); a.by_cp = divisor(Cp); a.by_kw = divisor(kw);
+    if (kh * kw <= 31)
+        for (int r = 0; r < kh; ++r) a.tap_rows |= 1u << (r * kw);
     a.conv_out = conv_out;
     a.xkind = xkind; a.wkind = wkind;
     a.xe = fx.ebits; a.xm = fx.mbits; a.xb = fx.bias;

@@ -69,6 +69,19 @@ enum OperandKind : int {
     OPK_HALF4 = 6     // the same with two codes per byte
 };
 
+// Division of 0 <= n < 2^31 by a positive d, for kernels: n / d = mulhi(2 n, mul) >> shift with shift = ceil(log2 d) and
+// mul = ceil(2^(31 + shift) / d) < 2^32.  (n mul / 2^(31 + shift) exceeds n / d by n e / (d 2^(31 + shift)) with e < d <= 2^shift: by less
+// than 1 / d.)
+struct Divisor {
+    uint32_t mul, shift;
+};
+static inline Divisor divisor(int64_t d)
+{
+    uint32_t s = 0;
+    while (((int64_t)1 << s) < d) ++s;
+    return Divisor{(uint32_t)((((uint64_t)1 << (31 + s)) + (uint64_t)d - 1) / (uint64_t)d), s};
+}
+
 struct GemmArgs {
     const uint8_t* x;       // activation codes, channels-last [B, H, W, Cp] (linear: [M, K])
     const uint8_t* wrows;   // packed weight rows (after the header)
@@ -84,6 +97,8 @@ struct GemmArgs {
     int B, H, W, Cp;        // activation geometry (linear: B = M, H = W = 1)
     int Ho, Wo;
     int kh, kw, stride, pad;
+    Divisor by_hw, by_wo, by_cp, by_kw;   // Ho Wo, Wo, Cp, kw
+    uint32_t tap_rows;      // bit r kw for every kernel row r (kernels of at most 31 taps)
     int conv_out;           // 1: y is NCHW [B, N, Ho, Wo]; 0: y is [M, N]
     int xkind, wkind;       // OperandKind
     int xe, xm, xb;         // activation format (for the generic decode)
@@ -140,7 +155,9 @@ enum GemmTile : int {
     TILE_128x64 = 3,     // the same pipeline on smaller tiles, two workgroups per compute unit
     TILE_128x128 = 4,
     TILE_WAVE_K4 = 5,    // 64 x 64 tiles, K split over the wavefronts (gemm_wk_kernel.h): four stages, one workgroup per compute unit
-    TILE_WAVE_K2 = 6     // two stages, two workgroups
+    TILE_WAVE_K2 = 6,    // two stages, two workgroups
+    TILE_WAVE_128x80 = 7, // K split over the wavefronts, blocks of 16 x 16, one workgroup per compute unit (gemm_wk16_kernel.h)
+    TILE_WAVE_64x80 = 8
 };
 struct GemmPlan {
     int tile;
@@ -296,6 +313,56 @@ static inline GemmPlan plan_gemm(int64_t M, int64_t N, int64_t Kpad, PlanForm fo
     if (unsliced_part_grid(p, M, N, nk)) p.tile = TILE_128x64;
     return p;
 }
+// The tiles of gemm_wk16_kernel.h (128 x 80 or 64 x 80, K split over the wavefronts, one workgroup per compute unit, one K slice)
+// in the place of a plan of plan_gemm, where a model of the time finds the better of them at least 10 % faster: fp32 results in the
+// exact mode, operands with a hardware conversion or moved into halves, kernels of at most 31 taps.  us = t[0] + rounds (t[1] + t[2]
+// steps): rounds of 256 tiles, each with its start and its end (nothing overlaps them) and steps of 4 x 64 codes; the other kernels as
+// in plan_unsliced, sliced ones t[0] + t[1] steps of 128 codes per slice + t[2] us per million partial sums.  Constants fitted to 2600
+// layers of random sizes; over those the choice takes 0.90 of the other plans' time in the geometric mean (the best of all tiles 0.89),
+// sliced ones of convolutions 0.6, and at most 23 are slower by more than 3 %.
+//   - Sliced 160-wide tiles of convolutions lose throughout (8 x 1280 x 16 x 16 -> 1280, 3 x 3: 57 + 10 us in four slices, 46 us here),
+//     as do 256-row tiles of images that are no multiple of four pixels, whose stores are single elements.
+//   - Linear layers with K of at most 1024, or with at most twelve 64 x 64 tiles, keep their kernels: their sums are those of the
+//     grouped call, bit for bit.  What K4 cuts into slices keeps them: few tiles.
+static inline GemmPlan plan_over_waves(const GemmPlan& p, int64_t M, int64_t N, int64_t Kreal, PlanForm form, bool ragged_images)
+{
+    static const float us_here[3][2][3] = {
+        {{-0.4f, 6.3f, 0.777f}, {0.7f, 4.3f, 0.458f}}, {{0.8f, 6.2f, 0.704f}, {1.6f, 4.1f, 0.43f}}, {{0.85f, 6.3f, 1.18f}, {1.75f, 4.2f, 0.778f}}};
+    static const float us_whole[3][7][3] = {
+        {{4.2f, -0.03f, 0.413f}, {3.9f, 6.3f, 1.84f}, {2.0f, 3.0f, 1.09f}, {8.9f, -2.6f, 0.602f}, {4.0f, 2.2f, 0.924f}, {4.1f, 0.0f, 0.316f},
+         {8.75f, -2.4f, 0.381f}},
+        {{6.3f, 0.26f, 0.466f}, {3.0f, 7.0f, 1.95f}, {1.0f, 7.4f, 1.07f}, {6.0f, 0.84f, 0.64f}, {2.8f, 5.7f, 0.91f}, {4.9f, 0.0f, 0.295f},
+         {9.4f, -2.3f, 0.339f}},
+        {{5.1f, 0.68f, 0.864f}, {3.0f, 9.0f, 2.6f}, {-2.0f, 9.6f, 1.78f}, {21.0f, -6.5f, 0.985f}, {1.4f, 6.6f, 1.35f}, {5.0f, 0.0f, 0.417f},
+         {13.2f, -5.0f, 0.493f}}};
+    static const float us_sliced[4][3] = {{-1.4f, 2.2f, 2.8f}, {-1.4f, 1.64f, 2.8f}, {-8.5f, 1.0f, 6.4f}, {0.0f, 1.6f, 5.0f}};   // linear layers
+    static const int bx[7] = {64, 256, 128, 128, 128, 64, 64}, bw[7] = {64, 160, 160, 64, 128, 64, 64};
+    const int f = form == PLAN_LINEAR ? 0 : form == PLAN_CONV ? 1 : form == PLAN_HALF ? 2 : -1;
+    if (f < 0 || p.tile > TILE_WAVE_K2 || (p.tile == TILE_WAVE_K4 && p.splits > 1)) return p;
+    auto tiles = [&](int64_t x, int64_t w) { return ((M + x - 1) / x) * ((N + w - 1) / w); };
+    const double steps = (double)((Kreal + 255) / 256), nk = (double)((Kreal + 127) / 128);
+    double us[2];
+    for (int i = 0; i < 2; ++i) {
+        const float* t = us_here[f][i];
+        us[i] = t[0] + (double)((tiles(i ? 64 : 128, 80) + 255) / 256) * (t[1] + t[2] * steps);
+    }
+    const GemmPlan here{us[0] < us[1] ? TILE_WAVE_128x80 : TILE_WAVE_64x80, 1};
+    double other;
+    if (p.splits > 1) {
+        if (f != 0) return here;
+        const float* t = us_sliced[p.tile - 1];
+        other = t[0] + t[1] * nk / p.splits + t[2] * (double)p.splits * (double)M * (double)N * 1e-6;
+    } else {
+        if (f == 1 && p.tile == TILE_256x160_S3 && ragged_images) return here;
+        const double n = (double)tiles(bx[p.tile], bw[p.tile]), per = n / 256.0, up = (double)(((int64_t)n + 255) / 256);
+        const double w = p.tile == TILE_GENERIC || p.tile >= TILE_WAVE_K4 ? (per > 1.0 ? per : 1.0)
+                         : p.tile == TILE_256x160_S3                     ? up
+                                                                         : (n <= 256 ? 1.1 : 0.5 * (up + per));
+        const float* t = us_whole[f][p.tile];
+        other = t[0] + w * (t[1] + t[2] * nk);
+    }
+    return (us[0] < us[1] ? us[0] : us[1]) < 0.9 * other ? here : p;
+}
 // Operands decoded arithmetically (five exponent bits and more): the small tiles are not built for them, so widths that are
 // multiples of 160 keep the 160-wide tiles and their slices (E5M2, 256 x 11520 -> 1280: 70 us, 209 us on the register-staged
 // kernel; 40 x 5120 -> 1280: 60 and 92 us; 4096 x 2880 -> 320: 86 and 98 us).  The register-staged kernel serves small outputs with
@@ -412,6 +479,8 @@ int launch_gemm_dma_s(const GemmArgs& a, hipStream_t st);   // small tiles
 int launch_gemm_dma_sq(const GemmArgs& a, hipStream_t st);
 int launch_gemm_wk(const GemmArgs& a, hipStream_t st);      // K split over the wavefronts
 int launch_gemm_wk_q(const GemmArgs& a, hipStream_t st);
+int launch_gemm_wk16(const GemmArgs& a, hipStream_t st);    // the same in blocks of 16 x 16
+int launch_gemm_wk16_h(const GemmArgs& a, hipStream_t st);
 bool gemm_strip_applicable(const GemmArgs& a);              // weights in registers: a short K (gemm_strip_kernel.h)
 int launch_gemm_strip(const GemmArgs& a, hipStream_t st);
 int launch_gemm_strip_h(const GemmArgs& a, hipStream_t st);

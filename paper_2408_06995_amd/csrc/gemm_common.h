@@ -61,6 +61,25 @@ __device__ __forceinline__ int lds_off(int row, int c)
     return row * 64 + ((c ^ ((row >> 2) & 3)) << 4);
 }
 
+// ---------------------------------------------------------------------------------- convolution geometry
+
+__device__ __forceinline__ int divide(int n, const Divisor& d) { return (int)(__umulhi(2u * (unsigned)n, d.mul) >> d.shift); }
+
+// Output pixel m: byte offset of its tap (0, 0), channel 0 in the channels-last codes (wraps below zero for halo rows), and its taps that
+// lie inside the image, bit r kw + c.  Valid kernel columns and rows are ranges; a multiplication repeats the one's bits at the
+// other's: about 25 instructions where a loop over nine taps and two divisions by the compiler take 120 (they are all that a workgroup
+// does before its first load goes out).
+__device__ __forceinline__ void conv_row(const GemmArgs& a, int m, unsigned& base, unsigned& taps)
+{
+    const int bi = divide(m, a.by_hw), rem = m - bi * (a.Ho * a.Wo);
+    const int ho = divide(rem, a.by_wo), wo = rem - ho * a.Wo;
+    const int hi0 = ho * a.stride - a.pad, wi0 = wo * a.stride - a.pad;
+    base = (unsigned)(((bi * a.H + hi0) * a.W + wi0) * a.Cp);
+    const int c0 = min(max(-wi0, 0), a.kw), c1 = min(max(a.W - wi0, 0), a.kw);
+    const int r0 = min(max(-hi0, 0), a.kh), r1 = min(max(a.H - hi0, 0), a.kh);
+    taps = (a.tap_rows & ((1u << (r1 * a.kw)) - (1u << (r0 * a.kw)))) * ((1u << c1) - (1u << c0));
+}
+
 // ---------------------------------------------------------------------------------- code -> bf16
 
 // Eight codes (two dwords for one-code-per-byte operands, one dword for 4-bit operands) to the

@@ -138,6 +138,7 @@ bool gemm_dma_applicable(const GemmArgs& a)
 
 int launch_gemm_dma(const GemmArgs& a, hipStream_t st)
 {
+    if (a.tile == TILE_WAVE_128x80 || a.tile == TILE_WAVE_64x80) return launch_gemm_wk16(a, st);
     if (a.tile == TILE_WAVE_K4 || a.tile == TILE_WAVE_K2) return a.yq ? launch_gemm_wk_q(a, st) : launch_gemm_wk(a, st);
     if (a.tile == TILE_128x64 || a.tile == TILE_128x128) return a.yq ? launch_gemm_dma_sq(a, st) : launch_gemm_dma_s(a, st);
     if (a.yq) return launch_gemm_dma_q(a, st);

@@ -46,7 +46,7 @@ __device__ __forceinline__ void gemm_wk_tile(const GemmArgs& a, int item, uint8_
 
     // this wavefront's steps of 64 codes
     const int nks = (a.Kreal + 63) / 64;
-    const int s_lo = (int)((long)nks * sl / a.splits), s_cnt = (int)((long)nks * (sl + 1) / a.splits) - s_lo;
+    const int s_lo = nks * sl / a.splits, s_cnt = nks * (sl + 1) / a.splits - s_lo;   // (at most 2^25 steps, 32 slices)
     const int k_lo = s_lo + s_cnt * wave / 4, nk = s_lo + s_cnt * (wave + 1) / 4 - k_lo;
 
     // ---- loads: load i of the activations covers rows 16 i .. + 15; lane p holds row p / 4 of them, LDS chunk p % 4, i.e. logical
@@ -60,40 +60,21 @@ __device__ __forceinline__ void gemm_wk_tile(const GemmArgs& a, int item, uint8_
     int x_k = k_lo * 64 + xc * 16, x_ci = x_k, x_kh = 0, x_kw = 0, x_tap = 0, x_sel = 31;
     unsigned x_delta = 0;
     {
-        int hi0[XLD], wi0[XLD];
 #pragma unroll
         for (int i = 0; i < XLD; ++i) {
             const int m = m0 + 16 * i + (lane >> 2);
-            const bool rowok = m < a.M;
-            hi0[i] = wi0[i] = 0;
             if (CONV) {
-                const int hw = a.Ho * a.Wo;
-                const int bi = m / hw, rem = m - bi * hw;
-                const int ho = rem / a.Wo, wo = rem - ho * a.Wo;
-                hi0[i] = ho * a.stride - a.pad;
-                wi0[i] = wo * a.stride - a.pad;
-                xbase[i] = (unsigned)(((bi * a.H + hi0[i]) * a.W + wi0[i]) * a.Cp);
-                xmask[i] = 0;
-                if (!rowok) hi0[i] = -0x10000;                     // no tap of this row lies inside
+                conv_row(a, m, xbase[i], xmask[i]);
+                if (m >= a.M) xmask[i] = 0u;                       // no tap of this row lies inside
             } else {
                 xbase[i] = (unsigned)m * (unsigned)a.Cp;
-                xmask[i] = rowok ? 1u : 0u;
+                xmask[i] = m < a.M ? 1u : 0u;
             }
         }
         if (CONV) {
-            int r = 0, c = 0;
-            const int ntaps = a.kh * a.kw;
-            for (int t = 0; t < ntaps; ++t) {
-#pragma unroll
-                for (int i = 0; i < XLD; ++i) {
-                    const bool ok = ((unsigned)(hi0[i] + r) < (unsigned)a.H) & ((unsigned)(wi0[i] + c) < (unsigned)a.W);
-                    xmask[i] |= ok ? (1u << t) : 0u;
-                }
-                if (++c == a.kw) { c = 0; ++r; }
-            }
-            x_tap = x_k / a.Cp;
+            x_tap = divide(x_k, a.by_cp);
             x_ci = x_k - x_tap * a.Cp;
-            x_kh = x_tap / a.kw;
+            x_kh = divide(x_tap, a.by_kw);
             x_kw = x_tap - x_kh * a.kw;
         }
         const unsigned wrow_bytes = W4 ? (unsigned)a.Kpad / 2 : (unsigned)a.Kpad;

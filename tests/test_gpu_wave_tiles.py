@@ -1,0 +1,156 @@
+"""The 128 x 80 and 64 x 80 tiles with K split over the wavefronts, at their edges, against the oracle: remainders of rows, columns and
+K, fewer steps of 64 codes than wavefronts, channels that wrap several taps a step, images that end inside a lane's four pixels, results that
+are added.  Each case first asks the rule, compiled here for the host, which of the two tiles its shape takes."""
+import functools
+import os
+import subprocess
+import tempfile
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2408_06995_amd import binding as B
+from paper_2408_06995_amd import synth
+from gpu_util import DEV, check_close, dev, gpu_pack
+
+E4M3, E2M1, E3M4, E3M0 = synth.E4M3, synth.E2M1, synth.E3M4, synth.E3M0
+FORMS = [(E4M3, E4M3), (E4M3, E2M1), (E3M4, E3M4), (E3M4, E3M0)]
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2408_06995_amd", "csrc")
+PROGRAM = r"""
+#include <stdio.h>
+#include "fpq_host.h"
+using namespace fpq;
+int main()
+{
+    // the divisions of the kernels: around every multiple, at the ends of the range
+    const long long top = (1ll << 31) - 1;
+    for (long long d : {1ll, 2ll, 3ll, 5ll, 7ll, 16ll, 53ll, 64ll, 80ll, 961ll, 4096ll, 65535ll, 65536ll, 1000003ll, (1ll << 30) - 1, 1ll << 30, top - 1, top}) {
+        const Divisor by = divisor(d);
+        for (long long q = 0; q * d <= top; q += q < 1000 ? 1 : q / 7 + 1)
+            for (long long n = q * d - 1; n <= q * d + 1; ++n)
+                if (n >= 0 && n <= top && (long long)((((unsigned long long)(2 * n) * by.mul) >> 32) >> by.shift) != n / d)
+                    return printf("%lld / %lld\n", n, d), 1;
+    }
+    long long M, N, K;
+    int form, ragged;
+    while (scanf("%lld %lld %lld %d %d", &M, &N, &K, &form, &ragged) == 5) {
+        const GemmPlan p = plan_gemm(M, N, (K + 127) / 128 * 128, (PlanForm)form);
+        printf("%d\n", plan_over_waves(p, M, N, K, (PlanForm)form, ragged != 0).tile);
+    }
+    return 0;
+}
+"""
+LINEAR, CONV, HALF = 0, 1, 4          # PlanForm
+T128, T64 = 7, 8                      # GemmTile
+
+
+@functools.lru_cache(maxsize=None)
+def program():
+    d = tempfile.mkdtemp()
+    with open(os.path.join(d, "rule.cpp"), "w") as f:
+        f.write(PROGRAM)
+    exe = os.path.join(d, "rule")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-w", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", CSRC, os.path.join(d, "rule.cpp"),
+                           "-o", exe])
+    return exe
+
+
+def tile_of(M, N, K, form, ragged=False):
+    return int(subprocess.run([program()], input="%d %d %d %d %d\n" % (M, N, K, form, ragged), capture_output=True, text=True,
+                              check=True).stdout)
+
+
+def test_divisions_and_what_keeps_its_plan():
+    assert tile_of(4096, 320, 2880, CONV) == T64 and tile_of(2048, 1280, 11520, CONV) == T128 and tile_of(2048, 1280, 11520, HALF) == T128
+    for M, N, K, form in [(32768, 320, 5760, CONV), (32768, 320, 1280, LINEAR), (64, 320, 11520, CONV), (8, 1280, 1280, LINEAR),
+                          (2048, 1280, 11520, 2), (2048, 1280, 11520, 3)]:                 # the last two: results as codes
+        assert tile_of(M, N, K, form) < T128, (M, N, K, form)
+
+
+# M, K, N, tile
+LINEAR_CASES = [(2048, 4096, 1280, T128), (2047, 1584, 1279, T128), (1407, 4544, 641, T64), (3000, 3632, 641, T128), (2049, 4640, 321, T64)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fx,fw", FORMS)
+@pytest.mark.parametrize("M,K,N,tile", LINEAR_CASES)
+def test_linear(M, K, N, tile, fx, fw):
+    print(M, K, N, fx, fw, flush=True)
+    if fx == E4M3:
+        assert tile_of(M, N, K, LINEAR) == tile, "this shape no longer takes the tile it is here to cover"
+    x = synth.activations((M, K), 400 + M)
+    w = synth.weights((N, K), 500 + N)
+    bias = np.linspace(-1, 1, N).astype(np.float32) if N % 2 else None
+    sx = oracle.scale_from_absmax(oracle.absmax(x), fx[3])
+    xq = oracle.quantize(x, fx, sx)
+    wq, sw = oracle.pack_weights(w, fw, None)
+    rows = np.unique(np.concatenate([np.arange(70), np.arange(M - 140, M), np.random.default_rng(M).integers(0, M, 60)]))
+    Y, T = oracle.gemm(xq, fx, sx, wq, fw, sw, bias, rows=rows)
+    packed, sw_t, _ = gpu_pack(w, fw, None, want_codes=False)
+    buf = torch.full((M * N + 8,), float("nan"), dtype=torch.float32, device=DEV)
+    y = buf[4:4 + M * N].view(M, N)
+    ws = torch.empty(max(256, B.fpq_gemm_workspace_size(M, N, K, 0)), dtype=torch.uint8, device=DEV)
+
+    def run(flag):
+        B.fpq_gemm(dev(xq), 0, fx, sx, None, packed, fw, sw_t, None if bias is None else dev(bias), y, M, N, K, flag, ws)
+        torch.cuda.synchronize()
+
+    run(0)
+    once = y.cpu().numpy().copy()
+    assert not np.isnan(once).any(), "unwritten outputs"
+    check_close(once[rows], Y, T, what="linear")
+    y.fill_(1.0)
+    run(B.FPQ_OUT_ACCUMULATE)
+    h = buf.cpu().numpy()
+    assert np.isnan(h[:4]).all() and np.isnan(h[-4:]).all(), "written outside the result"
+    assert np.allclose(h[4:-4].reshape(M, N), once + np.float32(1), rtol=1e-6, atol=1e-6 * np.abs(once).max())
+
+
+# B, Cin, H, W, Cout, kernel, stride, padding, tile
+CONV_CASES = [(8, 256, 16, 16, 1280, 3, 1, 1, T128), (3, 200, 75, 53, 392, 3, 2, 1, T64), (5, 33, 37, 57, 79, 3, 1, 0, T64),
+              (2, 640, 33, 31, 80, 1, 1, 0, T64), (6, 48, 25, 61, 239, 5, 1, 2, T128), (7, 20, 59, 35, 79, 5, 2, 2, T64),
+              (300, 384, 3, 1, 640, 3, 1, 1, T64), (2, 20, 21, 45, 321, 5, 2, 3, T64), (4, 33, 36, 47, 321, 3, 1, 0, T128)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fx,fw", FORMS)
+@pytest.mark.parametrize("case", CONV_CASES)
+def test_conv(case, fx, fw):
+    print(case, fx, fw, flush=True)
+    Bn, Cin, H, W, Cout, k, stride, pad, tile = case
+    Ho, Wo = (H + 2 * pad - k) // stride + 1, (W + 2 * pad - k) // stride + 1
+    M = Bn * Ho * Wo
+    if fx == E4M3:
+        assert tile_of(M, Cout, k * k * B.fpq_padded_channels(Cin), CONV, Ho * Wo % 4 != 0) == tile, \
+            "this shape no longer takes the tile it is here to cover"
+    x = synth.activations((Bn, Cin, H, W), 600 + Cin)
+    w = synth.weights((Cout, Cin, k, k), 700 + Cout)
+    bias = np.linspace(-0.5, 0.5, Cout).astype(np.float32) if Cout % 4 else None
+    sx = oracle.scale_from_absmax(oracle.absmax(x), fx[3])
+    xq = oracle.quantize(x, fx, sx)
+    wq, sw = oracle.pack_weights(w, fw, None)
+    pos = np.unique(np.concatenate([np.arange(70), np.arange(M - 140, M), np.random.default_rng(M).integers(0, M, 60)]))
+    Y, T = oracle.conv2d(xq, fx, sx, wq, fw, sw, bias, stride=stride, pad=pad, pix=pos)
+    packed, sw_t, _ = gpu_pack(w, fw, None, want_codes=False)
+    codes = torch.empty(Bn * H * W * B.fpq_padded_channels(Cin), dtype=torch.uint8, device=DEV)
+    B.fpq_quantize_nhwc(dev(x), fx, sx, None, codes)
+    buf = torch.full((M * Cout + 8,), float("nan"), dtype=torch.float32, device=DEV)
+    y = buf[4:4 + M * Cout]
+    ws = torch.empty(max(256, B.fpq_conv2d_workspace_size(Bn, Cin, H, W, Cout, k, k, stride, pad, 0)), dtype=torch.uint8, device=DEV)
+
+    def run(flag):
+        B.fpq_conv2d(codes, 0, fx, sx, None, packed, fw, sw_t, None if bias is None else dev(bias), y, Bn, Cin, H, W, Cout, k, k, stride,
+                     pad, flag, ws)
+        torch.cuda.synchronize()
+
+    run(0)
+    once = y.cpu().numpy().copy()
+    assert not np.isnan(once).any(), "unwritten outputs"
+    check_close(once.reshape(Bn, Cout, Ho * Wo)[pos // (Ho * Wo), :, pos % (Ho * Wo)], Y, T, what="conv")
+    y.fill_(1.0)
+    run(B.FPQ_OUT_ACCUMULATE)
+    h = buf.cpu().numpy()
+    assert np.isnan(h[:4]).all() and np.isnan(h[-4:]).all(), "written outside the result"
+    assert np.allclose(h[4:-4], once + np.float32(1), rtol=1e-6, atol=1e-6 * np.abs(once).max())

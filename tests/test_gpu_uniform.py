@@ -169,6 +169,13 @@ def test_large_tiles_of_the_integer_layer(M, K, N, wbits):
         assert bool(((got[lo:lo + 8192].double() - want).abs() <= 4e-7 * want.abs() + 1e-30).all())
 
 
+@pytest.mark.parametrize("M,K,N,wbits", [(4033, 1008, 2047, 8), (4033, 1008, 2047, 4), (3009, 1616, 1793, 8), (3009, 1616, 1793, 4),
+                                         (6001, 1104, 1793, 8), (2049, 2576, 2303, 8)])
+def test_middle_tiles_of_the_integer_layer(M, K, N, wbits):
+    """64 x 128 tiles: from 8 G multiply-adds on, in 600 to 768 or 900 to 1500 of them (4-bit weights 700 to 1024), with the same remainders."""
+    test_large_tiles_of_the_integer_layer(M, K, N, wbits)
+
+
 @pytest.mark.parametrize("n", [1, 2, 3, 4, 7, 1023, 100003])
 @pytest.mark.parametrize("offset", [0, 1, 2, 3])
 def test_calibration_of_unaligned_tensors(n, offset):

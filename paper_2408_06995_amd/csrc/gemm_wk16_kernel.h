@@ -17,6 +17,9 @@
 // 3 x 200 x 75 x 53 -> 392, stride 2: 23.6 -> 18.3 (dynamic).  Tried without gain: operands from memory straight into registers (sixteen rows
 // of 64 bytes a load are 61 cache accesses, 15 in the order that LDS allows: 79 us for the first of these), eight wavefronts with two
 // steps each in flight (the small tile 18.3 us where four take 17.6).
+// Four partial sums have no larger error than one or the slices had (root mean square of the difference to the sum in 64 bits, over the sum of the
+// products' magnitudes, before -> here): 8 x 1280 x 16 x 16 -> 1280 1.484e-9 -> 1.476e-9, E2M1 weights 9.7e-10 -> 6.5e-10; 1 x 320 x 64 x 64 -> 320
+// 2.05e-9 -> 2.07e-9; 3 x 200 x 75 x 53 -> 392 2.31e-9 -> 2.30e-9; 3000 x 3632 -> 641 2.53e-9 -> 1.92e-9.
 #pragma once
 #include "gemm_dma_kernel.h"
 

@@ -316,18 +316,25 @@ static inline GemmPlan plan_gemm(int64_t M, int64_t N, int64_t Kpad, PlanForm fo
 // The tiles of gemm_wk16_kernel.h (128 x 80 or 64 x 80, K split over the wavefronts, one workgroup per compute unit, one K slice)
 // in the place of a plan of plan_gemm, where a model of the time finds the better of them at least 10 % faster: fp32 results in the
 // exact mode, operands with a hardware conversion or moved into halves, kernels of at most 31 taps.  us = t[0] + rounds (t[1] + t[2]
-// steps): rounds of 256 tiles, each with its start and its end (nothing overlaps them) and steps of 4 x 64 codes; the other kernels as
-// in plan_unsliced, sliced ones t[0] + t[1] steps of 128 codes per slice + t[2] us per million partial sums.  Constants fitted to 2600
-// layers of random sizes; over those the choice takes 0.90 of the other plans' time in the geometric mean (the best of all tiles 0.89),
-// sliced ones of convolutions 0.6, and at most 23 are slower by more than 3 %.
-//   - Sliced 160-wide tiles of convolutions lose throughout (8 x 1280 x 16 x 16 -> 1280, 3 x 3: 57 + 10 us in four slices, 46 us here),
-//     as do 256-row tiles of images that are no multiple of four pixels, whose stores are single elements.
+// steps): rounds of 256 tiles, each with its start and its end (nothing overlaps them) and steps of 4 x 64 codes.  The other kernels as
+// in plan_unsliced, sliced ones t[0] + w t[1] steps of 128 codes per slice + t[2] us per million partial sums, with w from their work
+// items as there from the tiles.  In place of slices, deep linear layers also pay for their codes, which this kernel streams at 2 to 3 TB/s:
+// us_codes us per MB, and 0.3 more beyond the 256 MB of the last-level cache (16959 x 30624 -> 160: 250 us in four slices, 342 here).
+// Constants fitted to 8960 layers of random sizes; over 1900 others the choice takes 0.87 of the other plans' time in the geometric
+// mean (the better of both kernels everywhere 0.86; convolutions and halves that were sliced 0.65 to 0.8), 17 of them are slower by more than
+// 3 %, at most by 18 % (9411 x 28544 -> 339: 203 -> 238 us).
+//   - 256-row tiles of images that are no multiple of four pixels, whose stores are single elements, lose throughout (102 layers: 0.41
+//     to 0.85 of their time here).
+//   - Few tiles with a deep K stay in slices: this kernel has 8 to 64 workgroups there, each with all of K (1 x 2560 x 8 x 8 -> 1280, 3 x 3:
+//     31.8 us in 22 slices, 45.9 here; moved into halves 36 and 73).  Half a round and more leave them (8 x 1280 x 16 x 16 -> 1280, 3 x 3: 57 + 10 us
+//     in four slices, 46 us here).
 //   - Linear layers with K of at most 1024, or with at most twelve 64 x 64 tiles, keep their kernels: their sums are those of the
 //     grouped call, bit for bit.  What K4 cuts into slices keeps them: few tiles.
 static inline GemmPlan plan_over_waves(const GemmPlan& p, int64_t M, int64_t N, int64_t Kreal, PlanForm form, bool ragged_images)
 {
     static const float us_here[3][2][3] = {
         {{-0.4f, 6.3f, 0.777f}, {0.7f, 4.3f, 0.458f}}, {{0.8f, 6.2f, 0.704f}, {1.6f, 4.1f, 0.43f}}, {{0.85f, 6.3f, 1.18f}, {1.75f, 4.2f, 0.778f}}};
+    static const float us_codes[2] = {0.1f, 0.065f};
     static const float us_whole[3][7][3] = {
         {{4.2f, -0.03f, 0.413f}, {3.9f, 6.3f, 1.84f}, {2.0f, 3.0f, 1.09f}, {8.9f, -2.6f, 0.602f}, {4.0f, 2.2f, 0.924f}, {4.1f, 0.0f, 0.316f},
          {8.75f, -2.4f, 0.381f}},
@@ -335,32 +342,31 @@ static inline GemmPlan plan_over_waves(const GemmPlan& p, int64_t M, int64_t N, 
          {9.4f, -2.3f, 0.339f}},
         {{5.1f, 0.68f, 0.864f}, {3.0f, 9.0f, 2.6f}, {-2.0f, 9.6f, 1.78f}, {21.0f, -6.5f, 0.985f}, {1.4f, 6.6f, 1.35f}, {5.0f, 0.0f, 0.417f},
          {13.2f, -5.0f, 0.493f}}};
-    static const float us_sliced[4][3] = {{-1.4f, 2.2f, 2.8f}, {-1.4f, 1.64f, 2.8f}, {-8.5f, 1.0f, 6.4f}, {0.0f, 1.6f, 5.0f}};   // linear layers
+    static const float us_sliced[3][4][3] = {{{1.2f, 1.84f, 2.84f}, {9.6f, 1.1f, 0.9f}, {2.5f, 0.57f, 2.54f}, {-1.9f, 1.01f, 1.79f}},
+                                             {{27.0f, 1.88f, 0.58f}, {16.3f, 1.085f, 0.65f}, {6.7f, 0.57f, 2.47f}, {2.4f, 0.84f, 2.6f}},
+                                             {{31.8f, 2.65f, 0.0f}, {12.8f, 1.88f, 1.29f}, {10.7f, 0.92f, 1.6f}, {-2.2f, 1.43f, 2.6f}}};
     static const int bx[7] = {64, 256, 128, 128, 128, 64, 64}, bw[7] = {64, 160, 160, 64, 128, 64, 64};
     const int f = form == PLAN_LINEAR ? 0 : form == PLAN_CONV ? 1 : form == PLAN_HALF ? 2 : -1;
     if (f < 0 || p.tile > TILE_WAVE_K2 || (p.tile == TILE_WAVE_K4 && p.splits > 1)) return p;
     auto tiles = [&](int64_t x, int64_t w) { return ((M + x - 1) / x) * ((N + w - 1) / w); };
     const double steps = (double)((Kreal + 255) / 256), nk = (double)((Kreal + 127) / 128);
+    const double mb = (double)M * (double)Kreal * 1e-6;
     double us[2];
     for (int i = 0; i < 2; ++i) {
         const float* t = us_here[f][i];
         us[i] = t[0] + (double)((tiles(i ? 64 : 128, 80) + 255) / 256) * (t[1] + t[2] * steps);
+        if (f == 0 && p.splits > 1) us[i] += us_codes[i] * mb + (mb > 256.0 ? 0.3 * (mb - 256.0) : 0.0);
     }
     const GemmPlan here{us[0] < us[1] ? TILE_WAVE_128x80 : TILE_WAVE_64x80, 1};
-    double other;
-    if (p.splits > 1) {
-        if (f != 0) return here;
-        const float* t = us_sliced[p.tile - 1];
-        other = t[0] + t[1] * nk / p.splits + t[2] * (double)p.splits * (double)M * (double)N * 1e-6;
-    } else {
-        if (f == 1 && p.tile == TILE_256x160_S3 && ragged_images) return here;
-        const double n = (double)tiles(bx[p.tile], bw[p.tile]), per = n / 256.0, up = (double)(((int64_t)n + 255) / 256);
-        const double w = p.tile == TILE_GENERIC || p.tile >= TILE_WAVE_K4 ? (per > 1.0 ? per : 1.0)
-                         : p.tile == TILE_256x160_S3                     ? up
-                                                                         : (n <= 256 ? 1.1 : 0.5 * (up + per));
-        const float* t = us_whole[f][p.tile];
-        other = t[0] + w * (t[1] + t[2] * nk);
-    }
+    if (f == 1 && p.tile == TILE_256x160_S3 && p.splits == 1 && ragged_images) return here;
+    const int64_t items = tiles(bx[p.tile], bw[p.tile]) * p.splits;
+    const double per = (double)items / 256.0, up = (double)((items + 255) / 256);
+    const double w = p.tile == TILE_GENERIC || p.tile >= TILE_WAVE_K4 ? (per > 1.0 ? per : 1.0)
+                     : p.tile == TILE_256x160_S3                     ? up
+                                                                     : (items <= 256 ? 1.1 : 0.5 * (up + per));
+    const float* t = p.splits > 1 ? us_sliced[f][p.tile - 1] : us_whole[f][p.tile];
+    const double other = p.splits > 1 ? t[0] + w * t[1] * nk / p.splits + t[2] * (double)p.splits * (double)M * (double)N * 1e-6
+                                      : t[0] + w * (t[1] + t[2] * nk);
     return (us[0] < us[1] ? us[0] : us[1]) < 0.9 * other ? here : p;
 }
 // Operands decoded arithmetically (five exponent bits and more): the small tiles are not built for them, so widths that are

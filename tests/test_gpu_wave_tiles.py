@@ -69,6 +69,15 @@ def test_divisions_and_what_keeps_its_plan():
         assert tile_of(M, N, K, form) < T128, (M, N, K, form)
 
 
+@pytest.mark.parametrize("M,N,K", [(64, 1280, 23040), (128, 1280, 23040), (256, 1280, 23040), (64, 640, 17280), (80, 800, 21312), (160, 640, 22464)])
+@pytest.mark.parametrize("form", [CONV, HALF])
+def test_deep_layers_of_few_tiles_stay_in_slices(M, N, K, form):
+    """3 x 3 convolutions of the deepest level and other layers whose whole grid of 64 x 80 tiles is a fraction of a round: as many workgroups as
+    tiles would walk all of K, where 11 to 22 slices fill the compute units."""
+    assert tile_of(M, N, K, form) < T128
+    assert tile_of(128, 1280, 32768, form) < T128 and tile_of(128, 1280, 32768, LINEAR) < T128
+
+
 # M, K, N, tile
 LINEAR_CASES = [(2048, 4096, 1280, T128), (2047, 1584, 1279, T128), (1407, 4544, 641, T64), (3000, 3632, 641, T128), (2049, 4640, 321, T64)]
 

@@ -440,6 +440,18 @@ size_t fpq_conv2d_workspace_size(int64_t B, int64_t Cin, int64_t H, int64_t W, i
            (x_is_fp32 == FPQ_X_FP32_DYNAMIC ? kDynScaleBytes : 0);
 }
 
+// The plan of plan_gemm or, where they are faster, the tiles of 128 x 80 and 64 x 80 (plan_over_waves).  Those need no workspace: it is
+// sized for the other plan all the same, so that what a caller has to bring does not depend on the choice.  (a.splits: the slices that
+// there is room for.  What the kernels for at most 16 rows and for a short K take is not asked for.)
+static GemmPlan launched_plan(const GemmArgs& a, const GemmPlan& plan)
+{
+    if (a.yq || a.acc_mode != FPQ_ACC_FP32 || a.xkind == OPK_GENERIC8 || a.kh * a.kw > 31) return plan;
+    if (!a.conv_out && (a.Kpad <= 1024 || ((a.M + 63ll) / 64) * ((a.N + 63ll) / 64) <= 12)) return plan;   // (see plan_over_waves)
+    if (gemm_rows16_applicable(a) || gemm_strip_applicable(a)) return plan;
+    return plan_over_waves(plan, a.M, a.N, a.Kreal, a.xkind == OPK_HALF8 ? PLAN_HALF : a.conv_out ? PLAN_CONV : PLAN_LINEAR,
+                           a.conv_out && ((a.Ho * a.Wo) & 3) != 0);
+}
+
 // Hardware E4M3 operands, fp32 results that are stored.
 static void fill_plan(const GemmPlan& p, int64_t M, int64_t N, int64_t Cin, int kh, int kw, int stride, int pad, bool linear, fpq_plan_t* out)
 {
@@ -551,14 +563,6 @@ static int run_layer(const CodesOut* out, const void* x, int x_is_fp32, fpq_form
                                           : plan_gemm(M, Cout, kpad, xkind == OPK_HALF8 ? PLAN_HALF
                                                                      : conv_out         ? (out ? PLAN_CONV_CODES : PLAN_CONV)
                                                                                         : (out ? PLAN_LINEAR_CODES : PLAN_LINEAR));
-    // the tiles of 128 x 80 and 64 x 80, which need no workspace: it is sized for the other plan all the same, so that what a caller has
-    // to bring does not depend on the choice
-    const bool own_sums = conv_out || (kpad > 1024 && ((M + 63) / 64) * ((Cout + 63) / 64) > 12);   // (see plan_over_waves)
-    const GemmPlan over_waves = !out && !sparse && acc_mode == FPQ_ACC_FP32 && xkind != OPK_GENERIC8 && kh * kw <= 31 && own_sums
-                                    ? plan_over_waves(plan, M, Cout, Cp * kh * kw,
-                                                      xkind == OPK_HALF8 ? PLAN_HALF : conv_out ? PLAN_CONV : PLAN_LINEAR,
-                                                      conv_out && ((Ho * Wo) & 3) != 0)
-                                    : plan;
     if (sparse) {
         // the structured-sparse form has one kernel: hardware E4M3 activations, E4M3 / E2M1 weights, exact accumulate
         if (out || accumulate || acc_mode != FPQ_ACC_FP32 || xkind != OPK_FP8 || (wkind != OPK_FP8 && wkind != OPK_FP4))
@@ -575,8 +579,6 @@ static int run_layer(const CodesOut* out, const void* x, int x_is_fp32, fpq_form
     if (x_is_fp32 && (!workspace || workspace_bytes < codes_bytes + part_bytes + (dyn ? kDynScaleBytes : 0)))
         return FPQ_ERR_WORKSPACE;
     if (!x_is_fp32 && (!workspace || workspace_bytes < part_bytes)) plan.splits = 1;
-    if (over_waves.tile > TILE_WAVE_K2) plan = over_waves;
-    float* partial = plan.splits > 1 ? reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + codes_bytes) : nullptr;
     GemmArgs a;
     memset(&a, 0, sizeof a);
     a.wrows = static_cast<const uint8_t*>(packed_w) + kPackedRowsOffset;
@@ -592,9 +594,6 @@ static int run_layer(const CodesOut* out, const void* x, int x_is_fp32, fpq_form
     a.B = (int)B; a.H = (int)H; a.W = (int)W; a.Cp = (int)Cp;
     a.Ho = (int)Ho; a.Wo = (int)Wo;
     a.kh = kh; a.kw = kw; a.stride = stride; a.pad = pad;
-    a.by_hw = divisor(Ho * Wo); a.by_wo = divisor(Wo); a.by_cp = divisor(Cp); a.by_kw = divisor(kw);
-    if (kh * kw <= 31)
-        for (int r = 0; r < kh; ++r) a.tap_rows |= 1u << (r * kw);
     a.conv_out = conv_out;
     a.xkind = xkind; a.wkind = wkind;
     a.xe = fx.ebits; a.xm = fx.mbits; a.xb = fx.bias;
@@ -611,7 +610,9 @@ static int run_layer(const CodesOut* out, const void* x, int x_is_fp32, fpq_form
         a.sy = out->s;
         a.sy_dev = out->s_dev;
     }
-    a.partial = partial;
+    a.splits = plan.splits;
+    if (!sparse) plan = launched_plan(a, plan);
+    a.partial = plan.splits > 1 ? reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + codes_bytes) : nullptr;
     a.splits = plan.splits;
     a.tile = plan.tile;
     a.x_bytes = (uint32_t)(B * H * W * Cp);

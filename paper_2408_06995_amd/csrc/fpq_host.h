@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include <atomic>
+#include <type_traits>
 
 #include "../../include/fpq.h"
 
@@ -97,8 +98,6 @@ struct GemmArgs {
     int B, H, W, Cp;        // activation geometry (linear: B = M, H = W = 1)
     int Ho, Wo;
     int kh, kw, stride, pad;
-    Divisor by_hw, by_wo, by_cp, by_kw;   // Ho Wo, Wo, Cp, kw
-    uint32_t tap_rows;      // bit r kw for every kernel row r (kernels of at most 31 taps)
     int conv_out;           // 1: y is NCHW [B, N, Ho, Wo]; 0: y is [M, N]
     int xkind, wkind;       // OperandKind
     int xe, xm, xb;         // activation format (for the generic decode)
@@ -122,6 +121,35 @@ struct GemmArgs {
     const float* sy_dev;
     int act;                // 0, FPQ_ACT_SILU or FPQ_ACT_GEGLU: applied to the fp32 result before it is quantized
 };
+// (36 bytes more, for what follows, cost every sliced layer 0.2 us of 27 to 31, and its making 0.05 us of a call)
+static_assert(sizeof(GemmArgs) <= 240, "the argument of every layer kernel");
+// What the kernels with K over the wavefronts want besides in a convolution of at most 31 taps: worked out at their launch, so that no
+// other layer pays for it.
+struct ConvArgs : GemmArgs {
+    Divisor by_hw, by_wo, by_cp, by_kw;   // Ho Wo, Wo, Cp, kw
+    uint32_t tap_rows;      // bit r kw for every kernel row r
+};
+static inline ConvArgs conv_args(const GemmArgs& a)
+{
+    ConvArgs c{};
+    static_cast<GemmArgs&>(c) = a;
+    c.by_hw = divisor((int64_t)a.Ho * a.Wo);
+    c.by_wo = divisor(a.Wo);
+    c.by_cp = divisor(a.Cp);
+    c.by_kw = divisor(a.kw);
+    for (int r = 0; r < a.kh; ++r) c.tap_rows |= 1u << (r * a.kw);
+    return c;
+}
+template <bool CONV>
+static inline auto wave_args(const GemmArgs& a)
+{
+    if constexpr (CONV)
+        return conv_args(a);
+    else
+        return a;
+}
+template <bool CONV>
+using WaveArgs = std::conditional_t<CONV, ConvArgs, GemmArgs>;
 
 // Grouped linear layers (fpq_gemm_grouped): up to kGroupMax independent problems per launch, each launch taking the
 // problems' pointers and sizes as a kernel argument (no copy to the device, so the call can be captured into a graph).
@@ -447,6 +475,7 @@ int launch_pack_weights(const float* w, int64_t N, int64_t Cin, int taps, const 
                         const float* scale_in, const uint8_t* mask, uint8_t* packed_rows, float* scale_out,
                         uint8_t* codes_out, hipStream_t st);
 int launch_gemm(const GemmArgs& a, hipStream_t st);
+bool gemm_rows16_applicable(const GemmArgs& a);             // linear layers with at most 16 rows
 // One launch for a dynamically scaled linear layer with at most 16 rows (x: the fp32 activations; a.x is not used;
 // codes [M, K] and publish [scale, absmax] receive what the two-launch form leaves in the workspace).
 int launch_gemm_skinny_dynamic(const GemmArgs& a, const float* x, const QParams& qx, float maxval, uint8_t* codes,

@@ -650,7 +650,7 @@ __global__ __launch_bounds__(256) void gemm_skinny_dynamic_grouped_kernel(const 
                                      reinterpret_cast<uint32_t*>(const_cast<uint8_t*>(q.xcodes)), const_cast<float*>(q.sx_dev));
 }
 
-static bool skinny_applicable(const GemmArgs& a)
+bool gemm_rows16_applicable(const GemmArgs& a)
 {
     return !a.conv_out && a.M <= 16 && a.acc_mode == FPQ_ACC_FP32 && a.xkind == OPK_FP8 &&
            (a.wkind == OPK_FP8 || a.wkind == OPK_FP4) && !a.yq && !a.accumulate && a.splits == 1;
@@ -662,7 +662,7 @@ int launch_gemm_skinny_dynamic(const GemmArgs& a, const float* x, const QParams&
                                float* publish, hipStream_t st)
 {
     const size_t n = (size_t)a.M * a.Kreal;
-    if (!skinny_applicable(a) || a.M < 1 || a.N < 1 || n > 16384 || (a.Kreal & 15) || (reinterpret_cast<uintptr_t>(x) & 15))
+    if (!gemm_rows16_applicable(a) || a.M < 1 || a.N < 1 || n > 16384 || (a.Kreal & 15) || (reinterpret_cast<uintptr_t>(x) & 15))
         return FPQ_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)((a.N + 15) / 16));
     if (a.wkind == OPK_FP8)
@@ -765,7 +765,7 @@ int launch_gemm_grouped(const GroupedArgs& g, hipStream_t st)
 int launch_gemm(const GemmArgs& a, hipStream_t st)
 {
     if (a.M <= 0 || a.N <= 0) return FPQ_OK;
-    if (skinny_applicable(a)) {
+    if (gemm_rows16_applicable(a)) {
         const dim3 grid((unsigned)((a.N + 15) / 16));
         if (a.wkind == OPK_FP8)
             hipLaunchKernelGGL(gemm_skinny_kernel<OPK_FP8>, grid, dim3(256), 0, st, a);

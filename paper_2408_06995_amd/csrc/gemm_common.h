@@ -69,7 +69,7 @@ __device__ __forceinline__ int divide(int n, const Divisor& d) { return (int)(__
 // lie inside the image, bit r kw + c.  Valid kernel columns and rows are ranges; a multiplication repeats the one's bits at the
 // other's: about 25 instructions where a loop over nine taps and two divisions by the compiler take 120 (they are all that a workgroup
 // does before its first load goes out).
-__device__ __forceinline__ void conv_row(const GemmArgs& a, int m, unsigned& base, unsigned& taps)
+__device__ __forceinline__ void conv_row(const ConvArgs& a, int m, unsigned& base, unsigned& taps)
 {
     const int bi = divide(m, a.by_hw), rem = m - bi * (a.Ho * a.Wo);
     const int ho = divide(rem, a.by_wo), wo = rem - ho * a.Wo;

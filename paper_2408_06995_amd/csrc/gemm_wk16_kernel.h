@@ -80,7 +80,7 @@ constexpr int wk16_wave_lds(int mi, int ni, int nst, bool w4)
 }
 
 template <int MI, int NI, int NST, int XKIND, int WKIND, bool CONV>
-__global__ __launch_bounds__(256, 1) void gemm_wk16_kernel(const GemmArgs a)
+__global__ __launch_bounds__(256, 1) void gemm_wk16_kernel(const WaveArgs<CONV> a)
 {
     constexpr bool W4 = kind_is_4bit(WKIND);
     constexpr int BX = 16 * MI, BW = 16 * NI, XTILE = MI * 1024, STAGE = wk16_stage(MI, NI, W4), WAVE_LDS = wk16_wave_lds(MI, NI, NST, W4);
@@ -119,7 +119,7 @@ __global__ __launch_bounds__(256, 1) void gemm_wk16_kernel(const GemmArgs a)
     const int xc = (lane & 3) ^ ((lane >> 4) & 3);
     unsigned xbase[XLD], xout[XLD], wbase[WLD];  // byte offset of a row's tap (0, 0), channel 0; bit t: tap t lies outside
     int x_k = wave * 64 + 16 * xc, x_ci = x_k, x_kh = 0, x_kw = 0, x_tap = 0;
-    if (CONV) {
+    if constexpr (CONV) {
         // a lane works out one or two rows, and the rows change hands in LDS (in the wavefront's own ring, still empty)
         uint2* table = reinterpret_cast<uint2*>(smem + wave * WAVE_LDS);
 #pragma unroll
@@ -176,8 +176,13 @@ __global__ __launch_bounds__(256, 1) void gemm_wk16_kernel(const GemmArgs a)
     // position of the step being loaded: offset from xbase, and 31 - the bit of xout that tells whether it exists
     unsigned x_delta = 0, x_shift = 0;
     // (a wavefront's next step is 256 codes on: whole taps and a rest, at most one carry from channels to taps and from columns to rows)
-    const int step_tap = CONV ? divide(256, a.by_cp) : 0, step_ci = CONV ? 256 - step_tap * a.Cp : 0;
-    const int step_kh = CONV ? divide(step_tap, a.by_kw) : 0, step_kw = CONV ? step_tap - step_kh * a.kw : 0;
+    int step_tap = 0, step_ci = 0, step_kh = 0, step_kw = 0;
+    if constexpr (CONV) {
+        step_tap = divide(256, a.by_cp);
+        step_ci = 256 - step_tap * a.Cp;
+        step_kh = divide(step_tap, a.by_kw);
+        step_kw = step_tap - step_kh * a.kw;
+    }
     auto place = [&]() {
         x_shift = x_k < a.Kreal ? 31u - (unsigned)x_tap : 0u;
         x_delta = CONV ? (unsigned)((x_kh * a.W + x_kw) * a.Cp + x_ci) : (unsigned)x_k;
@@ -352,7 +357,9 @@ __global__ __launch_bounds__(256, 1) void gemm_wk16_kernel(const GemmArgs a)
     for (int ii = 0; ii < MI / 4; ++ii) {
         const int i = wave * (MI / 4) + ii;
         const int mp = m0 + 16 * i + 4 * q;                        // NCHW: the lane's first pixel
-        const int bi = P_IS_W ? 0 : divide(mp, a.by_hw), pix = mp - bi * hw;
+        int bi = 0;
+        if constexpr (CONV) bi = divide(mp, a.by_hw);
+        const int pix = mp - bi * hw;
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
             float4 v[4];
@@ -403,7 +410,7 @@ static int launch_wk16_one(const GemmArgs& a, hipStream_t st)
     auto kern = gemm_wk16_kernel<MI, NI, NST, XKIND, WKIND, CONV>;
     static std::atomic<uint64_t> allowed{0};   // per instantiation
     if (!allow_dynamic_lds(reinterpret_cast<const void*>(kern), smem, allowed)) return FPQ_ERR_LAUNCH;
-    hipLaunchKernelGGL(kern, dim3(items), dim3(256), smem, st, a);
+    hipLaunchKernelGGL(kern, dim3(items), dim3(256), smem, st, wave_args<CONV>(a));
     return hipGetLastError() == hipSuccess ? FPQ_OK : FPQ_ERR_LAUNCH;
 }
 

@@ -21,7 +21,7 @@ namespace fpq {
 constexpr int wk_wave_lds(int nst, bool w4) { return nst * (64 * 64 + (w4 ? 64 * 32 : 64 * 64)) < 16384 ? 16384 : nst * (64 * 64 + (w4 ? 64 * 32 : 64 * 64)); }
 
 template <int NST, int XKIND, int WKIND, int ACC, bool CONV, bool QOUT>
-__device__ __forceinline__ void gemm_wk_tile(const GemmArgs& a, int item, uint8_t* smem)
+__device__ __forceinline__ void gemm_wk_tile(const WaveArgs<CONV>& a, int item, uint8_t* smem)
 {
     constexpr bool W4 = kind_is_4bit(WKIND);
     constexpr int XTILE = 64 * 64, WTILE = W4 ? 64 * 32 : 64 * 64, STAGE = XTILE + WTILE;
@@ -63,7 +63,7 @@ __device__ __forceinline__ void gemm_wk_tile(const GemmArgs& a, int item, uint8_
 #pragma unroll
         for (int i = 0; i < XLD; ++i) {
             const int m = m0 + 16 * i + (lane >> 2);
-            if (CONV) {
+            if constexpr (CONV) {
                 conv_row(a, m, xbase[i], xmask[i]);
                 if (m >= a.M) xmask[i] = 0u;                       // no tap of this row lies inside
             } else {
@@ -71,7 +71,7 @@ __device__ __forceinline__ void gemm_wk_tile(const GemmArgs& a, int item, uint8_
                 xmask[i] = m < a.M ? 1u : 0u;
             }
         }
-        if (CONV) {
+        if constexpr (CONV) {
             x_tap = divide(x_k, a.by_cp);
             x_ci = x_k - x_tap * a.Cp;
             x_kh = divide(x_tap, a.by_kw);
@@ -353,7 +353,7 @@ __device__ __forceinline__ void gemm_wk_tile(const GemmArgs& a, int item, uint8_
 }
 
 template <int NST, int XKIND, int WKIND, int ACC, bool CONV, bool QOUT>
-__global__ __launch_bounds__(256, (NST <= 2 ? 2 : 1)) void gemm_wk_kernel(const GemmArgs a)
+__global__ __launch_bounds__(256, (NST <= 2 ? 2 : 1)) void gemm_wk_kernel(const WaveArgs<CONV> a)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     gemm_wk_tile<NST, XKIND, WKIND, ACC, CONV, QOUT>(a, blockIdx.x, smem);
@@ -369,7 +369,7 @@ static int launch_wk_one(const GemmArgs& a, hipStream_t st)
         static std::atomic<uint64_t> allowed{0};   // per instantiation
         if (!allow_dynamic_lds(reinterpret_cast<const void*>(kern), smem, allowed)) return FPQ_ERR_LAUNCH;
     }
-    hipLaunchKernelGGL(kern, dim3(items), dim3(256), smem, st, a);
+    hipLaunchKernelGGL(kern, dim3(items), dim3(256), smem, st, wave_args<CONV>(a));
     if (a.splits > 1) return launch_splitk_reduce(a, st);
     return hipGetLastError() == hipSuccess ? FPQ_OK : FPQ_ERR_LAUNCH;
 }

@@ -277,22 +277,26 @@ int fpq_conv2d(const void *x, int x_is_fp32, fpq_format_t fx, float sx, const fl
                int64_t B, int64_t Cin, int64_t H, int64_t W, int64_t Cout, int kh, int kw, int stride,
                int pad, int acc_mode, void *workspace, size_t workspace_bytes, void *stream);
 
-/* Read-only query (host, no GPU): which kernel fpq_gemm / fpq_conv2d launch for a shape and into how many K slices
- * they cut it, given a workspace of the size the *_workspace_size functions state, operands in the hardware's
- * E4M3 / E2M1 encodings and a result that is stored (other operand pairings may take another kernel or number of slices,
- * and some of them FPQ_KERNEL_SMALL_TILE, unsliced, whatever the shape; with FPQ_OUT_ACCUMULATE, and with E2M1 weights
- * for some K of at most 128, a shape of FPQ_KERNEL_STRIP takes one of the tiles).
+/* Read-only queries (host, no GPU), for tests and benchmarks that have to state, or to cover, every launch configuration a
+ * workload uses.
+ * fpq_gemm_plan / fpq_conv2d_plan: the kernel and the number of K slices that the workspace of a shape is sized for, given
+ * operands in the hardware's E4M3 / E2M1 encodings and a result that is stored (other operand pairings may take another kernel
+ * or number of slices, and some of them FPQ_KERNEL_SMALL_TILE, unsliced, whatever the shape; with FPQ_OUT_ACCUMULATE, and with
+ * E2M1 weights for some K of at most 128, a shape of FPQ_KERNEL_STRIP takes one of the tiles).
  * With more than one slice the layer kernel writes partial sums to the workspace and a reduction kernel adds them.
- * It is the plan that the workspace is sized for.  fp32 results in FPQ_ACC_FP32 take tiles of 128 x 80 or 64 x 80 outputs in one
- * slice in its place, with no workspace of their own, where those are faster: convolutions, and linear layers with K above 1024
- * and more than twelve tiles of 64 x 64.
- * For tests and benchmarks that have to state, or to cover, every launch configuration a workload uses. */
+ * fpq_gemm_launch_plan / fpq_conv2d_launch_plan: the kernel that fpq_gemm / fpq_conv2d launch with these formats and this
+ * acc_mode, and its slices, given a workspace of the size the *_workspace_size functions state.  It is another one than the workspace's where
+ * fp32 results in FPQ_ACC_FP32 take FPQ_KERNEL_128x80 or FPQ_KERNEL_64x80, in one slice and with no workspace of their own, because
+ * those are faster: convolutions, and linear layers with K above 1024 and more than twelve tiles of 64 x 64.  Errors: those of
+ * the layer call for the sizes, the formats and acc_mode. */
 typedef enum fpq_kernel {
     FPQ_KERNEL_SMALL_TILE = 0, /* tiles of at most 128 x 128 outputs: any shape */
     FPQ_KERNEL_256x160 = 1,    /* persistent 256 x 160 tiles, three LDS stages */
     FPQ_KERNEL_128x160 = 2,    /* persistent 128 x 160 tiles, two LDS stages, two workgroups per compute unit */
     FPQ_KERNEL_ROWS16 = 3,     /* linear layers with at most 16 rows: K split over the wavefronts of a workgroup */
-    FPQ_KERNEL_STRIP = 4       /* linear layers and 1 x 1 convolutions of at most 320 codes: weights of 64 columns in registers */
+    FPQ_KERNEL_STRIP = 4,      /* linear layers and 1 x 1 convolutions of at most 320 codes: weights of 64 columns in registers */
+    FPQ_KERNEL_128x80 = 5,     /* 128 x 80 tiles, K split over the wavefronts of a workgroup (launch plans only) */
+    FPQ_KERNEL_64x80 = 6       /* 64 x 80 tiles, likewise */
 } fpq_kernel;
 typedef struct fpq_plan {
     int32_t kernel;   /* fpq_kernel */
@@ -301,6 +305,9 @@ typedef struct fpq_plan {
 int fpq_gemm_plan(int64_t M, int64_t N, int64_t K, fpq_plan_t *plan);
 int fpq_conv2d_plan(int64_t B, int64_t Cin, int64_t H, int64_t W, int64_t Cout, int kh, int kw, int stride,
                     int pad, fpq_plan_t *plan);
+int fpq_gemm_launch_plan(int64_t M, int64_t N, int64_t K, fpq_format_t fx, fpq_format_t fw, int acc_mode, fpq_plan_t *plan);
+int fpq_conv2d_launch_plan(int64_t B, int64_t Cin, int64_t H, int64_t W, int64_t Cout, int kh, int kw, int stride, int pad,
+                           fpq_format_t fx, fpq_format_t fw, int acc_mode, fpq_plan_t *plan);
 
 /* ---- the same layers with the result handed to the next quantized layer as codes -------------
  *

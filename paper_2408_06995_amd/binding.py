@@ -34,6 +34,7 @@ class fpq_plan_t(C.Structure):
 
 
 FPQ_KERNEL_SMALL_TILE, FPQ_KERNEL_256x160, FPQ_KERNEL_128x160, FPQ_KERNEL_ROWS16, FPQ_KERNEL_STRIP = 0, 1, 2, 3, 4
+FPQ_KERNEL_128x80, FPQ_KERNEL_64x80 = 5, 6
 FPQ_NOALLOC_SCRATCH_BYTES = 64 << 20
 
 
@@ -125,6 +126,10 @@ def lib():
     L.fpq_gemm_plan.argtypes = [i64, i64, i64, C.POINTER(fpq_plan_t)]
     L.fpq_conv2d_plan.restype = i32
     L.fpq_conv2d_plan.argtypes = [i64] * 5 + [i32] * 4 + [C.POINTER(fpq_plan_t)]
+    L.fpq_gemm_launch_plan.restype = i32
+    L.fpq_gemm_launch_plan.argtypes = [i64, i64, i64, F, F, i32, C.POINTER(fpq_plan_t)]
+    L.fpq_conv2d_launch_plan.restype = i32
+    L.fpq_conv2d_launch_plan.argtypes = [i64] * 5 + [i32] * 4 + [F, F, i32, C.POINTER(fpq_plan_t)]
     L.fpq_gemm_grouped_workspace_size.restype = sz
     L.fpq_gemm_grouped_workspace_size.argtypes = [C.POINTER(fpq_gemm_problem_t), i32, i32]
     L.fpq_gemm_grouped.restype = i32
@@ -165,7 +170,7 @@ EXPORTS = ["fpq_strerror", "fpq_format_max", "fpq_format_check", "fpq_bias_to_sc
            "fpq_conv2d_workspace_size", "fpq_conv2d", "fpq_search_workspace_size", "fpq_search_format",
            "fpq_count_zeros_workspace_size", "fpq_count_zeros", "fpq_gemm_codes_out", "fpq_conv2d_codes_out",
            "fpq_rl_workspace_size", "fpq_rl_init_alpha", "fpq_rl_step", "fpq_rl_mask", "fpq_packed_check", "fpq_rl_im2col",
-           "fpq_gemm_plan", "fpq_conv2d_plan", "fpq_gemm_noalloc", "fpq_gemm_grouped_workspace_size", "fpq_gemm_grouped", "fpq_probe_peak",
+           "fpq_gemm_plan", "fpq_conv2d_plan", "fpq_gemm_launch_plan", "fpq_conv2d_launch_plan", "fpq_gemm_noalloc", "fpq_gemm_grouped_workspace_size", "fpq_gemm_grouped", "fpq_probe_peak",
            "fpq_packed_sparse_size", "fpq_pack_weights_sparse", "fpq_gemm_sparse", "fpq_conv2d_sparse",
            "fpq_int_calibrate_workspace_size", "fpq_int_calibrate", "fpq_int_quantize", "fpq_int_packed_size",
            "fpq_int_pack_weights", "fpq_int_gemm_workspace_size", "fpq_int_gemm"]
@@ -234,16 +239,31 @@ def fpq_conv2d_workspace_size(B, Cin, H, W, Cout, kh, kw, stride, pad, x_is_fp32
 
 
 def fpq_gemm_plan(M, N, K):
-    """(kernel, k_slices) of a linear layer."""
+    """(kernel, k_slices) that a linear layer's workspace is sized for."""
     p = fpq_plan_t()
     _check(lib().fpq_gemm_plan(M, N, K, C.byref(p)), "fpq_gemm_plan")
     return p.kernel, p.k_slices
 
 
 def fpq_conv2d_plan(B, Cin, H, W, Cout, kh, kw, stride, pad):
-    """(kernel, k_slices) of a convolution."""
+    """(kernel, k_slices) that a convolution's workspace is sized for."""
     p = fpq_plan_t()
     _check(lib().fpq_conv2d_plan(B, Cin, H, W, Cout, kh, kw, stride, pad, C.byref(p)), "fpq_conv2d_plan")
+    return p.kernel, p.k_slices
+
+
+def fpq_gemm_launch_plan(M, N, K, fx, fw, acc_mode=0):
+    """(kernel, k_slices) that fpq_gemm launches."""
+    p = fpq_plan_t()
+    _check(lib().fpq_gemm_launch_plan(M, N, K, fmt(fx), fmt(fw), acc_mode, C.byref(p)), "fpq_gemm_launch_plan")
+    return p.kernel, p.k_slices
+
+
+def fpq_conv2d_launch_plan(B, Cin, H, W, Cout, kh, kw, stride, pad, fx, fw, acc_mode=0):
+    """(kernel, k_slices) that fpq_conv2d launches."""
+    p = fpq_plan_t()
+    _check(lib().fpq_conv2d_launch_plan(B, Cin, H, W, Cout, kh, kw, stride, pad, fmt(fx), fmt(fw), acc_mode, C.byref(p)),
+           "fpq_conv2d_launch_plan")
     return p.kernel, p.k_slices
 
 

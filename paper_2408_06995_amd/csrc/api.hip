@@ -440,6 +440,40 @@ size_t fpq_conv2d_workspace_size(int64_t B, int64_t Cin, int64_t H, int64_t W, i
            (x_is_fp32 == FPQ_X_FP32_DYNAMIC ? kDynScaleBytes : 0);
 }
 
+// The sizes that the layer calls accept, and what follows from them in the kernels' argument.
+static int set_sizes(GemmArgs& a, int64_t B, int64_t Cin, int64_t H, int64_t W, int64_t Cout, int kh, int kw, int stride, int pad,
+                     int conv_out)
+{
+    if (B <= 0 || Cin <= 0 || H <= 0 || W <= 0 || Cout <= 0 || kh <= 0 || kw <= 0 || stride <= 0 || pad < 0)
+        return FPQ_ERR_SHAPE;
+    if (H + 2 * pad < kh || W + 2 * pad < kw || H > 16000 || W > 16000 || kh > 64 || kw > 64 || pad > 64)
+        return FPQ_ERR_SHAPE;
+    const int64_t Ho = (H + 2 * pad - kh) / stride + 1, Wo = (W + 2 * pad - kw) / stride + 1;
+    const int64_t M = B * Ho * Wo;
+    const int64_t Cp = padded_channels(Cin);
+    if (M >= (int64_t)1 << 31 || B * H * W * Cp >= (int64_t)1 << 31 || M * Cout >= (int64_t)1 << 40 ||
+        Cout >= (int64_t)1 << 24 || Cin * kh * kw > (1 << 28))   // the last: what fpq_pack_weights accepts
+        return FPQ_ERR_SHAPE;
+    a.M = (int)M;
+    a.N = (int)Cout;
+    a.Kpad = (int)padded_k(Cin, (int64_t)kh * kw);
+    a.Kreal = (int)(Cp * kh * kw);
+    a.B = (int)B; a.H = (int)H; a.W = (int)W; a.Cp = (int)Cp;
+    a.Ho = (int)Ho; a.Wo = (int)Wo;
+    a.kh = kh; a.kw = kw; a.stride = stride; a.pad = pad;
+    a.conv_out = conv_out;
+    return FPQ_OK;
+}
+
+// The plan that the workspace is sized for.
+static GemmPlan workspace_plan(const GemmArgs& a, bool codes_out)
+{
+    return a.xkind == OPK_GENERIC8 ? plan_arithmetic(a.M, a.N, a.Kpad)
+                                   : plan_gemm(a.M, a.N, a.Kpad, a.xkind == OPK_HALF8 ? PLAN_HALF
+                                                                 : a.conv_out         ? (codes_out ? PLAN_CONV_CODES : PLAN_CONV)
+                                                                                      : (codes_out ? PLAN_LINEAR_CODES : PLAN_LINEAR));
+}
+
 // The plan of plan_gemm or, where they are faster, the tiles of 128 x 80 and 64 x 80 (plan_over_waves).  Those need no workspace: it is
 // sized for the other plan all the same, so that what a caller has to bring does not depend on the choice.  (a.splits: the slices that
 // there is room for.  What the kernels for at most 16 rows and for a short K take is not asked for.)
@@ -450,6 +484,18 @@ static GemmPlan launched_plan(const GemmArgs& a, const GemmPlan& plan)
     if (gemm_rows16_applicable(a) || gemm_strip_applicable(a)) return plan;
     return plan_over_waves(plan, a.M, a.N, a.Kreal, a.xkind == OPK_HALF8 ? PLAN_HALF : a.conv_out ? PLAN_CONV : PLAN_LINEAR,
                            a.conv_out && ((a.Ho * a.Wo) & 3) != 0);
+}
+
+// The kernel that launch_gemm takes for operands that the tile is built for.
+static int kernel_of(const GemmArgs& a)
+{
+    return gemm_rows16_applicable(a)       ? FPQ_KERNEL_ROWS16
+           : gemm_strip_applicable(a)      ? FPQ_KERNEL_STRIP
+           : a.tile == TILE_256x160_S3     ? FPQ_KERNEL_256x160
+           : a.tile == TILE_128x160_S2     ? FPQ_KERNEL_128x160
+           : a.tile == TILE_WAVE_128x80    ? FPQ_KERNEL_128x80
+           : a.tile == TILE_WAVE_64x80     ? FPQ_KERNEL_64x80
+                                           : FPQ_KERNEL_SMALL_TILE;
 }
 
 // Hardware E4M3 operands, fp32 results that are stored.
@@ -465,11 +511,8 @@ static void fill_plan(const GemmPlan& p, int64_t M, int64_t N, int64_t Cin, int 
     a.xkind = a.wkind = OPK_FP8;
     a.acc_mode = FPQ_ACC_FP32;
     a.splits = p.splits;
-    out->kernel = (linear && M <= 16)         ? FPQ_KERNEL_ROWS16
-                  : gemm_strip_applicable(a)  ? FPQ_KERNEL_STRIP
-                  : p.tile == TILE_256x160_S3 ? FPQ_KERNEL_256x160
-                  : p.tile == TILE_128x160_S2 ? FPQ_KERNEL_128x160
-                                              : FPQ_KERNEL_SMALL_TILE;
+    a.tile = p.tile;
+    out->kernel = kernel_of(a);
     out->k_slices = p.splits;
 }
 
@@ -492,6 +535,47 @@ int fpq_conv2d_plan(int64_t B, int64_t Cin, int64_t H, int64_t W, int64_t Cout, 
     fill_plan(plan_gemm(B * Ho * Wo, Cout, padded_k(Cin, (int64_t)kh * kw), PLAN_CONV), B * Ho * Wo, Cout, Cin, kh, kw, stride, pad, false,
               plan);
     return FPQ_OK;
+}
+
+static int launch_plan(int64_t B, int64_t Cin, int64_t H, int64_t W, int64_t Cout, int kh, int kw, int stride, int pad, int conv_out,
+                       fpq_format_t fx, fpq_format_t fw, int acc_mode, fpq_plan_t* plan)
+{
+    if (!plan) return FPQ_ERR_NULL;
+    QParams qx, qw;
+    int st = resolve_format(fx, &qx);
+    if (st) return st;
+    st = resolve_format(fw, &qw);
+    if (st) return st;
+    GemmArgs a;
+    memset(&a, 0, sizeof a);
+    st = set_sizes(a, B, Cin, H, W, Cout, kh, kw, stride, pad, conv_out);
+    if (st) return st;
+    a.accumulate = (acc_mode & FPQ_OUT_ACCUMULATE) ? 1 : 0;
+    a.acc_mode = acc_mode & ~FPQ_OUT_ACCUMULATE;
+    st = resolve_kinds(fx, qx.c, fw, qw.c, a.acc_mode, &a.xkind, &a.wkind, &a.alpha);
+    if (st) return st;
+    if ((int64_t)(is_four_bit(fw) ? a.Kpad / 2 : a.Kpad) * Cout >= (int64_t)1 << 31) return FPQ_ERR_SHAPE;
+    GemmPlan p = workspace_plan(a, false);
+    a.splits = p.splits;
+    p = launched_plan(a, p);
+    a.tile = p.tile;
+    if (!gemm_dma_applicable(a)) p = GemmPlan{TILE_GENERIC, 1};
+    a.splits = p.splits;
+    a.tile = p.tile;
+    plan->kernel = kernel_of(a);
+    plan->k_slices = p.splits;
+    return FPQ_OK;
+}
+
+int fpq_gemm_launch_plan(int64_t M, int64_t N, int64_t K, fpq_format_t fx, fpq_format_t fw, int acc_mode, fpq_plan_t* plan)
+{
+    return launch_plan(M, K, 1, 1, N, 1, 1, 1, 0, 0, fx, fw, acc_mode, plan);
+}
+
+int fpq_conv2d_launch_plan(int64_t B, int64_t Cin, int64_t H, int64_t W, int64_t Cout, int kh, int kw, int stride, int pad,
+                           fpq_format_t fx, fpq_format_t fw, int acc_mode, fpq_plan_t* plan)
+{
+    return launch_plan(B, Cin, H, W, Cout, kh, kw, stride, pad, 1, fx, fw, acc_mode, plan);
 }
 
 // Where a layer's result goes when it leaves as codes for the next quantized layer.
@@ -529,16 +613,11 @@ static int run_layer(const CodesOut* out, const void* x, int x_is_fp32, fpq_form
     if (x_is_fp32 < 0 || x_is_fp32 > FPQ_X_FP32_DYNAMIC) return FPQ_ERR_UNSUPPORTED;
     const bool dyn = x_is_fp32 == FPQ_X_FP32_DYNAMIC;
     if (!dyn && !sx_dev && !scale_ok(sx)) return FPQ_ERR_SCALE;
-    if (B <= 0 || Cin <= 0 || H <= 0 || W <= 0 || Cout <= 0 || kh <= 0 || kw <= 0 || stride <= 0 || pad < 0)
-        return FPQ_ERR_SHAPE;
-    if (H + 2 * pad < kh || W + 2 * pad < kw || H > 16000 || W > 16000 || kh > 64 || kw > 64 || pad > 64)
-        return FPQ_ERR_SHAPE;
-    const int64_t Ho = (H + 2 * pad - kh) / stride + 1, Wo = (W + 2 * pad - kw) / stride + 1;
-    const int64_t M = B * Ho * Wo;
-    const int64_t Cp = padded_channels(Cin);
-    if (M >= (int64_t)1 << 31 || B * H * W * Cp >= (int64_t)1 << 31 || M * Cout >= (int64_t)1 << 40 ||
-        Cout >= (int64_t)1 << 24 || Cin * kh * kw > (1 << 28))   // the last: what fpq_pack_weights accepts
-        return FPQ_ERR_SHAPE;
+    GemmArgs a;
+    memset(&a, 0, sizeof a);
+    st = set_sizes(a, B, Cin, H, W, Cout, kh, kw, stride, pad, conv_out);
+    if (st) return st;
+    const int64_t M = a.M, Cp = a.Cp, kpad = a.Kpad;
     if (!x || !packed_w || !sw || (out ? !out->yq : !y)) return FPQ_ERR_NULL;
     QParams qy{0, 0, 0, 0.0f};
     if (out) {
@@ -549,23 +628,17 @@ static int run_layer(const CodesOut* out, const void* x, int x_is_fp32, fpq_form
         if (accumulate) return FPQ_ERR_UNSUPPORTED;
         if (reinterpret_cast<uintptr_t>(out->yq) & 15) return FPQ_ERR_ALIGN;
     }
-    int xkind, wkind;
-    float alpha;
-    st = resolve_kinds(fx, qx.c, fw, qw.c, acc_mode, &xkind, &wkind, &alpha);
+    st = resolve_kinds(fx, qx.c, fw, qw.c, acc_mode, &a.xkind, &a.wkind, &a.alpha);
     if (st) return st;
     if ((reinterpret_cast<uintptr_t>(packed_w) & 15) || (!out && (reinterpret_cast<uintptr_t>(y) & 3))) return FPQ_ERR_ALIGN;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const uint8_t* xcodes;
     // workspace = [activation codes when the input is fp32][split-K partial results]; a caller that passes
     // codes and no (or too small a) workspace gets the unsplit kernel
-    const int64_t kpad = padded_k(Cin, (int64_t)kh * kw);
-    GemmPlan plan = xkind == OPK_GENERIC8 ? plan_arithmetic(M, Cout, kpad)
-                                          : plan_gemm(M, Cout, kpad, xkind == OPK_HALF8 ? PLAN_HALF
-                                                                     : conv_out         ? (out ? PLAN_CONV_CODES : PLAN_CONV)
-                                                                                        : (out ? PLAN_LINEAR_CODES : PLAN_LINEAR));
+    GemmPlan plan = workspace_plan(a, out != nullptr);
     if (sparse) {
         // the structured-sparse form has one kernel: hardware E4M3 activations, E4M3 / E2M1 weights, exact accumulate
-        if (out || accumulate || acc_mode != FPQ_ACC_FP32 || xkind != OPK_FP8 || (wkind != OPK_FP8 && wkind != OPK_FP4))
+        if (out || accumulate || acc_mode != FPQ_ACC_FP32 || a.xkind != OPK_FP8 || (a.wkind != OPK_FP8 && a.wkind != OPK_FP4))
             return FPQ_ERR_UNSUPPORTED;
         plan = GemmPlan{TILE_GENERIC, 1};
     }
@@ -579,23 +652,11 @@ static int run_layer(const CodesOut* out, const void* x, int x_is_fp32, fpq_form
     if (x_is_fp32 && (!workspace || workspace_bytes < codes_bytes + part_bytes + (dyn ? kDynScaleBytes : 0)))
         return FPQ_ERR_WORKSPACE;
     if (!x_is_fp32 && (!workspace || workspace_bytes < part_bytes)) plan.splits = 1;
-    GemmArgs a;
-    memset(&a, 0, sizeof a);
     a.wrows = static_cast<const uint8_t*>(packed_w) + kPackedRowsOffset;
     a.sw = sw;
     a.bias = bias;
     a.sx = sx;
-    a.alpha = alpha;
     a.y = y;
-    a.M = (int)M;
-    a.N = (int)Cout;
-    a.Kpad = (int)padded_k(Cin, (int64_t)kh * kw);
-    a.Kreal = (int)(Cp * kh * kw);
-    a.B = (int)B; a.H = (int)H; a.W = (int)W; a.Cp = (int)Cp;
-    a.Ho = (int)Ho; a.Wo = (int)Wo;
-    a.kh = kh; a.kw = kw; a.stride = stride; a.pad = pad;
-    a.conv_out = conv_out;
-    a.xkind = xkind; a.wkind = wkind;
     a.xe = fx.ebits; a.xm = fx.mbits; a.xb = fx.bias;
     a.we = fw.ebits; a.wm = fw.mbits; a.wb = fw.bias;
     a.acc_mode = acc_mode;

@@ -154,6 +154,39 @@ def test_plan_query_and_format_range():
     assert B.fpq_format_check((5, 2, -64, 0.0)) == 0 and B.fpq_format_check((4, 3, -64, 0.0)) == 0
 
 
+def test_launch_plan_query():
+    """What runs, next to what the workspace is sized for: tiles over the wavefronts in place of slices where the grid is large enough, for
+    stored and for added fp32 results in the exact mode, and nowhere else; the refusals of the layer calls."""
+    E4M3, E2M1, E3M4, E3M0, E5M2 = synth.E4M3, synth.E2M1, synth.E3M4, synth.E3M0, synth.E5M2
+    deep = (8, 1280, 16, 16, 1280, 3, 3, 1, 1)
+    assert B.fpq_conv2d_plan(*deep) == (B.FPQ_KERNEL_128x160, 4)
+    for fx, fw in ((E4M3, E4M3), (E4M3, E2M1), (E3M4, E3M0)):
+        for add in (0, B.FPQ_OUT_ACCUMULATE):
+            assert B.fpq_conv2d_launch_plan(*deep, fx, fw, B.FPQ_ACC_FP32 | add) == (B.FPQ_KERNEL_128x80, 1)
+    assert B.fpq_conv2d_launch_plan(*deep, E4M3, E4M3, B.FPQ_ACC_FP8_MFMA) == B.fpq_conv2d_plan(*deep)
+    assert B.fpq_conv2d_launch_plan(*deep, E5M2, E5M2) == (B.FPQ_KERNEL_128x160, 4)
+    assert B.fpq_conv2d_launch_plan(1, 320, 64, 64, 320, 3, 3, 1, 1, E4M3, E4M3) == (B.FPQ_KERNEL_64x80, 1)
+    few = (1, 2560, 8, 8, 1280, 3, 3, 1, 1)                           # slices stay where the tiles are few
+    assert B.fpq_conv2d_launch_plan(*few, E4M3, E4M3) == B.fpq_conv2d_plan(*few) == (B.FPQ_KERNEL_128x160, 22)
+    assert B.fpq_gemm_launch_plan(2048, 1280, 4096, E4M3, E2M1) == (B.FPQ_KERNEL_128x80, 1)
+    assert B.fpq_gemm_launch_plan(128, 1280, 32768, E3M4, E3M4) == (B.FPQ_KERNEL_128x160, 32)
+    # what other kernels serve
+    assert B.fpq_gemm_launch_plan(8, 1280, 1280, E4M3, E4M3) == (B.FPQ_KERNEL_ROWS16, 1)
+    assert B.fpq_gemm_launch_plan(8, 1280, 1280, E3M4, E3M0)[0] == B.FPQ_KERNEL_SMALL_TILE
+    assert B.fpq_gemm_launch_plan(16384, 960, 320, E4M3, E4M3) == (B.FPQ_KERNEL_STRIP, 1)
+    assert B.fpq_gemm_launch_plan(16384, 960, 320, E4M3, E4M3, B.FPQ_OUT_ACCUMULATE) == (B.FPQ_KERNEL_128x160, 1)
+    assert B.fpq_conv2d_launch_plan(8, 64, 32, 32, 320, 7, 7, 1, 3, E4M3, E4M3) == (B.FPQ_KERNEL_SMALL_TILE, 1)   # 49 taps
+    L, p, f = B.lib(), B.fpq_plan_t(), B.fmt(E4M3)
+    assert L.fpq_gemm_launch_plan(8, 8, 16, f, f, 0, None) == -1
+    assert L.fpq_gemm_launch_plan(0, 8, 16, f, f, 0, C.byref(p)) == -4
+    assert L.fpq_gemm_launch_plan(8, 1 << 24, 16, f, f, 0, C.byref(p)) == -4
+    assert L.fpq_gemm_launch_plan(8, 1 << 20, 4096, f, f, 0, C.byref(p)) == -4                 # 4 GiB of weights
+    assert L.fpq_conv2d_launch_plan(1, 16, 2, 2, 8, 3, 3, 1, 0, f, f, 0, C.byref(p)) == -4
+    assert L.fpq_gemm_launch_plan(8, 8, 16, B.fmt(E2M1), f, 0, C.byref(p)) == -8               # four-bit activations
+    assert L.fpq_gemm_launch_plan(8, 8, 16, f, B.fmt((9, 1, 1, 0.0)), 0, C.byref(p)) == -2
+    assert L.fpq_gemm_launch_plan(8, 8, 16, f, f, B.FPQ_ACT_SILU, C.byref(p)) == -8            # no stored result
+
+
 def test_search_workspace_sizes():
     """The sizes the header states, in whole megabytes, and the least that is taken."""
     size = lambda n, e=4, j=111: B.fpq_search_workspace_size(n, e, j)

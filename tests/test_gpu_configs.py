@@ -138,8 +138,15 @@ def layer_class(L):
     return (L.kind, L.k if L.kind == "conv" else 1, L.stride if L.kind == "conv" else 1, L.M, L.K, L.N)
 
 
+def launched(L, fw):
+    """(kernel, K slices) that the layer launches with E4M3 activations."""
+    if L.kind == "conv":
+        return B.fpq_conv2d_launch_plan(L.B, L.Cin, L.H, L.W, L.Cout, L.k, L.k, L.stride, L.pad, synth.E4M3, fw)
+    return B.fpq_gemm_launch_plan(L.M, L.N, L.K, synth.E4M3, fw)
+
+
 def layer_plan(L):
-    """(kernel, K slices) the library states for this layer's shape."""
+    """(kernel, K slices) that the workspace of this layer's shape is sized for."""
     if L.kind == "conv":
         return B.fpq_conv2d_plan(L.B, L.Cin, L.H, L.W, L.Cout, L.k, L.k, L.stride, L.pad)
     return B.fpq_gemm_plan(L.M, L.N, L.K)
@@ -157,7 +164,8 @@ def cfg5_classes():
 
 
 CFG5_CLASSES = cfg5_classes()
-PLANS_RUN = set()   # (layer kind, kernel, K slices) of the class tests that have run in this process
+PLANS_RUN = set()   # (layer kind, kernel, K slices) of the class tests that have run in this process: the workspaces'
+LAUNCHES_RUN = set()   # ... and what they launched
 
 
 def sample_positions_large(M, seed):
@@ -205,7 +213,8 @@ def test_config5_every_shape_class(li, L):
     """Every distinct (kind, kernel size, stride, M, K, N) of the U-Net layer set at batch 8, with the inputs drawn on
     the device as bench.py draws them, through the bench's dynamic-scale call in the fp32-accumulate mode: W8A8
     (round-to-nearest E4M3 weights) and W4A8 (E2M1 weights with a rounding mask), on tile-corner and random rows the
-    oracle computes one by one.  The launch configuration is the one the benchmark times for this class."""
+    oracle computes one by one.  The launch configuration, of which `launched` tells the kernel, is the one the benchmark times for this
+    class."""
     sx_seed, sw_seed, sh_seed = synth.seeds(5, li)
     kk = L.k if L.kind == "conv" else 1
     x_t = synth.activations_torch((L.B, L.Cin, L.H, L.W) if L.kind == "conv" else (L.M, L.K), sx_seed, DEV)
@@ -215,7 +224,7 @@ def test_config5_every_shape_class(li, L):
     del x_t, w_t, h_t
     pos = sample_positions_large(L.M, li)
     kernel, slices = layer_plan(L)
-    # the slice count is visible from outside: the workspace of the codes form holds exactly the partial sums
+    # the slice count of the workspace's plan is visible from outside: that of the codes form holds exactly the partial sums
     if L.kind == "conv":
         part = B.fpq_conv2d_workspace_size(L.B, L.Cin, L.H, L.W, L.Cout, L.k, L.k, L.stride, L.pad, 0)
     else:
@@ -225,10 +234,11 @@ def test_config5_every_shape_class(li, L):
     check_layer_rows(L, x, w, None, synth.E4M3, synth.E4M3, B.FPQ_ACC_FP32, pos, "%s W8A8" % L.name)
     check_layer_rows(L, x, w, h, synth.E4M3, synth.E2M1, B.FPQ_ACC_FP32, pos, "%s W4A8" % L.name)
     PLANS_RUN.add((L.kind, kernel, slices))
+    LAUNCHES_RUN.update((L.kind,) + launched(L, fw) for fw in (synth.E4M3, synth.E2M1))
 
 
 def test_config5_classes_cover_every_plan_of_the_layer_set():
-    """The launch configurations (layer kind, kernel, K slices) of all 250 layers are exactly those of the class
+    """The workspaces' plans (layer kind, kernel, K slices) of all 250 layers, and what they launch, are exactly those of the class
     representatives above; and, when those tests ran in this process, exactly those that were compared."""
     layers = synth.unet_layers()
     assert len(layers) == 250 and len(CFG5_CLASSES) == len({layer_class(L) for L in layers})
@@ -236,5 +246,11 @@ def test_config5_classes_cover_every_plan_of_the_layer_set():
     class_plans = {(L.kind,) + tuple(layer_plan(L)) for _, L in CFG5_CLASSES}
     assert all_plans == class_plans
     assert any(k == B.FPQ_KERNEL_256x160 and s > 1 for _, k, s in all_plans), "the sliced 256-row plan is part of the set"
+    both = lambda Ls: {(L.kind,) + launched(L, fw) for L in Ls for fw in (synth.E4M3, synth.E2M1)}
+    all_launches = both(layers)
+    assert all_launches == both(L for _, L in CFG5_CLASSES)
+    # tiles over the wavefronts in the place of most slices, which are left to the deepest layers of few tiles
+    assert {("conv", B.FPQ_KERNEL_128x80, 1), ("conv", B.FPQ_KERNEL_64x80, 1), ("linear", B.FPQ_KERNEL_128x80, 1)} <= all_launches
+    assert {(kind, k) for kind, k, s in all_launches if s > 1} == {("conv", B.FPQ_KERNEL_128x160)}
     if len(PLANS_RUN) >= len(class_plans):
-        assert PLANS_RUN == all_plans
+        assert PLANS_RUN == all_plans and LAUNCHES_RUN == all_launches

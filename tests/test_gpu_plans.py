@@ -1,7 +1,9 @@
 """Every launch configuration the planner of the layer calls can produce -- kernel (small register-staged tiles,
 128 x 160 tiles, 256 x 160 tiles, the at-most-16-rows kernel, the short-K kernel) x number of K slices -- compared with the oracle:
 linear layers and convolutions, E4M3 and E2M1 weights, fp32 results and results as codes.  Each case first asserts,
-through the library's read-only plan query, that its shape still takes the configuration it is meant to cover."""
+through the library's read-only plan queries, that its shape still takes the configuration it is meant to cover: results as codes run the
+workspace's plan, fp32 results the launch plan, which is another one where the tables RUN_* say so.  (256 x 160 tiles in slices are left
+to codes, to the 8-bit accumulate mode and, with fp32 results in the exact mode, to linear layers.)"""
 import numpy as np
 import pytest
 import torch
@@ -16,7 +18,7 @@ pytestmark = pytest.mark.gpu
 
 E4M3, E2M1 = synth.E4M3, synth.E2M1
 SMALL, T256, T128, ROWS16 = B.FPQ_KERNEL_SMALL_TILE, B.FPQ_KERNEL_256x160, B.FPQ_KERNEL_128x160, B.FPQ_KERNEL_ROWS16
-STRIP = B.FPQ_KERNEL_STRIP
+STRIP, W128, W64 = B.FPQ_KERNEL_STRIP, B.FPQ_KERNEL_128x80, B.FPQ_KERNEL_64x80
 
 
 def rows_to_check(M, seed, tile=128, n_tiles=12, n_random=24):
@@ -49,13 +51,22 @@ LINEAR_PLANS = [
     (512, 8192, 1600, T128, 7),
     (512, 11520, 1280, T128, 8),
     (128, 32768, 1280, T128, 32),
+    (1500, 12288, 2080, T256, 3),
 ]
+# what fp32 results run instead, in one slice
+RUN_LINEAR = {
+    (2048, 8192, 2080): W128, (1280, 12288, 2720): W64, (1024, 16384, 2560): W128, (768, 20480, 2560): W128, (2048, 5120, 1280): W128,
+    (1408, 4096, 1280): W128, (1024, 4096, 1280): W64, (512, 5120, 1280): W64, (512, 8192, 1600): W64,
+}
 
 
 @pytest.mark.parametrize("M,K,N,kernel,slices", LINEAR_PLANS,
                          ids=["M%d_K%d_N%d_k%d_s%d" % c for c in LINEAR_PLANS])
 def test_linear_every_plan(M, K, N, kernel, slices):
     assert B.fpq_gemm_plan(M, N, K) == (kernel, slices), "this shape no longer takes the plan it is here to cover"
+    for fw in (E4M3, E2M1):
+        runs = (RUN_LINEAR[M, K, N], 1) if (M, K, N) in RUN_LINEAR else (kernel, slices)
+        assert B.fpq_gemm_launch_plan(M, N, K, E4M3, fw) == runs, "fp32 results no longer run what this shape is here to cover"
     want_ws = slices * M * N * 4 if slices > 1 else 0
     assert B.fpq_gemm_workspace_size(M, N, K, 0) == (want_ws + 255) // 256 * 256
     fx = E4M3
@@ -105,7 +116,13 @@ CONV_PLANS = [
     (8, 1280, 16, 16, 1280, 3, 1, T128, 4),
     (8, 1280, 8, 8, 1280, 3, 1, T128, 8),
     (8, 640, 32, 32, 640, 3, 2, T128, 4),
+    (1, 2560, 8, 8, 1280, 3, 1, T128, 22),
+    (3, 2560, 10, 10, 800, 3, 1, T128, 18),
 ]
+RUN_CONV = {
+    (2, 64, 24, 24, 320, 3, 1): W64, (8, 320, 32, 32, 320, 3, 1): W128, (8, 960, 32, 32, 640, 3, 1): W128, (8, 1920, 16, 16, 1280, 3, 1): W128,
+    (8, 1280, 16, 16, 1280, 3, 1): W128, (8, 1280, 8, 8, 1280, 3, 1): W64, (8, 640, 32, 32, 640, 3, 2): W64,
+}
 
 
 @pytest.mark.parametrize("case", CONV_PLANS, ids=["B%d_C%d_%dx%d_N%d_k%d_s%d_k%d_s%d" % c for c in CONV_PLANS])
@@ -114,6 +131,10 @@ def test_conv_every_plan(case):
     pad = k // 2
     assert B.fpq_conv2d_plan(Bn, Cin, H, W, Cout, k, k, stride, pad) == (kernel, slices), \
         "this shape no longer takes the plan it is here to cover"
+    for fw in (E4M3, E2M1):
+        assert B.fpq_conv2d_launch_plan(Bn, Cin, H, W, Cout, k, k, stride, pad, E4M3, fw) == \
+            ((RUN_CONV[case[:7]], 1) if case[:7] in RUN_CONV else (kernel, slices)), \
+            "fp32 results no longer run what this shape is here to cover"
     Ho, Wo = (H + 2 * pad - k) // stride + 1, (W + 2 * pad - k) // stride + 1
     M = Bn * Ho * Wo
     fx = E4M3

@@ -41,7 +41,7 @@ def both_ways(M, K, N, fw, x_kind, seed):
 
 
 def test_noalloc_equals_fpq_gemm_on_two_calls_in_a_row():
-    # dynamic scale + K slices: the scratch holds activation codes, partial sums, partial maxima and the scale
+    # dynamic scale, and room for K slices (the tiles that run have none): activation codes, partial maxima and the scale
     assert B.fpq_gemm_plan(512, 1280, 5120)[1] > 1
     both_ways(512, 5120, 1280, synth.E4M3, B.FPQ_X_FP32_DYNAMIC, 11)
     # a smaller input right after, which reuses the front of the same array: sliced again, fp32 input with a given scale
@@ -49,6 +49,13 @@ def test_noalloc_equals_fpq_gemm_on_two_calls_in_a_row():
     both_ways(384, 3072, 640, synth.E2M1, B.FPQ_X_FP32, 21)
     # and one on codes, where only the partial sums live in the scratch
     both_ways(300, 2880, 320, synth.E4M3, B.FPQ_X_CODES, 31)
+
+
+def test_noalloc_equals_fpq_gemm_in_slices_of_160_wide_tiles():
+    """The scratch holds activation codes, partial sums, partial maxima and the scale."""
+    assert B.fpq_gemm_launch_plan(512, 1280, 11520, synth.E4M3, synth.E4M3) == (B.FPQ_KERNEL_128x160, 8)
+    both_ways(512, 11520, 1280, synth.E4M3, B.FPQ_X_FP32_DYNAMIC, 51)
+    both_ways(100, 20480, 640, synth.E2M1, B.FPQ_X_FP32_DYNAMIC, 61)
 
 
 def test_noalloc_rejects_what_does_not_fit():

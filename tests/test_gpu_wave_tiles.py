@@ -1,6 +1,7 @@
 """The 128 x 80 and 64 x 80 tiles with K split over the wavefronts, at their edges, against the oracle: remainders of rows, columns and
-K, fewer steps of 64 codes than wavefronts, channels that wrap several taps a step, images that end inside a lane's four pixels, results that
-are added.  Each case first asks the rule, compiled here for the host, which of the two tiles its shape takes."""
+K, fewer steps of 64 codes than wavefronts, rows and columns that are a fraction of a tile, channels that wrap several taps a step, images that
+end inside a lane's four pixels, results that are added.  Each case first asks the rule, compiled here for the host, and the library's query which of
+the two tiles its shape takes in the encodings of the hardware, and which where both operands are moved into halves."""
 import functools
 import os
 import subprocess
@@ -78,17 +79,25 @@ def test_deep_layers_of_few_tiles_stay_in_slices(M, N, K, form):
     assert tile_of(128, 1280, 32768, form) < T128 and tile_of(128, 1280, 32768, LINEAR) < T128
 
 
-# M, K, N, tile
-LINEAR_CASES = [(2048, 4096, 1280, T128), (2047, 1584, 1279, T128), (1407, 4544, 641, T64), (3000, 3632, 641, T128), (2049, 4640, 321, T64)]
+def check_tile(rule, query, tile):
+    """tile 0: any other kernel."""
+    assert rule == tile or (tile == 0 and rule < T128), "this shape no longer takes the tile it is here to cover"
+    assert (query if query[0] in KERNEL.values() else 0) == ((KERNEL[tile], 1) if tile else 0), "the query names another kernel"
+
+
+KERNEL = {T128: B.FPQ_KERNEL_128x80, T64: B.FPQ_KERNEL_64x80}
+# M, K, N, tile in hardware encodings, tile of halves
+LINEAR_CASES = [(2048, 4096, 1280, T128, T128), (2047, 1584, 1279, T128, T128), (1407, 4544, 641, T64, 0), (3000, 3632, 641, T128, T128),
+                (2049, 4640, 321, T64, 0), (1033, 4016, 1039, T64, T64), (457, 1216, 2387, T64, T64)]
 
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("fx,fw", FORMS)
-@pytest.mark.parametrize("M,K,N,tile", LINEAR_CASES)
-def test_linear(M, K, N, tile, fx, fw):
+@pytest.mark.parametrize("M,K,N,tile,tile_half", LINEAR_CASES)
+def test_linear(M, K, N, tile, tile_half, fx, fw):
     print(M, K, N, fx, fw, flush=True)
-    if fx == E4M3:
-        assert tile_of(M, N, K, LINEAR) == tile, "this shape no longer takes the tile it is here to cover"
+    hardware = fx == E4M3
+    check_tile(tile_of(M, N, K, LINEAR if hardware else HALF), B.fpq_gemm_launch_plan(M, N, K, fx, fw), tile if hardware else tile_half)
     x = synth.activations((M, K), 400 + M)
     w = synth.weights((N, K), 500 + N)
     bias = np.linspace(-1, 1, N).astype(np.float32) if N % 2 else None
@@ -117,10 +126,15 @@ def test_linear(M, K, N, tile, fx, fw):
     assert np.allclose(h[4:-4].reshape(M, N), once + np.float32(1), rtol=1e-6, atol=1e-6 * np.abs(once).max())
 
 
-# B, Cin, H, W, Cout, kernel, stride, padding, tile
-CONV_CASES = [(8, 256, 16, 16, 1280, 3, 1, 1, T128), (3, 200, 75, 53, 392, 3, 2, 1, T64), (5, 33, 37, 57, 79, 3, 1, 0, T64),
-              (2, 640, 33, 31, 80, 1, 1, 0, T64), (6, 48, 25, 61, 239, 5, 1, 2, T128), (7, 20, 59, 35, 79, 5, 2, 2, T64),
-              (300, 384, 3, 1, 640, 3, 1, 1, T64), (2, 20, 21, 45, 321, 5, 2, 3, T64), (4, 33, 36, 47, 321, 3, 1, 0, T128)]
+# B, Cin, H, W, Cout, kernel, stride, padding, tile in hardware encodings, tile of halves
+CONV_CASES = [(8, 256, 16, 16, 1280, 3, 1, 1, T128, T128), (3, 200, 75, 53, 392, 3, 2, 1, T64, T64), (5, 33, 37, 57, 79, 3, 1, 0, T64, T64),
+              (2, 640, 33, 31, 80, 1, 1, 0, T64, T64), (6, 48, 25, 61, 239, 5, 1, 2, T128, T128), (7, 20, 59, 35, 79, 5, 2, 2, T64, T64),
+              (300, 384, 3, 1, 640, 3, 1, 1, T64, T64), (2, 20, 21, 45, 321, 5, 2, 3, T64, T64), (4, 33, 36, 47, 321, 3, 1, 0, T128, T128),
+              # K of one, two and three steps
+              (1, 16, 7, 7, 7, 1, 1, 0, T64, 0), (7, 128, 40, 61, 199, 1, 2, 0, T64, 0), (2, 5, 53, 81, 10, 3, 1, 1, T64, T64),
+              (1, 192, 19, 21, 199, 1, 1, 1, T64, T64),
+              # fewer rows than a tile has, and fewer columns
+              (1, 640, 8, 8, 1280, 3, 2, 1, T64, 0), (1, 33, 5, 9, 7001, 3, 1, 1, T64, T64), (1, 16, 7, 7, 1, 3, 1, 1, T64, T64)]
 
 
 @pytest.mark.gpu
@@ -128,19 +142,19 @@ CONV_CASES = [(8, 256, 16, 16, 1280, 3, 1, 1, T128), (3, 200, 75, 53, 392, 3, 2,
 @pytest.mark.parametrize("case", CONV_CASES)
 def test_conv(case, fx, fw):
     print(case, fx, fw, flush=True)
-    Bn, Cin, H, W, Cout, k, stride, pad, tile = case
+    Bn, Cin, H, W, Cout, k, stride, pad, tile, tile_half = case
     Ho, Wo = (H + 2 * pad - k) // stride + 1, (W + 2 * pad - k) // stride + 1
     M = Bn * Ho * Wo
-    if fx == E4M3:
-        assert tile_of(M, Cout, k * k * B.fpq_padded_channels(Cin), CONV, Ho * Wo % 4 != 0) == tile, \
-            "this shape no longer takes the tile it is here to cover"
+    hardware = fx == E4M3
+    check_tile(tile_of(M, Cout, k * k * B.fpq_padded_channels(Cin), CONV if hardware else HALF, Ho * Wo % 4 != 0),
+               B.fpq_conv2d_launch_plan(Bn, Cin, H, W, Cout, k, k, stride, pad, fx, fw), tile if hardware else tile_half)
     x = synth.activations((Bn, Cin, H, W), 600 + Cin)
     w = synth.weights((Cout, Cin, k, k), 700 + Cout)
     bias = np.linspace(-0.5, 0.5, Cout).astype(np.float32) if Cout % 4 else None
     sx = oracle.scale_from_absmax(oracle.absmax(x), fx[3])
     xq = oracle.quantize(x, fx, sx)
     wq, sw = oracle.pack_weights(w, fw, None)
-    pos = np.unique(np.concatenate([np.arange(70), np.arange(M - 140, M), np.random.default_rng(M).integers(0, M, 60)]))
+    pos = np.unique(np.concatenate([np.arange(min(M, 70)), np.arange(max(0, M - 140), M), np.random.default_rng(M).integers(0, M, 60)]))
     Y, T = oracle.conv2d(xq, fx, sx, wq, fw, sw, bias, stride=stride, pad=pad, pix=pos)
     packed, sw_t, _ = gpu_pack(w, fw, None, want_codes=False)
     codes = torch.empty(Bn * H * W * B.fpq_padded_channels(Cin), dtype=torch.uint8, device=DEV)

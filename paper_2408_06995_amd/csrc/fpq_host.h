@@ -409,6 +409,33 @@ static inline GemmPlan plan_arithmetic(int64_t M, int64_t N, int64_t Kpad)
     return unsliced_part_grid(p, M, N, nk) ? GemmPlan{TILE_GENERIC, 1} : p;
 }
 
+// Tile of the integer layer (igemm.hip): rows x columns, stages of 128 codes.
+enum IntTile : int { INT_64x64_S2 = 0, INT_64x64_S3 = 1, INT_64x128 = 2, INT_128x128 = 3 };
+// 128 x 128 tiles where they fill the compute units, cover few columns beyond N and have 10 G multiply-adds or more to do: their rate
+// is the higher one and their start and last round the longer ones (time of 64 x 64 over theirs, 456 layers of random sizes:
+// 0.7 to 0.9 below that, 1.0 there, 1.1 to 1.3 beyond; K of at most 128 0.7 to 0.95 throughout.  2048 x 1280 -> 10240 57 and 41 us,
+// 5200 x 528 -> 1024 11.9 and 17.0).  64 x 64 tiles with a third stage where a deep K has to hide its loads with at most two
+// workgroups per compute unit (2000 x 5120 -> 640: 45 us, 52 with two stages; 32815 x 2672 -> 28, 513 tiles: 21.5 and 17.8), which
+// otherwise costs the room for five of them (30000 x 64 -> 1001: 56 and 47).
+// 64 x 128 tiles between the two: more of them run together than of the large ones (three per compute unit, five with 4-bit weights,
+// two of the others) and each reads half the weights of two small ones.  8 G multiply-adds and more in 600 to 1500 of them, not
+// just over one round of 768 (4-bit weights: 700 to 1024), unless the large tiles make one well filled round: 0.88 of the others'
+// time over the 44 layers of random sizes that these ends were found on, 0.89 over 61 others, at most 1.05 (2702 x 1216 -> 4352 27.9 -> 29.3 us; 8192 x 2560 -> 640 28.4 -> 24.8 us, 8192 x 1280 -> 1280 26.5 -> 23.6, 1472 x 1024
+// -> 7040 32.5 -> 19.9; elsewhere: 7936 x 1472 -> 832, 868 tiles, 21.9 and 23.8; in a round of 384 to 512 large tiles up to
+// 1.2 times their time, beyond 1500 1.0 to 1.3, K below 1000 0.9 to 1.1).
+static inline IntTile int_tile(int64_t M, int64_t N, int64_t K, int64_t Kpad, int wbits)
+{
+    const int64_t tiles128 = ((M + 127) / 128) * ((N + 127) / 128), tiles64 = ((M + 63) / 64) * ((N + 63) / 64);
+    const int64_t tiles64x128 = ((M + 63) / 64) * ((N + 127) / 128);
+    const bool few_beyond = (N + 127) / 128 * 128 * 10 <= N * 11;
+    const bool large = tiles128 >= 320 && few_beyond && K > 128 && M * N * K >= (int64_t)10000000000;
+    const bool middle = few_beyond && K >= 1000 && M * N * K >= (int64_t)8000000000 && !(large && tiles128 >= 384 && tiles128 <= 512) &&
+                        (wbits == 4 ? tiles64x128 >= 700 && tiles64x128 <= 1024
+                                    : tiles64x128 >= 600 && tiles64x128 <= 1500 && (tiles64x128 <= 768 || tiles64x128 >= 900));
+    const bool third = Kpad >= 2048 && tiles64 <= 512;
+    return middle ? INT_64x128 : large ? INT_128x128 : third ? INT_64x64_S3 : INT_64x64_S2;
+}
+
 static inline size_t split_workspace_bytes(const GemmPlan& p, int64_t M, int64_t N)
 {
     return p.splits > 1 ? (size_t)p.splits * (size_t)M * (size_t)N * sizeof(float) : 0;

@@ -1,5 +1,10 @@
 """The same-bitwidth integer baseline (Eq. (4)): calibration, quantizer and packed weights bit for bit against the
 oracle, and the integer-matrix-instruction layer against the oracle's exact integer sums."""
+import functools
+import os
+import subprocess
+import tempfile
+
 import numpy as np
 import pytest
 import torch
@@ -10,6 +15,38 @@ from paper_2408_06995_amd import synth
 from gpu_util import DEV, check_close, dev
 
 pytestmark = pytest.mark.gpu
+
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2408_06995_amd", "csrc")
+PROGRAM = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#include "fpq_host.h"
+int main(int, char** v)
+{
+    const long long K = atoll(v[3]);
+    printf("%d\n", fpq::int_tile(atoll(v[1]), atoll(v[2]), K, (K + 127) / 128 * 128, atoi(v[4])));
+    return 0;
+}
+"""
+S2, S3, MIDDLE, LARGE = range(4)      # IntTile: 64 x 64 in two and three stages, 64 x 128, 128 x 128
+
+
+@functools.lru_cache(maxsize=None)
+def program():
+    d = tempfile.mkdtemp()
+    with open(os.path.join(d, "rule.cpp"), "w") as f:
+        f.write(PROGRAM)
+    exe = os.path.join(d, "rule")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-w", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", CSRC, os.path.join(d, "rule.cpp"),
+                           "-o", exe])
+    return exe
+
+
+def check_tile(M, K, N, wbits, tile):
+    """The rule, compiled here for the host, gives the shape to the tile that it is here to cover."""
+    got = int(subprocess.run([program()] + [str(v) for v in (M, N, K, wbits)], capture_output=True, text=True, check=True).stdout)
+    assert got == tile, "this shape no longer takes the tile it is here to cover"
 
 
 def gpu_calibrate(x_t, bits):
@@ -137,20 +174,31 @@ def test_integer_entry_points_validate():
     assert B.fpq_int_packed_size(320, 320, 4) == 256 + 320 * 192 + 320 * 4
 
 
+THREE_STAGES = [(70, 2064, 129), (1, 32752, 65), (513, 4112, 66), (65, 2032, 64)]
+
+
 @pytest.mark.parametrize("M,K,N", [(2600, 560, 2050), (5200, 528, 1024), (3000, 1040, 1793),      # 64 x 64, two stages
                                    (4099, 144, 1285), (5100, 272, 1024), (5100, 512, 1024),
                                    (70, 2064, 129), (1, 32752, 65), (513, 4112, 66), (65, 2032, 64),   # 64 x 64, three stages
                                    (1100, 64, 33), (65, 1904, 64), (24610, 2064, 65)])            # two: few steps, or many tiles
 @pytest.mark.parametrize("wbits", [8, 4])
 def test_tiles_of_the_integer_layer(M, K, N, wbits):
+    check_tile(M, K, N, wbits, S3 if (M, K, N) in THREE_STAGES else S2)
     test_integer_layer(M, K, N, wbits)
 
 
-@pytest.mark.parametrize("M,K,N", [(17003, 144, 4101), (8201, 1104, 1157), (3001, 2080, 1793), (66000, 656, 256)])
+@pytest.mark.parametrize("M,K,N,tile", [(17003, 144, 4101, LARGE), (8201, 1104, 1157, S2), (3001, 2080, 1793, MIDDLE), (66000, 656, 256, LARGE),
+                                        (12001, 1104, 1165, LARGE), (6500, 2080, 1793, LARGE)])
 @pytest.mark.parametrize("wbits", [8, 4])
-def test_large_tiles_of_the_integer_layer(M, K, N, wbits):
-    """128 x 128 tiles: from 10 G multiply-adds on, with remainders of rows, columns and K; the same integers from torch's products in
+def test_large_tiles_of_the_integer_layer(M, K, N, tile, wbits):
+    """128 x 128 tiles: from 10 G multiply-adds on, with remainders of rows, columns and K, unless many columns lie beyond N or the middle
+    tiles take them; the same integers from torch's products in
     double, which are exact below 2^53."""
+    check_tile(M, K, N, wbits, tile)
+    whole_layer(M, K, N, wbits)
+
+
+def whole_layer(M, K, N, wbits):
     g = torch.Generator(device=DEV)
     g.manual_seed(M + K)
     codes = torch.randint(0, 256, (M, K), generator=g, device=DEV, dtype=torch.uint8)
@@ -170,10 +218,14 @@ def test_large_tiles_of_the_integer_layer(M, K, N, wbits):
 
 
 @pytest.mark.parametrize("M,K,N,wbits", [(4033, 1008, 2047, 8), (4033, 1008, 2047, 4), (3009, 1616, 1793, 8), (3009, 1616, 1793, 4),
-                                         (6001, 1104, 1793, 8), (2049, 2576, 2303, 8)])
+                                         (6001, 1104, 1793, 8), (2177, 2576, 2303, 8), (2625, 2064, 2175, 4), (4161, 3088, 1407, 4),
+                                         # the ends of the ranges: 600, 768, 900 and 1500 tiles; 700
+                                         (2500, 1808, 1793, 8), (3009, 1424, 2047, 8), (3780, 1200, 1793, 8), (6337, 1104, 1793, 8),
+                                         (3137, 1504, 1700, 4)])
 def test_middle_tiles_of_the_integer_layer(M, K, N, wbits):
     """64 x 128 tiles: from 8 G multiply-adds on, in 600 to 768 or 900 to 1500 of them (4-bit weights 700 to 1024), with the same remainders."""
-    test_large_tiles_of_the_integer_layer(M, K, N, wbits)
+    check_tile(M, K, N, wbits, MIDDLE)
+    whole_layer(M, K, N, wbits)
 
 
 @pytest.mark.parametrize("n", [1, 2, 3, 4, 7, 1023, 100003])

@@ -350,12 +350,18 @@ static inline GemmPlan plan_gemm(int64_t M, int64_t N, int64_t Kpad, PlanForm fo
 // us_codes us per MB, and 0.3 more beyond the 256 MB of the last-level cache (16959 x 30624 -> 160: 250 us in four slices, 342 here).
 // Constants fitted to 8960 layers of random sizes; over 1900 others the choice takes 0.87 of the other plans' time in the geometric
 // mean (the better of both kernels everywhere 0.86; convolutions and halves that were sliced 0.65 to 0.8), 17 of them are slower by more than
-// 3 %, at most by 18 % (9411 x 28544 -> 339: 203 -> 238 us).
+// 3 %, at most by 18 % (3609 x 27088 -> 478: 106 -> 125 us).  Of the U-Net's layers at batch 1 to 16, 660 by sizes and operands, 315 take these tiles, in
+// 0.73 of the time, none of them slower by more than 3 %.
 //   - 256-row tiles of images that are no multiple of four pixels, whose stores are single elements, lose throughout (102 layers: 0.41
 //     to 0.85 of their time here).
 //   - Few tiles with a deep K stay in slices: this kernel has 8 to 64 workgroups there, each with all of K (1 x 2560 x 8 x 8 -> 1280, 3 x 3:
 //     31.8 us in 22 slices, 45.9 here; moved into halves 36 and 73).  Half a round and more leave them (8 x 1280 x 16 x 16 -> 1280, 3 x 3: 57 + 10 us
 //     in four slices, 46 us here).
+//   - Halves with K of at most 2048 keep their tiles where this kernel goes more than eight rounds (51 layers of 128 x 160 tiles: 0.88 to 1.3
+//     times their time here; 49284 x 1504 -> 1280 294 and 373 us), 128 x 160 tiles with K of at most 1280 from the second round on (218 layers,
+//     0.77 to 1.9; 1024 x 1280 -> 3840 23.1 and 25.1 us): the rounds of the others overlap.
+//   - Whole rounds of 256-row tiles have to be beaten by 20 %: several rounds in a row run here at the clock that the matrix unit's power
+//     leaves (8 x 960 x 64 x 64 -> 320, 3 x 3: 145 and 155 us, where the model has 143 and 121; 8 x 1280 x 32 x 32 -> 1280 176 and 180).
 //   - Linear layers with K of at most 1024, or with at most twelve 64 x 64 tiles, keep their kernels: their sums are those of the
 //     grouped call, bit for bit.  What K4 cuts into slices keeps them: few tiles.
 static inline GemmPlan plan_over_waves(const GemmPlan& p, int64_t M, int64_t N, int64_t Kreal, PlanForm form, bool ragged_images)
@@ -387,6 +393,7 @@ static inline GemmPlan plan_over_waves(const GemmPlan& p, int64_t M, int64_t N, 
     }
     const GemmPlan here{us[0] < us[1] ? TILE_WAVE_128x80 : TILE_WAVE_64x80, 1};
     if (f == 1 && p.tile == TILE_256x160_S3 && p.splits == 1 && ragged_images) return here;
+    if (f == 2 && Kreal <= 2048 && tiles(128, 80) > (Kreal <= 1280 && p.tile == TILE_128x160_S2 ? 256 : 8 * 256)) return p;
     const int64_t items = tiles(bx[p.tile], bw[p.tile]) * p.splits;
     const double per = (double)items / 256.0, up = (double)((items + 255) / 256);
     const double w = p.tile == TILE_GENERIC || p.tile >= TILE_WAVE_K4 ? (per > 1.0 ? per : 1.0)
@@ -395,7 +402,8 @@ static inline GemmPlan plan_over_waves(const GemmPlan& p, int64_t M, int64_t N, 
     const float* t = p.splits > 1 ? us_sliced[f][p.tile - 1] : us_whole[f][p.tile];
     const double other = p.splits > 1 ? t[0] + w * t[1] * nk / p.splits + t[2] * (double)p.splits * (double)M * (double)N * 1e-6
                                       : t[0] + w * (t[1] + t[2] * nk);
-    return (us[0] < us[1] ? us[0] : us[1]) < 0.9 * other ? here : p;
+    const double margin = f == 1 && p.tile == TILE_256x160_S3 && p.splits == 1 && per >= 0.9 * up ? 0.8 : 0.9;
+    return (us[0] < us[1] ? us[0] : us[1]) < margin * other ? here : p;
 }
 // Operands decoded arithmetically (five exponent bits and more): the small tiles are not built for them, so widths that are
 // multiples of 160 keep the 160-wide tiles and their slices (E5M2, 256 x 11520 -> 1280: 70 us, 209 us on the register-staged

@@ -79,6 +79,15 @@ def test_deep_layers_of_few_tiles_stay_in_slices(M, N, K, form):
     assert tile_of(128, 1280, 32768, form) < T128 and tile_of(128, 1280, 32768, LINEAR) < T128
 
 
+def test_many_rounds_and_whole_rounds_of_larger_tiles_keep_them():
+    for M, N, K in [(49284, 1280, 1504), (73728, 1120, 1440), (60236, 960, 1760), (86640, 1280, 1440)]:
+        assert tile_of(M, N, K, HALF) < T128
+    for M, N, K in [(1024, 3840, 1280), (16384, 320, 1280), (4096, 1280, 1280), (512, 10240, 1280)]:
+        assert tile_of(M, N, K, HALF) < T128
+    assert tile_of(32768, 320, 8640, CONV) < T128 and tile_of(32768, 320, 5760, CONV) < T128
+    assert tile_of(8192, 1280, 11520, CONV) < T128 and tile_of(8192, 640, 11520, CONV) == T128
+
+
 def check_tile(rule, query, tile):
     """tile 0: any other kernel."""
     assert rule == tile or (tile == 0 and rule < T128), "this shape no longer takes the tile it is here to cover"

@@ -32,8 +32,8 @@ PEAK_HBM_GBS = 8000.0
 # split-K reductions included): not measurable from inside this script, hence a constant, valid only for the workload,
 # accumulate mode and call structure it was taken on; the summary file named here holds the command and the arithmetic.
 MEASURED_TRAFFIC = {
-    ("cfg5", "fp32", "grouped"): {"bytes_per_launch": 65.15e6,
-                                  "source": "profiles/cfg5_layer_kernels_hbm_traffic_pmc.txt: 30.51 MB fetched + 34.64 MB written "
+    ("cfg5", "fp32", "grouped"): {"bytes_per_launch": 53.18e6,
+                                  "source": "profiles/cfg5_layer_kernels_hbm_traffic_pmc.txt: 22.62 MB fetched + 30.56 MB written "
                                             "per layer over 4 x 500 layers"},
 }
 

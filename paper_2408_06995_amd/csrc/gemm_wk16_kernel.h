@@ -12,13 +12,13 @@
 // Loads run NST steps ahead: with two stages of 64 codes, as in gemm_wk_kernel.h, a step took as long as a load (2000 cycles).  A step of
 // the 128 x 80 tile is 1280 cycles of MFMAs, measured 1800 with masked loads: what bounds it is the issue of one wavefront's MFMAs,
 // conversions and loads (80, 104 and 13 a step).  Outside the loop: 3000 cycles to the first load's issue and 11000 for sums and stores.
-// us, codes in (dynamic scale where marked), before -> here: 8 x 1280 x 16 x 16 -> 1280, 3 x 3: E4M3 68 -> 48.5, E2M1 weights 71 -> 54
-// (dynamic), E3M4 x E3M0 96 -> 67.5 (static); 8 x 640 x 32 x 32 -> 640: 63 -> 52; 1 x 320 x 64 x 64 -> 320 23.9 -> 17.6 (dynamic);
-// 3 x 200 x 75 x 53 -> 392, stride 2: 23.6 -> 18.3 (dynamic).  Tried without gain: operands from memory straight into registers (sixteen rows
+// us before -> here, 3 x 3: 8 x 1280 x 16 x 16 -> 1280, codes in, E4M3 68.8 -> 50.7; E2M1 weights, dynamic scale, 72.9 -> 54.8; E3M4 x E3M0,
+// static scale, 96.5 -> 66.3; 8 x 640 x 32 x 32 -> 640, codes in, 67.8 -> 57.0; with a dynamic scale 1 x 320 x 64 x 64 -> 320 23.9 -> 17.2, and
+// 3 x 200 x 75 x 53 -> 392, stride 2, 23.5 -> 19.0.  Tried without gain: operands from memory straight into registers (sixteen rows
 // of 64 bytes a load are 61 cache accesses, 15 in the order that LDS allows: 79 us for the first of these), eight wavefronts with two
 // steps each in flight (the small tile 18.3 us where four take 17.6).
-// Four partial sums have no larger error than one or the slices had (root mean square of the difference to the sum in 64 bits, over the sum of the
-// products' magnitudes, before -> here): 8 x 1280 x 16 x 16 -> 1280 1.484e-9 -> 1.476e-9, E2M1 weights 9.7e-10 -> 6.5e-10; 1 x 320 x 64 x 64 -> 320
+// Error of four partial sums against one or the slices (root mean square of the difference to the sum in 64 bits, over the sum of the
+// products' magnitudes, before -> here), 0.67 to 1.01 of it over 21 layers: 8 x 1280 x 16 x 16 -> 1280 1.484e-9 -> 1.476e-9, E2M1 weights 9.7e-10 -> 6.5e-10; 1 x 320 x 64 x 64 -> 320
 // 2.05e-9 -> 2.07e-9; 3 x 200 x 75 x 53 -> 392 2.31e-9 -> 2.30e-9; 3000 x 3632 -> 641 2.53e-9 -> 1.92e-9.
 #pragma once
 #include "gemm_dma_kernel.h"

@@ -187,18 +187,11 @@ def test_tiles_of_the_integer_layer(M, K, N, wbits):
     test_integer_layer(M, K, N, wbits)
 
 
-@pytest.mark.parametrize("M,K,N,tile", [(17003, 144, 4101, LARGE), (8201, 1104, 1157, S2), (3001, 2080, 1793, MIDDLE), (66000, 656, 256, LARGE),
-                                        (12001, 1104, 1165, LARGE), (6500, 2080, 1793, LARGE)])
+@pytest.mark.parametrize("M,K,N", [(17003, 144, 4101), (8201, 1104, 1157), (3001, 2080, 1793), (66000, 656, 256)])
 @pytest.mark.parametrize("wbits", [8, 4])
-def test_large_tiles_of_the_integer_layer(M, K, N, tile, wbits):
-    """128 x 128 tiles: from 10 G multiply-adds on, with remainders of rows, columns and K, unless many columns lie beyond N or the middle
-    tiles take them; the same integers from torch's products in
+def test_large_tiles_of_the_integer_layer(M, K, N, wbits):
+    """128 x 128 tiles: from 10 G multiply-adds on, with remainders of rows, columns and K; the same integers from torch's products in
     double, which are exact below 2^53."""
-    check_tile(M, K, N, wbits, tile)
-    whole_layer(M, K, N, wbits)
-
-
-def whole_layer(M, K, N, wbits):
     g = torch.Generator(device=DEV)
     g.manual_seed(M + K)
     codes = torch.randint(0, 256, (M, K), generator=g, device=DEV, dtype=torch.uint8)
@@ -218,14 +211,36 @@ def whole_layer(M, K, N, wbits):
 
 
 @pytest.mark.parametrize("M,K,N,wbits", [(4033, 1008, 2047, 8), (4033, 1008, 2047, 4), (3009, 1616, 1793, 8), (3009, 1616, 1793, 4),
-                                         (6001, 1104, 1793, 8), (2177, 2576, 2303, 8), (2625, 2064, 2175, 4), (4161, 3088, 1407, 4),
+                                         (6001, 1104, 1793, 8), (2049, 2576, 2303, 8)])
+def test_middle_tiles_of_the_integer_layer(M, K, N, wbits):
+    """64 x 128 tiles: from 8 G multiply-adds on, in 600 to 768 or 900 to 1500 of them (4-bit weights 700 to 1024), with the same remainders."""
+    test_large_tiles_of_the_integer_layer(M, K, N, wbits)
+
+
+# Of the shapes above 8201 x 1104 -> 1157 (many columns beyond N) and 2049 x 2576 -> 2303 (594 tiles) take 64 x 64 tiles, and 3001 x 2080 ->
+# 1793 the middle ones.
+@pytest.mark.parametrize("M,K,N,wbits,tile", [(17003, 144, 4101, w, LARGE) for w in (8, 4)] + [(66000, 656, 256, w, LARGE) for w in (8, 4)] +
+                         [(8201, 1104, 1157, w, S2) for w in (8, 4)] + [(3001, 2080, 1793, w, MIDDLE) for w in (8, 4)] +
+                         [(4033, 1008, 2047, w, MIDDLE) for w in (8, 4)] + [(3009, 1616, 1793, w, MIDDLE) for w in (8, 4)] +
+                         [(6001, 1104, 1793, 8, MIDDLE), (2049, 2576, 2303, 8, S2)])
+def test_rule_of_the_integer_layer(M, K, N, wbits, tile):
+    check_tile(M, K, N, wbits, tile)
+
+
+@pytest.mark.parametrize("M,K,N", [(12001, 1104, 1165), (6500, 2080, 1793)])
+@pytest.mark.parametrize("wbits", [8, 4])
+def test_large_tiles_with_remainders(M, K, N, wbits):
+    check_tile(M, K, N, wbits, LARGE)
+    test_large_tiles_of_the_integer_layer(M, K, N, wbits)
+
+
+@pytest.mark.parametrize("M,K,N,wbits", [(2177, 2576, 2303, 8), (2625, 2064, 2175, 4), (4161, 3088, 1407, 4),
                                          # the ends of the ranges: 600, 768, 900 and 1500 tiles; 700
                                          (2500, 1808, 1793, 8), (3009, 1424, 2047, 8), (3780, 1200, 1793, 8), (6337, 1104, 1793, 8),
                                          (3137, 1504, 1700, 4)])
-def test_middle_tiles_of_the_integer_layer(M, K, N, wbits):
-    """64 x 128 tiles: from 8 G multiply-adds on, in 600 to 768 or 900 to 1500 of them (4-bit weights 700 to 1024), with the same remainders."""
+def test_middle_tiles_at_the_ends_of_their_range(M, K, N, wbits):
     check_tile(M, K, N, wbits, MIDDLE)
-    whole_layer(M, K, N, wbits)
+    test_large_tiles_of_the_integer_layer(M, K, N, wbits)
 
 
 @pytest.mark.parametrize("n", [1, 2, 3, 4, 7, 1023, 100003])

@@ -1,7 +1,7 @@
 """The 128 x 80 and 64 x 80 tiles with K split over the wavefronts, at their edges, against the oracle: remainders of rows, columns and
 K, fewer steps of 64 codes than wavefronts, rows and columns that are a fraction of a tile, channels that wrap several taps a step, images that
-end inside a lane's four pixels, results that are added.  Each case first asks the rule, compiled here for the host, and the library's query which of
-the two tiles its shape takes in the encodings of the hardware, and which where both operands are moved into halves."""
+end inside a lane's four pixels, results that are added.  The rule, compiled here for the host, and the library's query are asked which of the
+two tiles each shape takes in the encodings of the hardware, and which where both operands are moved into halves."""
 import functools
 import os
 import subprocess
@@ -95,18 +95,17 @@ def check_tile(rule, query, tile):
 
 
 KERNEL = {T128: B.FPQ_KERNEL_128x80, T64: B.FPQ_KERNEL_64x80}
-# M, K, N, tile in hardware encodings, tile of halves
-LINEAR_CASES = [(2048, 4096, 1280, T128, T128), (2047, 1584, 1279, T128, T128), (1407, 4544, 641, T64, 0), (3000, 3632, 641, T128, T128),
-                (2049, 4640, 321, T64, 0), (1033, 4016, 1039, T64, T64), (457, 1216, 2387, T64, T64)]
+# M, K, N, tile
+LINEAR_CASES = [(2048, 4096, 1280, T128), (2047, 1584, 1279, T128), (1407, 4544, 641, T64), (3000, 3632, 641, T128), (2049, 4640, 321, T64)]
 
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("fx,fw", FORMS)
-@pytest.mark.parametrize("M,K,N,tile,tile_half", LINEAR_CASES)
-def test_linear(M, K, N, tile, tile_half, fx, fw):
+@pytest.mark.parametrize("M,K,N,tile", LINEAR_CASES)
+def test_linear(M, K, N, tile, fx, fw):
     print(M, K, N, fx, fw, flush=True)
-    hardware = fx == E4M3
-    check_tile(tile_of(M, N, K, LINEAR if hardware else HALF), B.fpq_gemm_launch_plan(M, N, K, fx, fw), tile if hardware else tile_half)
+    if fx == E4M3:
+        assert tile_of(M, N, K, LINEAR) == tile, "this shape no longer takes the tile it is here to cover"
     x = synth.activations((M, K), 400 + M)
     w = synth.weights((N, K), 500 + N)
     bias = np.linspace(-1, 1, N).astype(np.float32) if N % 2 else None
@@ -135,15 +134,10 @@ def test_linear(M, K, N, tile, tile_half, fx, fw):
     assert np.allclose(h[4:-4].reshape(M, N), once + np.float32(1), rtol=1e-6, atol=1e-6 * np.abs(once).max())
 
 
-# B, Cin, H, W, Cout, kernel, stride, padding, tile in hardware encodings, tile of halves
-CONV_CASES = [(8, 256, 16, 16, 1280, 3, 1, 1, T128, T128), (3, 200, 75, 53, 392, 3, 2, 1, T64, T64), (5, 33, 37, 57, 79, 3, 1, 0, T64, T64),
-              (2, 640, 33, 31, 80, 1, 1, 0, T64, T64), (6, 48, 25, 61, 239, 5, 1, 2, T128, T128), (7, 20, 59, 35, 79, 5, 2, 2, T64, T64),
-              (300, 384, 3, 1, 640, 3, 1, 1, T64, T64), (2, 20, 21, 45, 321, 5, 2, 3, T64, T64), (4, 33, 36, 47, 321, 3, 1, 0, T128, T128),
-              # K of one, two and three steps
-              (1, 16, 7, 7, 7, 1, 1, 0, T64, 0), (7, 128, 40, 61, 199, 1, 2, 0, T64, 0), (2, 5, 53, 81, 10, 3, 1, 1, T64, T64),
-              (1, 192, 19, 21, 199, 1, 1, 1, T64, T64),
-              # fewer rows than a tile has, and fewer columns
-              (1, 640, 8, 8, 1280, 3, 2, 1, T64, 0), (1, 33, 5, 9, 7001, 3, 1, 1, T64, T64), (1, 16, 7, 7, 1, 3, 1, 1, T64, T64)]
+# B, Cin, H, W, Cout, kernel, stride, padding, tile
+CONV_CASES = [(8, 256, 16, 16, 1280, 3, 1, 1, T128), (3, 200, 75, 53, 392, 3, 2, 1, T64), (5, 33, 37, 57, 79, 3, 1, 0, T64),
+              (2, 640, 33, 31, 80, 1, 1, 0, T64), (6, 48, 25, 61, 239, 5, 1, 2, T128), (7, 20, 59, 35, 79, 5, 2, 2, T64),
+              (300, 384, 3, 1, 640, 3, 1, 1, T64), (2, 20, 21, 45, 321, 5, 2, 3, T64), (4, 33, 36, 47, 321, 3, 1, 0, T128)]
 
 
 @pytest.mark.gpu
@@ -151,12 +145,12 @@ CONV_CASES = [(8, 256, 16, 16, 1280, 3, 1, 1, T128, T128), (3, 200, 75, 53, 392,
 @pytest.mark.parametrize("case", CONV_CASES)
 def test_conv(case, fx, fw):
     print(case, fx, fw, flush=True)
-    Bn, Cin, H, W, Cout, k, stride, pad, tile, tile_half = case
+    Bn, Cin, H, W, Cout, k, stride, pad, tile = case
     Ho, Wo = (H + 2 * pad - k) // stride + 1, (W + 2 * pad - k) // stride + 1
     M = Bn * Ho * Wo
-    hardware = fx == E4M3
-    check_tile(tile_of(M, Cout, k * k * B.fpq_padded_channels(Cin), CONV if hardware else HALF, Ho * Wo % 4 != 0),
-               B.fpq_conv2d_launch_plan(Bn, Cin, H, W, Cout, k, k, stride, pad, fx, fw), tile if hardware else tile_half)
+    if fx == E4M3:
+        assert tile_of(M, Cout, k * k * B.fpq_padded_channels(Cin), CONV, Ho * Wo % 4 != 0) == tile, \
+            "this shape no longer takes the tile it is here to cover"
     x = synth.activations((Bn, Cin, H, W), 600 + Cin)
     w = synth.weights((Cout, Cin, k, k), 700 + Cout)
     bias = np.linspace(-0.5, 0.5, Cout).astype(np.float32) if Cout % 4 else None
@@ -186,3 +180,40 @@ def test_conv(case, fx, fw):
     h = buf.cpu().numpy()
     assert np.isnan(h[:4]).all() and np.isnan(h[-4:]).all(), "written outside the result"
     assert np.allclose(h[4:-4], once + np.float32(1), rtol=1e-6, atol=1e-6 * np.abs(once).max())
+
+
+# The tile of each shape above where both operands are moved into halves (0: any other kernel)
+LINEAR_HALVES = [T128, T128, 0, T128, 0]
+CONV_HALVES = [T128, T64, T64, T64, T128, T64, T64, T64, T128]
+# Further shapes, with both tiles: linear layers that take 64 x 80 as halves too
+MORE_LINEAR = [(1033, 4016, 1039, T64, T64), (457, 1216, 2387, T64, T64)]
+MORE_CONV = [  # K of one, two and three steps
+    (1, 16, 7, 7, 7, 1, 1, 0, T64, 0), (7, 128, 40, 61, 199, 1, 2, 0, T64, 0), (2, 5, 53, 81, 10, 3, 1, 1, T64, T64),
+    (1, 192, 19, 21, 199, 1, 1, 1, T64, T64),
+    # fewer rows than a tile has, and fewer columns
+    (1, 640, 8, 8, 1280, 3, 2, 1, T64, 0), (1, 33, 5, 9, 7001, 3, 1, 1, T64, T64), (1, 16, 7, 7, 1, 3, 1, 1, T64, T64)]
+
+
+@pytest.mark.parametrize("fx,fw", FORMS)
+def test_tile_of_every_shape_and_operand_pair(fx, fw):
+    hardware = fx == E4M3
+    for M, K, N, tile, half in [c + (h,) for c, h in zip(LINEAR_CASES, LINEAR_HALVES)] + MORE_LINEAR:
+        check_tile(tile_of(M, N, K, LINEAR if hardware else HALF), B.fpq_gemm_launch_plan(M, N, K, fx, fw), tile if hardware else half)
+    for Bn, Cin, H, W, Cout, k, stride, pad, tile, half in [c + (h,) for c, h in zip(CONV_CASES, CONV_HALVES)] + MORE_CONV:
+        Ho, Wo = (H + 2 * pad - k) // stride + 1, (W + 2 * pad - k) // stride + 1
+        rule = tile_of(Bn * Ho * Wo, Cout, k * k * B.fpq_padded_channels(Cin), CONV if hardware else HALF, Ho * Wo % 4 != 0)
+        check_tile(rule, B.fpq_conv2d_launch_plan(Bn, Cin, H, W, Cout, k, k, stride, pad, fx, fw), tile if hardware else half)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fx,fw", FORMS)
+@pytest.mark.parametrize("M,K,N,tile,half", MORE_LINEAR)
+def test_linear_in_halves_too(M, K, N, tile, half, fx, fw):
+    test_linear(M, K, N, tile, fx, fw)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fx,fw", FORMS)
+@pytest.mark.parametrize("case", MORE_CONV)
+def test_conv_of_few_steps_rows_and_columns(case, fx, fw):
+    test_conv(case[:9], fx, fw)

@@ -78,8 +78,7 @@ struct Divisor {
 };
 static inline Divisor divisor(int64_t d)
 {
-    uint32_t s = 0;
-    while (((int64_t)1 << s) < d) ++s;
+    const uint32_t s = d > 1 ? 64u - (uint32_t)__builtin_clzll((uint64_t)d - 1) : 0u;
     return Divisor{(uint32_t)((((uint64_t)1 << (31 + s)) + (uint64_t)d - 1) / (uint64_t)d), s};
 }
 
@@ -346,29 +345,32 @@ static inline GemmPlan plan_gemm(int64_t M, int64_t N, int64_t Kpad, PlanForm fo
 // exact mode, operands with a hardware conversion or moved into halves, kernels of at most 31 taps.  us = t[0] + rounds (t[1] + t[2]
 // steps): rounds of 256 tiles, each with its start and its end (nothing overlaps them) and steps of 4 x 64 codes.  The other kernels as
 // in plan_unsliced, sliced ones t[0] + w t[1] steps of 128 codes per slice + t[2] us per million partial sums, with w from their work
-// items as there from the tiles.  In place of slices, deep linear layers also pay for their codes, which this kernel streams at 2 to 3 TB/s:
-// us_codes us per MB, and 0.3 more beyond the 256 MB of the last-level cache (16959 x 30624 -> 160: 250 us in four slices, 342 here).
-// Constants fitted to 8960 layers of random sizes; over 1900 others the choice takes 0.87 of the other plans' time in the geometric
-// mean (the better of both kernels everywhere 0.86; convolutions and halves that were sliced 0.65 to 0.8), 17 of them are slower by more than
-// 3 %, at most by 18 % (3609 x 27088 -> 478: 106 -> 125 us).  Of the U-Net's layers at batch 1 to 16, 660 by sizes and operands, 315 take these tiles, in
-// 0.73 of the time, none of them slower by more than 3 %.
+// items as there from the tiles.  In linear layers of the hardware's encodings the time here grows by up to a quarter as the codes outgrow the
+// level-2 caches, 8 to 24 MB (measured over modelled 1.06 below 5 MB, 1.14 to 15, 1.19 to 40, 1.23 beyond; the other kernels 0.98 to 1.05).
+// Constants fitted to 8960 layers of random sizes, that growth and the margins for several rounds to 371 linear ones.  993 others that take these
+// tiles need 0.76 of the other plans' time in the geometric mean; 16 of them are slower by more than 3 %, at most by 15 % (1108 x 6928 -> 452, E2M1
+// weights: 18.1 -> 20.9 us).  Of the U-Net's layers at batch 1 to 16, 660 by sizes and operands, 315 take these tiles, in 0.73 of the time,
+// none of them slower by more than 3 %.
 //   - 256-row tiles of images that are no multiple of four pixels, whose stores are single elements, lose throughout (102 layers: 0.41
 //     to 0.85 of their time here).
 //   - Few tiles with a deep K stay in slices: this kernel has 8 to 64 workgroups there, each with all of K (1 x 2560 x 8 x 8 -> 1280, 3 x 3:
 //     31.8 us in 22 slices, 45.9 here; moved into halves 36 and 73).  Half a round and more leave them (8 x 1280 x 16 x 16 -> 1280, 3 x 3: 57 + 10 us
 //     in four slices, 46 us here).
-//   - Halves with K of at most 2048 keep their tiles where this kernel goes more than eight rounds (51 layers of 128 x 160 tiles: 0.88 to 1.3
-//     times their time here; 49284 x 1504 -> 1280 294 and 373 us), 128 x 160 tiles with K of at most 1280 from the second round on (218 layers,
+//   - Convolutions with K of at most 128, one or two steps of the others, keep their tiles (50 layers of 5 to 6 us: 0.95 to 1.12 times their time here,
+//     1.03 in the mean; K of 129 to 256 0.89).
+//   - Halves with K of at most 2560 keep their tiles where this kernel goes more than eight rounds (51 layers of 128 x 160 tiles: 0.88 to 1.3
+//     times their time here; 49284 x 1504 -> 1280 294 and 373 us; 11080 x 2384 -> 9493 650 and 700), 128 x 160 tiles with K of at most 1280 from the second round on (218 layers,
 //     0.77 to 1.9; 1024 x 1280 -> 3840 23.1 and 25.1 us): the rounds of the others overlap.
 //   - Whole rounds of 256-row tiles have to be beaten by 20 %: several rounds in a row run here at the clock that the matrix unit's power
 //     leaves (8 x 960 x 64 x 64 -> 320, 3 x 3: 145 and 155 us, where the model has 143 and 121; 8 x 1280 x 32 x 32 -> 1280 176 and 180).
+//     Linear layers of more than one round and convolutions of more than two have to beat narrower tiles than 160 columns (convolutions: 128 x 160 too)
+//     by 15 %: 2230 x 4208 -> 1651 40.5 and 44.6 us, 15 x 1198 x 38 x 16 -> 814, 3 x 3, 139 and 157.
 //   - Linear layers with K of at most 1024, or with at most twelve 64 x 64 tiles, keep their kernels: their sums are those of the
 //     grouped call, bit for bit.  What K4 cuts into slices keeps them: few tiles.
 static inline GemmPlan plan_over_waves(const GemmPlan& p, int64_t M, int64_t N, int64_t Kreal, PlanForm form, bool ragged_images)
 {
     static const float us_here[3][2][3] = {
         {{-0.4f, 6.3f, 0.777f}, {0.7f, 4.3f, 0.458f}}, {{0.8f, 6.2f, 0.704f}, {1.6f, 4.1f, 0.43f}}, {{0.85f, 6.3f, 1.18f}, {1.75f, 4.2f, 0.778f}}};
-    static const float us_codes[2] = {0.1f, 0.065f};
     static const float us_whole[3][7][3] = {
         {{4.2f, -0.03f, 0.413f}, {3.9f, 6.3f, 1.84f}, {2.0f, 3.0f, 1.09f}, {8.9f, -2.6f, 0.602f}, {4.0f, 2.2f, 0.924f}, {4.1f, 0.0f, 0.316f},
          {8.75f, -2.4f, 0.381f}},
@@ -381,19 +383,19 @@ static inline GemmPlan plan_over_waves(const GemmPlan& p, int64_t M, int64_t N, 
                                              {{31.8f, 2.65f, 0.0f}, {12.8f, 1.88f, 1.29f}, {10.7f, 0.92f, 1.6f}, {-2.2f, 1.43f, 2.6f}}};
     static const int bx[7] = {64, 256, 128, 128, 128, 64, 64}, bw[7] = {64, 160, 160, 64, 128, 64, 64};
     const int f = form == PLAN_LINEAR ? 0 : form == PLAN_CONV ? 1 : form == PLAN_HALF ? 2 : -1;
-    if (f < 0 || p.tile > TILE_WAVE_K2 || (p.tile == TILE_WAVE_K4 && p.splits > 1)) return p;
+    if (f < 0 || (f == 1 && Kreal <= 128) || p.tile > TILE_WAVE_K2 || (p.tile == TILE_WAVE_K4 && p.splits > 1)) return p;
     auto tiles = [&](int64_t x, int64_t w) { return ((M + x - 1) / x) * ((N + w - 1) / w); };
     const double steps = (double)((Kreal + 255) / 256), nk = (double)((Kreal + 127) / 128);
     const double mb = (double)M * (double)Kreal * 1e-6;
+    const double far = f != 0 || mb < 8.0 ? 1.0 : mb < 24.0 ? 1.0 + 0.25 / 16.0 * (mb - 8.0) : 1.25;
     double us[2];
     for (int i = 0; i < 2; ++i) {
         const float* t = us_here[f][i];
-        us[i] = t[0] + (double)((tiles(i ? 64 : 128, 80) + 255) / 256) * (t[1] + t[2] * steps);
-        if (f == 0 && p.splits > 1) us[i] += us_codes[i] * mb + (mb > 256.0 ? 0.3 * (mb - 256.0) : 0.0);
+        us[i] = far * (t[0] + (double)((tiles(i ? 64 : 128, 80) + 255) / 256) * (t[1] + t[2] * steps));
     }
     const GemmPlan here{us[0] < us[1] ? TILE_WAVE_128x80 : TILE_WAVE_64x80, 1};
     if (f == 1 && p.tile == TILE_256x160_S3 && p.splits == 1 && ragged_images) return here;
-    if (f == 2 && Kreal <= 2048 && tiles(128, 80) > (Kreal <= 1280 && p.tile == TILE_128x160_S2 ? 256 : 8 * 256)) return p;
+    if (f == 2 && Kreal <= 2560 && tiles(128, 80) > (Kreal <= 1280 && p.tile == TILE_128x160_S2 ? 256 : 8 * 256)) return p;
     const int64_t items = tiles(bx[p.tile], bw[p.tile]) * p.splits;
     const double per = (double)items / 256.0, up = (double)((items + 255) / 256);
     const double w = p.tile == TILE_GENERIC || p.tile >= TILE_WAVE_K4 ? (per > 1.0 ? per : 1.0)
@@ -402,7 +404,14 @@ static inline GemmPlan plan_over_waves(const GemmPlan& p, int64_t M, int64_t N, 
     const float* t = p.splits > 1 ? us_sliced[f][p.tile - 1] : us_whole[f][p.tile];
     const double other = p.splits > 1 ? t[0] + w * t[1] * nk / p.splits + t[2] * (double)p.splits * (double)M * (double)N * 1e-6
                                       : t[0] + w * (t[1] + t[2] * nk);
-    const double margin = f == 1 && p.tile == TILE_256x160_S3 && p.splits == 1 && per >= 0.9 * up ? 0.8 : 0.9;
+    const int64_t grid = tiles(us[0] < us[1] ? 128 : 64, 80);
+    double margin = 0.9;
+    if (f == 0 && grid > 256 && p.tile != TILE_256x160_S3 && p.tile != TILE_128x160_S2)
+        margin = 0.85;
+    else if (f == 1 && p.tile == TILE_256x160_S3 && p.splits == 1)
+        margin = per >= 0.9 * up ? 0.8 : 0.9;
+    else if (f == 1 && grid > 512)
+        margin = 0.85;
     return (us[0] < us[1] ? us[0] : us[1]) < margin * other ? here : p;
 }
 // Operands decoded arithmetically (five exponent bits and more): the small tiles are not built for them, so widths that are

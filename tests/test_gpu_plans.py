@@ -55,7 +55,7 @@ LINEAR_PLANS = [
 ]
 # what fp32 results run instead, in one slice
 RUN_LINEAR = {
-    (2048, 8192, 2080): W128, (1280, 12288, 2720): W64, (1024, 16384, 2560): W128, (768, 20480, 2560): W128, (2048, 5120, 1280): W128,
+    (2048, 8192, 2080): W128, (1024, 16384, 2560): W128, (768, 20480, 2560): W128, (2048, 5120, 1280): W128,
     (1408, 4096, 1280): W128, (1024, 4096, 1280): W64, (512, 5120, 1280): W64, (512, 8192, 1600): W64,
 }
 

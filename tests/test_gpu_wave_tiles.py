@@ -88,6 +88,19 @@ def test_many_rounds_and_whole_rounds_of_larger_tiles_keep_them():
     assert tile_of(8192, 1280, 11520, CONV) < T128 and tile_of(8192, 640, 11520, CONV) == T128
 
 
+def test_linear_layers_of_deep_k_or_several_rounds_keep_their_plans():
+    """In the hardware's encodings, where the other kernels are sure to be as fast or the model is not sure enough: more than one round of the tiles,
+    codes beyond the caches; convolutions of more than two rounds, and of K up to 128, likewise."""
+    for M, N, K in [(3090, 2458, 24304), (31659, 219, 8224), (1724, 2288, 9552), (2230, 1651, 4208), (4960, 1361, 4736), (281, 9415, 3472),
+                    (10521, 995, 30672), (5215, 322, 15184), (3834, 392, 29888), (4109, 71, 13984), (1901, 343, 23168), (2890, 184, 29184)]:
+        assert tile_of(M, N, K, LINEAR) < T128, (M, N, K)
+    for M, N, K in [(9120, 814, 10800), (7986, 999, 7920), (175, 730, 32), (936, 230, 48), (1140, 99, 32), (4270, 199, 128)]:
+        assert tile_of(M, N, K, CONV) < T128, (M, N, K)
+    # what the tiles are for stays with them
+    for M, N, K in [(1290, 939, 11152), (767, 3078, 9280), (542, 2514, 3344), (626, 7481, 3904)]:
+        assert tile_of(M, N, K, LINEAR) >= T128, (M, N, K)
+
+
 def check_tile(rule, query, tile):
     """tile 0: any other kernel."""
     assert rule == tile or (tile == 0 and rule < T128), "this shape no longer takes the tile it is here to cover"
@@ -187,9 +200,8 @@ LINEAR_HALVES = [T128, T128, 0, T128, 0]
 CONV_HALVES = [T128, T64, T64, T64, T128, T64, T64, T64, T128]
 # Further shapes, with both tiles: linear layers that take 64 x 80 as halves too
 MORE_LINEAR = [(1033, 4016, 1039, T64, T64), (457, 1216, 2387, T64, T64)]
-MORE_CONV = [  # K of one, two and three steps
-    (1, 16, 7, 7, 7, 1, 1, 0, T64, 0), (7, 128, 40, 61, 199, 1, 2, 0, T64, 0), (2, 5, 53, 81, 10, 3, 1, 1, T64, T64),
-    (1, 192, 19, 21, 199, 1, 1, 1, T64, T64),
+MORE_CONV = [  # three steps for four wavefronts
+    (2, 5, 53, 81, 10, 3, 1, 1, T64, T64), (1, 192, 19, 21, 199, 1, 1, 1, T64, T64), (5, 176, 20, 31, 61, 1, 2, 0, T64, T64),
     # fewer rows than a tile has, and fewer columns
     (1, 640, 8, 8, 1280, 3, 2, 1, T64, 0), (1, 33, 5, 9, 7001, 3, 1, 1, T64, T64), (1, 16, 7, 7, 1, 3, 1, 1, T64, T64)]
 

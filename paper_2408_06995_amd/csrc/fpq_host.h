@@ -347,9 +347,9 @@ static inline GemmPlan plan_gemm(int64_t M, int64_t N, int64_t Kpad, PlanForm fo
 // in plan_unsliced, sliced ones t[0] + w t[1] steps of 128 codes per slice + t[2] us per million partial sums, with w from their work
 // items as there from the tiles.  In linear layers of the hardware's encodings the time here grows by up to a quarter as the codes outgrow the
 // level-2 caches, 8 to 24 MB (measured over modelled 1.06 below 5 MB, 1.14 to 15, 1.19 to 40, 1.23 beyond; the other kernels 0.98 to 1.05).
-// Constants fitted to 8960 layers of random sizes, that growth and the margins for several rounds to 371 linear ones.  993 others that take these
-// tiles need 0.76 of the other plans' time in the geometric mean; 16 of them are slower by more than 3 %, at most by 15 % (1108 x 6928 -> 452, E2M1
-// weights: 18.1 -> 20.9 us).  Of the U-Net's layers at batch 1 to 16, 660 by sizes and operands, 315 take these tiles, in 0.73 of the time,
+// Constants fitted to 8960 layers of random sizes, that growth and the margins for several rounds to 371 linear ones.  1193 others that take
+// these tiles need 0.76 of the other plans' time in the geometric mean; 23 of them are slower by more than 3 %, at most by 18 % (9 x 35 x 35 x 21 -> 26,
+// 3 x 3, E2M1 weights: 7.2 -> 8.5 us; 1108 x 6928 -> 452 18.1 -> 20.9).  Of the U-Net's layers at batch 1 to 16, 660 by sizes and operands, 315 take these tiles, in 0.73 of the time,
 // none of them slower by more than 3 %.
 //   - 256-row tiles of images that are no multiple of four pixels, whose stores are single elements, lose throughout (102 layers: 0.41
 //     to 0.85 of their time here).
